@@ -2270,6 +2270,164 @@ __global__ void __launch_bounds__(1024)
                      reinterpret_cast<T*>(lds_raw), red, blockDim.x, (blockDim.x + 63) / 64);
 }
 
+// The CG of a bottom level of more than 1024 cells with everything an
+// iteration reads in registers or LDS.  The level's domain is cut into runs
+// of CPT cells along one axis, one run per lane (BottomTables: columns): a
+// lane keeps its cells' coefficients, x, r and q in registers, the direction
+// p is in LDS (lanes of a wavefront are neighbours along axis b, so their
+// accesses fall on consecutive banks), and the neighbours inside a run are
+// the lane's own.  The face between two cells of a run is held once.
+// The strided form (k_bottom_cg_lds<T, 4 or 8>) re-reads seven coefficients
+// and six neighbour indices per cell from the L2 in every iteration, which is
+// what bounds it: 24 x 12 x 16 cells 953 us per solve, 15 x 11 x 19
+// 421 us; this form 275 and 123 us, two block
+// reductions and the LDS reads of p per iteration being left.
+template <typename T>
+__host__ __device__ constexpr bool cg_x_in_lds(int cpt) {
+  return sizeof(T) == 8 && cpt >= 5;
+}
+
+template <typename T, int CPT>
+__global__ void __launch_bounds__(1024)
+    k_bottom_cg_cols(BottomTables bt, const T* __restrict__ diag, const T* __restrict__ coef,
+                     const T* __restrict__ rhs, T* __restrict__ out, int accumulate, double tol,
+                     int maxiter, int singular, int* iters_out) {
+  extern __shared__ unsigned char lds_raw[];
+  __shared__ double red[32];
+  T* p = reinterpret_cast<T*>(lds_raw);
+  // FP64 runs of 5 leave no registers for x: it goes to LDS behind p
+  constexpr bool XL = cg_x_in_lds<T>(CPT);
+  T* xs = p + bt.n;
+  int phase = 0;
+  const int n = bt.n, nw = (blockDim.x + 63) / 64;
+  const int tid = threadIdx.x;
+  const int plane = bt.nb * bt.nc;
+  const int col = tid % plane, a0 = tid / plane * CPT;
+  const int ib = col % bt.nb, ic = col / bt.nb;
+  const int cnt = min(CPT, bt.na - a0);  // <= 0: an idle lane
+  const int base = col + plane * a0;
+  // element of the neighbour columns (walls: the cell itself, coefficient 0)
+  T kbl[CPT], kbh[CPT], kcl[CPT], kch[CPT], ka[CPT + 1], dg[CPT], x[XL ? 1 : CPT], r[CPT], q[CPT];
+  int dbl = 0, dbh = 0, dcl = 0, dch = 0, dal = 0, dah = 0;
+  if (cnt > 0) {
+    dbl = ib > 0 ? -1 : bt.nb - 1;
+    dbh = ib < bt.nb - 1 ? 1 : 1 - bt.nb;
+    dcl = ic > 0 ? -bt.nb : (bt.nc - 1) * bt.nb;
+    dch = ic < bt.nc - 1 ? bt.nb : (1 - bt.nc) * bt.nb;
+    dal = a0 > 0 ? -plane : (bt.na - 1) * plane;
+    dah = a0 + cnt < bt.na ? cnt * plane : -a0 * plane;
+  }
+  double s = 0.0;
+  ka[0] = T(0);
+#pragma unroll
+  for (int m = 0; m < CPT; ++m) {
+    if (!XL) x[XL ? 0 : m] = T(0);
+    r[m] = T(0);
+    q[m] = T(0);
+    kbl[m] = kbh[m] = kcl[m] = kch[m] = ka[m + 1] = T(0);
+    dg[m] = T(1);
+    if (m < cnt) {
+      const int c = bt.perm[base + m * plane];
+      if (XL) xs[base + m * plane] = T(0);
+      r[m] = rhs[bt.map_rhs[c]];
+      s += (double)r[m];
+      dg[m] = diag[c];
+      // wall faces hold 0
+      kbl[m] = coef[(2 * bt.axb) * n + c];
+      kbh[m] = coef[(2 * bt.axb + 1) * n + c];
+      kcl[m] = coef[(2 * bt.axc) * n + c];
+      kch[m] = coef[(2 * bt.axc + 1) * n + c];
+      if (m == 0) ka[0] = coef[(2 * bt.axa) * n + c];
+      ka[m + 1] = coef[(2 * bt.axa + 1) * n + c];
+    }
+  }
+  if (singular) {
+    s = block_sum_w(s, red, phase, nw);
+    const T mean = (T)(s / n);
+#pragma unroll
+    for (int m = 0; m < CPT; ++m)
+      if (m < cnt) r[m] = r[m] - mean;
+  }
+  s = 0.0;
+#pragma unroll
+  for (int m = 0; m < CPT; ++m) s += (double)r[m] * (double)r[m];
+  double rho = block_sum_w(s, red, phase, nw);
+  const double bnorm = sqrt(rho);
+  int it = 0;
+  if (bnorm > 0.0) {
+#pragma unroll
+    for (int m = 0; m < CPT; ++m)
+      if (m < cnt) p[base + m * plane] = r[m];
+    while (it < maxiter) {
+      __syncthreads();
+      s = 0.0;
+      if (cnt > 0) {
+        T pv[CPT];
+#pragma unroll
+        for (int m = 0; m < CPT; ++m) pv[m] = m < cnt ? p[base + m * plane] : T(0);
+        const T plo = p[base + dal];
+        const T phi = p[base + dah];
+#pragma unroll
+        for (int m = 0; m < CPT; ++m) {
+          if (m < cnt) {
+            const int e = base + m * plane;
+            T off = kbl[m] * p[e + dbl];
+            off = off + kbh[m] * p[e + dbh];
+            off = off + kcl[m] * p[e + dcl];
+            off = off + kch[m] * p[e + dch];
+            off = off + ka[m] * (m > 0 ? pv[m > 0 ? m - 1 : 0] : plo);
+            off = off + ka[m + 1] * (m < cnt - 1 ? pv[m < CPT - 1 ? m + 1 : m] : phi);
+            q[m] = dg[m] * pv[m] - off;
+            s += (double)pv[m] * (double)q[m];
+          }
+        }
+      }
+      const double pq = block_sum_w(s, red, phase, nw);
+      const T alT = (T)(rho / pq);
+      s = 0.0;
+#pragma unroll
+      for (int m = 0; m < CPT; ++m) {
+        if (m < cnt) {
+          const int e = base + m * plane;
+          if (XL)
+            xs[e] = xs[e] + alT * p[e];
+          else
+            x[XL ? 0 : m] = x[XL ? 0 : m] + alT * p[e];
+          r[m] = r[m] - alT * q[m];
+          s += (double)r[m] * (double)r[m];
+        }
+      }
+      ++it;
+      const double rho_new = block_sum_w(s, red, phase, nw);
+      if (!(sqrt(rho_new) > tol * bnorm)) break;
+      const T btT = (T)(rho_new / rho);
+      // every lane has read its neighbours' p: the reductions' barriers
+#pragma unroll
+      for (int m = 0; m < CPT; ++m)
+        if (m < cnt) p[base + m * plane] = r[m] + btT * p[base + m * plane];
+      rho = rho_new;
+    }
+  }
+  T mean = T(0);
+  if (singular) {
+    s = 0.0;
+#pragma unroll
+    for (int m = 0; m < CPT; ++m)
+      if (m < cnt) s += (double)(XL ? xs[base + m * plane] : x[XL ? 0 : m]);
+    mean = (T)(block_sum_w(s, red, phase, nw) / n);
+  }
+#pragma unroll
+  for (int m = 0; m < CPT; ++m) {
+    if (m < cnt) {
+      const long long o = bt.map_out[bt.perm[base + m * plane]];
+      const T xv = XL ? xs[base + m * plane] : x[XL ? 0 : m];
+      const T v = singular ? xv - mean : xv;
+      out[o] = accumulate ? out[o] + v : v;
+    }
+  }
+  if (tid == 0) *iters_out = it;
+}
+
 // ---------------------------------------------------------------------------
 // The coarse tail (launch_tail): one work-group, a barrier between passes.
 // Every pass evaluates the operator with eval and stores each result once,
@@ -3083,12 +3241,51 @@ hipError_t launch_bottom_setup(hipStream_t st, const BottomTables& bt, const Ste
   return hipGetLastError();
 }
 
+BottomColumns bottom_columns(const int ext[3]) {
+  BottomColumns best;
+  if ((long long)ext[0] * ext[1] * ext[2] <= 1024) return best;
+  long long lanes_best = 0;
+  for (int c = 2; c <= kCgMaxRun; ++c)
+    for (int a = 0; a < 3; ++a) {
+      const int b = a == 0 ? 1 : 0, d = a == 2 ? 1 : 2;
+      const long long lanes = (long long)ext[b] * ext[d] * ((ext[a] + c - 1) / c);
+      // the shortest run that fits (most lanes at work); among its axes the
+      // one with the fewest idle cells
+      if (lanes > 1024 || (best.cpt && (best.cpt < c || lanes >= lanes_best))) continue;
+      best = {c, a, b, d};
+      lanes_best = lanes;
+    }
+  return best;
+}
+
 template <typename T>
 hipError_t launch_bottom_cg(hipStream_t st, const BottomTables& bt, const T* diag, const T* coef,
                             const T* rhs, T* out, int accumulate, T* work, double tol,
                             int maxiter, int singular, int* iters_out) {
   if (bt.n <= 0) return hipSuccess;
   const size_t lds = sizeof(T) * (size_t)bt.n;
+  if (bt.cpt > 0) {
+    const int lanes = bt.nb * bt.nc * ((bt.na + bt.cpt - 1) / bt.cpt);
+    if (lanes > 1024 || bt.cpt < 2 || bt.cpt > kCgMaxRun || lds > 61440 ||
+        bt.na * bt.nb * bt.nc != bt.n)
+      return hipErrorInvalidValue;
+    const int nt = (lanes + 63) / 64 * 64;
+    const size_t need = cg_x_in_lds<T>(bt.cpt) ? 2 * lds : lds;
+    if (need > 65536) {
+      // p and x of up to 5120 cells: 80 of the 160 KiB a work-group may have
+      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_bottom_cg_cols<T, 5>),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize,
+                                               (int)need);
+      if (e != hipSuccess) return e;
+    }
+#define CGC(C) \
+  hipLaunchKernelGGL((k_bottom_cg_cols<T, C>), dim3(1), dim3(nt), need, st, bt, diag, coef, rhs, \
+                     out, accumulate, tol, maxiter, singular, iters_out)
+    if (bt.cpt == 2) CGC(2); else if (bt.cpt == 3) CGC(3); else if (bt.cpt == 4) CGC(4);
+    else CGC(5);
+#undef CGC
+    return hipGetLastError();
+  }
   if (lds <= 61440 && bt.n <= 8 * 1024) {  // stays under 64 KiB with the reduction scratch
     // up to 1024 cells one per lane in whole wavefronts, then 1024 lanes
     const int nt = bt.n <= 1024 ? (bt.n + 63) / 64 * 64 : 1024;

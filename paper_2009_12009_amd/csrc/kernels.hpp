@@ -277,7 +277,22 @@ struct BottomTables {
   const int* aidx;       // [n] element index of the cell in the level's a (ng 0)
   const int* map_rhs;    // [n] element index in the rhs MultiFab (ng 0)
   const int* map_out;    // [n] element index in the output MultiFab (ng 1)
+  // CG by columns (launch_bottom_cg): the level's domain as nb x nc columns of
+  // na cells along the axis axa (axb, axc the other two), each column cut into
+  // runs of cpt cells, one run per lane.  perm[ib + nb (ic + nc ia)] = cell.
+  // cpt = 0: no such layout (see BottomColumns).
+  const int* perm = nullptr;
+  int cpt = 0, axa = 0, axb = 0, axc = 0, na = 0, nb = 0, nc = 0;
 };
+
+// The column layout of a bottom level of extents ext[3], or cpt = 0 where the
+// level is not one: at most 1024 cells (one per lane already), or no axis on
+// which runs of at most kCgMaxRun cells leave at most 1024 lanes.
+constexpr int kCgMaxRun = 5;
+struct BottomColumns {
+  int cpt = 0, axa = 0, axb = 0, axc = 0;
+};
+BottomColumns bottom_columns(const int ext[3]);
 template <typename T>
 hipError_t launch_bottom_setup(hipStream_t st, const BottomTables& bt, const StencilArgs<T>& op,
                                T* diag, T* coef);

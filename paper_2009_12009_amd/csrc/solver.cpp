@@ -177,6 +177,10 @@ struct mg_solver {
   std::vector<int> h_nbr, h_fidx, h_aidx, h_map_rhs, h_map_out;
   int *d_nbr = nullptr, *d_fidx = nullptr, *d_aidx = nullptr, *d_map_rhs = nullptr,
       *d_map_out = nullptr;
+  // bottom CG by columns: the layout (cpt = 0: none) and its cell order
+  BottomColumns bcols;
+  std::vector<int> h_perm;
+  int* d_perm = nullptr;
   double *bdiag64 = nullptr, *bcoef64 = nullptr, *bwork64 = nullptr;
   float *bdiag32 = nullptr, *bcoef32 = nullptr, *bwork32 = nullptr;
   // scratch
@@ -806,6 +810,16 @@ int build_plan(mg_solver* s, const std::vector<IBox>& boxes, Bump& bump) {
             gmap[(i - D.lo[0]) + (size_t)gn[0] * ((j - D.lo[1]) + (size_t)gn[1] * (k - D.lo[2]))] =
                 c++;
     }
+    s->bcols = bottom_columns(gn);
+    s->h_perm.clear();
+    if (s->bcols.cpt > 0) {
+      const BottomColumns& bc = s->bcols;
+      const size_t st[3] = {1, (size_t)gn[0], (size_t)gn[0] * gn[1]};
+      for (int ia = 0; ia < gn[bc.axa]; ++ia)
+        for (int ic = 0; ic < gn[bc.axc]; ++ic)
+          for (int ib = 0; ib < gn[bc.axb]; ++ib)
+            s->h_perm.push_back(gmap[ib * st[bc.axb] + ic * st[bc.axc] + ia * st[bc.axa]]);
+    }
     c = 0;
     for (int b = 0; b < bl.nbox; ++b) {
       const IBox& B = bl.boxes[b];
@@ -900,6 +914,7 @@ int build_plan(mg_solver* s, const std::vector<IBox>& boxes, Bump& bump) {
   s->d_aidx = bump.take<int>(nb);
   s->d_map_rhs = bump.take<int>(nb);
   s->d_map_out = bump.take<int>(nb);
+  s->d_perm = s->h_perm.empty() ? nullptr : bump.take<int>(nb);
   if (f32) {
     s->bdiag32 = bump.take<float>(nb);
     s->bcoef32 = bump.take<float>(6 * (size_t)nb);
@@ -981,6 +996,17 @@ BottomTables bottom_tables(const mg_solver* s) {
   bt.aidx = s->d_aidx;
   bt.map_rhs = s->d_map_rhs;
   bt.map_out = s->d_map_out;
+  if (s->d_perm) {
+    const IBox& D = s->L.back().domain;
+    bt.perm = s->d_perm;
+    bt.cpt = s->bcols.cpt;
+    bt.axa = s->bcols.axa;
+    bt.axb = s->bcols.axb;
+    bt.axc = s->bcols.axc;
+    bt.na = ext(D, bt.axa);
+    bt.nb = ext(D, bt.axb);
+    bt.nc = ext(D, bt.axc);
+  }
   return bt;
 }
 
@@ -2257,6 +2283,8 @@ int upload_tables(mg_solver* s) {
   HIPTRY(hipMemcpyAsync(s->d_aidx, s->h_aidx.data(), sizeof(int) * nb, hipMemcpyHostToDevice, s->st));
   HIPTRY(hipMemcpyAsync(s->d_map_rhs, s->h_map_rhs.data(), sizeof(int) * nb, hipMemcpyHostToDevice, s->st));
   HIPTRY(hipMemcpyAsync(s->d_map_out, s->h_map_out.data(), sizeof(int) * nb, hipMemcpyHostToDevice, s->st));
+  if (s->d_perm)
+    HIPTRY(hipMemcpyAsync(s->d_perm, s->h_perm.data(), sizeof(int) * nb, hipMemcpyHostToDevice, s->st));
   if (s->tail_lev > 0) {
     for (Level& lv : s->L) {
       if (!lv.h_tcells.empty())
