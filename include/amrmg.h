@@ -37,6 +37,16 @@
  *   the handle.  fill_boundary keeps a process-wide cache of exchange plans;
  *   each cached plan holds one small device table (released by
  *   mg_release_caches).
+ * - Storage of the levels: mg_solve keeps every level as one grid split into
+ *   its red and black cells whenever the hierarchy has at least two levels and
+ *   nu1, nu2 >= 1 (the caller's MultiFabs are gathered on entry, the solution
+ *   scattered into phi's valid cells on return).  Interpolation, restriction
+ *   and the stop test are then always part of a smoothing pass and there are
+ *   no ghost cells, so the options and tile shapes marked [boxes] change
+ *   nothing; they apply to solvers that keep levels as boxes (a single level,
+ *   nu1 or nu2 = 0, the composite solve) and tile shapes also to mg_apply and
+ *   mg_time_smoother.  A face that two boxes share must hold the same
+ *   coefficient in both (the one of the box above it is used).
  * - Streams: work is enqueued on the stream given (NULL = the default
  *   stream).  mg_solve returns after its result is complete; fill_boundary,
  *   mg_apply and mg_face_grad_logb are asynchronous with respect to the host.
@@ -111,7 +121,7 @@ typedef struct {
   int32_t aggregate;           /* [0] merge boxes once they stop coarsening and
                                       keep coarsening the merged box            */
   double bottom_rel_tol;       /* [1e-4] CG stops at ||r||2 <= tol*||rhs||2     */
-  int32_t fused_min_edge;      /* [0] levels (above the bottom) whose box
+  int32_t fused_min_edge;      /* [0] [boxes] levels (above the bottom) whose box
                                       edges are all >= this run each red/black
                                       sweep as one pass into a second buffer
                                       plus a pass over the box boundary layers
@@ -128,7 +138,7 @@ typedef struct {
                                       FP64; iters then counts CG iterations.
                                       The composite solve uses flexible GMRES
                                       instead (see mg_create_amr)              */
-  int32_t ghost_write;         /* [1] on levels using half-sweeps (even extents
+  int32_t ghost_write;         /* [1] [boxes] on levels using half-sweeps (even extents
                                       in periodic directions), each update of a
                                       cell on a box's boundary layer is also
                                       stored into the face ghosts that mirror it,
@@ -136,7 +146,7 @@ typedef struct {
                                       interpolation needs an exchange (same
                                       result); 0 = exchange before every
                                       half-sweep                               */
-  int32_t interp_fold;         /* [1] where a level and the next coarser one
+  int32_t interp_fold;         /* [1] [boxes] where a level and the next coarser one
                                       both write through (and the coarser one
                                       is smoothed, not the bottom), the
                                       interpolation of the correction is done
@@ -150,7 +160,7 @@ typedef struct {
                                       2-norm: 0 = CG, 1 = BiCGStab (the two
                                       Krylov bottom solvers of the paper's
                                       section on linear solvers)              */
-  int32_t restrict_fold;       /* [1] where a coarse level is smoothed from
+  int32_t restrict_fold;       /* [1] [boxes] where a coarse level is smoothed from
                                       zero and its boxes are the finer boxes
                                       coarsened one to one, the restriction of
                                       the finer residual is done by that
@@ -160,7 +170,7 @@ typedef struct {
                                       1 = on levels >= 2, and on level 1 where
                                       tune measured it faster; 2 = on every
                                       such level; 0 = separate passes         */
-  int32_t stop_fold;           /* [1] FP64 V-cycle solves (krylov 0, more than
+  int32_t stop_fold;           /* [1] [boxes] FP64 V-cycle solves (krylov 0, more than
                                       one level, nu1 >= 1, level 0 not fused):
                                       the stop test's residual pass also does
                                       the next cycle's first red half-sweep,
@@ -287,7 +297,7 @@ int mg_set_coefficients_global(mg_solver_t* s, const void* acoef_global,
 /* Solve A phi = rhs by V-cycles until max|rhs - A phi| <= max(rel_tol *
  * max|rhs|, abs_tol) ("Linear Solvers"; the stop norm is the max norm of
  * "Parallel Reductions").  phi: MG_F64 cell MultiFab with ngrow 1, in:
- * initial guess, out: solution (its ghost cells are overwritten).  rhs:
+ * initial guess, out: solution (its ghost cells may be overwritten).  rhs:
  * MG_F64 cell MultiFab, ngrow 0 or 1.  Both over the solver's boxes.  For an
  * all-periodic singular problem the returned phi has zero mean.
  * resid_history: host array of max_iter + 1 doubles or NULL; entry k is the
@@ -387,7 +397,7 @@ int mg_stream_copy(void* dst, const void* src, size_t bytes, void* hip_stream);
 int mg_time_smoother(mg_solver_t* s, mg_multifab_t* phi, const mg_multifab_t* rhs,
                      int32_t reps, double* mean_ms);
 
-/* Override the tile shape of the level-0 smoother (kernel 0: block lx x ly
+/* [boxes] Override the tile shape of the level-0 smoother (kernel 0: block lx x ly
  * lanes covering 2*lx x ly cells, tz planes per work-group) or of the
  * level-0 one-lane-per-cell kernels (kernel 1: lx x ly cells); kernel 2 = the
  * smoother variant that also stores each lane's unchanged pair cell, so cache

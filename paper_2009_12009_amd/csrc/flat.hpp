@@ -1,0 +1,157 @@
+// The split-colour layout of a level and the launchers of its kernels.
+//
+// The level's boxes cover its domain, so the V-cycle keeps each level as one
+// grid instead of a list of boxes, and each array as two halves, the red
+// cells ((i + j + k) even) and the black ones.  Row (j, k) of a half holds the
+// colour's cell of each x-pair p: cell i = 2p + ((j + k + colour) & 1).  A
+// half-sweep then reads the other colour, its own right-hand side and every
+// face, each as whole lines, and writes its own colour without reading it:
+// 4.5 values per cell against 6 where red and black share cache lines.  No
+// ghost layer exists (neighbours past a wall are not used, periodic ones wrap),
+// so there is no exchange either.
+//
+// Faces hold the operator's coefficient c = (beta b) / h_d^2.  x faces: the
+// even ones [0, half), the odd ones [half, 2 half), rows like a cell row (pair
+// p: faces 2p and 2p + 1; face nx is the even entry nx / 2).  y and z faces:
+// the half of colour c holds the low face of the colour's cells, with one more
+// row (y) or plane (z) for the high boundary, so the high y face of a cell is
+// the low face of the other colour's cell above it.
+#pragma once
+
+#include <hip/hip_runtime_api.h>
+
+#include "kernels.hpp"
+#include "tables.hpp"
+
+namespace amrmg {
+
+// Extents, pitch and array sizes of a level (np = x-pairs per row; sp = row
+// pitch in elements, at least nx / 2 + 1; half, yh,
+// zh = elements of one half of a cell or x-face, y-face and z-face array).
+struct FlatDims {
+  int nx, ny, nz, np, sp;
+  int wall;  // bit 2d: the low side along d is a wall, 2d + 1: the high side
+  int half, yh, zh;
+};
+
+// elem: bytes of an element.
+FlatDims flat_dims(const int n[3], const int periodic[3], int elem);
+// Whether the level's arrays fit the kernels' 32-bit element offsets.
+bool flat_fits(const int n[3], int elem);
+
+// The operator on a level.
+template <typename T>
+struct FlatOp {
+  FlatDims d;
+  const T* x;
+  const T* y;
+  const T* z;
+  const T* a;  // alpha * a, both halves, or null for a = 1
+  T alpha;
+};
+
+// Launch order and cache hints of a pass: stream = the level's arrays exceed
+// the last-level cache (read-once loads carry the non-temporal hint); reverse =
+// walk the level from its end.
+struct FlatPass {
+  int stream = 0;
+  int reverse = 0;
+};
+
+// One half-sweep: out (the colour's half) = (f + sum c other) / diag.  f: both
+// halves.  With zero_guess other is taken as 0 and not read.  With ec (both
+// halves of the next coarser level's correction, dims cd) every value read of
+// the other colour gets its coarse parent's correction added first.  With old
+// (the colour's half before the update) max |f - A phi| over the colour's
+// cells is folded into *normbits.
+template <typename T>
+hipError_t launch_flat_half(hipStream_t st, const FlatOp<T>& op, FlatPass ps, const T* other,
+                            T* out, const T* f, int colour, bool zero_guess,
+                            const FlatDims* cd = nullptr, const T* ec = nullptr,
+                            const T* old = nullptr, unsigned long long* normbits = nullptr);
+
+// Coarse right-hand side of a level whose black cells were updated last: their
+// residual is zero, so cf = R r sums the red cells' residuals (four of the
+// eight children).  v, f: both halves of the fine level, cf both halves of
+// the coarse one (dims cd).
+template <typename T>
+hipError_t launch_flat_restrict(hipStream_t st, const FlatOp<T>& op, FlatPass ps, const T* v,
+                                const T* f, const FlatDims& cd, T* cf);
+
+// out = f - A v (f non-null) or A v (f null) on both colours; out may be null
+// (norm only) and narrower than T.  normbits: max |out|; dots (one per block,
+// flat_resid_blocks of them): partial sums of v * out.
+template <typename T, typename TO>
+hipError_t launch_flat_resid(hipStream_t st, const FlatOp<T>& op, FlatPass ps, const T* v,
+                             const T* f, TO* out, unsigned long long* normbits, double* dots);
+int flat_resid_blocks(const FlatDims& d);
+
+// Box MultiFab (double, ng 0 or 1) <-> the split-colour array, valid cells.
+// lo: low corner of the domain.  normbits (gather): max |value|.
+hipError_t launch_flat_gather(hipStream_t st, const BoxInfo* boxes, int nbox, int max_cells,
+                              const int lo[3], const FlatDims& d, const double* src, int ng,
+                              double* dst, unsigned long long* normbits);
+hipError_t launch_flat_scatter(hipStream_t st, const BoxInfo* boxes, int nbox, int max_cells,
+                               const int lo[3], const FlatDims& d, const double* src, double* dst,
+                               int ng);
+// Coefficients from a level's box arrays: faces of direction dir scaled by
+// (beta b) ih (a face shared by two boxes is taken from the box above it),
+// cell coefficient as alpha * a.
+template <typename T>
+hipError_t launch_flat_faces(hipStream_t st, const BoxInfo* boxes, int nbox, int max_faces,
+                             const int lo[3], const FlatDims& d, int dir, const T* b, T beta, T ih,
+                             T* dst);
+template <typename T>
+hipError_t launch_flat_acoef(hipStream_t st, const BoxInfo* boxes, int nbox, int max_cells,
+                             const int lo[3], const FlatDims& d, const T* a, T alpha, T* dst);
+
+// Vectors of the level (both halves, n = 2 half elements, padding zero).
+constexpr int kFlatDotBlocks = 1024;
+// *out = sum a * z (z double or float), partials: kFlatDotBlocks doubles.
+template <typename TZ>
+hipError_t launch_flat_dot(hipStream_t st, long long n, const double* a, const TZ* z,
+                           double* partials, double* out);
+// p = z (first) or z + (*num / *den) p
+template <typename TZ>
+hipError_t launch_flat_cg_p(hipStream_t st, long long n, double* p, const TZ* z,
+                            const double* num, const double* den, int first);
+// x += al p, r -= al q, al = *num / *den; max |r|; r32 (nullable) = r rounded
+hipError_t launch_flat_cg_xr(hipStream_t st, long long n, double* x, const double* p, double* r,
+                             const double* q, const double* num, const double* den,
+                             unsigned long long* normbits, float* r32);
+// v += e
+hipError_t launch_flat_update(hipStream_t st, long long n, double* v, const float* e);
+// v -= mean of v over the level's cells (padding untouched); partials and sum
+// as in launch_flat_dot
+hipError_t launch_flat_remove_mean(hipStream_t st, const FlatDims& d, double* v, double* partials,
+                                   double* sum);
+hipError_t launch_flat_maxabs(hipStream_t st, long long n, const double* v,
+                              unsigned long long* normbits);
+
+// The coarsest levels and a CG bottom of at most kTailMaxBottom cells in one
+// work-group: every pass a loop of its lanes with a barrier after it, the
+// correction, right-hand side and residual of the levels in LDS where they all
+// fit.  Same arithmetic per cell as the launches above.
+template <typename T>
+struct FlatTailLevel {
+  FlatOp<T> op;
+  T* e;
+  T* f;
+  T* r;  // residual of the red cells (one half)
+};
+template <typename T>
+struct FlatTail {
+  int nlev, nu1, nu2, reverse;
+  FlatTailLevel<T> lev[kTailMaxLevels];
+  FlatDims bd;  // bottom level
+  T *be, *bf;
+  BottomTables bt;  // maps into be, bf
+  const T *bdiag, *bcoef;
+  double tol;
+  int maxiter, singular;
+  int* iters;
+};
+template <typename T>
+hipError_t launch_flat_tail(hipStream_t st, const FlatTail<T>& t);
+
+}  // namespace amrmg

@@ -1,0 +1,956 @@
+// gfx950 kernels of the V-cycle on the split-colour layout (flat.hpp).
+//
+// Operator and rounding: c phi is accumulated with explicit fused multiply-adds
+// in the order xlo, xhi, ylo, yhi, zlo, zhi and the compiler fuses nothing by
+// itself (contract off), so every kernel that updates a cell - a half-sweep of
+// its own or the one-work-group tail - rounds the same way.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+
+#include "device.hpp"
+#include "flat.hpp"
+
+namespace amrmg {
+
+namespace {
+
+__device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+
+template <typename T, int V, bool NT>
+__device__ __forceinline__ void ldv(T (&d)[V], const T* p) {
+  if constexpr (V == 1) {
+    d[0] = NT ? __builtin_nontemporal_load(p) : *p;
+  } else {
+    using X = T __attribute__((ext_vector_type(V)));
+    const X* q = reinterpret_cast<const X*>(p);
+    const X x = NT ? __builtin_nontemporal_load(q) : *q;
+#pragma unroll
+    for (int v = 0; v < V; ++v) d[v] = x[v];
+  }
+}
+
+// Stores the first `n` of V values (p aligned to V elements).
+template <typename T, int V>
+__device__ __forceinline__ void stv(T* p, const T (&s)[V], int n) {
+  if constexpr (V > 1) {
+    if (n >= V) {
+      using X = T __attribute__((ext_vector_type(V)));
+      X x;
+#pragma unroll
+      for (int v = 0; v < V; ++v) x[v] = s[v];
+      *reinterpret_cast<X*>(p) = x;
+      return;
+    }
+  }
+#pragma unroll
+  for (int v = 0; v < V; ++v)
+    if (v < n) p[v] = s[v];
+}
+
+// Coefficients of V consecutive cells of a colour (pairs p0 .. p0 + V - 1 of
+// row (j, k)); s = (j + k + colour) & 1, the cells' offset in their pairs.
+template <typename T, int V>
+struct Coef {
+  T xl[V], xh[V], yl[V], yh[V], zl[V], zh[V], a[V];
+};
+
+template <typename T, int V, bool NT>
+__device__ __forceinline__ void load_coef(Coef<T, V>& c, const FlatOp<T>& op, int colour, int s,
+                                          int p0, int j, int k) {
+  const FlatDims& d = op.d;
+  const int r = p0 + d.sp * (j + d.ny * k);
+  T ev[V], od[V];
+  ldv<T, V, NT>(ev, op.x + r);
+  ldv<T, V, NT>(od, op.x + d.half + r);
+  // the face past the last pair of the group, for cells on odd columns
+  const T en = s ? op.x[r + V] : ev[V - 1];
+#pragma unroll
+  for (int v = 0; v < V; ++v) {
+    c.xl[v] = s ? od[v] : ev[v];
+    c.xh[v] = s ? (v + 1 < V ? ev[v + 1 < V ? v + 1 : v] : en) : od[v];
+  }
+  const int ry = p0 + d.sp * (j + (d.ny + 1) * k);
+  ldv<T, V, NT>(c.yl, op.y + colour * d.yh + ry);
+  ldv<T, V, NT>(c.yh, op.y + (1 - colour) * d.yh + ry + d.sp);
+  ldv<T, V, NT>(c.zl, op.z + colour * d.zh + r);
+  ldv<T, V, NT>(c.zh, op.z + (1 - colour) * d.zh + r + d.sp * d.ny);
+  if (op.a) ldv<T, V, NT>(c.a, op.a + colour * d.half + r);
+}
+
+// The cells' neighbours, all of the other colour (O: its half).  Past a wall
+// an in-range element is read and not used.
+template <typename T, int V>
+struct Nb {
+  T xl[V], xh[V], yl[V], yh[V], zl[V], zh[V];
+};
+
+struct RowIx {
+  int jm, jp, km, kp;  // neighbour rows and planes, wrapped or clamped
+};
+
+__device__ __forceinline__ RowIx row_ix(const FlatDims& d, int j, int k) {
+  RowIx x;
+  x.jm = j > 0 ? j - 1 : ((d.wall & 4) ? 0 : d.ny - 1);
+  x.jp = j < d.ny - 1 ? j + 1 : ((d.wall & 8) ? j : 0);
+  x.km = k > 0 ? k - 1 : ((d.wall & 16) ? 0 : d.nz - 1);
+  x.kp = k < d.nz - 1 ? k + 1 : ((d.wall & 32) ? k : 0);
+  return x;
+}
+
+template <typename T, int V>
+__device__ __forceinline__ void load_nb(Nb<T, V>& n, const FlatDims& d, const T* O, int s, int p0,
+                                        int j, int k, const RowIx& x) {
+  const int row = d.sp * (j + d.ny * k);
+  T c[V];
+  ldv<T, V, false>(c, O + row + p0);
+  const int pl = p0 > 0 ? p0 - 1 : ((d.wall & 1) ? 0 : d.np - 1);
+  const int ph = p0 + V < d.np ? p0 + V : ((d.wall & 2) ? p0 : 0);
+  const T ex = O[row + (s ? ph : pl)];
+#pragma unroll
+  for (int v = 0; v < V; ++v) {
+    n.xl[v] = s ? c[v] : (v > 0 ? c[v > 0 ? v - 1 : 0] : ex);
+    n.xh[v] = s ? (v + 1 < V ? c[v + 1 < V ? v + 1 : v] : ex) : c[v];
+  }
+  ldv<T, V, false>(n.yl, O + p0 + d.sp * (x.jm + d.ny * k));
+  ldv<T, V, false>(n.yh, O + p0 + d.sp * (x.jp + d.ny * k));
+  ldv<T, V, false>(n.zl, O + p0 + d.sp * (j + d.ny * x.km));
+  ldv<T, V, false>(n.zh, O + p0 + d.sp * (j + d.ny * x.kp));
+}
+
+// Coarse parents' corrections of the other-colour neighbours of the cells:
+// own[v] the parent of pair p0 + v, x[v] that of the pair next to the cell
+// (p - 1 or p + 1), y and z those of the neighbour rows in the next coarse row
+// and plane.
+template <typename T, int V>
+struct Par {
+  T own[V], x[V], y[V], z[V];
+};
+
+template <typename T>
+__device__ __forceinline__ T coarse_at(const FlatDims& c, const T* e, int I, int J, int K) {
+  return e[((I + J + K) & 1) * c.half + (I >> 1) + c.sp * (J + c.ny * K)];
+}
+
+template <typename T, int V>
+__device__ __forceinline__ void load_par(Par<T, V>& q, const FlatDims& d, const FlatDims& c,
+                                         const T* e, int s, int p0, int j, int k) {
+  const int J = j >> 1, K = k >> 1;
+  // wrapped or clamped as the fine neighbours are (nx = 2 c.nx and so on)
+  const int Jn = (j & 1) ? (J < c.ny - 1 ? J + 1 : ((d.wall & 8) ? J : 0))
+                         : (J > 0 ? J - 1 : ((d.wall & 4) ? 0 : c.ny - 1));
+  const int Kn = (k & 1) ? (K < c.nz - 1 ? K + 1 : ((d.wall & 32) ? K : 0))
+                         : (K > 0 ? K - 1 : ((d.wall & 16) ? 0 : c.nz - 1));
+#pragma unroll
+  for (int v = 0; v < V; ++v) {
+    const int I = p0 + v < c.nx ? p0 + v : c.nx - 1;
+    const int In = s ? (I < c.nx - 1 ? I + 1 : ((d.wall & 2) ? I : 0))
+                     : (I > 0 ? I - 1 : ((d.wall & 1) ? 0 : c.nx - 1));
+    q.own[v] = coarse_at(c, e, I, J, K);
+    q.x[v] = coarse_at(c, e, In, J, K);
+    q.y[v] = coarse_at(c, e, I, Jn, K);
+    q.z[v] = coarse_at(c, e, I, J, Kn);
+  }
+}
+
+template <typename T, int V>
+__device__ __forceinline__ void add_par(Nb<T, V>& n, const Par<T, V>& q, int s, int j, int k) {
+#pragma unroll
+  for (int v = 0; v < V; ++v) {
+    n.xl[v] = n.xl[v] + (s ? q.own[v] : q.x[v]);
+    n.xh[v] = n.xh[v] + (s ? q.x[v] : q.own[v]);
+    n.yl[v] = n.yl[v] + ((j & 1) ? q.own[v] : q.y[v]);
+    n.yh[v] = n.yh[v] + ((j & 1) ? q.y[v] : q.own[v]);
+    n.zl[v] = n.zl[v] + ((k & 1) ? q.own[v] : q.z[v]);
+    n.zh[v] = n.zh[v] + ((k & 1) ? q.z[v] : q.own[v]);
+  }
+}
+
+template <typename T, int V>
+__device__ __forceinline__ T diag_of(const FlatOp<T>& op, const Coef<T, V>& c, int v, int s, int p,
+                                     int j, int k) {
+#pragma clang fp contract(off)
+  const FlatDims& d = op.d;
+  T g = op.a ? c.a[v] : op.alpha;
+  g = g + ((d.wall & 1) && p == 0 && !s ? T(2) * c.xl[v] : c.xl[v]);
+  g = g + ((d.wall & 2) && p == d.np - 1 && s ? T(2) * c.xh[v] : c.xh[v]);
+  g = g + ((d.wall & 4) && j == 0 ? T(2) * c.yl[v] : c.yl[v]);
+  g = g + ((d.wall & 8) && j == d.ny - 1 ? T(2) * c.yh[v] : c.yh[v]);
+  g = g + ((d.wall & 16) && k == 0 ? T(2) * c.zl[v] : c.zl[v]);
+  g = g + ((d.wall & 32) && k == d.nz - 1 ? T(2) * c.zh[v] : c.zh[v]);
+  return g;
+}
+
+template <typename T, int V>
+__device__ __forceinline__ T off_of(const FlatOp<T>& op, const Coef<T, V>& c, const Nb<T, V>& n,
+                                    int v, int s, int p, int j, int k) {
+#pragma clang fp contract(off)
+  const FlatDims& d = op.d;
+  T o = (d.wall & 1) && p == 0 && !s ? T(0) : c.xl[v] * n.xl[v];
+  o = (d.wall & 2) && p == d.np - 1 && s ? o : fma_(c.xh[v], n.xh[v], o);
+  o = (d.wall & 4) && j == 0 ? o : fma_(c.yl[v], n.yl[v], o);
+  o = (d.wall & 8) && j == d.ny - 1 ? o : fma_(c.yh[v], n.yh[v], o);
+  o = (d.wall & 16) && k == 0 ? o : fma_(c.zl[v], n.zl[v], o);
+  o = (d.wall & 32) && k == d.nz - 1 ? o : fma_(c.zh[v], n.zh[v], o);
+  return o;
+}
+
+template <typename T>
+__device__ __forceinline__ T resid_of(T f, T diag, T v, T off) {
+#pragma clang fp contract(off)
+  return f - fma_(diag, v, -off);
+}
+
+// Blocks are dealt to the 8 XCDs round robin: block b takes tile (b % 8) n/8 +
+// b / 8, so that each XCD walks one contiguous part of the level and finds its
+// tiles' neighbours in its own L2.
+__device__ __forceinline__ int xcd_tile(int n, int reverse) {
+  const int b = blockIdx.x, q = n / 8;
+  const int t = b < 8 * q ? (b % 8) * q + b / 8 : b;
+  return reverse ? n - 1 - t : t;
+}
+
+struct Grid2 {
+  int lxl;      // log2 of lanes along x
+  int nbx, nb;  // blocks along x, in all
+  int reverse;
+};
+
+// Half-sweep.  Bound by HBM on the finest level: 4.5 values per cell, 604 MB at
+// 256^3 FP64, 113 us = 5.3 TB/s (the box form moves 856 MB in 146-170 us); FP32
+// 53 us (80).  Blocks are one row group deep along z: the level's planes are
+// re-read from the L2 by the neighbouring blocks of the same XCD, and many
+// small blocks keep more loads in flight than a march along z.  V pairs per
+// lane (flat_width) make 16-byte loads; the block's lanes are 2^lxl along x by
+// rows (j + ny k).  ZG: from zero; PE: with the coarse correction; STOP: with
+// the norm of the colour's residual before the update.
+template <typename T, int V, bool ZG, bool PE, bool STOP, bool NT>
+__global__ void __launch_bounds__(256)
+    k_flat_half(FlatOp<T> op, Grid2 g, const T* __restrict__ other, T* __restrict__ out,
+                const T* __restrict__ f, int colour, FlatDims cd, const T* __restrict__ ec,
+                const T* __restrict__ old, unsigned long long* normbits) {
+#pragma clang fp contract(off)
+  const FlatDims& d = op.d;
+  const int t = xcd_tile(g.nb, g.reverse);
+  const int p0 = ((t % g.nbx << g.lxl) + (threadIdx.x & ((1 << g.lxl) - 1))) * V;
+  const int row = (t / g.nbx) * (256 >> g.lxl) + (threadIdx.x >> g.lxl);
+  const bool act = p0 < d.np && row < d.ny * d.nz;
+  unsigned long long mx = 0;
+  if (act) {
+    const int k = row / d.ny, j = row - k * d.ny;
+    const int s = (j + k + colour) & 1;
+    const int at = p0 + d.sp * row;
+    T fv[V], ov[V];
+    Coef<T, V> c;
+    Nb<T, V> n;
+    Par<T, V> q;
+    ldv<T, V, NT>(fv, f + colour * d.half + at);
+    load_coef<T, V, NT>(c, op, colour, s, p0, j, k);
+    if (!ZG) load_nb<T, V>(n, d, other, s, p0, j, k, row_ix(d, j, k));
+    if (PE) load_par<T, V>(q, d, cd, ec, s, p0, j, k);
+    if (STOP) ldv<T, V, NT>(ov, old + at);
+    if (PE) add_par<T, V>(n, q, s, j, k);
+    T nv[V];
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      const T diag = diag_of<T, V>(op, c, v, s, p0 + v, j, k);
+      const T off = ZG ? T(0) : off_of<T, V>(op, c, n, v, s, p0 + v, j, k);
+      nv[v] = (ZG ? fv[v] : fv[v] + off) / diag;
+      if (STOP && p0 + v < d.np) {
+        const unsigned long long bits = absbits(resid_of(fv[v], diag, ov[v], off));
+        mx = bits > mx ? bits : mx;
+      }
+    }
+    stv<T, V>(out + at, nv, d.np - p0);
+  }
+  if (STOP) block_max_u64(mx, normbits);
+}
+
+// Residual and restriction in one pass, red cells only: 4.6 values per fine
+// cell, 113 us at 256^3 FP64 (box form, both colours: 148 us).  A lane takes
+// coarse cell (I, J, K): the red cells of pair I on rows 2J, 2J + 1 of planes
+// 2K, 2K + 1, four stencils in flight at once.
+template <typename T, bool NT>
+__global__ void __launch_bounds__(256)
+    k_flat_restrict(FlatOp<T> op, Grid2 g, const T* __restrict__ v, const T* __restrict__ f,
+                    FlatDims cd, T* __restrict__ cf) {
+#pragma clang fp contract(off)
+  const FlatDims& d = op.d;
+  const int t = xcd_tile(g.nb, g.reverse);
+  const int I = (t % g.nbx << g.lxl) + (threadIdx.x & ((1 << g.lxl) - 1));
+  const int row = (t / g.nbx) * (256 >> g.lxl) + (threadIdx.x >> g.lxl);
+  if (I >= d.np || row >= cd.ny * cd.nz) return;
+  const int K = row / cd.ny, J = row - K * cd.ny;
+  T zs[2];
+#pragma unroll
+  for (int dk = 0; dk < 2; ++dk) {
+    T r[2];
+#pragma unroll
+    for (int dj = 0; dj < 2; ++dj) {
+      const int j = 2 * J + dj, k = 2 * K + dk, s = (dj + dk) & 1;
+      const int at = I + d.sp * (j + d.ny * k);
+      Coef<T, 1> c;
+      Nb<T, 1> n;
+      T fv[1];
+      ldv<T, 1, NT>(fv, f + at);
+      load_coef<T, 1, NT>(c, op, 0, s, I, j, k);
+      load_nb<T, 1>(n, d, v + d.half, s, I, j, k, row_ix(d, j, k));
+      r[dj] = resid_of(fv[0], diag_of<T, 1>(op, c, 0, s, I, j, k), v[at],
+                       off_of<T, 1>(op, c, n, 0, s, I, j, k));
+    }
+    zs[dk] = r[0] + r[1];
+  }
+  cf[((I + J + K) & 1) * cd.half + (I >> 1) + cd.sp * row] = (zs[0] + zs[1]) * T(0.125);
+}
+
+template <typename T, typename TO, int V, bool NT>
+__global__ void __launch_bounds__(256)
+    k_flat_resid(FlatOp<T> op, Grid2 g, const T* __restrict__ v, const T* __restrict__ f,
+                 TO* __restrict__ out, unsigned long long* normbits, double* __restrict__ dots) {
+#pragma clang fp contract(off)
+  const FlatDims& d = op.d;
+  const int t = xcd_tile(g.nb, g.reverse);
+  const int p0 = ((t % g.nbx << g.lxl) + (threadIdx.x & ((1 << g.lxl) - 1))) * V;
+  const int row = (t / g.nbx) * (256 >> g.lxl) + (threadIdx.x >> g.lxl);
+  unsigned long long mx = 0;
+  double dot = 0.0;
+  if (p0 < d.np && row < d.ny * d.nz) {
+    const int k = row / d.ny, j = row - k * d.ny;
+    const int at = p0 + d.sp * row;
+    const RowIx rx = row_ix(d, j, k);
+#pragma unroll
+    for (int colour = 0; colour < 2; ++colour) {
+      const int s = (j + k + colour) & 1;
+      T fv[V], cv[V];
+      TO rv[V];
+      Coef<T, V> c;
+      Nb<T, V> n;
+      if (f) ldv<T, V, NT>(fv, f + colour * d.half + at);
+      ldv<T, V, false>(cv, v + colour * d.half + at);
+      load_coef<T, V, NT>(c, op, colour, s, p0, j, k);
+      load_nb<T, V>(n, d, v + (1 - colour) * d.half, s, p0, j, k, rx);
+#pragma unroll
+      for (int u = 0; u < V; ++u) {
+        const T diag = diag_of<T, V>(op, c, u, s, p0 + u, j, k);
+        const T off = off_of<T, V>(op, c, n, u, s, p0 + u, j, k);
+        const T r = f ? resid_of(fv[u], diag, cv[u], off) : fma_(diag, cv[u], -off);
+        rv[u] = (TO)r;
+        if (p0 + u < d.np) {
+          const unsigned long long bits = absbits(r);
+          mx = bits > mx ? bits : mx;
+          if (dots) dot += (double)cv[u] * (double)r;
+        }
+      }
+      if (out) stv<TO, V>(out + colour * d.half + at, rv, d.np - p0);
+    }
+  }
+  if (normbits) block_max_u64(mx, normbits);
+  if (dots) {
+    __shared__ double red[32];
+    int phase = 0;
+    dot = block_sum(dot, red, phase);
+    if (threadIdx.x == 0) dots[blockIdx.x] = dot;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Between box arrays and the split-colour layout; grid.y = box, lanes stride
+// the box's cells or faces.
+
+__device__ __forceinline__ int split_at(const FlatDims& d, int i, int j, int k) {
+  return ((i + j + k) & 1) * d.half + (i >> 1) + d.sp * (j + d.ny * k);
+}
+
+template <bool GATHER>
+__global__ void __launch_bounds__(256)
+    k_flat_boxes(const BoxInfo* __restrict__ boxes, int3 lo, FlatDims d, const double* src,
+                 double* dst, int ng, unsigned long long* normbits) {
+  const BoxInfo B = boxes[blockIdx.y];
+  const int nx = B.hi[0] - B.lo[0] + 1, ny = B.hi[1] - B.lo[1] + 1, nz = B.hi[2] - B.lo[2] + 1;
+  const long long off = ng ? B.off_g1 : B.off_g0;
+  const int sy = nx + 2 * ng;
+  const long long sz = (long long)sy * (ny + 2 * ng);
+  const unsigned total = nx * ny * nz;
+  unsigned long long mx = 0;
+  for (unsigned e = blockIdx.x * 256 + threadIdx.x; e < total; e += gridDim.x * 256) {
+    const int t = e / nx, il = e - t * nx, kl = t / ny, jl = t - kl * ny;
+    const long long b = off + (il + ng) + (long long)sy * (jl + ng) + sz * (kl + ng);
+    const int q = split_at(d, B.lo[0] - lo.x + il, B.lo[1] - lo.y + jl, B.lo[2] - lo.z + kl);
+    if (GATHER) {
+      const double v = src[b];
+      dst[q] = v;
+      const unsigned long long bits = absbits(v);
+      mx = bits > mx ? bits : mx;
+    } else {
+      dst[b] = src[q];
+    }
+  }
+  if (GATHER && normbits) block_max_u64(mx, normbits);
+}
+
+template <typename T>
+__global__ void __launch_bounds__(256)
+    k_flat_faces(const BoxInfo* __restrict__ boxes, int3 lo, FlatDims d, int dir,
+                 const T* __restrict__ b, T beta, T ih, T* __restrict__ dst) {
+#pragma clang fp contract(off)
+  const BoxInfo B = boxes[blockIdx.y];
+  int n[3];
+  for (int a = 0; a < 3; ++a) n[a] = B.hi[a] - B.lo[a] + 1 + (a == dir ? 1 : 0);
+  const int dn[3] = {d.nx, d.ny, d.nz};
+  const int l[3] = {lo.x, lo.y, lo.z};
+  const unsigned total = n[0] * n[1] * n[2];
+  for (unsigned e = blockIdx.x * 256 + threadIdx.x; e < total; e += gridDim.x * 256) {
+    int q[3];
+    const int t = e / n[0];
+    q[0] = e - t * n[0];
+    q[2] = t / n[1];
+    q[1] = t - q[2] * n[1];
+    // a box's last face is the next box's first, unless the domain ends there
+    if (q[dir] == n[dir] - 1 && B.hi[dir] - l[dir] + 1 != dn[dir]) continue;
+    for (int a = 0; a < 3; ++a) q[a] += B.lo[a] - l[a];
+    const T c = (beta * b[B.off_f[dir] + e]) * ih;
+    if (dir == 0)
+      dst[(q[0] & 1) * d.half + (q[0] >> 1) + d.sp * (q[1] + d.ny * q[2])] = c;
+    else if (dir == 1)
+      dst[((q[0] + q[1] + q[2]) & 1) * d.yh + (q[0] >> 1) + d.sp * (q[1] + (d.ny + 1) * q[2])] = c;
+    else
+      dst[((q[0] + q[1] + q[2]) & 1) * d.zh + (q[0] >> 1) + d.sp * (q[1] + d.ny * q[2])] = c;
+  }
+}
+
+template <typename T>
+__global__ void __launch_bounds__(256)
+    k_flat_acoef(const BoxInfo* __restrict__ boxes, int3 lo, FlatDims d, const T* __restrict__ a,
+                 T alpha, T* __restrict__ dst) {
+  const BoxInfo B = boxes[blockIdx.y];
+  const int nx = B.hi[0] - B.lo[0] + 1, ny = B.hi[1] - B.lo[1] + 1, nz = B.hi[2] - B.lo[2] + 1;
+  const unsigned total = nx * ny * nz;
+  for (unsigned e = blockIdx.x * 256 + threadIdx.x; e < total; e += gridDim.x * 256) {
+    const int t = e / nx, il = e - t * nx, kl = t / ny, jl = t - kl * ny;
+    dst[split_at(d, B.lo[0] - lo.x + il, B.lo[1] - lo.y + jl, B.lo[2] - lo.z + kl)] =
+        alpha * a[B.off_g0 + e];
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Vectors: both halves of an array as one run of n elements (a multiple of 4),
+// padding included.
+
+template <typename TZ>
+__global__ void __launch_bounds__(256)
+    k_flat_dot(long long n, const double* __restrict__ a, const TZ* __restrict__ z,
+               double* __restrict__ partials) {
+  __shared__ double red[32];
+  int phase = 0;
+  double s0 = 0.0, s1 = 0.0;
+  const long long step = (long long)gridDim.x * 512;
+  for (long long e = (blockIdx.x * 256ll + threadIdx.x) * 2; e < n; e += step) {
+    double av[2];
+    TZ zv[2];
+    ldv<double, 2, false>(av, a + e);
+    ldv<TZ, 2, false>(zv, z + e);
+    s0 += av[0] * (double)zv[0];
+    s1 += av[1] * (double)zv[1];
+  }
+  const double s = block_sum(s0 + s1, red, phase);
+  if (threadIdx.x == 0) partials[blockIdx.x] = s;
+}
+
+template <typename TZ>
+__global__ void __launch_bounds__(256)
+    k_flat_cg_p(long long n, double* __restrict__ p, const TZ* __restrict__ z, const double* num,
+                const double* den, int first) {
+  const double be = first ? 0.0 : *num / *den;
+  for (long long e = (blockIdx.x * 256ll + threadIdx.x) * 2; e < n; e += gridDim.x * 512ll) {
+    TZ zv[2];
+    double pv[2] = {0.0, 0.0};
+    ldv<TZ, 2, false>(zv, z + e);
+    if (!first) ldv<double, 2, false>(pv, p + e);
+    for (int v = 0; v < 2; ++v) pv[v] = first ? (double)zv[v] : (double)zv[v] + be * pv[v];
+    stv<double, 2>(p + e, pv, 2);
+  }
+}
+
+__global__ void __launch_bounds__(256)
+    k_flat_cg_xr(long long n, double* __restrict__ x, const double* __restrict__ p,
+                 double* __restrict__ r, const double* __restrict__ q, const double* num,
+                 const double* den, unsigned long long* normbits, float* __restrict__ r32) {
+  const double al = *num / *den;
+  unsigned long long mx = 0;
+  for (long long e = (blockIdx.x * 256ll + threadIdx.x) * 2; e < n; e += gridDim.x * 512ll) {
+    double xv[2], pv[2], rv[2], qv[2];
+    ldv<double, 2, false>(xv, x + e);
+    ldv<double, 2, false>(pv, p + e);
+    ldv<double, 2, false>(rv, r + e);
+    ldv<double, 2, false>(qv, q + e);
+    float rs[2];
+    for (int v = 0; v < 2; ++v) {
+      xv[v] += al * pv[v];
+      rv[v] -= al * qv[v];
+      rs[v] = (float)rv[v];
+      const unsigned long long bits = absbits(rv[v]);
+      mx = bits > mx ? bits : mx;
+    }
+    stv<double, 2>(x + e, xv, 2);
+    stv<double, 2>(r + e, rv, 2);
+    if (r32) stv<float, 2>(r32 + e, rs, 2);
+  }
+  block_max_u64(mx, normbits);
+}
+
+__global__ void __launch_bounds__(256)
+    k_flat_update(long long n, double* __restrict__ v, const float* __restrict__ e) {
+  for (long long i = (blockIdx.x * 256ll + threadIdx.x) * 2; i < n; i += gridDim.x * 512ll) {
+    double a[2];
+    float b[2];
+    ldv<double, 2, false>(a, v + i);
+    ldv<float, 2, false>(b, e + i);
+    for (int u = 0; u < 2; ++u) a[u] += (double)b[u];
+    stv<double, 2>(v + i, a, 2);
+  }
+}
+
+__global__ void __launch_bounds__(256)
+    k_flat_sum(long long n, const double* __restrict__ v, double* __restrict__ partials) {
+  __shared__ double red[32];
+  int phase = 0;
+  double s = 0.0;
+  for (long long e = blockIdx.x * 256ll + threadIdx.x; e < n; e += gridDim.x * 256ll) s += v[e];
+  s = block_sum(s, red, phase);
+  if (threadIdx.x == 0) partials[blockIdx.x] = s;
+}
+
+// grid.y = half
+__global__ void __launch_bounds__(256)
+    k_flat_shift(FlatDims d, double* __restrict__ v, const double* sum) {
+  const double m = *sum / ((double)d.nx * d.ny * d.nz);
+  double* h = v + (long long)blockIdx.y * d.half;
+  const unsigned total = d.sp * d.ny * d.nz;
+  for (unsigned e = blockIdx.x * 256 + threadIdx.x; e < total; e += gridDim.x * 256)
+    if (e % d.sp < d.np) h[e] -= m;
+}
+
+__global__ void __launch_bounds__(256)
+    k_flat_maxabs(long long n, const double* __restrict__ v, unsigned long long* normbits) {
+  unsigned long long mx = 0;
+  for (long long e = blockIdx.x * 256ll + threadIdx.x; e < n; e += gridDim.x * 256ll) {
+    const unsigned long long bits = absbits(v[e]);
+    mx = bits > mx ? bits : mx;
+  }
+  block_max_u64(mx, normbits);
+}
+
+// ---------------------------------------------------------------------------
+// The tail.
+
+// LDS (elements) of one tail level: e and f (both halves), r (red half).
+__host__ __device__ inline int tail_elems(const FlatDims& d) { return 5 * d.half; }
+
+template <typename T>
+struct TailArr {
+  T *e, *f, *r;
+};
+
+template <typename T, bool LDS>
+__global__ void __launch_bounds__(kTailLanes) k_flat_tail(FlatTail<T> tp) {
+#pragma clang fp contract(off)
+  extern __shared__ __align__(16) unsigned char flat_lds[];
+  __shared__ double red[32];
+  T* const lds = reinterpret_cast<T*>(flat_lds);
+  const int tid = threadIdx.x, nt = kTailLanes;
+  // level l's arrays: in LDS one level after the other, then the bottom's e, f
+  // and the CG's p
+  auto arr = [&](int l) {
+    TailArr<T> a;
+    if (LDS) {
+      int o = 0;
+      for (int m = 0; m < l; ++m) o += tail_elems(tp.lev[m].op.d);
+      const FlatDims& d = l < tp.nlev ? tp.lev[l < kTailMaxLevels ? l : 0].op.d : tp.bd;
+      a.e = lds + o;
+      a.f = a.e + 2 * d.half;
+      a.r = a.f + 2 * d.half;
+    } else if (l < tp.nlev) {
+      const FlatTailLevel<T>& L = tp.lev[l < kTailMaxLevels ? l : 0];
+      a = {L.e, L.f, L.r};
+    } else {
+      a = {tp.be, tp.bf, nullptr};
+    }
+    return a;
+  };
+  // one cell's update: colour's cell of pair p of row (j, k)
+  auto update = [&](const FlatOp<T>& op, const TailArr<T>& A, const Coef<T, 1>& c, int colour,
+                    int p, int j, int k, bool zg, const FlatDims* cd, const T* ec) {
+    const FlatDims& d = op.d;
+    const int s = (j + k + colour) & 1;
+    const int at = p + d.sp * (j + d.ny * k);
+    const T diag = diag_of<T, 1>(op, c, 0, s, p, j, k);
+    T off = T(0);
+    if (!zg) {
+      Nb<T, 1> n;
+      load_nb<T, 1>(n, d, A.e + (1 - colour) * d.half, s, p, j, k, row_ix(d, j, k));
+      if (ec) {
+        Par<T, 1> q;
+        load_par<T, 1>(q, d, *cd, ec, s, p, j, k);
+        add_par<T, 1>(n, q, s, j, k);
+      }
+      off = off_of<T, 1>(op, c, n, 0, s, p, j, k);
+    }
+    const T fv = A.f[colour * d.half + at];
+    A.e[colour * d.half + at] = (zg ? fv : fv + off) / diag;
+  };
+  // both colours' coefficients of the lane's pair, kept while the level fits
+  // one pair per lane
+  struct Mine {
+    Coef<T, 1> c[2];
+    int p, j, k;
+  };
+  auto mine = [&](const FlatOp<T>& op, int q) {
+    Mine m;
+    const FlatDims& d = op.d;
+    const int t = q / d.np;
+    m.p = q - t * d.np;
+    m.k = t / d.ny;
+    m.j = t - m.k * d.ny;
+    for (int c = 0; c < 2; ++c)
+      load_coef<T, 1, false>(m.c[c], op, c, (m.j + m.k + c) & 1, m.p, m.j, m.k);
+    return m;
+  };
+  auto half = [&](const FlatOp<T>& op, const TailArr<T>& A, const Mine& own, bool one, int npair,
+                  int colour, bool zg, const FlatDims* cd, const T* ec) {
+    if (one) {
+      if (tid < npair) update(op, A, own.c[colour], colour, own.p, own.j, own.k, zg, cd, ec);
+    } else {
+      for (int q = tid; q < npair; q += nt) {
+        const Mine m = mine(op, q);
+        update(op, A, m.c[colour], colour, m.p, m.j, m.k, zg, cd, ec);
+      }
+    }
+    __syncthreads();
+  };
+  if (LDS) {
+    // the first level's right-hand side
+    const FlatDims& d = tp.lev[0].op.d;
+    const TailArr<T> A = arr(0);
+    for (int e = tid; e < 2 * d.half; e += nt) A.f[e] = tp.lev[0].f[e];
+    __syncthreads();
+  }
+  for (int l = 0; l < tp.nlev; ++l) {
+    const FlatOp<T>& op = tp.lev[l].op;
+    const FlatDims& d = op.d;
+    const TailArr<T> A = arr(l), C = arr(l + 1);
+    const int npair = d.np * d.ny * d.nz;
+    const bool one = npair <= nt;
+    Mine own;
+    if (one && tid < npair) own = mine(op, tid);
+    for (int k = 0; k < tp.nu1; ++k) {
+      half(op, A, own, one, npair, 0, k == 0, nullptr, nullptr);
+      half(op, A, own, one, npair, 1, false, nullptr, nullptr);
+    }
+    // residual of the red cells (the black ones' is zero)
+    for (int q = tid; q < npair; q += nt) {
+      const Mine m = one ? own : mine(op, q);
+      const int s = (m.j + m.k) & 1, at = m.p + d.sp * (m.j + d.ny * m.k);
+      Nb<T, 1> n;
+      load_nb<T, 1>(n, d, A.e + d.half, s, m.p, m.j, m.k, row_ix(d, m.j, m.k));
+      A.r[at] = resid_of(A.f[at], diag_of<T, 1>(op, m.c[0], 0, s, m.p, m.j, m.k), A.e[at],
+                         off_of<T, 1>(op, m.c[0], n, 0, s, m.p, m.j, m.k));
+    }
+    __syncthreads();
+    const FlatDims& cd = l + 1 < tp.nlev ? tp.lev[l + 1 < kTailMaxLevels ? l + 1 : 0].op.d : tp.bd;
+    const int ncell = cd.nx * cd.ny * cd.nz;
+    for (int q = tid; q < ncell; q += nt) {
+      const int t = q / cd.nx, I = q - t * cd.nx, K = t / cd.ny, J = t - K * cd.ny;
+      const int b = I + d.sp * (2 * J + d.ny * 2 * K);
+      const int bz = d.sp * d.ny;
+      const T z0 = A.r[b] + A.r[b + d.sp];
+      const T z1 = A.r[b + bz] + A.r[b + bz + d.sp];
+      C.f[((I + J + K) & 1) * cd.half + (I >> 1) + cd.sp * (J + cd.ny * K)] = (z0 + z1) * T(0.125);
+    }
+    __syncthreads();
+  }
+  {
+    const TailArr<T> B = arr(tp.nlev);
+    T* p = LDS ? B.f + 2 * tp.bd.half : lds;
+    const BottomTables& bt = tp.bt;
+    if (bt.n <= 64) {
+      if (tid < 64)
+        cg_lds_run<T, 1, true>(bt, tp.bdiag, tp.bcoef, B.f, B.e, 0, tp.tol, tp.maxiter,
+                               tp.singular, tp.iters, p, red, 64, 1);
+    } else {
+      cg_lds_run<T, 1>(bt, tp.bdiag, tp.bcoef, B.f, B.e, 0, tp.tol, tp.maxiter, tp.singular,
+                       tp.iters, p, red, nt, (bt.n + 63) / 64);
+    }
+  }
+  __syncthreads();
+  const int c0 = tp.reverse ? 1 : 0;
+  for (int l = tp.nlev - 1; l >= 0; --l) {
+    const FlatOp<T>& op = tp.lev[l].op;
+    const FlatDims& d = op.d;
+    const TailArr<T> A = arr(l), C = arr(l + 1);
+    const FlatDims& cd = l + 1 < tp.nlev ? tp.lev[l + 1 < kTailMaxLevels ? l + 1 : 0].op.d : tp.bd;
+    const int npair = d.np * d.ny * d.nz;
+    const bool one = npair <= nt;
+    Mine own;
+    if (one && tid < npair) own = mine(op, tid);
+    for (int k = 0; k < tp.nu2; ++k) {
+      half(op, A, own, one, npair, c0, false, k == 0 ? &cd : nullptr, k == 0 ? C.e : nullptr);
+      half(op, A, own, one, npair, 1 - c0, false, nullptr, nullptr);
+    }
+  }
+  if (LDS) {
+    const FlatDims& d = tp.lev[0].op.d;
+    const TailArr<T> A = arr(0);
+    for (int q = tid; q < d.np * d.ny * d.nz; q += nt) {
+      const int t = q / d.np, at = q - t * d.np + d.sp * t;
+      tp.lev[0].e[at] = A.e[at];
+      tp.lev[0].e[d.half + at] = A.e[d.half + at];
+    }
+  }
+}
+
+// Lanes along x for `width` work items per row: the smallest power of two that
+// covers them, at most a wavefront (a wavefront's loads are then one run).
+Grid2 grid_of(int width, int rows, int reverse) {
+  Grid2 g;
+  g.lxl = 0;
+  while (g.lxl < 6 && (1 << g.lxl) < width) ++g.lxl;
+  const int lx = 1 << g.lxl, ly = 256 / lx;
+  g.nbx = (width + lx - 1) / lx;
+  g.nb = g.nbx * ((rows + ly - 1) / ly);
+  g.reverse = reverse;
+  return g;
+}
+
+// Pairs per lane: two FP64 or four FP32 make 16-byte loads.  One where a
+// periodic row is no multiple of that (the group's last neighbour wraps), and
+// on levels too small to fill the chip that way.
+template <typename T>
+int flat_width(const FlatDims& d) {
+  const int v = 16 / (int)sizeof(T);
+  if (!(d.wall & 2) && d.np % v) return 1;
+  return (long long)d.np * d.ny * d.nz >= v * 262144ll ? v : 1;
+}
+
+int vec_blocks(long long n) { return (int)std::min<long long>((n + 511) / 512, 4096); }
+
+// Rows of at least a cache line start on one; shorter rows (whole levels of
+// which the tail keeps in LDS) on 16 bytes.
+int flat_pitch(int nx, int elem) {
+  const int need = nx / 2 + 1, to = need >= 128 / elem ? 128 / elem : 16 / elem;
+  return (need + to - 1) / to * to;
+}
+
+}  // namespace
+
+FlatDims flat_dims(const int n[3], const int periodic[3], int elem) {
+  FlatDims d;
+  d.nx = n[0];
+  d.ny = n[1];
+  d.nz = n[2];
+  d.np = (n[0] + 1) / 2;
+  const int line = 128 / elem;
+  d.sp = flat_pitch(n[0], elem);
+  d.wall = 0;
+  for (int a = 0; a < 3; ++a)
+    if (!periodic[a]) d.wall |= 3 << (2 * a);
+  // past the end: the widest load that starts inside a row
+  auto up = [&](long long v) { return (int)((v + line + 63) / 64 * 64); };
+  d.half = up((long long)d.sp * d.ny * d.nz);
+  d.yh = up((long long)d.sp * (d.ny + 1) * d.nz);
+  d.zh = up((long long)d.sp * d.ny * (d.nz + 1));
+  return d;
+}
+
+bool flat_fits(const int n[3], int elem) {
+  const int line = 128 / elem;
+  const long long sp = flat_pitch(n[0], elem);
+  return 2 * (sp * (n[1] + 1) * (n[2] + 1) + line + 64) < (1ll << 31);
+}
+
+template <typename T>
+hipError_t launch_flat_half(hipStream_t st, const FlatOp<T>& op, FlatPass ps, const T* other,
+                            T* out, const T* f, int colour, bool zero_guess, const FlatDims* cd,
+                            const T* ec, const T* old, unsigned long long* normbits) {
+  const FlatDims c = cd ? *cd : FlatDims{};
+  const int V = flat_width<T>(op.d);
+  const Grid2 g = grid_of((op.d.np + V - 1) / V, op.d.ny * op.d.nz, ps.reverse);
+#define FH2(W, ZG, PE, SP, NT)                                                                 \
+  hipLaunchKernelGGL((k_flat_half<T, W, ZG, PE, SP, NT>), dim3(g.nb), dim3(256), 0, st, op, g, \
+                     other, out, f, colour, c, ec, old, normbits)
+#define FH1(W, NT)                                                                 \
+  if (zero_guess) FH2(W, true, false, false, NT);                                  \
+  else if (ec) FH2(W, false, true, false, NT);                                     \
+  else if (old) FH2(W, false, false, true, NT);                                    \
+  else FH2(W, false, false, false, NT)
+  constexpr int W = 16 / sizeof(T);
+  if (V == 1) {
+    FH1(1, false);
+  } else if (ps.stream) {
+    FH1(W, true);
+  } else {
+    FH1(W, false);
+  }
+#undef FH1
+#undef FH2
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_flat_restrict(hipStream_t st, const FlatOp<T>& op, FlatPass ps, const T* v,
+                                const T* f, const FlatDims& cd, T* cf) {
+  if (cd.nx != op.d.np || 2 * cd.ny != op.d.ny || 2 * cd.nz != op.d.nz || 2 * cd.nx != op.d.nx)
+    return hipErrorInvalidValue;
+  const Grid2 g = grid_of(op.d.np, cd.ny * cd.nz, ps.reverse);
+  if (ps.stream)
+    hipLaunchKernelGGL((k_flat_restrict<T, true>), dim3(g.nb), dim3(256), 0, st, op, g, v, f, cd,
+                       cf);
+  else
+    hipLaunchKernelGGL((k_flat_restrict<T, false>), dim3(g.nb), dim3(256), 0, st, op, g, v, f, cd,
+                       cf);
+  return hipGetLastError();
+}
+
+int flat_resid_blocks(const FlatDims& d) { return grid_of(d.np, d.ny * d.nz, 0).nb; }
+
+template <typename T, typename TO>
+hipError_t launch_flat_resid(hipStream_t st, const FlatOp<T>& op, FlatPass ps, const T* v,
+                             const T* f, TO* out, unsigned long long* normbits, double* dots) {
+  const Grid2 g = grid_of(op.d.np, op.d.ny * op.d.nz, ps.reverse);
+  if (ps.stream)
+    hipLaunchKernelGGL((k_flat_resid<T, TO, 1, true>), dim3(g.nb), dim3(256), 0, st, op, g, v, f,
+                       out, normbits, dots);
+  else
+    hipLaunchKernelGGL((k_flat_resid<T, TO, 1, false>), dim3(g.nb), dim3(256), 0, st, op, g, v, f,
+                       out, normbits, dots);
+  return hipGetLastError();
+}
+
+static dim3 box_grid(int nbox, int cells) {
+  return dim3(std::min((cells + 1023) / 1024, 1024), nbox);
+}
+
+hipError_t launch_flat_gather(hipStream_t st, const BoxInfo* boxes, int nbox, int max_cells,
+                              const int lo[3], const FlatDims& d, const double* src, int ng,
+                              double* dst, unsigned long long* normbits) {
+  hipLaunchKernelGGL((k_flat_boxes<true>), box_grid(nbox, max_cells), dim3(256), 0, st, boxes,
+                     make_int3(lo[0], lo[1], lo[2]), d, src, dst, ng, normbits);
+  return hipGetLastError();
+}
+
+hipError_t launch_flat_scatter(hipStream_t st, const BoxInfo* boxes, int nbox, int max_cells,
+                               const int lo[3], const FlatDims& d, const double* src, double* dst,
+                               int ng) {
+  hipLaunchKernelGGL((k_flat_boxes<false>), box_grid(nbox, max_cells), dim3(256), 0, st, boxes,
+                     make_int3(lo[0], lo[1], lo[2]), d, src, dst, ng, nullptr);
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_flat_faces(hipStream_t st, const BoxInfo* boxes, int nbox, int max_faces,
+                             const int lo[3], const FlatDims& d, int dir, const T* b, T beta, T ih,
+                             T* dst) {
+  hipLaunchKernelGGL((k_flat_faces<T>), box_grid(nbox, max_faces), dim3(256), 0, st, boxes,
+                     make_int3(lo[0], lo[1], lo[2]), d, dir, b, beta, ih, dst);
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_flat_acoef(hipStream_t st, const BoxInfo* boxes, int nbox, int max_cells,
+                             const int lo[3], const FlatDims& d, const T* a, T alpha, T* dst) {
+  hipLaunchKernelGGL((k_flat_acoef<T>), box_grid(nbox, max_cells), dim3(256), 0, st, boxes,
+                     make_int3(lo[0], lo[1], lo[2]), d, a, alpha, dst);
+  return hipGetLastError();
+}
+
+template <typename TZ>
+hipError_t launch_flat_dot(hipStream_t st, long long n, const double* a, const TZ* z,
+                           double* partials, double* out) {
+  const int nb = std::min(vec_blocks(n), kFlatDotBlocks);
+  hipLaunchKernelGGL((k_flat_dot<TZ>), dim3(nb), dim3(256), 0, st, n, a, z, partials);
+  const hipError_t e = hipGetLastError();
+  return e != hipSuccess ? e : launch_sum_final(st, partials, nb, out);
+}
+
+template <typename TZ>
+hipError_t launch_flat_cg_p(hipStream_t st, long long n, double* p, const TZ* z,
+                            const double* num, const double* den, int first) {
+  hipLaunchKernelGGL((k_flat_cg_p<TZ>), dim3(vec_blocks(n)), dim3(256), 0, st, n, p, z, num, den,
+                     first);
+  return hipGetLastError();
+}
+
+hipError_t launch_flat_cg_xr(hipStream_t st, long long n, double* x, const double* p, double* r,
+                             const double* q, const double* num, const double* den,
+                             unsigned long long* normbits, float* r32) {
+  hipLaunchKernelGGL(k_flat_cg_xr, dim3(vec_blocks(n)), dim3(256), 0, st, n, x, p, r, q, num, den,
+                     normbits, r32);
+  return hipGetLastError();
+}
+
+hipError_t launch_flat_update(hipStream_t st, long long n, double* v, const float* e) {
+  hipLaunchKernelGGL(k_flat_update, dim3(vec_blocks(n)), dim3(256), 0, st, n, v, e);
+  return hipGetLastError();
+}
+
+hipError_t launch_flat_remove_mean(hipStream_t st, const FlatDims& d, double* v, double* partials,
+                                   double* sum) {
+  const long long n = 2ll * d.half;
+  const int nb = std::min(vec_blocks(n), kFlatDotBlocks);
+  hipLaunchKernelGGL(k_flat_sum, dim3(nb), dim3(256), 0, st, n, v, partials);
+  hipError_t e = hipGetLastError();
+  if (e == hipSuccess) e = launch_sum_final(st, partials, nb, sum);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_flat_shift, dim3(vec_blocks(d.half), 2), dim3(256), 0, st, d, v, sum);
+  return hipGetLastError();
+}
+
+hipError_t launch_flat_maxabs(hipStream_t st, long long n, const double* v,
+                              unsigned long long* normbits) {
+  hipLaunchKernelGGL(k_flat_maxabs, dim3(vec_blocks(n)), dim3(256), 0, st, n, v, normbits);
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_flat_tail(hipStream_t st, const FlatTail<T>& t) {
+  if (t.nlev < 1 || t.nlev > kTailMaxLevels || t.bt.n < 1 || t.bt.n > kTailMaxBottom)
+    return hipErrorInvalidValue;
+  long long el = 4ll * t.bd.half + t.bt.n;
+  for (int l = 0; l < t.nlev; ++l) el += tail_elems(t.lev[l].op.d);
+  if (el * (long long)sizeof(T) <= 60 * 1024) {
+    hipLaunchKernelGGL((k_flat_tail<T, true>), dim3(1), dim3(kTailLanes), el * sizeof(T), st, t);
+  } else {
+    hipLaunchKernelGGL((k_flat_tail<T, false>), dim3(1), dim3(kTailLanes), t.bt.n * sizeof(T), st,
+                       t);
+  }
+  return hipGetLastError();
+}
+
+#define INST(T)                                                                                    \
+  template hipError_t launch_flat_half<T>(hipStream_t, const FlatOp<T>&, FlatPass, const T*, T*,   \
+                                          const T*, int, bool, const FlatDims*, const T*,          \
+                                          const T*, unsigned long long*);                          \
+  template hipError_t launch_flat_restrict<T>(hipStream_t, const FlatOp<T>&, FlatPass, const T*,   \
+                                              const T*, const FlatDims&, T*);                      \
+  template hipError_t launch_flat_faces<T>(hipStream_t, const BoxInfo*, int, int, const int*,      \
+                                           const FlatDims&, int, const T*, T, T, T*);              \
+  template hipError_t launch_flat_acoef<T>(hipStream_t, const BoxInfo*, int, int, const int*,      \
+                                           const FlatDims&, const T*, T, T*);                      \
+  template hipError_t launch_flat_dot<T>(hipStream_t, long long, const double*, const T*, double*, \
+                                         double*);                                                 \
+  template hipError_t launch_flat_cg_p<T>(hipStream_t, long long, double*, const T*,               \
+                                          const double*, const double*, int);                      \
+  template hipError_t launch_flat_tail<T>(hipStream_t, const FlatTail<T>&);
+
+INST(double)
+INST(float)
+#undef INST
+
+template hipError_t launch_flat_resid<double, double>(hipStream_t, const FlatOp<double>&, FlatPass,
+                                                      const double*, const double*, double*,
+                                                      unsigned long long*, double*);
+template hipError_t launch_flat_resid<double, float>(hipStream_t, const FlatOp<double>&, FlatPass,
+                                                     const double*, const double*, float*,
+                                                     unsigned long long*, double*);
+
+}  // namespace amrmg

@@ -17,6 +17,7 @@
 #include <mutex>
 #include <type_traits>
 
+#include "device.hpp"
 #include "kernels.hpp"
 
 namespace amrmg {
@@ -36,35 +37,6 @@ __device__ __forceinline__ long long cidx(const BoxDims& d, int ng, int il, int 
   const long long sy = d.nx + 2 * ng;
   const long long sz = sy * (d.ny + 2 * ng);
   return (il + ng) + sy * (jl + ng) + sz * (kl + ng);
-}
-
-__device__ __forceinline__ unsigned long long absbits(double v) {
-  return (unsigned long long)__double_as_longlong(fabs(v));
-}
-__device__ __forceinline__ unsigned long long absbits(float v) { return absbits((double)v); }
-
-// Fold a per-lane value into the norm slot at dst as an unsigned max over
-// the block, into the block's way of the slot (kNormWays words on separate
-// cache lines, so the blocks of a launch do not all meet on one line).  The
-// block's atomic is skipped when its way already holds at least its value:
-// a way only grows, so a value read at any time that is >= m makes the
-// atomic a no-op.
-__device__ void block_max_u64(unsigned long long v, unsigned long long* dst) {
-  dst += kNormStride * (blockIdx.x % kNormWays);
-  __shared__ unsigned long long red[16];
-  for (int o = 32; o > 0; o >>= 1) {
-    unsigned long long w = (unsigned long long)__shfl_xor((long long)v, o);
-    v = w > v ? w : v;
-  }
-  const int tid = threadIdx.x + blockDim.x * threadIdx.y;
-  const int nw = (blockDim.x * blockDim.y + 63) / 64;
-  if ((tid & 63) == 0) red[tid >> 6] = v;
-  __syncthreads();
-  if (tid == 0) {
-    unsigned long long m = red[0];
-    for (int w = 1; w < nw; ++w) m = red[w] > m ? red[w] : m;
-    if (m > __hip_atomic_load(dst, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(dst, m);
-  }
 }
 
 // floor(a / 2) for any sign: the coarse index of fine index a.
@@ -946,8 +918,6 @@ __global__ void __launch_bounds__(256)
   P[pc] = (v.f + c.off) / c.diag;
 }
 
-__device__ double block_sum(double v, double* red, int& phase);
-
 // out = rhs - A phi (mode 0) or A phi (mode 1), one lane per cell, U planes
 // gathered at a time; optional NaN-propagating max |out|.
 // NX (mode 0): also write phi after a red half-sweep into pnext (same ghost
@@ -1220,26 +1190,6 @@ __global__ void __launch_bounds__(256)
   const int kend = min(t.z0 + tz - 1, B.hi[2]);
   T* V = v + (ng ? B.off_g1 : B.off_g0);
   for (int k = t.z0; k <= kend; ++k) V[cidx(d, ng, i - B.lo[0], j - B.lo[1], k - B.lo[2])] = T(0);
-}
-
-// Block sum in a fixed order: lanes by butterfly (every lane ends with the
-// same bits), then the first nw waves in index order (every wave of the
-// work-group takes part in the barrier; later waves' sums are left out).
-__device__ double block_sum_w(double v, double* red, int& phase, int nw) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  const int tid = threadIdx.x + blockDim.x * threadIdx.y;
-  double* buf = red + phase * 16;
-  phase ^= 1;
-  if ((tid & 63) == 0) buf[tid >> 6] = v;
-  __syncthreads();
-  double s = buf[0];
-  for (int w = 1; w < nw; ++w) s += buf[w];
-  return s;
-}
-
-// ... over every wave of the work-group.
-__device__ double block_sum(double v, double* red, int& phase) {
-  return block_sum_w(v, red, phase, (blockDim.x * blockDim.y + 63) / 64);
 }
 
 __global__ void __launch_bounds__(256)
@@ -2108,157 +2058,6 @@ __global__ void __launch_bounds__(256)
 // neighbours): an iteration then reads nothing but LDS.  The work-group is
 // sized to the bottom level (one wavefront for 64 cells), so its reductions
 // cross few wavefronts.  Same arithmetic per cell as k_bottom_cg.
-// The body runs on any work-group: lanes stride the cells by nt (lane l owns
-// l, l+nt, ...), the dot products add the first nw waves' sums, and every
-// wave takes part in the barriers (lanes past the cells hold zeros).  p:
-// n values of LDS.
-// The CG's sums and barriers.  ONE_WAVE: the CG runs in wavefront 0 alone
-// (n <= 64, lanes 0..63): the butterfly leaves the sum in every lane (the
-// value the work-group form reads back for one wave) and LDS needs only
-// wave-level ordering.
-template <bool ONE_WAVE>
-__device__ __forceinline__ double cg_sum(double v, double* red, int& phase, int nw) {
-  if (ONE_WAVE) {
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    return v;
-  }
-  return block_sum_w(v, red, phase, nw);
-}
-
-template <bool ONE_WAVE>
-__device__ __forceinline__ void cg_sync() {
-  if (ONE_WAVE) {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  } else {
-    __syncthreads();
-  }
-}
-
-template <typename T, int CPT, bool ONE_WAVE = false>
-__device__ __forceinline__ void cg_lds_run(const BottomTables& bt, const T* __restrict__ diag,
-                                           const T* __restrict__ coef, const T* __restrict__ rhs,
-                                           T* __restrict__ out, int accumulate, double tol,
-                                           int maxiter, int singular, int* iters_out, T* p,
-                                           double* red, int nt, int nw) {
-  // no multiply-add fusion: whether the compiler fuses a product into an
-  // addition depends on the code around it, and the work-group and the
-  // one-wavefront forms (and every kernel that runs this body) must round
-  // the same way
-#pragma clang fp contract(off)
-  int phase = 0;
-  const int n = bt.n;
-  const int tid = threadIdx.x;
-  // stencil in registers up to two cells per lane (more would spill)
-  constexpr bool REG = CPT <= 2;
-  constexpr int RC = REG ? CPT : 1;
-  T x[CPT], r[CPT], q[CPT], dg[RC], cf[RC][6];
-  int nb[RC][6];
-  double s = 0.0;
-#pragma unroll
-  for (int m = 0; m < CPT; ++m) {
-    const int c = tid + m * nt;
-    x[m] = T(0);
-    r[m] = T(0);
-    if (c < n) {
-      r[m] = rhs[bt.map_rhs[c]];
-      s += (double)r[m];
-    }
-    if (REG) {
-      dg[m % RC] = c < n ? diag[c] : T(1);
-      for (int f = 0; f < 6; ++f) {
-        nb[m % RC][f] = c < n ? bt.nbr[f * n + c] : -1;
-        cf[m % RC][f] = c < n ? coef[f * n + c] : T(0);
-      }
-    }
-  }
-  if (singular) {
-    s = cg_sum<ONE_WAVE>(s, red, phase, nw);
-    const T mean = (T)(s / n);
-#pragma unroll
-    for (int m = 0; m < CPT; ++m)
-      if (tid + m * nt < n) r[m] = r[m] - mean;
-  }
-  s = 0.0;
-#pragma unroll
-  for (int m = 0; m < CPT; ++m) s += (double)r[m] * (double)r[m];
-  double rho = cg_sum<ONE_WAVE>(s, red, phase, nw);
-  const double bnorm = sqrt(rho);
-  int it = 0;
-  if (bnorm > 0.0) {
-#pragma unroll
-    for (int m = 0; m < CPT; ++m)
-      if (tid + m * nt < n) p[tid + m * nt] = r[m];
-    while (it < maxiter) {
-      cg_sync<ONE_WAVE>();
-      s = 0.0;
-#pragma unroll
-      for (int m = 0; m < CPT; ++m) {
-        const int c = tid + m * nt;
-        q[m] = T(0);
-        if (c < n) {
-          T off = T(0);
-          if (REG) {
-#pragma unroll
-            for (int f = 0; f < 6; ++f)
-              off = off + (nb[m % RC][f] < 0 ? T(0) : cf[m % RC][f] * p[nb[m % RC][f]]);
-            q[m] = dg[m % RC] * p[c] - off;
-          } else {
-            for (int f = 0; f < 6; ++f) {
-              const int k = bt.nbr[f * n + c];
-              off = off + (k < 0 ? T(0) : coef[f * n + c] * p[k]);
-            }
-            q[m] = diag[c] * p[c] - off;
-          }
-          s += (double)p[c] * (double)q[m];
-        }
-      }
-      const double pq = cg_sum<ONE_WAVE>(s, red, phase, nw);
-      const T alT = (T)(rho / pq);
-      s = 0.0;
-#pragma unroll
-      for (int m = 0; m < CPT; ++m) {
-        const int c = tid + m * nt;
-        if (c < n) {
-          x[m] = x[m] + alT * p[c];
-          r[m] = r[m] - alT * q[m];
-          s += (double)r[m] * (double)r[m];
-        }
-      }
-      ++it;
-      const double rho_new = cg_sum<ONE_WAVE>(s, red, phase, nw);
-      if (!(sqrt(rho_new) > tol * bnorm)) break;
-      const T btT = (T)(rho_new / rho);
-#pragma unroll
-      for (int m = 0; m < CPT; ++m) {
-        const int c = tid + m * nt;
-        if (c < n) p[c] = r[m] + btT * p[c];
-      }
-      rho = rho_new;
-    }
-  }
-  if (singular) {
-    s = 0.0;
-#pragma unroll
-    for (int m = 0; m < CPT; ++m)
-      if (tid + m * nt < n) s += (double)x[m];
-    s = cg_sum<ONE_WAVE>(s, red, phase, nw);
-    const T mean = (T)(s / n);
-#pragma unroll
-    for (int m = 0; m < CPT; ++m) x[m] = x[m] - mean;
-  }
-#pragma unroll
-  for (int m = 0; m < CPT; ++m) {
-    const int c = tid + m * nt;
-    if (c < n) {
-      const long long o = bt.map_out[c];
-      out[o] = accumulate ? out[o] + x[m] : x[m];
-    }
-  }
-  if (tid == 0) *iters_out = it;
-}
-
 template <typename T, int CPT>
 __global__ void __launch_bounds__(1024)
     k_bottom_cg_lds(BottomTables bt, const T* __restrict__ diag, const T* __restrict__ coef,

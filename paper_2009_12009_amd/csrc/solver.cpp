@@ -29,6 +29,7 @@
 #include <vector>
 
 #include "../../include/amrmg.h"
+#include "flat.hpp"
 #include "host.hpp"
 #include "kernels.hpp"
 #include "tables.hpp"
@@ -156,6 +157,16 @@ struct Level {
   unsigned *d_tcells = nullptr, *d_trc = nullptr;
 };
 
+// A level in the split-colour layout (flat.hpp): operator, correction,
+// right-hand side, and the red residual where the tail keeps it in memory.
+template <typename T>
+struct FlatLevel {
+  FlatOp<T> op{};
+  T *x = nullptr, *y = nullptr, *z = nullptr, *a = nullptr;
+  T *e = nullptr, *f = nullptr, *r = nullptr;
+  int stream = 0;
+};
+
 struct ProfRec {
   int fam;
   hipEvent_t a, b;
@@ -190,6 +201,19 @@ struct mg_solver {
   double* d_sum = nullptr;
   double* d_partials = nullptr;
   double* tune_scratch = nullptr;
+  // the solve's own storage: every level in the split-colour layout (flat_on)
+  bool flat = false;
+  std::vector<FlatLevel<double>> f64;  // FP32 refinement: level 0 only
+  std::vector<FlatLevel<float>> f32;
+  int flat_tail = -1;  // first level of the one-launch tail (-1: none)
+  double* fphi[2] = {nullptr, nullptr};  // iterates of the folded stop test; FP32: fphi[0]
+  double* frhs = nullptr;
+  double *fr = nullptr, *fp = nullptr, *fq = nullptr, *fz = nullptr;  // preconditioned CG
+  double* fpart = nullptr;
+  std::vector<int> h_fmap_rhs, h_fmap_out;
+  int *d_fmap_rhs = nullptr, *d_fmap_out = nullptr;
+  char* flat_base = nullptr;
+  size_t flat_bytes = 0;
   // runtime
   char* ws = nullptr;
   size_t ws_bytes = 0, ws_need = 0;
@@ -551,7 +575,110 @@ bool make_wt_tables(Level& lv, const int periodic[3]) {
 // cycle's first half-sweep (needs the level hierarchy: call after it is set).
 bool stop_fold_on(const mg_solver* s) {
   return s->opts.stop_fold && s->opts.precision == MG_PREC_F64 && !s->opts.krylov &&
-         !s->composite && s->opts.nu1 >= 1 && s->L.size() > 1 && !s->L[0].fused;
+         !s->composite && s->opts.nu1 >= 1 && s->L.size() > 1 && !s->L[0].fused && !s->flat;
+}
+
+// Whether mg_solve keeps its levels in the split-colour layout: a hierarchy
+// with smoothing on both sides of the coarse correction whose smoothed levels
+// have even extents and even low corners (true of every level that has been
+// coarsened by 2; it makes the colours alternate across periodic wraps and a
+// pair's parent its own index) and fit 32-bit element offsets.  Otherwise - a
+// single level, nu1 or nu2 = 0, the composite solve - levels stay lists of
+// boxes.
+bool flat_on(const mg_solver* s) {
+  if (s->L.size() < 2 || s->composite || s->opts.nu1 < 1 || s->opts.nu2 < 1) return false;
+  for (size_t l = 0; l + 1 < s->L.size(); ++l)
+    for (int d = 0; d < 3; ++d)
+      if (ext(s->L[l].domain, d) % 2 || s->L[l].domain.lo[d] % 2 ||
+          ext(s->L[l + 1].domain, d) * 2 != ext(s->L[l].domain, d))
+        return false;
+  const IBox& D = s->L[0].domain;
+  const int n[3] = {ext(D, 0), ext(D, 1), ext(D, 2)};
+  return flat_fits(n, 8) && flat_fits(n, 4);
+}
+
+// The first level of the tail: the levels from it to a CG bottom of at most
+// kTailMaxBottom cells hold at most opts.coarse_tail cells each.
+int flat_tail_level(const mg_solver* s) {
+  const int nl = (int)s->L.size();
+  if (s->opts.coarse_tail <= 0 || nl < 3 || s->opts.bottom_solver != 0 ||
+      s->L.back().ncell > kTailMaxBottom)
+    return -1;
+  int start = nl - 1;
+  while (start > 1 && nl - start < kTailMaxLevels + 1 &&
+         s->L[start - 1].ncell <= s->opts.coarse_tail)
+    --start;
+  return start < nl - 1 ? start : -1;
+}
+
+template <typename T>
+std::vector<FlatLevel<T>>& flat_levels(mg_solver* s);
+template <>
+std::vector<FlatLevel<double>>& flat_levels<double>(mg_solver* s) { return s->f64; }
+template <>
+std::vector<FlatLevel<float>>& flat_levels<float>(mg_solver* s) { return s->f32; }
+
+// Arrays of one level (bottom: correction and right-hand side only; ef:
+// whether it has those).
+template <typename T>
+void layout_flat(mg_solver* s, size_t l, bool ef, Bump& bump) {
+  std::vector<FlatLevel<T>>& F = flat_levels<T>(s);
+  if (F.size() <= l) F.resize(l + 1);
+  FlatLevel<T>& v = F[l];
+  const IBox& D = s->L[l].domain;
+  const int n[3] = {ext(D, 0), ext(D, 1), ext(D, 2)};
+  // FP32 refinement: FP64's level 0 has the FP32 arrays' row pitch
+  v.op.d = flat_dims(n, s->periodic, s->opts.precision == MG_PREC_F32_REFINE ? 4 : sizeof(T));
+  const FlatDims& d = v.op.d;
+  // the arrays of a half-sweep against the 256 MiB last-level cache
+  v.stream = 4.5 * sizeof(T) * (double)s->L[l].ncell > 256.0 * (1 << 20) ? 1 : 0;
+  if (l + 1 < s->L.size()) {
+    v.x = bump.take<T>(2 * (size_t)d.half);
+    v.y = bump.take<T>(2 * (size_t)d.yh);
+    v.z = bump.take<T>(2 * (size_t)d.zh);
+    if (s->has_a) v.a = bump.take<T>(2 * (size_t)d.half);
+    if (s->flat_tail >= 1 && (int)l >= s->flat_tail) v.r = bump.take<T>(d.half);
+  }
+  if (ef) {
+    v.e = bump.take<T>(2 * (size_t)d.half);
+    v.f = bump.take<T>(2 * (size_t)d.half);
+  }
+  v.op.x = v.x;
+  v.op.y = v.y;
+  v.op.z = v.z;
+  v.op.a = v.a;
+}
+
+void layout_flat_all(mg_solver* s, Bump& bump) {
+  const bool f32 = s->opts.precision == MG_PREC_F32_REFINE;
+  s->f64.clear();
+  s->f32.clear();
+  s->flat_base = bump.take<char>(0);
+  const size_t from = bump.off;
+  for (size_t l = 0; l < s->L.size(); ++l) {
+    if (!f32 || l == 0) layout_flat<double>(s, l, !f32 && (l > 0 || s->opts.krylov), bump);
+    if (f32) layout_flat<float>(s, l, true, bump);
+  }
+  const size_t n = 2 * (size_t)s->f64[0].op.d.half;
+  s->frhs = bump.take<double>(n);
+  s->fphi[0] = bump.take<double>(n);
+  if (!f32 && !s->opts.krylov) s->fphi[1] = bump.take<double>(n);
+  if (s->opts.krylov) {
+    // FP64: the V-cycle's right-hand side and result are r and z
+    if (f32) {
+      s->fr = bump.take<double>(n);
+      s->fz = bump.take<double>(n);
+    } else {
+      s->fr = s->f64[0].f;
+      s->fz = s->f64[0].e;
+    }
+    s->fp = bump.take<double>(n);
+    s->fq = bump.take<double>(n);
+  }
+  s->fpart = bump.take<double>(std::max(kFlatDotBlocks, flat_resid_blocks(s->f64[0].op.d)));
+  s->flat_bytes = bump.off - from;
+  s->d_fmap_rhs = bump.take<int>(s->nb);
+  s->d_fmap_out = s->d_fmap_rhs;  // same layout of both
 }
 
 // LDS bytes of the tail kernel starting at level t: the bottom CG's p (FP64
@@ -779,6 +906,9 @@ int build_plan(mg_solver* s, const std::vector<IBox>& boxes, Bump& bump) {
     c.fold_rs = l >= 2;
   }
 
+  s->flat = flat_on(s);
+  s->flat_tail = s->flat ? flat_tail_level(s) : -1;
+
   // the level-0 residual restricts as it goes: every level-0 box splits
   // into whole 2x2x2 blocks (true whenever there is a level 1)
   s->rr_fold = s->L.size() >= 2 && s->opts.restrict_fold >= 1 && !s->composite;
@@ -797,8 +927,12 @@ int build_plan(mg_solver* s, const std::vector<IBox>& boxes, Bump& bump) {
   s->h_aidx.assign(nb, 0);
   s->h_map_rhs.assign(nb, 0);
   s->h_map_out.assign(nb, 0);
+  s->h_fmap_rhs.assign(s->flat ? nb : 0, 0);
+  FlatDims fb{};
   {
     const IBox& D = bl.domain;
+    const int n3[3] = {ext(D, 0), ext(D, 1), ext(D, 2)};
+    fb = flat_dims(n3, s->periodic, s->opts.precision == MG_PREC_F32_REFINE ? 4 : 8);
     const int gn[3] = {ext(D, 0), ext(D, 1), ext(D, 2)};
     std::vector<int> gmap((size_t)gn[0] * gn[1] * gn[2], -1);
     int c = 0;
@@ -834,6 +968,10 @@ int build_plan(mg_solver* s, const std::vector<IBox>& boxes, Bump& bump) {
             s->h_map_rhs[c] = (int)(I.off_g0 + g0);
             s->h_map_out[c] =
                 (int)(I.off_g1 + (il + 1) + (int64_t)(nx + 2) * ((jl + 1) + (int64_t)(ny + 2) * (kl + 1)));
+            if (s->flat) {
+              const int I = i - D.lo[0], J = j - D.lo[1], K = k - D.lo[2];
+              s->h_fmap_rhs[c] = ((I + J + K) & 1) * fb.half + (I >> 1) + fb.sp * (J + fb.ny * K);
+            }
             const int p[3] = {i, j, k};
             const int loc[3] = {il, jl, kl};
             for (int f = 0; f < 6; ++f) {
@@ -931,6 +1069,7 @@ int build_plan(mg_solver* s, const std::vector<IBox>& boxes, Bump& bump) {
   s->d_partials =
       bump.take<double>(std::max<size_t>({1, s->L[0].cap_cell, s->L[0].t_vec.size()}));
   if (s->opts.tune == 2) s->tune_scratch = bump.take<double>(s->L[0].n_g1);
+  if (s->flat) layout_flat_all(s, bump);
   s->d_tail = s->tail_lev > 0 ? bump.take<char>(sizeof(TailPlan<double>)) : nullptr;
   s->ws_need = bump.off + 256;
   return MG_OK;
@@ -1083,6 +1222,29 @@ int setup_coefficients(mg_solver* s, const mg_multifab_t* acoef, const mg_multif
   return MG_OK;
 }
 
+// The split-colour levels' coefficients from the levels' box arrays.
+template <typename T>
+int flat_coefficients(mg_solver* s) {
+  constexpr bool f32 = sizeof(T) == 4;
+  std::vector<FlatLevel<T>>& F = flat_levels<T>(s);
+  for (size_t l = 0; l < F.size() && l + 1 < s->L.size(); ++l) {
+    const Level& lv = s->L[l];
+    FlatLevel<T>& v = F[l];
+    const StencilArgs<T> op = stencil_of<T>(s, lv, f32);
+    v.op.alpha = op.alpha;
+    const T* b[3] = {op.b0, op.b1, op.b2};
+    const T ih[3] = {op.ih0, op.ih1, op.ih2};
+    T* dst[3] = {v.x, v.y, v.z};
+    for (int d = 0; d < 3; ++d)
+      HIPTRY(launch_flat_faces<T>(s->st, lv.d_info, lv.nbox, lv.max_faces, lv.domain.lo, v.op.d, d,
+                                  b[d], op.beta, ih[d], dst[d]));
+    if (s->has_a)
+      HIPTRY(launch_flat_acoef<T>(s->st, lv.d_info, lv.nbox, lv.max_faces, lv.domain.lo, v.op.d,
+                                  op.a, op.alpha, v.a));
+  }
+  return MG_OK;
+}
+
 int coarsen_all(mg_solver* s) {
   const bool f32 = s->opts.precision == MG_PREC_F32_REFINE;
   for (size_t l = 0; l + 1 < s->L.size(); ++l) {
@@ -1101,6 +1263,11 @@ int coarsen_all(mg_solver* s) {
         HIPTRY((launch_convert<double, float>(s->st, lv.b64[d], lv.b32[d], lv.n_f[d])));
       if (s->has_a) HIPTRY((launch_convert<double, float>(s->st, lv.a64, lv.a32, lv.n_g0)));
     }
+  }
+  if (s->flat) {
+    int rc;
+    if ((rc = flat_coefficients<double>(s))) return rc;
+    if (f32 && (rc = flat_coefficients<float>(s))) return rc;
   }
   const Level& bl = s->L.back();
   BottomTables bt = bottom_tables(s);
@@ -1326,6 +1493,123 @@ int coarse_cycle(mg_solver* s, size_t l, bool f32, const T* rf = nullptr) {
   return smooth<T>(s, lv, op, D.e, D.rhs, 0, s->opts.nu2, false, prof, s->opts.krylov != 0);
 }
 
+// The bottom's tables with the split-colour layout's element maps.
+BottomTables flat_bottom_tables(const mg_solver* s) {
+  BottomTables bt = bottom_tables(s);
+  bt.map_rhs = s->d_fmap_rhs;
+  bt.map_out = s->d_fmap_out;
+  return bt;
+}
+
+template <typename T>
+FlatTail<T> flat_tail_args(mg_solver* s) {
+  constexpr bool f32 = sizeof(T) == 4;
+  std::vector<FlatLevel<T>>& F = flat_levels<T>(s);
+  FlatTail<T> t{};
+  t.nlev = (int)s->L.size() - 1 - s->flat_tail;
+  t.nu1 = s->opts.nu1;
+  t.nu2 = s->opts.nu2;
+  t.reverse = s->opts.krylov != 0;
+  for (int i = 0; i < t.nlev; ++i) {
+    const FlatLevel<T>& v = F[s->flat_tail + i];
+    t.lev[i] = {v.op, v.e, v.f, v.r};
+  }
+  t.bd = F.back().op.d;
+  t.be = F.back().e;
+  t.bf = F.back().f;
+  t.bt = flat_bottom_tables(s);
+  t.bdiag = f32 ? (const T*)s->bdiag32 : (const T*)s->bdiag64;
+  t.bcoef = f32 ? (const T*)s->bcoef32 : (const T*)s->bcoef64;
+  t.tol = s->opts.bottom_rel_tol;
+  t.maxiter = s->opts.bottom_max_iter > 0 ? s->opts.bottom_max_iter : s->nb;
+  t.singular = s->singular ? 1 : 0;
+  t.iters = s->d_iters;
+  return t;
+}
+
+// Passes over a level walk it alternately forwards and backwards, so that a
+// pass starts on the data the one before it touched last.
+struct FlatWalk {
+  FlatPass ps;
+  explicit FlatWalk(int stream) { ps.stream = stream; }
+  FlatPass next() {
+    const FlatPass p = ps;
+    ps.reverse ^= 1;
+    return p;
+  }
+};
+
+// Post-smoothing of level l's array v (right-hand side f): the first half-sweep
+// adds the next coarser level's correction to the values it reads and
+// overwrites its own colour, the second overwrites the other colour, so the
+// interpolation has no pass of its own.  Red then black, or black then red
+// (krylov: the mirror image of the pre-smoothing).
+template <typename T>
+int flat_post(mg_solver* s, size_t l, T* v, const T* f, FlatWalk& w) {
+  std::vector<FlatLevel<T>>& F = flat_levels<T>(s);
+  const FlatOp<T>& op = F[l].op;
+  const size_t h = op.d.half;
+  const int c0 = s->opts.krylov ? 1 : 0;
+  for (int k = 0; k < s->opts.nu2; ++k)
+    for (int u = 0; u < 2; ++u) {
+      const int c = u ? 1 - c0 : c0;
+      const bool pe = k == 0 && u == 0;
+      ProfScope ps(s, pe ? 4 : 0, l == 0);
+      HIPTRY(launch_flat_half<T>(s->st, op, w.next(), v + (1 - c) * h, v + c * h, f, c, false,
+                                 pe ? &F[l + 1].op.d : nullptr, pe ? F[l + 1].e : nullptr));
+    }
+  return MG_OK;
+}
+
+// Level l from a zero guess: correction e from the right-hand side f.
+template <typename T>
+int flat_cycle(mg_solver* s, size_t l) {
+  std::vector<FlatLevel<T>>& F = flat_levels<T>(s);
+  constexpr bool f32 = sizeof(T) == 4;
+  FlatLevel<T>& v = F[l];
+  const FlatOp<T>& op = v.op;
+  int rc;
+  if ((int)l == s->flat_tail) {
+    HIPTRY(launch_flat_tail<T>(s->st, flat_tail_args<T>(s)));
+    return MG_OK;
+  }
+  if (l + 1 == s->L.size()) {
+    const BottomTables bt = flat_bottom_tables(s);
+    const T* diag = f32 ? (const T*)s->bdiag32 : (const T*)s->bdiag64;
+    const T* coef = f32 ? (const T*)s->bcoef32 : (const T*)s->bcoef64;
+    T* work = f32 ? (T*)s->bwork32 : (T*)s->bwork64;
+    const int maxit = s->opts.bottom_max_iter > 0 ? s->opts.bottom_max_iter : s->nb;
+    const int sing = s->singular ? 1 : 0;
+    if (s->opts.bottom_solver == 1)
+      HIPTRY(launch_bottom_bicgstab<T>(s->st, bt, diag, coef, v.f, v.e, 0, work,
+                                       s->opts.bottom_rel_tol, maxit, sing, s->d_iters));
+    else
+      HIPTRY(launch_bottom_cg<T>(s->st, bt, diag, coef, v.f, v.e, 0, work, s->opts.bottom_rel_tol,
+                                 maxit, sing, s->d_iters));
+    return MG_OK;
+  }
+  const size_t h = op.d.half;
+  FlatWalk w(v.stream);
+  for (int k = 0; k < s->opts.nu1; ++k)
+    for (int c = 0; c < 2; ++c) {
+      ProfScope ps(s, 0, l == 0);
+      HIPTRY(launch_flat_half<T>(s->st, op, w.next(), v.e + (1 - c) * h, v.e + c * h, v.f, c,
+                                 k == 0 && c == 0));
+    }
+  {
+    ProfScope ps(s, 1, l == 0);
+    HIPTRY(launch_flat_restrict<T>(s->st, op, w.next(), v.e, v.f, F[l + 1].op.d, F[l + 1].f));
+  }
+  {
+    ProfScope ps(s, 5, l == 0);
+    if (l == 0 && s->opts.use_graph)
+      HIPTRY(hipGraphLaunch(f32 ? s->graph32 : s->graph64, s->st));
+    else if ((rc = flat_cycle<T>(s, l + 1)))
+      return rc;
+  }
+  return flat_post<T>(s, l, v.e, v.f, w);
+}
+
 int capture_graphs(mg_solver* s) {
   if (!s->opts.use_graph || s->L.size() < 2) {
     s->opts.use_graph = 0;
@@ -1337,8 +1621,12 @@ int capture_graphs(mg_solver* s) {
   const bool saved = s->profile;
   s->profile = false;
   // the level-0 residual pass restricts into level 1 itself with rr_fold
-  int rc = f32 ? coarse_cycle<float>(s, 1, true, s->rr_fold ? nullptr : s->L[0].r32)
-               : coarse_cycle<double>(s, 1, false, s->rr_fold ? nullptr : s->L[0].r64);
+  int rc;
+  if (s->flat)
+    rc = f32 ? flat_cycle<float>(s, 1) : flat_cycle<double>(s, 1);
+  else
+    rc = f32 ? coarse_cycle<float>(s, 1, true, s->rr_fold ? nullptr : s->L[0].r32)
+             : coarse_cycle<double>(s, 1, false, s->rr_fold ? nullptr : s->L[0].r64);
   s->profile = saved;
   hipError_t e = hipStreamEndCapture(s->st, &g);
   if (rc) return rc;
@@ -2283,6 +2571,12 @@ int upload_tables(mg_solver* s) {
   HIPTRY(hipMemcpyAsync(s->d_aidx, s->h_aidx.data(), sizeof(int) * nb, hipMemcpyHostToDevice, s->st));
   HIPTRY(hipMemcpyAsync(s->d_map_rhs, s->h_map_rhs.data(), sizeof(int) * nb, hipMemcpyHostToDevice, s->st));
   HIPTRY(hipMemcpyAsync(s->d_map_out, s->h_map_out.data(), sizeof(int) * nb, hipMemcpyHostToDevice, s->st));
+  if (s->flat) {
+    // padding and guard elements are zero for good
+    HIPTRY(hipMemsetAsync(s->flat_base, 0, s->flat_bytes, s->st));
+    HIPTRY(hipMemcpyAsync(s->d_fmap_rhs, s->h_fmap_rhs.data(), sizeof(int) * nb,
+                          hipMemcpyHostToDevice, s->st));
+  }
   if (s->d_perm)
     HIPTRY(hipMemcpyAsync(s->d_perm, s->h_perm.data(), sizeof(int) * nb, hipMemcpyHostToDevice, s->st));
   if (s->tail_lev > 0) {
@@ -3296,6 +3590,251 @@ int solve_folded(mg_solver* s, double* P, const double* F, int rng, double tol, 
   return MG_OK;
 }
 
+// Stop test of the V-cycle and refinement loops on the residual norm rn after
+// `it` cycles: 1 = stop (status set), 0 = go on.
+struct StopTest {
+  mg_solver* s;
+  double tol;
+  mg_info_t* inf;
+  double* hist;
+  int status = MG_OK, rising = 0;
+  double rn = 0, first = 0, prev = 0, prev2 = 0;
+  int operator()(int it, double norm) {
+    rn = norm;
+    if (hist) hist[it] = rn;
+    if (s->opts.verbose) fprintf(stderr, "amrmg cycle %d  max|r| = %.6e\n", it, rn);
+    if (!std::isfinite(rn)) {
+      status = fail(MG_ERR_NAN, "residual norm is not finite");
+      return 1;
+    }
+    if (it == 0) first = rn;
+    if (rn <= tol) {
+      inf->converged = 1;
+      return 1;
+    }
+    if (it == s->opts.max_iter) {
+      status = fail(MG_ERR_NOT_CONVERGED, "max_iter reached");
+      return 1;
+    }
+    if (it > 0) rising = rn > prev ? rising + 1 : 0;
+    if (rising >= 3 && rn > first) {
+      status = fail(MG_ERR_DIVERGED, "residual grew for 3 cycles");
+      return 1;
+    }
+    prev2 = prev;
+    prev = rn;
+    return 0;
+  }
+};
+
+// FP64 V-cycles on the split-colour layout.  The stop test shares a pass with
+// the next cycle's first half-sweep: the red update of a cell computes
+// everything its residual needs, and after a black half-sweep the black cells'
+// residual is zero (to rounding), so the norm over the red cells is the norm.
+// (The first test, of the caller's guess, takes both colours in a pass of its
+// own.)  That half-sweep and the black one after it write the other iterate
+// array - neither reads the colour it writes - so the iterate a norm was taken
+// of survives its cycle: the norm travels to the host while the cycle runs and
+// is read before the next test, except where the norms' geometric trend puts it
+// near the tolerance (a converged solve would run one cycle for nothing).
+int solve_flat(mg_solver* s, double tol, mg_info_t* inf, double* hist, int* status, int* result) {
+  FlatLevel<double>& v = s->f64[0];
+  const FlatOp<double>& op = v.op;
+  const size_t h = op.d.half;
+  StopTest stop{s, tol, inf, hist};
+  FlatWalk w(v.stream);
+  int cur = 0, it = 0, rc;
+  auto decide = [&]() -> int {
+    if (hipEventSynchronize(s->ev_norm[it & 1]) != hipSuccess) return -1;
+    const unsigned long long* hn = s->h_norm + (size_t)(1 + (it & 1)) * kNormSlot;
+    unsigned long long m = 0;
+    for (int k = 0; k < kNormWays; ++k) m = std::max(m, hn[k * kNormStride]);
+    double rn;
+    std::memcpy(&rn, &m, sizeof(double));
+    return stop(it, rn);
+  };
+  while (true) {
+    const double* c = s->fphi[cur];
+    double* n = s->fphi[1 - cur];
+    const int slot = 1 + (it & 1);
+    HIPTRY(launch_fill_u64(s->st, norm_slot(s, slot), kNormSlot, 0ull));
+    if (it == 0) {
+      ProfScope ps(s, 1, true);
+      HIPTRY((launch_flat_resid<double, double>(s->st, op, w.next(), c, s->frhs, nullptr,
+                                                norm_slot(s, slot), nullptr)));
+    }
+    {
+      ProfScope ps(s, it == 0 ? 0 : 1, true);
+      HIPTRY(launch_flat_half<double>(s->st, op, w.next(), c + h, n, s->frhs, 0, false, nullptr,
+                                      nullptr, it == 0 ? nullptr : c,
+                                      it == 0 ? nullptr : norm_slot(s, slot)));
+    }
+    HIPTRY(hipMemcpyAsync(s->h_norm + (size_t)slot * kNormSlot, norm_slot(s, slot),
+                          sizeof(unsigned long long) * kNormSlot, hipMemcpyDeviceToHost, s->st));
+    HIPTRY(hipEventRecord(s->ev_norm[it & 1], s->st));
+    bool wait = it < 2 || it >= s->opts.max_iter;
+    if (!wait) wait = !(stop.prev * (stop.prev / stop.prev2) > 8.0 * tol);
+    if (wait) {
+      const int d = decide();
+      if (d < 0) return fail(MG_ERR_HIP, "norm read-back failed");
+      if (d) break;
+    }
+    for (int k = 0; k < s->opts.nu1; ++k)
+      for (int col = k == 0 ? 1 : 0; col < 2; ++col) {
+        ProfScope ps(s, 0, true);
+        HIPTRY(launch_flat_half<double>(s->st, op, w.next(), n + (1 - col) * h, n + col * h,
+                                        s->frhs, col, false));
+      }
+    {
+      ProfScope ps(s, 1, true);
+      HIPTRY(launch_flat_restrict<double>(s->st, op, w.next(), n, s->frhs, s->f64[1].op.d,
+                                          s->f64[1].f));
+    }
+    {
+      ProfScope ps(s, 5, true);
+      if (s->opts.use_graph)
+        HIPTRY(hipGraphLaunch(s->graph64, s->st));
+      else if ((rc = flat_cycle<double>(s, 1)))
+        return rc;
+    }
+    if ((rc = flat_post<double>(s, 0, n, s->frhs, w))) return rc;
+    if (!wait) {
+      const int d = decide();
+      if (d < 0) return fail(MG_ERR_HIP, "norm read-back failed");
+      if (d) break;
+    }
+    cur = 1 - cur;
+    ++it;
+  }
+  *status = stop.status;
+  *result = cur;
+  inf->iters = it;
+  inf->abs_resid = stop.rn;
+  return MG_OK;
+}
+
+// FP64 residual, one FP32 V-cycle from zero on it, FP64 update.
+int solve_flat_refine(mg_solver* s, double tol, mg_info_t* inf, double* hist, int* status) {
+  const FlatOp<double>& op = s->f64[0].op;
+  StopTest stop{s, tol, inf, hist};
+  FlatWalk w(s->f64[0].stream);
+  int it = 0, rc;
+  while (true) {
+    HIPTRY(launch_fill_u64(s->st, norm_slot(s, 1), kNormSlot, 0ull));
+    {
+      ProfScope ps(s, 1, true);
+      HIPTRY((launch_flat_resid<double, float>(s->st, op, w.next(), s->fphi[0], s->frhs,
+                                               s->f32[0].f, norm_slot(s, 1), nullptr)));
+    }
+    double rn;
+    if ((rc = read_norm(s, 1, &rn))) return rc;
+    if (stop(it, rn)) break;
+    if ((rc = flat_cycle<float>(s, 0))) return rc;
+    {
+      ProfScope ps(s, 6, true);
+      HIPTRY(launch_flat_update(s->st, 2ll * op.d.half, s->fphi[0], s->f32[0].e));
+    }
+    ++it;
+  }
+  *status = stop.status;
+  inf->iters = it;
+  inf->abs_resid = stop.rn;
+  return MG_OK;
+}
+
+// solve_pcg on the split-colour layout: vectors are whole arrays, their padding
+// zero.
+int solve_flat_pcg(mg_solver* s, double tol, mg_info_t* inf, double* hist, int* status) {
+  const FlatOp<double>& op = s->f64[0].op;
+  const long long n = 2ll * op.d.half;
+  const bool f32 = s->opts.precision == MG_PREC_F32_REFINE;
+  double *x = s->fphi[0], *r = s->fr, *p = s->fp, *q = s->fq;
+  FlatWalk w(s->f64[0].stream);
+  int rc;
+  // f - A x into buf, mean taken out when singular; max |r| read back
+  auto true_residual = [&](double* buf, double* norm) -> int {
+    HIPTRY(launch_fill_u64(s->st, norm_slot(s, 2), kNormSlot, 0ull));
+    {
+      ProfScope ps(s, 1, true);
+      HIPTRY((launch_flat_resid<double, double>(s->st, op, w.next(), x, s->frhs, buf,
+                                                s->singular ? nullptr : norm_slot(s, 2), nullptr)));
+    }
+    if (s->singular) {
+      HIPTRY(launch_flat_remove_mean(s->st, op.d, buf, s->fpart, s->d_sum));
+      HIPTRY(launch_flat_maxabs(s->st, n, buf, norm_slot(s, 2)));
+    }
+    return read_norm(s, 2, norm);
+  };
+  double rn;
+  if ((rc = true_residual(r, &rn))) return rc;
+  int it = 0;
+  bool restart = true, r32_current = false;
+  *status = MG_OK;
+  while (true) {
+    if (hist) hist[it] = rn;
+    if (s->opts.verbose) fprintf(stderr, "amrmg pcg %d  max|r| = %.6e\n", it, rn);
+    if (!std::isfinite(rn)) {
+      *status = fail(MG_ERR_NAN, "residual norm is not finite");
+      break;
+    }
+    if (rn <= tol) {
+      double rt;
+      if ((rc = true_residual(q, &rt))) return rc;
+      if (rt <= tol) {
+        inf->converged = 1;
+        break;
+      }
+      HIPTRY(hipMemcpyAsync(r, q, sizeof(double) * n, hipMemcpyDeviceToDevice, s->st));
+      restart = true;
+      r32_current = false;
+    }
+    if (it == s->opts.max_iter) {
+      *status = fail(MG_ERR_NOT_CONVERGED, "max_iter reached");
+      break;
+    }
+    double* rho_new = s->d_cg + (it & 1);
+    double* rho_old = s->d_cg + ((it + 1) & 1);
+    if (f32) {
+      if (!r32_current) HIPTRY((launch_convert<double, float>(s->st, r, s->f32[0].f, n)));
+      if ((rc = flat_cycle<float>(s, 0))) return rc;
+    } else if ((rc = flat_cycle<double>(s, 0))) {
+      return rc;
+    }
+    {
+      ProfScope ps(s, 6, true);
+      if (f32 && !s->singular) {
+        HIPTRY(launch_flat_dot<float>(s->st, n, r, s->f32[0].e, s->fpart, rho_new));
+        HIPTRY(launch_flat_cg_p<float>(s->st, n, p, s->f32[0].e, rho_new, rho_old, restart));
+      } else {
+        if (f32) HIPTRY((launch_convert<float, double>(s->st, s->f32[0].e, s->fz, n)));
+        if (s->singular)
+          HIPTRY(launch_flat_remove_mean(s->st, op.d, s->fz, s->fpart, s->d_sum));
+        HIPTRY(launch_flat_dot<double>(s->st, n, r, s->fz, s->fpart, rho_new));
+        HIPTRY(launch_flat_cg_p<double>(s->st, n, p, s->fz, rho_new, rho_old, restart));
+      }
+    }
+    restart = false;
+    {
+      ProfScope ps(s, 1, true);
+      HIPTRY((launch_flat_resid<double, double>(s->st, op, w.next(), p, nullptr, q, nullptr,
+                                                s->fpart)));
+    }
+    {
+      ProfScope ps(s, 6, true);
+      HIPTRY(launch_sum_final(s->st, s->fpart, flat_resid_blocks(op.d), s->d_cg + 2));
+      HIPTRY(launch_fill_u64(s->st, norm_slot(s, 2), kNormSlot, 0ull));
+      HIPTRY(launch_flat_cg_xr(s->st, n, x, p, r, q, rho_new, s->d_cg + 2, norm_slot(s, 2),
+                               f32 ? s->f32[0].f : nullptr));
+      r32_current = f32;
+    }
+    ++it;
+    if ((rc = read_norm(s, 2, &rn))) return rc;
+  }
+  inf->iters = it;
+  inf->abs_resid = rn;
+  return MG_OK;
+}
+
 int mg_solve(mg_solver_t* s, mg_multifab_t* phi, const mg_multifab_t* rhs, double rel_tol,
              double abs_tol, mg_info_t* info, double* resid_history) {
   const auto t0 = std::chrono::steady_clock::now();
@@ -3315,12 +3854,16 @@ int mg_solve(mg_solver_t* s, mg_multifab_t* phi, const mg_multifab_t* rhs, doubl
   mg_info_t inf;
   std::memset(&inf, 0, sizeof(inf));
   inf.nlevels = (int)s->L.size();
-  inf.tail_level = std::max(s->tail_lev, 0);
+  inf.tail_level = std::max(s->flat ? s->flat_tail : s->tail_lev, 0);
   inf.setup_ms = s->setup_ms;
 
   HIPTRY(launch_fill_u64(s->st, s->d_norm, 4 * kNormSlot, 0ull));
-  HIPTRY(launch_maxabs<double>(s->st, l0.d_cell, (int)l0.t_cell.size(), l0.s_cell, l0.d_info, F,
-                               rng, s->d_norm));
+  if (s->flat)
+    HIPTRY(launch_flat_gather(s->st, l0.d_info, l0.nbox, l0.max_faces, l0.domain.lo,
+                              s->f64[0].op.d, F, rng, s->frhs, s->d_norm));
+  else
+    HIPTRY(launch_maxabs<double>(s->st, l0.d_cell, (int)l0.t_cell.size(), l0.s_cell, l0.d_info, F,
+                                 rng, s->d_norm));
   double normf;
   if ((rc = read_norm(s, 0, &normf))) return rc;
   int status = MG_OK;
@@ -3331,6 +3874,22 @@ int mg_solve(mg_solver_t* s, mg_multifab_t* phi, const mg_multifab_t* rhs, doubl
     HIPTRY(hipStreamSynchronize(s->st));
     inf.converged = 1;
     if (resid_history) resid_history[0] = 0.0;
+  } else if (s->flat) {
+    const double tol = std::max(rel_tol * normf, abs_tol);
+    const FlatDims& d = s->f64[0].op.d;
+    HIPTRY(launch_flat_gather(s->st, l0.d_info, l0.nbox, l0.max_faces, l0.domain.lo, d, P, 1,
+                              s->fphi[0], nullptr));
+    int cur = 0;
+    if (s->opts.krylov)
+      rc = solve_flat_pcg(s, tol, &inf, resid_history, &status);
+    else if (f32)
+      rc = solve_flat_refine(s, tol, &inf, resid_history, &status);
+    else
+      rc = solve_flat(s, tol, &inf, resid_history, &status, &cur);
+    if (rc) return rc;
+    HIPTRY(launch_flat_scatter(s->st, l0.d_info, l0.nbox, l0.max_faces, l0.domain.lo, d,
+                               s->fphi[cur], P, 1));
+    inf.rel_resid = inf.abs_resid / normf;
   } else if (s->opts.krylov) {
     status = solve_pcg(s, P, F, rng, std::max(rel_tol * normf, abs_tol), &inf, resid_history);
     inf.rel_resid = inf.abs_resid / normf;
