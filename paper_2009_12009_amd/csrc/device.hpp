@@ -39,11 +39,43 @@ __device__ void block_max_u64(unsigned long long v, unsigned long long* dst) {
   }
 }
 
-// Block sum in a fixed order: lanes by butterfly (every lane ends with the
-// same bits), then the first nw waves in index order (every wave of the
-// work-group takes part in the barrier; later waves' sums are left out).
+// v of the lane that DPP control CTRL pairs with this one.
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, true);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readlane((int)b, lane);
+  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
+// Sum over a wavefront (all 64 lanes active), the same bits in every lane:
+// inside rows of 16 lanes by DPP (neighbours, pairs, mirrored halves, mirrored
+// row), then the four rows' sums.  A butterfly of shuffles goes through LDS six
+// times, which is most of a small CG iteration.
+__device__ __forceinline__ double wave_sum(double v) {
+  v += dpp<0xB1>(v);   // quad_perm [1, 0, 3, 2]
+  v += dpp<0x4E>(v);   // quad_perm [2, 3, 0, 1]
+  v += dpp<0x141>(v);  // row_half_mirror
+  v += dpp<0x140>(v);  // row_mirror
+  return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
+}
+
+// Block sum in a fixed order: lanes by butterfly, or by wave_sum with FAST, then
+// the first nw waves in index order (every wave of the work-group takes part in
+// the barrier; later waves' sums are left out).
+template <bool FAST = false>
 __device__ double block_sum_w(double v, double* red, int& phase, int nw) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  if (FAST)
+    v = wave_sum(v);
+  else
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
   const int tid = threadIdx.x + blockDim.x * threadIdx.y;
   double* buf = red + phase * 16;
   phase ^= 1;
@@ -64,16 +96,15 @@ __device__ double block_sum(double v, double* red, int& phase) {
 // wave takes part in the barriers (lanes past the cells hold zeros).  p:
 // n values of LDS.
 // The CG's sums and barriers.  ONE_WAVE: the CG runs in wavefront 0 alone
-// (n <= 64, lanes 0..63): the butterfly leaves the sum in every lane (the
-// value the work-group form reads back for one wave) and LDS needs only
+// (n <= 64, lanes 0..63): wave_sum leaves the sum in every lane (the value
+// the work-group form reads back for one wave) and LDS needs only
 // wave-level ordering.
 template <bool ONE_WAVE>
 __device__ __forceinline__ double cg_sum(double v, double* red, int& phase, int nw) {
   if (ONE_WAVE) {
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    return v;
+    return wave_sum(v);
   }
-  return block_sum_w(v, red, phase, nw);
+  return block_sum_w<true>(v, red, phase, nw);
 }
 
 template <bool ONE_WAVE>
@@ -135,14 +166,17 @@ __device__ __forceinline__ void cg_lds_run(const BottomTables& bt, const T* __re
 #pragma unroll
   for (int m = 0; m < CPT; ++m) s += (double)r[m] * (double)r[m];
   double rho = cg_sum<ONE_WAVE>(s, red, phase, nw);
-  const double bnorm = sqrt(rho);
+  // stop at ||r|| <= tol ||rhs||, compared as squares
+  const double stop = tol * tol * rho;
   int it = 0;
-  if (bnorm > 0.0) {
+  if (rho > 0.0) {
 #pragma unroll
     for (int m = 0; m < CPT; ++m)
       if (tid + m * nt < n) p[tid + m * nt] = r[m];
     while (it < maxiter) {
       cg_sync<ONE_WAVE>();
+      // off the chain of dependent steps, unlike a quotient by rho below
+      const double inv = 1.0 / rho;
       s = 0.0;
 #pragma unroll
       for (int m = 0; m < CPT; ++m) {
@@ -179,8 +213,8 @@ __device__ __forceinline__ void cg_lds_run(const BottomTables& bt, const T* __re
       }
       ++it;
       const double rho_new = cg_sum<ONE_WAVE>(s, red, phase, nw);
-      if (!(sqrt(rho_new) > tol * bnorm)) break;
-      const T btT = (T)(rho_new / rho);
+      if (!(rho_new > stop)) break;
+      const T btT = (T)(rho_new * inv);
 #pragma unroll
       for (int m = 0; m < CPT; ++m) {
         const int c = tid + m * nt;

@@ -142,16 +142,15 @@ struct FlatTailLevel {
 template <typename T>
 struct FlatTail {
   int nlev, nu1, nu2, reverse;
-  FlatTailLevel<T> lev[kTailMaxLevels];
-  FlatDims bd;  // bottom level
-  T *be, *bf;
-  BottomTables bt;  // maps into be, bf
+  FlatTailLevel<T> lev[kTailMaxLevels + 1];  // lev[nlev]: the bottom's extents, e and f
+  BottomTables bt;                           // maps into the bottom's f and e
   const T *bdiag, *bcoef;
   double tol;
   int maxiter, singular;
   int* iters;
 };
+// dt: a copy of t in device memory.
 template <typename T>
-hipError_t launch_flat_tail(hipStream_t st, const FlatTail<T>& t);
+hipError_t launch_flat_tail(hipStream_t st, const FlatTail<T>& t, const FlatTail<T>* dt);
 
 }  // namespace amrmg

@@ -547,119 +547,160 @@ __global__ void __launch_bounds__(256)
 // LDS (elements) of one tail level: e and f (both halves), r (red half).
 __host__ __device__ inline int tail_elems(const FlatDims& d) { return 5 * d.half; }
 
+// Pointers read from the plan are known to be global, so that their loads do
+// not share a wait counter with LDS.
+template <typename T>
+__device__ __forceinline__ T* as_global(T* p) {
+  return (T*)(__attribute__((address_space(1))) T*)p;
+}
+
+template <typename T>
+__device__ __forceinline__ FlatOp<T> tail_op(const FlatTail<T>* tp, int l) {
+  FlatOp<T> op = tp->lev[l].op;
+  op.x = as_global(op.x);
+  op.y = as_global(op.y);
+  op.z = as_global(op.z);
+  op.a = as_global(op.a);
+  return op;
+}
+
+// A level's arrays: both halves of e and f, r the red half.
 template <typename T>
 struct TailArr {
   T *e, *f, *r;
 };
 
 template <typename T, bool LDS>
-__global__ void __launch_bounds__(kTailLanes) k_flat_tail(FlatTail<T> tp) {
+__device__ __forceinline__ TailArr<T> tail_arr(const FlatTail<T>* tp, T* lds, int l) {
+  TailArr<T> a;
+  if (LDS) {
+    // one level after the other, then the bottom's e, f and the CG's p
+    int o = 0;
+    for (int m = 0; m < l; ++m) o += tail_elems(tp->lev[m].op.d);
+    const int h = tp->lev[l].op.d.half;
+    a.e = lds + o;
+    a.f = a.e + 2 * h;
+    a.r = a.f + 2 * h;
+  } else {
+    a.e = as_global(tp->lev[l].e);
+    a.f = as_global(tp->lev[l].f);
+    a.r = as_global(tp->lev[l].r);
+  }
+  return a;
+}
+
+// A pair of the level and both its cells' coefficients.
+template <typename T>
+struct TailPair {
+  Coef<T, 1> c[2];
+  int p, j, k;
+};
+
+template <typename T>
+__device__ __forceinline__ TailPair<T> tail_pair(const FlatOp<T>& op, int q) {
+  TailPair<T> m;
+  const FlatDims& d = op.d;
+  const int t = q / d.np;
+  m.p = q - t * d.np;
+  m.k = t / d.ny;
+  m.j = t - m.k * d.ny;
+#pragma unroll
+  for (int c = 0; c < 2; ++c)
+    load_coef<T, 1, false>(m.c[c], op, c, (m.j + m.k + c) & 1, m.p, m.j, m.k);
+  return m;
+}
+
+// The update of the colour's cell of a pair.
+template <typename T, int COLOUR, bool ZG, bool PE>
+__device__ __forceinline__ void tail_update(const FlatOp<T>& op, const TailArr<T>& A,
+                                            const TailPair<T>& m, const FlatDims& cd,
+                                            const T* ec) {
+#pragma clang fp contract(off)
+  const FlatDims& d = op.d;
+  const Coef<T, 1>& c = m.c[COLOUR];
+  const int s = (m.j + m.k + COLOUR) & 1;
+  const int at = m.p + d.sp * (m.j + d.ny * m.k);
+  const T diag = diag_of<T, 1>(op, c, 0, s, m.p, m.j, m.k);
+  T off = T(0);
+  if (!ZG) {
+    Nb<T, 1> n;
+    load_nb<T, 1>(n, d, A.e + (1 - COLOUR) * d.half, s, m.p, m.j, m.k, row_ix(d, m.j, m.k));
+    if (PE) {
+      Par<T, 1> q;
+      load_par<T, 1>(q, d, cd, ec, s, m.p, m.j, m.k);
+      add_par<T, 1>(n, q, s, m.j, m.k);
+    }
+    off = off_of<T, 1>(op, c, n, 0, s, m.p, m.j, m.k);
+  }
+  const T fv = A.f[COLOUR * d.half + at];
+  A.e[COLOUR * d.half + at] = (ZG ? fv : fv + off) / diag;
+}
+
+// One half-sweep of the work-group.  own: the lane's pair where the level has
+// at most one per lane, else unused.
+template <typename T, int COLOUR, bool ZG, bool PE, int NT>
+__device__ __forceinline__ void tail_half(const FlatOp<T>& op, const TailArr<T>& A,
+                                          const TailPair<T>& own, int npair, const FlatDims& cd,
+                                          const T* ec) {
+  if (npair <= NT) {
+    if ((int)threadIdx.x < npair) tail_update<T, COLOUR, ZG, PE>(op, A, own, cd, ec);
+  } else {
+    for (int q = threadIdx.x; q < npair; q += NT)
+      tail_update<T, COLOUR, ZG, PE>(op, A, tail_pair(op, q), cd, ec);
+  }
+  __syncthreads();
+}
+
+// The coarsest levels and the CG in one work-group, latency bound: a barrier and
+// one LDS round trip per half-sweep, since a lane keeps its pair's coefficients
+// in registers for the whole visit of a level and e, f and r are in LDS.  8^3
+// and 4^3 cells FP64: 20 us, the CG's iterations most of it (the box form,
+// arrays in the L2: 36 us; with the plan as a by-value argument the compiler
+// spilled: 81 us).  NT lanes: 512 where every level has at most that many
+// pairs and the bottom that many cells, else 1024.
+template <typename T, bool LDS, int NT>
+__global__ void __launch_bounds__(NT) k_flat_tail(const FlatTail<T>* __restrict__ tp) {
 #pragma clang fp contract(off)
   extern __shared__ __align__(16) unsigned char flat_lds[];
   __shared__ double red[32];
   T* const lds = reinterpret_cast<T*>(flat_lds);
-  const int tid = threadIdx.x, nt = kTailLanes;
-  // level l's arrays: in LDS one level after the other, then the bottom's e, f
-  // and the CG's p
-  auto arr = [&](int l) {
-    TailArr<T> a;
-    if (LDS) {
-      int o = 0;
-      for (int m = 0; m < l; ++m) o += tail_elems(tp.lev[m].op.d);
-      const FlatDims& d = l < tp.nlev ? tp.lev[l < kTailMaxLevels ? l : 0].op.d : tp.bd;
-      a.e = lds + o;
-      a.f = a.e + 2 * d.half;
-      a.r = a.f + 2 * d.half;
-    } else if (l < tp.nlev) {
-      const FlatTailLevel<T>& L = tp.lev[l < kTailMaxLevels ? l : 0];
-      a = {L.e, L.f, L.r};
-    } else {
-      a = {tp.be, tp.bf, nullptr};
-    }
-    return a;
-  };
-  // one cell's update: colour's cell of pair p of row (j, k)
-  auto update = [&](const FlatOp<T>& op, const TailArr<T>& A, const Coef<T, 1>& c, int colour,
-                    int p, int j, int k, bool zg, const FlatDims* cd, const T* ec) {
-    const FlatDims& d = op.d;
-    const int s = (j + k + colour) & 1;
-    const int at = p + d.sp * (j + d.ny * k);
-    const T diag = diag_of<T, 1>(op, c, 0, s, p, j, k);
-    T off = T(0);
-    if (!zg) {
-      Nb<T, 1> n;
-      load_nb<T, 1>(n, d, A.e + (1 - colour) * d.half, s, p, j, k, row_ix(d, j, k));
-      if (ec) {
-        Par<T, 1> q;
-        load_par<T, 1>(q, d, *cd, ec, s, p, j, k);
-        add_par<T, 1>(n, q, s, j, k);
-      }
-      off = off_of<T, 1>(op, c, n, 0, s, p, j, k);
-    }
-    const T fv = A.f[colour * d.half + at];
-    A.e[colour * d.half + at] = (zg ? fv : fv + off) / diag;
-  };
-  // both colours' coefficients of the lane's pair, kept while the level fits
-  // one pair per lane
-  struct Mine {
-    Coef<T, 1> c[2];
-    int p, j, k;
-  };
-  auto mine = [&](const FlatOp<T>& op, int q) {
-    Mine m;
-    const FlatDims& d = op.d;
-    const int t = q / d.np;
-    m.p = q - t * d.np;
-    m.k = t / d.ny;
-    m.j = t - m.k * d.ny;
-    for (int c = 0; c < 2; ++c)
-      load_coef<T, 1, false>(m.c[c], op, c, (m.j + m.k + c) & 1, m.p, m.j, m.k);
-    return m;
-  };
-  auto half = [&](const FlatOp<T>& op, const TailArr<T>& A, const Mine& own, bool one, int npair,
-                  int colour, bool zg, const FlatDims* cd, const T* ec) {
-    if (one) {
-      if (tid < npair) update(op, A, own.c[colour], colour, own.p, own.j, own.k, zg, cd, ec);
-    } else {
-      for (int q = tid; q < npair; q += nt) {
-        const Mine m = mine(op, q);
-        update(op, A, m.c[colour], colour, m.p, m.j, m.k, zg, cd, ec);
-      }
-    }
-    __syncthreads();
-  };
+  const int tid = threadIdx.x;
+  const int nlev = tp->nlev;
   if (LDS) {
     // the first level's right-hand side
-    const FlatDims& d = tp.lev[0].op.d;
-    const TailArr<T> A = arr(0);
-    for (int e = tid; e < 2 * d.half; e += nt) A.f[e] = tp.lev[0].f[e];
+    const int n = 2 * tp->lev[0].op.d.half;
+    const T* f = as_global(tp->lev[0].f);
+    T* to = tail_arr<T, LDS>(tp, lds, 0).f;
+    for (int e = tid; e < n; e += NT) to[e] = f[e];
     __syncthreads();
   }
-  for (int l = 0; l < tp.nlev; ++l) {
-    const FlatOp<T>& op = tp.lev[l].op;
+  for (int l = 0; l < nlev; ++l) {
+    const FlatOp<T> op = tail_op(tp, l);
     const FlatDims& d = op.d;
-    const TailArr<T> A = arr(l), C = arr(l + 1);
+    const FlatDims cd = tp->lev[l + 1].op.d;
+    const TailArr<T> A = tail_arr<T, LDS>(tp, lds, l), C = tail_arr<T, LDS>(tp, lds, l + 1);
     const int npair = d.np * d.ny * d.nz;
-    const bool one = npair <= nt;
-    Mine own;
-    if (one && tid < npair) own = mine(op, tid);
-    for (int k = 0; k < tp.nu1; ++k) {
-      half(op, A, own, one, npair, 0, k == 0, nullptr, nullptr);
-      half(op, A, own, one, npair, 1, false, nullptr, nullptr);
+    TailPair<T> own;
+    if (npair <= NT && tid < npair) own = tail_pair(op, tid);
+    for (int k = 0; k < tp->nu1; ++k) {
+      if (k == 0)
+        tail_half<T, 0, true, false, NT>(op, A, own, npair, cd, nullptr);
+      else
+        tail_half<T, 0, false, false, NT>(op, A, own, npair, cd, nullptr);
+      tail_half<T, 1, false, false, NT>(op, A, own, npair, cd, nullptr);
     }
     // residual of the red cells (the black ones' is zero)
-    for (int q = tid; q < npair; q += nt) {
-      const Mine m = one ? own : mine(op, q);
-      const int s = (m.j + m.k) & 1, at = m.p + d.sp * (m.j + d.ny * m.k);
+    for (int q = tid; q < npair; q += NT) {
+      if (npair > NT) own = tail_pair(op, q);
+      const int s = (own.j + own.k) & 1, at = own.p + d.sp * (own.j + d.ny * own.k);
       Nb<T, 1> n;
-      load_nb<T, 1>(n, d, A.e + d.half, s, m.p, m.j, m.k, row_ix(d, m.j, m.k));
-      A.r[at] = resid_of(A.f[at], diag_of<T, 1>(op, m.c[0], 0, s, m.p, m.j, m.k), A.e[at],
-                         off_of<T, 1>(op, m.c[0], n, 0, s, m.p, m.j, m.k));
+      load_nb<T, 1>(n, d, A.e + d.half, s, own.p, own.j, own.k, row_ix(d, own.j, own.k));
+      A.r[at] = resid_of(A.f[at], diag_of<T, 1>(op, own.c[0], 0, s, own.p, own.j, own.k), A.e[at],
+                         off_of<T, 1>(op, own.c[0], n, 0, s, own.p, own.j, own.k));
     }
     __syncthreads();
-    const FlatDims& cd = l + 1 < tp.nlev ? tp.lev[l + 1 < kTailMaxLevels ? l + 1 : 0].op.d : tp.bd;
     const int ncell = cd.nx * cd.ny * cd.nz;
-    for (int q = tid; q < ncell; q += nt) {
+    for (int q = tid; q < ncell; q += NT) {
       const int t = q / cd.nx, I = q - t * cd.nx, K = t / cd.ny, J = t - K * cd.ny;
       const int b = I + d.sp * (2 * J + d.ny * 2 * K);
       const int bz = d.sp * d.ny;
@@ -670,41 +711,60 @@ __global__ void __launch_bounds__(kTailLanes) k_flat_tail(FlatTail<T> tp) {
     __syncthreads();
   }
   {
-    const TailArr<T> B = arr(tp.nlev);
-    T* p = LDS ? B.f + 2 * tp.bd.half : lds;
-    const BottomTables& bt = tp.bt;
+    const TailArr<T> B = tail_arr<T, LDS>(tp, lds, nlev);
+    T* p = LDS ? B.f + 2 * tp->lev[nlev].op.d.half : lds;
+    BottomTables bt = tp->bt;
+    bt.nbr = as_global(bt.nbr);
+    bt.map_rhs = as_global(bt.map_rhs);
+    bt.map_out = as_global(bt.map_out);
+    const T* diag = as_global(tp->bdiag);
+    const T* coef = as_global(tp->bcoef);
     if (bt.n <= 64) {
       if (tid < 64)
-        cg_lds_run<T, 1, true>(bt, tp.bdiag, tp.bcoef, B.f, B.e, 0, tp.tol, tp.maxiter,
-                               tp.singular, tp.iters, p, red, 64, 1);
+        cg_lds_run<T, 1, true>(bt, diag, coef, B.f, B.e, 0, tp->tol, tp->maxiter, tp->singular,
+                               as_global(tp->iters), p, red, 64, 1);
     } else {
-      cg_lds_run<T, 1>(bt, tp.bdiag, tp.bcoef, B.f, B.e, 0, tp.tol, tp.maxiter, tp.singular,
-                       tp.iters, p, red, nt, (bt.n + 63) / 64);
+      cg_lds_run<T, 1>(bt, diag, coef, B.f, B.e, 0, tp->tol, tp->maxiter, tp->singular,
+                       as_global(tp->iters), p, red, NT, (bt.n + 63) / 64);
     }
   }
   __syncthreads();
-  const int c0 = tp.reverse ? 1 : 0;
-  for (int l = tp.nlev - 1; l >= 0; --l) {
-    const FlatOp<T>& op = tp.lev[l].op;
+  const bool reverse = tp->reverse != 0;
+  for (int l = nlev - 1; l >= 0; --l) {
+    const FlatOp<T> op = tail_op(tp, l);
     const FlatDims& d = op.d;
-    const TailArr<T> A = arr(l), C = arr(l + 1);
-    const FlatDims& cd = l + 1 < tp.nlev ? tp.lev[l + 1 < kTailMaxLevels ? l + 1 : 0].op.d : tp.bd;
+    const FlatDims cd = tp->lev[l + 1].op.d;
+    const TailArr<T> A = tail_arr<T, LDS>(tp, lds, l);
+    const T* ec = tail_arr<T, LDS>(tp, lds, l + 1).e;
     const int npair = d.np * d.ny * d.nz;
-    const bool one = npair <= nt;
-    Mine own;
-    if (one && tid < npair) own = mine(op, tid);
-    for (int k = 0; k < tp.nu2; ++k) {
-      half(op, A, own, one, npair, c0, false, k == 0 ? &cd : nullptr, k == 0 ? C.e : nullptr);
-      half(op, A, own, one, npair, 1 - c0, false, nullptr, nullptr);
+    TailPair<T> own;
+    if (npair <= NT && tid < npair) own = tail_pair(op, tid);
+    if (reverse) {
+      for (int k = 0; k < tp->nu2; ++k) {
+        if (k == 0)
+          tail_half<T, 1, false, true, NT>(op, A, own, npair, cd, ec);
+        else
+          tail_half<T, 1, false, false, NT>(op, A, own, npair, cd, ec);
+        tail_half<T, 0, false, false, NT>(op, A, own, npair, cd, ec);
+      }
+    } else {
+      for (int k = 0; k < tp->nu2; ++k) {
+        if (k == 0)
+          tail_half<T, 0, false, true, NT>(op, A, own, npair, cd, ec);
+        else
+          tail_half<T, 0, false, false, NT>(op, A, own, npair, cd, ec);
+        tail_half<T, 1, false, false, NT>(op, A, own, npair, cd, ec);
+      }
     }
   }
   if (LDS) {
-    const FlatDims& d = tp.lev[0].op.d;
-    const TailArr<T> A = arr(0);
-    for (int q = tid; q < d.np * d.ny * d.nz; q += nt) {
+    const FlatDims d = tp->lev[0].op.d;
+    const T* e = tail_arr<T, LDS>(tp, lds, 0).e;
+    T* to = as_global(tp->lev[0].e);
+    for (int q = tid; q < d.np * d.ny * d.nz; q += NT) {
       const int t = q / d.np, at = q - t * d.np + d.sp * t;
-      tp.lev[0].e[at] = A.e[at];
-      tp.lev[0].e[d.half + at] = A.e[d.half + at];
+      to[at] = e[at];
+      to[d.half + at] = e[d.half + at];
     }
   }
 }
@@ -912,17 +972,23 @@ hipError_t launch_flat_maxabs(hipStream_t st, long long n, const double* v,
 }
 
 template <typename T>
-hipError_t launch_flat_tail(hipStream_t st, const FlatTail<T>& t) {
-  if (t.nlev < 1 || t.nlev > kTailMaxLevels || t.bt.n < 1 || t.bt.n > kTailMaxBottom)
+hipError_t launch_flat_tail(hipStream_t st, const FlatTail<T>& t, const FlatTail<T>* dt) {
+  if (!dt || t.nlev < 1 || t.nlev > kTailMaxLevels || t.bt.n < 1 || t.bt.n > kTailMaxBottom)
     return hipErrorInvalidValue;
-  long long el = 4ll * t.bd.half + t.bt.n;
+  long long el = 4ll * t.lev[t.nlev].op.d.half + t.bt.n;
   for (int l = 0; l < t.nlev; ++l) el += tail_elems(t.lev[l].op.d);
-  if (el * (long long)sizeof(T) <= 60 * 1024) {
-    hipLaunchKernelGGL((k_flat_tail<T, true>), dim3(1), dim3(kTailLanes), el * sizeof(T), st, t);
-  } else {
-    hipLaunchKernelGGL((k_flat_tail<T, false>), dim3(1), dim3(kTailLanes), t.bt.n * sizeof(T), st,
-                       t);
+  bool small = t.bt.n <= 512;
+  for (int l = 0; l < t.nlev; ++l) {
+    const FlatDims& d = t.lev[l].op.d;
+    small = small && d.np * d.ny * d.nz <= 512;
   }
+  const bool fits = el * (long long)sizeof(T) <= 60 * 1024;
+#define FT(L, N, BYTES) \
+  hipLaunchKernelGGL((k_flat_tail<T, L, N>), dim3(1), dim3(N), BYTES, st, dt)
+  if (fits && small) FT(true, 512, el * sizeof(T));
+  else if (fits) FT(true, 1024, el * sizeof(T));
+  else FT(false, 1024, t.bt.n * sizeof(T));
+#undef FT
   return hipGetLastError();
 }
 
@@ -940,7 +1006,7 @@ hipError_t launch_flat_tail(hipStream_t st, const FlatTail<T>& t) {
                                          double*);                                                 \
   template hipError_t launch_flat_cg_p<T>(hipStream_t, long long, double*, const T*,               \
                                           const double*, const double*, int);                      \
-  template hipError_t launch_flat_tail<T>(hipStream_t, const FlatTail<T>&);
+  template hipError_t launch_flat_tail<T>(hipStream_t, const FlatTail<T>&, const FlatTail<T>*);
 
 INST(double)
 INST(float)

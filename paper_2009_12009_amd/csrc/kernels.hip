@@ -2079,7 +2079,7 @@ __global__ void __launch_bounds__(1024)
 // The strided form (k_bottom_cg_lds<T, 4 or 8>) re-reads seven coefficients
 // and six neighbour indices per cell from the L2 in every iteration, which is
 // what bounds it: 24 x 12 x 16 cells 953 us per solve, 15 x 11 x 19
-// 421 us; this form 275 and 123 us, two block
+// 421 us; this form 214 and 92 us, two block
 // reductions and the LDS reads of p per iteration being left.
 template <typename T>
 __host__ __device__ constexpr bool cg_x_in_lds(int cpt) {
@@ -2141,7 +2141,7 @@ __global__ void __launch_bounds__(1024)
     }
   }
   if (singular) {
-    s = block_sum_w(s, red, phase, nw);
+    s = block_sum_w<true>(s, red, phase, nw);
     const T mean = (T)(s / n);
 #pragma unroll
     for (int m = 0; m < CPT; ++m)
@@ -2150,10 +2150,10 @@ __global__ void __launch_bounds__(1024)
   s = 0.0;
 #pragma unroll
   for (int m = 0; m < CPT; ++m) s += (double)r[m] * (double)r[m];
-  double rho = block_sum_w(s, red, phase, nw);
-  const double bnorm = sqrt(rho);
+  double rho = block_sum_w<true>(s, red, phase, nw);
+  const double stop = tol * tol * rho;
   int it = 0;
-  if (bnorm > 0.0) {
+  if (rho > 0.0) {
 #pragma unroll
     for (int m = 0; m < CPT; ++m)
       if (m < cnt) p[base + m * plane] = r[m];
@@ -2181,7 +2181,7 @@ __global__ void __launch_bounds__(1024)
           }
         }
       }
-      const double pq = block_sum_w(s, red, phase, nw);
+      const double pq = block_sum_w<true>(s, red, phase, nw);
       const T alT = (T)(rho / pq);
       s = 0.0;
 #pragma unroll
@@ -2197,8 +2197,8 @@ __global__ void __launch_bounds__(1024)
         }
       }
       ++it;
-      const double rho_new = block_sum_w(s, red, phase, nw);
-      if (!(sqrt(rho_new) > tol * bnorm)) break;
+      const double rho_new = block_sum_w<true>(s, red, phase, nw);
+      if (!(rho_new > stop)) break;
       const T btT = (T)(rho_new / rho);
       // every lane has read its neighbours' p: the reductions' barriers
 #pragma unroll
@@ -2213,7 +2213,7 @@ __global__ void __launch_bounds__(1024)
 #pragma unroll
     for (int m = 0; m < CPT; ++m)
       if (m < cnt) s += (double)(XL ? xs[base + m * plane] : x[XL ? 0 : m]);
-    mean = (T)(block_sum_w(s, red, phase, nw) / n);
+    mean = (T)(block_sum_w<true>(s, red, phase, nw) / n);
   }
 #pragma unroll
   for (int m = 0; m < CPT; ++m) {

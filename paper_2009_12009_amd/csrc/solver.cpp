@@ -212,6 +212,7 @@ struct mg_solver {
   double* fpart = nullptr;
   std::vector<int> h_fmap_rhs, h_fmap_out;
   int *d_fmap_rhs = nullptr, *d_fmap_out = nullptr;
+  char* d_ftail = nullptr;  // FlatTail of the solver's precision
   char* flat_base = nullptr;
   size_t flat_bytes = 0;
   // runtime
@@ -679,6 +680,7 @@ void layout_flat_all(mg_solver* s, Bump& bump) {
   s->flat_bytes = bump.off - from;
   s->d_fmap_rhs = bump.take<int>(s->nb);
   s->d_fmap_out = s->d_fmap_rhs;  // same layout of both
+  s->d_ftail = s->flat_tail > 0 ? bump.take<char>(sizeof(FlatTail<double>)) : nullptr;
 }
 
 // LDS bytes of the tail kernel starting at level t: the bottom CG's p (FP64
@@ -1514,9 +1516,7 @@ FlatTail<T> flat_tail_args(mg_solver* s) {
     const FlatLevel<T>& v = F[s->flat_tail + i];
     t.lev[i] = {v.op, v.e, v.f, v.r};
   }
-  t.bd = F.back().op.d;
-  t.be = F.back().e;
-  t.bf = F.back().f;
+  t.lev[t.nlev] = {F.back().op, F.back().e, F.back().f, nullptr};
   t.bt = flat_bottom_tables(s);
   t.bdiag = f32 ? (const T*)s->bdiag32 : (const T*)s->bdiag64;
   t.bcoef = f32 ? (const T*)s->bcoef32 : (const T*)s->bcoef64;
@@ -1525,6 +1525,20 @@ FlatTail<T> flat_tail_args(mg_solver* s) {
   t.singular = s->singular ? 1 : 0;
   t.iters = s->d_iters;
   return t;
+}
+
+// The tail's device plan, through pinned staging (the operators' alpha is set
+// with the first coefficients and never changes).
+template <typename T>
+int upload_flat_tail(mg_solver* s) {
+  FlatTail<T>* h = nullptr;
+  HIPTRY(hipHostMalloc((void**)&h, sizeof(FlatTail<T>), hipHostMallocDefault));
+  *h = flat_tail_args<T>(s);
+  hipError_t e = hipMemcpyAsync(s->d_ftail, h, sizeof(FlatTail<T>), hipMemcpyHostToDevice, s->st);
+  if (e == hipSuccess) e = hipStreamSynchronize(s->st);
+  hipHostFree(h);
+  HIPTRY(e);
+  return MG_OK;
 }
 
 // Passes over a level walk it alternately forwards and backwards, so that a
@@ -1570,7 +1584,8 @@ int flat_cycle(mg_solver* s, size_t l) {
   const FlatOp<T>& op = v.op;
   int rc;
   if ((int)l == s->flat_tail) {
-    HIPTRY(launch_flat_tail<T>(s->st, flat_tail_args<T>(s)));
+    HIPTRY(launch_flat_tail<T>(s->st, flat_tail_args<T>(s),
+                               reinterpret_cast<const FlatTail<T>*>(s->d_ftail)));
     return MG_OK;
   }
   if (l + 1 == s->L.size()) {
@@ -3314,6 +3329,11 @@ int mg_create(const mg_box_t* boxes, int32_t nbox, const mg_geom_t* geom, const 
     if ((rc = upload_tables(s.get()))) return rc;
     if ((rc = setup_coefficients(s.get(), acoef, bcoef))) return rc;
     if ((rc = coarsen_all(s.get()))) return rc;
+    if (s->flat_tail > 0) {
+      rc = s->opts.precision == MG_PREC_F32_REFINE ? upload_flat_tail<float>(s.get())
+                                                   : upload_flat_tail<double>(s.get());
+      if (rc) return rc;
+    }
     if ((rc = autotune(s.get()))) return rc;
     if ((rc = capture_graphs(s.get()))) return rc;
     HIPTRY(hipStreamSynchronize(s->st));
