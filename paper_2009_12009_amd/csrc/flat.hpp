@@ -78,6 +78,21 @@ template <typename T>
 hipError_t launch_flat_restrict(hipStream_t st, const FlatOp<T>& op, FlatPass ps, const T* v,
                                 const T* f, const FlatDims& cd, T* cf);
 
+// Two sweeps in one launch on blocks with a rim (nu = 2), dst != src:
+// pre_zero: from a zero guess, then cf = R r as launch_flat_restrict;
+// pre_after_red: the same where src is the red half after the first half-sweep;
+// post_red / post_black: src (both halves of the level's array, of which the
+// colour that is not updated first is read) plus the coarse correction ec,
+// then two sweeps starting with that colour.  dst: both halves.  cd: the coarser
+// level.  Same result as the separate launches.
+// Only on levels of at most one block per CU: flat_block_pairs, the pairs of a
+// block, is 0 elsewhere (there it costs more than the launches it saves).
+int flat_block_pairs(const FlatDims& d, int elem);
+enum class FlatBlockMode { pre_zero, pre_after_red, post_red, post_black };
+template <typename T>
+hipError_t launch_flat_block(hipStream_t st, const FlatOp<T>& op, FlatBlockMode mode, const T* src,
+                             const T* f, T* dst, const FlatDims& cd, T* cf, const T* ec);
+
 // out = f - A v (f non-null) or A v (f null) on both colours; out may be null
 // (norm only) and narrower than T.  normbits: max |out|; dots (one per block,
 // flat_resid_blocks of them): partial sums of v * out.

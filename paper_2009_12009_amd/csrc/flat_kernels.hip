@@ -1,9 +1,10 @@
 // gfx950 kernels of the V-cycle on the split-colour layout (flat.hpp).
 //
 // Operator and rounding: c phi is accumulated with explicit fused multiply-adds
-// in the order xlo, xhi, ylo, yhi, zlo, zhi and the compiler fuses nothing by
-// itself (contract off), so every kernel that updates a cell - a half-sweep of
-// its own or the one-work-group tail - rounds the same way.
+// in the order own pair, pair beside, ylo, yhi, zlo, zhi, a cell's update is (f +
+// sum) times 1 / diag, and the compiler fuses nothing by itself (contract off),
+// so every kernel that updates a cell - a half-sweep of its own, blocks of
+// sweeps, the one-work-group tail - rounds the same way.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -50,26 +51,29 @@ __device__ __forceinline__ void stv(T* p, const T (&s)[V], int n) {
 }
 
 // Coefficients of V consecutive cells of a colour (pairs p0 .. p0 + V - 1 of
-// row (j, k)); s = (j + k + colour) & 1, the cells' offset in their pairs.
+// row (j, k); sh = (j + k + colour) & 1, the cells' offset in their pairs).
+// Along x a cell has a neighbour in its own pair (face 2p + 1, o) and one in the
+// pair beside it (the pair before for sh = 0, after for sh = 1; s).
 template <typename T, int V>
 struct Coef {
-  T xl[V], xh[V], yl[V], yh[V], zl[V], zh[V], a[V];
+  T o[V], s[V], yl[V], yh[V], zl[V], zh[V], a[V];
 };
 
 template <typename T, int V, bool NT>
-__device__ __forceinline__ void load_coef(Coef<T, V>& c, const FlatOp<T>& op, int colour, int s,
+__device__ __forceinline__ void load_coef(Coef<T, V>& c, const FlatOp<T>& op, int colour, int sh,
                                           int p0, int j, int k) {
   const FlatDims& d = op.d;
   const int r = p0 + d.sp * (j + d.ny * k);
-  T ev[V], od[V];
-  ldv<T, V, NT>(ev, op.x + r);
-  ldv<T, V, NT>(od, op.x + d.half + r);
-  // the face past the last pair of the group, for cells on odd columns
-  const T en = s ? op.x[r + V] : ev[V - 1];
+  ldv<T, V, NT>(c.o, op.x + d.half + r);
+  if (V == 1) {
+    c.s[0] = op.x[r + sh];
+  } else {
+    T ev[V];
+    ldv<T, V, NT>(ev, op.x + r);
+    // the face past the last pair of the group, for cells on odd columns
+    const T en = sh ? op.x[r + V] : ev[V - 1];
 #pragma unroll
-  for (int v = 0; v < V; ++v) {
-    c.xl[v] = s ? od[v] : ev[v];
-    c.xh[v] = s ? (v + 1 < V ? ev[v + 1 < V ? v + 1 : v] : en) : od[v];
+    for (int v = 0; v < V; ++v) c.s[v] = sh ? (v + 1 < V ? ev[v + 1 < V ? v + 1 : v] : en) : ev[v];
   }
   const int ry = p0 + d.sp * (j + (d.ny + 1) * k);
   ldv<T, V, NT>(c.yl, op.y + colour * d.yh + ry);
@@ -83,7 +87,7 @@ __device__ __forceinline__ void load_coef(Coef<T, V>& c, const FlatOp<T>& op, in
 // an in-range element is read and not used.
 template <typename T, int V>
 struct Nb {
-  T xl[V], xh[V], yl[V], yh[V], zl[V], zh[V];
+  T o[V], s[V], yl[V], yh[V], zl[V], zh[V];
 };
 
 struct RowIx {
@@ -100,19 +104,16 @@ __device__ __forceinline__ RowIx row_ix(const FlatDims& d, int j, int k) {
 }
 
 template <typename T, int V>
-__device__ __forceinline__ void load_nb(Nb<T, V>& n, const FlatDims& d, const T* O, int s, int p0,
+__device__ __forceinline__ void load_nb(Nb<T, V>& n, const FlatDims& d, const T* O, int sh, int p0,
                                         int j, int k, const RowIx& x) {
   const int row = d.sp * (j + d.ny * k);
-  T c[V];
-  ldv<T, V, false>(c, O + row + p0);
+  ldv<T, V, false>(n.o, O + row + p0);
   const int pl = p0 > 0 ? p0 - 1 : ((d.wall & 1) ? 0 : d.np - 1);
   const int ph = p0 + V < d.np ? p0 + V : ((d.wall & 2) ? p0 : 0);
-  const T ex = O[row + (s ? ph : pl)];
+  const T ex = O[row + (sh ? ph : pl)];
 #pragma unroll
-  for (int v = 0; v < V; ++v) {
-    n.xl[v] = s ? c[v] : (v > 0 ? c[v > 0 ? v - 1 : 0] : ex);
-    n.xh[v] = s ? (v + 1 < V ? c[v + 1 < V ? v + 1 : v] : ex) : c[v];
-  }
+  for (int v = 0; v < V; ++v)
+    n.s[v] = sh ? (v + 1 < V ? n.o[v + 1 < V ? v + 1 : v] : ex) : (v > 0 ? n.o[v > 0 ? v - 1 : 0] : ex);
   ldv<T, V, false>(n.yl, O + p0 + d.sp * (x.jm + d.ny * k));
   ldv<T, V, false>(n.yh, O + p0 + d.sp * (x.jp + d.ny * k));
   ldv<T, V, false>(n.zl, O + p0 + d.sp * (j + d.ny * x.km));
@@ -120,9 +121,8 @@ __device__ __forceinline__ void load_nb(Nb<T, V>& n, const FlatDims& d, const T*
 }
 
 // Coarse parents' corrections of the other-colour neighbours of the cells:
-// own[v] the parent of pair p0 + v, x[v] that of the pair next to the cell
-// (p - 1 or p + 1), y and z those of the neighbour rows in the next coarse row
-// and plane.
+// own[v] the parent of pair p0 + v, x[v] that of the pair beside the cell, y and
+// z those of the neighbour rows in the next coarse row and plane.
 template <typename T, int V>
 struct Par {
   T own[V], x[V], y[V], z[V];
@@ -135,7 +135,7 @@ __device__ __forceinline__ T coarse_at(const FlatDims& c, const T* e, int I, int
 
 template <typename T, int V>
 __device__ __forceinline__ void load_par(Par<T, V>& q, const FlatDims& d, const FlatDims& c,
-                                         const T* e, int s, int p0, int j, int k) {
+                                         const T* e, int sh, int p0, int j, int k) {
   const int J = j >> 1, K = k >> 1;
   // wrapped or clamped as the fine neighbours are (nx = 2 c.nx and so on)
   const int Jn = (j & 1) ? (J < c.ny - 1 ? J + 1 : ((d.wall & 8) ? J : 0))
@@ -145,8 +145,8 @@ __device__ __forceinline__ void load_par(Par<T, V>& q, const FlatDims& d, const 
 #pragma unroll
   for (int v = 0; v < V; ++v) {
     const int I = p0 + v < c.nx ? p0 + v : c.nx - 1;
-    const int In = s ? (I < c.nx - 1 ? I + 1 : ((d.wall & 2) ? I : 0))
-                     : (I > 0 ? I - 1 : ((d.wall & 1) ? 0 : c.nx - 1));
+    const int In = sh ? (I < c.nx - 1 ? I + 1 : ((d.wall & 2) ? I : 0))
+                      : (I > 0 ? I - 1 : ((d.wall & 1) ? 0 : c.nx - 1));
     q.own[v] = coarse_at(c, e, I, J, K);
     q.x[v] = coarse_at(c, e, In, J, K);
     q.y[v] = coarse_at(c, e, I, Jn, K);
@@ -155,11 +155,11 @@ __device__ __forceinline__ void load_par(Par<T, V>& q, const FlatDims& d, const 
 }
 
 template <typename T, int V>
-__device__ __forceinline__ void add_par(Nb<T, V>& n, const Par<T, V>& q, int s, int j, int k) {
+__device__ __forceinline__ void add_par(Nb<T, V>& n, const Par<T, V>& q, int j, int k) {
 #pragma unroll
   for (int v = 0; v < V; ++v) {
-    n.xl[v] = n.xl[v] + (s ? q.own[v] : q.x[v]);
-    n.xh[v] = n.xh[v] + (s ? q.x[v] : q.own[v]);
+    n.o[v] = n.o[v] + q.own[v];
+    n.s[v] = n.s[v] + q.x[v];
     n.yl[v] = n.yl[v] + ((j & 1) ? q.own[v] : q.y[v]);
     n.yh[v] = n.yh[v] + ((j & 1) ? q.y[v] : q.own[v]);
     n.zl[v] = n.zl[v] + ((k & 1) ? q.own[v] : q.z[v]);
@@ -167,33 +167,56 @@ __device__ __forceinline__ void add_par(Nb<T, V>& n, const Par<T, V>& q, int s, 
   }
 }
 
+// Which faces of a cell lie on a wall.
+struct Walls {
+  bool s, yl, yh, zl, zh;
+};
+
+__device__ __forceinline__ Walls walls_of(const FlatDims& d, int sh, int p, int j, int k) {
+  Walls w;
+  w.s = sh ? (d.wall & 2) && p == d.np - 1 : (d.wall & 1) && p == 0;
+  w.yl = (d.wall & 4) && j == 0;
+  w.yh = (d.wall & 8) && j == d.ny - 1;
+  w.zl = (d.wall & 16) && k == 0;
+  w.zh = (d.wall & 32) && k == d.nz - 1;
+  return w;
+}
+
+// A wall face counts twice (phi_ghost = -phi).
 template <typename T, int V>
-__device__ __forceinline__ T diag_of(const FlatOp<T>& op, const Coef<T, V>& c, int v, int s, int p,
-                                     int j, int k) {
+__device__ __forceinline__ T diag_of(const FlatOp<T>& op, const Coef<T, V>& c, int v,
+                                     const Walls& w) {
 #pragma clang fp contract(off)
-  const FlatDims& d = op.d;
   T g = op.a ? c.a[v] : op.alpha;
-  g = g + ((d.wall & 1) && p == 0 && !s ? T(2) * c.xl[v] : c.xl[v]);
-  g = g + ((d.wall & 2) && p == d.np - 1 && s ? T(2) * c.xh[v] : c.xh[v]);
-  g = g + ((d.wall & 4) && j == 0 ? T(2) * c.yl[v] : c.yl[v]);
-  g = g + ((d.wall & 8) && j == d.ny - 1 ? T(2) * c.yh[v] : c.yh[v]);
-  g = g + ((d.wall & 16) && k == 0 ? T(2) * c.zl[v] : c.zl[v]);
-  g = g + ((d.wall & 32) && k == d.nz - 1 ? T(2) * c.zh[v] : c.zh[v]);
+  g = g + c.o[v];
+  g = g + (w.s ? T(2) * c.s[v] : c.s[v]);
+  g = g + (w.yl ? T(2) * c.yl[v] : c.yl[v]);
+  g = g + (w.yh ? T(2) * c.yh[v] : c.yh[v]);
+  g = g + (w.zl ? T(2) * c.zl[v] : c.zl[v]);
+  g = g + (w.zh ? T(2) * c.zh[v] : c.zh[v]);
   return g;
 }
 
+// ... and has no neighbour: a coefficient of 0.
 template <typename T, int V>
-__device__ __forceinline__ T off_of(const FlatOp<T>& op, const Coef<T, V>& c, const Nb<T, V>& n,
-                                    int v, int s, int p, int j, int k) {
+__device__ __forceinline__ void drop_walls(Coef<T, V>& c, int v, const Walls& w) {
+  c.s[v] = w.s ? T(0) : c.s[v];
+  c.yl[v] = w.yl ? T(0) : c.yl[v];
+  c.yh[v] = w.yh ? T(0) : c.yh[v];
+  c.zl[v] = w.zl ? T(0) : c.zl[v];
+  c.zh[v] = w.zh ? T(0) : c.zh[v];
+}
+
+// sum of c phi over the neighbours (walls dropped from c)
+template <typename T, int V>
+__device__ __forceinline__ T off_of(const Coef<T, V>& c, const Nb<T, V>& n, int v) {
 #pragma clang fp contract(off)
-  const FlatDims& d = op.d;
-  T o = (d.wall & 1) && p == 0 && !s ? T(0) : c.xl[v] * n.xl[v];
-  o = (d.wall & 2) && p == d.np - 1 && s ? o : fma_(c.xh[v], n.xh[v], o);
-  o = (d.wall & 4) && j == 0 ? o : fma_(c.yl[v], n.yl[v], o);
-  o = (d.wall & 8) && j == d.ny - 1 ? o : fma_(c.yh[v], n.yh[v], o);
-  o = (d.wall & 16) && k == 0 ? o : fma_(c.zl[v], n.zl[v], o);
-  o = (d.wall & 32) && k == d.nz - 1 ? o : fma_(c.zh[v], n.zh[v], o);
-  return o;
+  T o = c.o[v] * n.o[v];
+  o = fma_(c.s[v], n.s[v], o);
+  o = fma_(c.yl[v], n.yl[v], o);
+  o = fma_(c.yh[v], n.yh[v], o);
+  o = fma_(c.zl[v], n.zl[v], o);
+  return fma_(c.zh[v], n.zh[v], o);
 }
 
 template <typename T>
@@ -250,13 +273,15 @@ __global__ void __launch_bounds__(256)
     if (!ZG) load_nb<T, V>(n, d, other, s, p0, j, k, row_ix(d, j, k));
     if (PE) load_par<T, V>(q, d, cd, ec, s, p0, j, k);
     if (STOP) ldv<T, V, NT>(ov, old + at);
-    if (PE) add_par<T, V>(n, q, s, j, k);
+    if (PE) add_par<T, V>(n, q, j, k);
     T nv[V];
 #pragma unroll
     for (int v = 0; v < V; ++v) {
-      const T diag = diag_of<T, V>(op, c, v, s, p0 + v, j, k);
-      const T off = ZG ? T(0) : off_of<T, V>(op, c, n, v, s, p0 + v, j, k);
-      nv[v] = (ZG ? fv[v] : fv[v] + off) / diag;
+      const Walls w = walls_of(d, s, p0 + v, j, k);
+      const T diag = diag_of<T, V>(op, c, v, w);
+      drop_walls<T, V>(c, v, w);
+      const T off = ZG ? T(0) : off_of<T, V>(c, n, v);
+      nv[v] = (ZG ? fv[v] : fv[v] + off) * (T(1) / diag);
       if (STOP && p0 + v < d.np) {
         const unsigned long long bits = absbits(resid_of(fv[v], diag, ov[v], off));
         mx = bits > mx ? bits : mx;
@@ -296,8 +321,10 @@ __global__ void __launch_bounds__(256)
       ldv<T, 1, NT>(fv, f + at);
       load_coef<T, 1, NT>(c, op, 0, s, I, j, k);
       load_nb<T, 1>(n, d, v + d.half, s, I, j, k, row_ix(d, j, k));
-      r[dj] = resid_of(fv[0], diag_of<T, 1>(op, c, 0, s, I, j, k), v[at],
-                       off_of<T, 1>(op, c, n, 0, s, I, j, k));
+      const Walls w = walls_of(d, s, I, j, k);
+      const T diag = diag_of<T, 1>(op, c, 0, w);
+      drop_walls<T, 1>(c, 0, w);
+      r[dj] = resid_of(fv[0], diag, v[at], off_of<T, 1>(c, n, 0));
     }
     zs[dk] = r[0] + r[1];
   }
@@ -332,8 +359,10 @@ __global__ void __launch_bounds__(256)
       load_nb<T, V>(n, d, v + (1 - colour) * d.half, s, p0, j, k, rx);
 #pragma unroll
       for (int u = 0; u < V; ++u) {
-        const T diag = diag_of<T, V>(op, c, u, s, p0 + u, j, k);
-        const T off = off_of<T, V>(op, c, n, u, s, p0 + u, j, k);
+        const Walls w = walls_of(d, s, p0 + u, j, k);
+        const T diag = diag_of<T, V>(op, c, u, w);
+        drop_walls<T, V>(c, u, w);
+        const T off = off_of<T, V>(c, n, u);
         const T r = f ? resid_of(fv[u], diag, cv[u], off) : fma_(diag, cv[u], -off);
         rv[u] = (TO)r;
         if (p0 + u < d.np) {
@@ -351,6 +380,186 @@ __global__ void __launch_bounds__(256)
     int phase = 0;
     dot = block_sum(dot, red, phase);
     if (threadIdx.x == 0) dots[blockIdx.x] = dot;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Two sweeps in one launch, for levels whose passes are launches rather than
+// memory traffic.  A work-group takes a block of OP pairs by OY by OZ rows,
+// grown by 4 cells on every side, and runs the half-sweeps on the grown block:
+// every half-sweep spoils one more layer of its rim, so the block itself comes
+// out right, and no work-group needs another's values.  A lane keeps its
+// pairs' coefficients in registers; the values are in LDS.  The results go to
+// other arrays than the values came from (neighbouring work-groups still read
+// those).
+// MODE 0: pre-smoothing from zero (red, black, red, black), then the red
+// residual's restriction; MODE 1: the same after a red half-sweep done elsewhere
+// (black, red, black; src its red half); MODE 2: post-smoothing, colour C0
+// first (src the other colour's half, to which the coarse correction is added
+// as it is loaded).
+// One work-group per CU (94 VGPRs, 1024 lanes; FP32 60, two); a block takes 6.5
+// to 8 us, of which the coefficients' loads 2-3.  32^3 FP64 7.3 us for five
+// launches of 3.6-6.7 us, 16^3 6.5.  A second round of blocks loses the gain:
+// 64^3 FP64 (512 blocks) 20-21 us against 25 (pre) and 19 (post) for the separate
+// launches; blocks of 8 pairs (one round) spill there and take 22.  FP32's fit:
+// 64^3 11 us against 15 in two rounds of 4 and 22 for the launches.
+// Blocks of OP pairs by 8 rows by 8 planes.
+constexpr int kBlkOY = 8, kBlkOZ = 8, kBlkH = 4, kBlkLanes = 1024;
+template <int OP>
+struct Blk {
+  static constexpr int GX = OP + kBlkH, GY = kBlkOY + 2 * kBlkH, GZ = kBlkOZ + 2 * kBlkH;
+  static constexpr int NP = GX * GY * GZ, M = NP / kBlkLanes;
+  static constexpr int PAD = GX * GY;  // neighbour reads past the block's ends
+  static_assert(NP % kBlkLanes == 0, "whole pairs per lane");
+};
+
+template <typename T>
+struct BlkPair {
+  Coef<T, 1> c[2];
+  T f[2], rdiag[2], diag;  // diag: the red cell's
+  int side[2];             // LDS offset of the pair beside the colour's cell
+  int at;                  // element in the level's arrays
+  int rim;                 // layers outside the block (<= 0: inside)
+  bool in;                 // a pair of the domain (or its periodic image)
+};
+
+template <typename T, int OP, int COLOUR>
+__device__ __forceinline__ T blk_off(const BlkPair<T>& b, const T* O) {
+  constexpr int GX = Blk<OP>::GX, GXY = GX * Blk<OP>::GY;
+  Nb<T, 1> n;
+  n.o[0] = O[0];
+  n.s[0] = O[b.side[COLOUR]];
+  n.yl[0] = O[-GX];
+  n.yh[0] = O[GX];
+  n.zl[0] = O[-GXY];
+  n.zh[0] = O[GXY];
+  return off_of<T, 1>(b.c[COLOUR], n, 0);
+}
+
+template <typename T, int OP, int MODE, int C0>
+__global__ void __launch_bounds__(kBlkLanes)
+    k_flat_block(FlatOp<T> op, int nbx, int nby, const T* __restrict__ src,
+                 const T* __restrict__ f, T* __restrict__ dst, FlatDims cd, T* __restrict__ cf,
+                 const T* __restrict__ ec) {
+#pragma clang fp contract(off)
+  using B = Blk<OP>;
+  constexpr int kBlkGX = B::GX, kBlkGY = B::GY, kBlkNP = B::NP, kBlkM = B::M, kBlkPad = B::PAD,
+                kBlkOP = OP;
+  __shared__ T lds[2][kBlkNP + 2 * kBlkPad];
+  T* const e[2] = {lds[0] + kBlkPad, lds[1] + kBlkPad};
+  const FlatDims& d = op.d;
+  const int tid = threadIdx.x;
+  const int bx = blockIdx.x % nbx, by = blockIdx.x / nbx % nby, bz = blockIdx.x / nbx / nby;
+  const int p0 = bx * kBlkOP, y0 = by * kBlkOY, z0 = bz * kBlkOZ;
+  BlkPair<T> b[kBlkM];
+#pragma unroll
+  for (int m = 0; m < kBlkM; ++m) {
+    const int q = tid + m * kBlkLanes;
+    const int lx = q % kBlkGX, ly = q / kBlkGX % kBlkGY, lz = q / (kBlkGX * kBlkGY);
+    int p = p0 - kBlkH / 2 + lx, j = y0 - kBlkH + ly, k = z0 - kBlkH + lz;
+    // along x the nearer cell of the pair counts
+    b[m].rim = max(max(2 * max(kBlkH / 2 - lx, lx - (kBlkH / 2 + kBlkOP - 1)) - 1,
+                       max(kBlkH - ly, ly - (kBlkH + kBlkOY - 1))),
+                   max(kBlkH - lz, lz - (kBlkH + kBlkOZ - 1)));
+    bool in = true;
+    if (d.wall & 1)
+      in = in && p >= 0 && p < d.np;
+    else
+      p = (p % d.np + d.np) % d.np;
+    if (d.wall & 4)
+      in = in && j >= 0 && j < d.ny;
+    else
+      j = (j % d.ny + d.ny) % d.ny;
+    if (d.wall & 16)
+      in = in && k >= 0 && k < d.nz;
+    else
+      k = (k % d.nz + d.nz) % d.nz;
+    b[m].in = in;
+    b[m].at = 0;
+    T v = T(0);
+    if (in) {
+      const int at = p + d.sp * (j + d.ny * k);
+      b[m].at = at;
+      if (MODE == 1) v = src[at];
+      if (MODE == 2) v = src[at] + coarse_at(cd, ec, p, j >> 1, k >> 1);
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        const int sh = (j + k + c) & 1;
+        b[m].f[c] = f[c * d.half + at];
+        load_coef<T, 1, false>(b[m].c[c], op, c, sh, p, j, k);
+        const Walls w = walls_of(d, sh, p, j, k);
+        const T diag = diag_of<T, 1>(op, b[m].c[c], 0, w);
+        drop_walls<T, 1>(b[m].c[c], 0, w);
+        b[m].rdiag[c] = T(1) / diag;
+        if (c == 0) b[m].diag = diag;
+        b[m].side[c] = sh ? 1 : -1;
+      }
+    }
+    // slots outside the domain are read with a coefficient of 0
+    e[MODE == 2 ? 1 - C0 : 0][q] = v;
+    e[MODE == 2 ? C0 : 1][q] = T(0);
+  }
+  for (int q = tid; q < kBlkPad; q += kBlkLanes)
+    for (int c = 0; c < 2; ++c) {
+      e[c][q - kBlkPad] = T(0);
+      e[c][kBlkNP + q] = T(0);
+    }
+  __syncthreads();
+  // half-sweep number t (0 ..) of a run that ends on the block itself after
+  // the last: layers beyond `layers` are spoiled by then and skipped
+#define BLK_HALF(COL, ZG, LAYERS)                                                              \
+  {                                                                                            \
+    _Pragma("unroll") for (int m = 0; m < kBlkM; ++m) {                                        \
+      const int q = tid + m * kBlkLanes;                                                       \
+      if (b[m].in && b[m].rim <= LAYERS)                                                       \
+        e[COL][q] = (ZG ? b[m].f[COL] : b[m].f[COL] + blk_off<T, OP, COL>(b[m], e[1 - (COL)] + q)) * \
+                    b[m].rdiag[COL];                                                           \
+    }                                                                                          \
+    __syncthreads();                                                                           \
+  }
+  if (MODE == 0) BLK_HALF(0, true, 4)
+  if (MODE <= 1) {
+    BLK_HALF(1, false, 3)
+    BLK_HALF(0, false, 2)
+    BLK_HALF(1, false, 1)
+  } else {
+    BLK_HALF(C0, false, 3)
+    BLK_HALF(1 - C0, false, 2)
+    BLK_HALF(C0, false, 1)
+    BLK_HALF(1 - C0, false, 0)
+  }
+#undef BLK_HALF
+  T r[kBlkM];
+#pragma unroll
+  for (int m = 0; m < kBlkM; ++m) {
+    const int q = tid + m * kBlkLanes;
+    // inside the block and, for periodic domains too, not a wrapped image
+    const int lx = q % kBlkGX, ly = q / kBlkGX % kBlkGY, lz = q / (kBlkGX * kBlkGY);
+    const bool own = b[m].rim <= 0 && p0 - kBlkH / 2 + lx < d.np && y0 - kBlkH + ly < d.ny &&
+                     z0 - kBlkH + lz < d.nz;
+    r[m] = T(0);
+    if (own) {
+      dst[b[m].at] = e[0][q];
+      dst[d.half + b[m].at] = e[1][q];
+      if (MODE <= 1)
+        r[m] = resid_of(b[m].f[0], b[m].diag, e[0][q], blk_off<T, OP, 0>(b[m], e[1] + q));
+    }
+  }
+  if (MODE <= 1) {
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < kBlkM; ++m) e[0][tid + m * kBlkLanes] = r[m];
+    __syncthreads();
+    if (tid < kBlkOP * (kBlkOY / 2) * (kBlkOZ / 2)) {
+      const int cx = tid % kBlkOP, cy = tid / kBlkOP % (kBlkOY / 2), cz = tid / (kBlkOP * (kBlkOY / 2));
+      const int I = p0 + cx, J = y0 / 2 + cy, K = z0 / 2 + cz;
+      if (I < cd.nx && J < cd.ny && K < cd.nz) {
+        const int q = kBlkH / 2 + cx + kBlkGX * (kBlkH + 2 * cy + kBlkGY * (kBlkH + 2 * cz));
+        const T zl = e[0][q] + e[0][q + kBlkGX];
+        const T zh = e[0][q + kBlkGX * kBlkGY] + e[0][q + kBlkGX * kBlkGY + kBlkGX];
+        cf[((I + J + K) & 1) * cd.half + (I >> 1) + cd.sp * (J + cd.ny * K)] = (zl + zh) * T(0.125);
+      }
+    }
   }
 }
 
@@ -589,10 +798,12 @@ __device__ __forceinline__ TailArr<T> tail_arr(const FlatTail<T>* tp, T* lds, in
   return a;
 }
 
-// A pair of the level and both its cells' coefficients.
+// A pair of the level and both its cells' coefficients (walls dropped) and
+// diagonals.
 template <typename T>
 struct TailPair {
   Coef<T, 1> c[2];
+  T diag, rdiag[2];  // diag: the red cell's
   int p, j, k;
 };
 
@@ -605,8 +816,15 @@ __device__ __forceinline__ TailPair<T> tail_pair(const FlatOp<T>& op, int q) {
   m.k = t / d.ny;
   m.j = t - m.k * d.ny;
 #pragma unroll
-  for (int c = 0; c < 2; ++c)
-    load_coef<T, 1, false>(m.c[c], op, c, (m.j + m.k + c) & 1, m.p, m.j, m.k);
+  for (int c = 0; c < 2; ++c) {
+    const int sh = (m.j + m.k + c) & 1;
+    load_coef<T, 1, false>(m.c[c], op, c, sh, m.p, m.j, m.k);
+    const Walls w = walls_of(d, sh, m.p, m.j, m.k);
+    const T diag = diag_of<T, 1>(op, m.c[c], 0, w);
+    drop_walls<T, 1>(m.c[c], 0, w);
+    m.rdiag[c] = T(1) / diag;
+    if (c == 0) m.diag = diag;
+  }
   return m;
 }
 
@@ -620,7 +838,6 @@ __device__ __forceinline__ void tail_update(const FlatOp<T>& op, const TailArr<T
   const Coef<T, 1>& c = m.c[COLOUR];
   const int s = (m.j + m.k + COLOUR) & 1;
   const int at = m.p + d.sp * (m.j + d.ny * m.k);
-  const T diag = diag_of<T, 1>(op, c, 0, s, m.p, m.j, m.k);
   T off = T(0);
   if (!ZG) {
     Nb<T, 1> n;
@@ -628,12 +845,12 @@ __device__ __forceinline__ void tail_update(const FlatOp<T>& op, const TailArr<T
     if (PE) {
       Par<T, 1> q;
       load_par<T, 1>(q, d, cd, ec, s, m.p, m.j, m.k);
-      add_par<T, 1>(n, q, s, m.j, m.k);
+      add_par<T, 1>(n, q, m.j, m.k);
     }
-    off = off_of<T, 1>(op, c, n, 0, s, m.p, m.j, m.k);
+    off = off_of<T, 1>(c, n, 0);
   }
   const T fv = A.f[COLOUR * d.half + at];
-  A.e[COLOUR * d.half + at] = (ZG ? fv : fv + off) / diag;
+  A.e[COLOUR * d.half + at] = (ZG ? fv : fv + off) * m.rdiag[COLOUR];
 }
 
 // One half-sweep of the work-group.  own: the lane's pair where the level has
@@ -695,8 +912,7 @@ __global__ void __launch_bounds__(NT) k_flat_tail(const FlatTail<T>* __restrict_
       const int s = (own.j + own.k) & 1, at = own.p + d.sp * (own.j + d.ny * own.k);
       Nb<T, 1> n;
       load_nb<T, 1>(n, d, A.e + d.half, s, own.p, own.j, own.k, row_ix(d, own.j, own.k));
-      A.r[at] = resid_of(A.f[at], diag_of<T, 1>(op, own.c[0], 0, s, own.p, own.j, own.k), A.e[at],
-                         off_of<T, 1>(op, own.c[0], n, 0, s, own.p, own.j, own.k));
+      A.r[at] = resid_of(A.f[at], own.diag, A.e[at], off_of<T, 1>(own.c[0], n, 0));
     }
     __syncthreads();
     const int ncell = cd.nx * cd.ny * cd.nz;
@@ -871,6 +1087,47 @@ hipError_t launch_flat_restrict(hipStream_t st, const FlatOp<T>& op, FlatPass ps
   return hipGetLastError();
 }
 
+// Blocks of OP pairs that cover a level.
+static long long blocks_of(const FlatDims& d, int op) {
+  return (long long)((d.np + op - 1) / op) * ((d.ny + kBlkOY - 1) / kBlkOY) *
+         ((d.nz + kBlkOZ - 1) / kBlkOZ);
+}
+
+int flat_block_pairs(const FlatDims& d, int elem) {
+  if (blocks_of(d, 4) <= 256) return 4;
+  return elem == 4 && blocks_of(d, 8) <= 256 ? 8 : 0;
+}
+
+template <typename T>
+hipError_t launch_flat_block(hipStream_t st, const FlatOp<T>& op, FlatBlockMode mode, const T* src,
+                             const T* f, T* dst, const FlatDims& cd, T* cf, const T* ec) {
+  const FlatDims& d = op.d;
+  if (2 * cd.nx != d.nx || 2 * cd.ny != d.ny || 2 * cd.nz != d.nz) return hipErrorInvalidValue;
+  const int w = flat_block_pairs(d, sizeof(T));
+  if (w == 0) return hipErrorInvalidValue;
+  const int nbx = (d.np + w - 1) / w, nby = (d.ny + kBlkOY - 1) / kBlkOY;
+  const dim3 grid((unsigned)blocks_of(d, w));
+#define FBK(W, M, C)                                                                               \
+  hipLaunchKernelGGL((k_flat_block<T, W, M, C>), grid, dim3(kBlkLanes), 0, st, op, nbx, nby, src, \
+                     f, dst, cd, cf, ec)
+#define FB(M, C)                          \
+  if constexpr (sizeof(T) == 4) {         \
+    if (w == 8) FBK(8, M, C);             \
+    else FBK(4, M, C);                    \
+  } else {                                \
+    FBK(4, M, C);                         \
+  }
+  switch (mode) {
+    case FlatBlockMode::pre_zero: FB(0, 0) break;
+    case FlatBlockMode::pre_after_red: FB(1, 0) break;
+    case FlatBlockMode::post_red: src += d.half; FB(2, 0) break;
+    case FlatBlockMode::post_black: FB(2, 1) break;
+  }
+#undef FB
+#undef FBK
+  return hipGetLastError();
+}
+
 int flat_resid_blocks(const FlatDims& d) { return grid_of(d.np, d.ny * d.nz, 0).nb; }
 
 template <typename T, typename TO>
@@ -1006,6 +1263,8 @@ hipError_t launch_flat_tail(hipStream_t st, const FlatTail<T>& t, const FlatTail
                                          double*);                                                 \
   template hipError_t launch_flat_cg_p<T>(hipStream_t, long long, double*, const T*,               \
                                           const double*, const double*, int);                      \
+  template hipError_t launch_flat_block<T>(hipStream_t, const FlatOp<T>&, FlatBlockMode, const T*, \
+                                           const T*, T*, const FlatDims&, T*, const T*);           \
   template hipError_t launch_flat_tail<T>(hipStream_t, const FlatTail<T>&, const FlatTail<T>*);
 
 INST(double)

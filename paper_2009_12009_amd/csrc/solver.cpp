@@ -164,7 +164,11 @@ struct FlatLevel {
   FlatOp<T> op{};
   T *x = nullptr, *y = nullptr, *z = nullptr, *a = nullptr;
   T *e = nullptr, *f = nullptr, *r = nullptr;
+  // levels smoothed in blocks: the post-smoothing's result (else in e)
+  T* e2 = nullptr;
+  bool block = false;
   int stream = 0;
+  T* out() const { return block ? e2 : e; }
 };
 
 struct ProfRec {
@@ -207,6 +211,7 @@ struct mg_solver {
   std::vector<FlatLevel<float>> f32;
   int flat_tail = -1;  // first level of the one-launch tail (-1: none)
   double* fphi[2] = {nullptr, nullptr};  // iterates of the folded stop test; FP32: fphi[0]
+  double *fmid = nullptr, *fred = nullptr;  // finest level in blocks: between them, red half
   double* frhs = nullptr;
   double *fr = nullptr, *fp = nullptr, *fq = nullptr, *fz = nullptr;  // preconditioned CG
   double* fpart = nullptr;
@@ -612,6 +617,13 @@ int flat_tail_level(const mg_solver* s) {
   return start < nl - 1 ? start : -1;
 }
 
+// Whether level l (extents d, elements of elem bytes) is smoothed two sweeps to
+// a launch (launch_flat_block): the V(2,2) cycle on small levels.
+bool flat_in_blocks(const mg_solver* s, size_t l, const FlatDims& d, int elem) {
+  return s->opts.nu1 == 2 && s->opts.nu2 == 2 && l + 1 < s->L.size() &&
+         (s->flat_tail < 1 || (int)l < s->flat_tail) && flat_block_pairs(d, elem) > 0;
+}
+
 template <typename T>
 std::vector<FlatLevel<T>>& flat_levels(mg_solver* s);
 template <>
@@ -643,6 +655,8 @@ void layout_flat(mg_solver* s, size_t l, bool ef, Bump& bump) {
   if (ef) {
     v.e = bump.take<T>(2 * (size_t)d.half);
     v.f = bump.take<T>(2 * (size_t)d.half);
+    v.block = flat_in_blocks(s, l, d, sizeof(T));
+    if (v.block) v.e2 = bump.take<T>(2 * (size_t)d.half);
   }
   v.op.x = v.x;
   v.op.y = v.y;
@@ -663,7 +677,14 @@ void layout_flat_all(mg_solver* s, Bump& bump) {
   const size_t n = 2 * (size_t)s->f64[0].op.d.half;
   s->frhs = bump.take<double>(n);
   s->fphi[0] = bump.take<double>(n);
-  if (!f32 && !s->opts.krylov) s->fphi[1] = bump.take<double>(n);
+  s->fmid = s->fred = nullptr;
+  if (!f32 && !s->opts.krylov) {
+    s->fphi[1] = bump.take<double>(n);
+    if (flat_in_blocks(s, 0, s->f64[0].op.d, 8)) {
+      s->fmid = bump.take<double>(n);
+      s->fred = bump.take<double>(n / 2);
+    }
+  }
   if (s->opts.krylov) {
     // FP64: the V-cycle's right-hand side and result are r and z
     if (f32) {
@@ -671,7 +692,7 @@ void layout_flat_all(mg_solver* s, Bump& bump) {
       s->fz = bump.take<double>(n);
     } else {
       s->fr = s->f64[0].f;
-      s->fz = s->f64[0].e;
+      s->fz = s->f64[0].out();
     }
     s->fp = bump.take<double>(n);
     s->fq = bump.take<double>(n);
@@ -1570,12 +1591,28 @@ int flat_post(mg_solver* s, size_t l, T* v, const T* f, FlatWalk& w) {
       const bool pe = k == 0 && u == 0;
       ProfScope ps(s, pe ? 4 : 0, l == 0);
       HIPTRY(launch_flat_half<T>(s->st, op, w.next(), v + (1 - c) * h, v + c * h, f, c, false,
-                                 pe ? &F[l + 1].op.d : nullptr, pe ? F[l + 1].e : nullptr));
+                                 pe ? &F[l + 1].op.d : nullptr, pe ? F[l + 1].out() : nullptr));
     }
   return MG_OK;
 }
 
-// Level l from a zero guess: correction e from the right-hand side f.
+template <typename T>
+int flat_cycle(mg_solver* s, size_t l);
+
+// The levels below l (from level 1 on replayed as a graph).
+template <typename T>
+int flat_below(mg_solver* s, size_t l) {
+  ProfScope ps(s, 5, l == 0);
+  if (l > 0 || !s->opts.use_graph) return flat_cycle<T>(s, l + 1);
+  HIPTRY(hipGraphLaunch(sizeof(T) == 4 ? s->graph32 : s->graph64, s->st));
+  return MG_OK;
+}
+
+FlatBlockMode flat_post_mode(const mg_solver* s) {
+  return s->opts.krylov ? FlatBlockMode::post_black : FlatBlockMode::post_red;
+}
+
+// Level l from a zero guess: correction (out()) from the right-hand side f.
 template <typename T>
 int flat_cycle(mg_solver* s, size_t l) {
   std::vector<FlatLevel<T>>& F = flat_levels<T>(s);
@@ -1604,6 +1641,18 @@ int flat_cycle(mg_solver* s, size_t l) {
     return MG_OK;
   }
   const size_t h = op.d.half;
+  if (v.block) {
+    {
+      ProfScope ps(s, 0, l == 0);
+      HIPTRY(launch_flat_block<T>(s->st, op, FlatBlockMode::pre_zero, nullptr, v.f, v.e,
+                                  F[l + 1].op.d, F[l + 1].f, nullptr));
+    }
+    if ((rc = flat_below<T>(s, l))) return rc;
+    ProfScope ps(s, 4, l == 0);
+    HIPTRY(launch_flat_block<T>(s->st, op, flat_post_mode(s), v.e, v.f, v.e2, F[l + 1].op.d,
+                                nullptr, F[l + 1].out()));
+    return MG_OK;
+  }
   FlatWalk w(v.stream);
   for (int k = 0; k < s->opts.nu1; ++k)
     for (int c = 0; c < 2; ++c) {
@@ -1615,13 +1664,7 @@ int flat_cycle(mg_solver* s, size_t l) {
     ProfScope ps(s, 1, l == 0);
     HIPTRY(launch_flat_restrict<T>(s->st, op, w.next(), v.e, v.f, F[l + 1].op.d, F[l + 1].f));
   }
-  {
-    ProfScope ps(s, 5, l == 0);
-    if (l == 0 && s->opts.use_graph)
-      HIPTRY(hipGraphLaunch(f32 ? s->graph32 : s->graph64, s->st));
-    else if ((rc = flat_cycle<T>(s, l + 1)))
-      return rc;
-  }
+  if ((rc = flat_below<T>(s, l))) return rc;
   return flat_post<T>(s, l, v.e, v.f, w);
 }
 
@@ -3676,6 +3719,7 @@ int solve_flat(mg_solver* s, double tol, mg_info_t* inf, double* hist, int* stat
   while (true) {
     const double* c = s->fphi[cur];
     double* n = s->fphi[1 - cur];
+    double* red = s->fmid ? s->fred : n;  // the red half after the first half-sweep
     const int slot = 1 + (it & 1);
     HIPTRY(launch_fill_u64(s->st, norm_slot(s, slot), kNormSlot, 0ull));
     if (it == 0) {
@@ -3685,7 +3729,7 @@ int solve_flat(mg_solver* s, double tol, mg_info_t* inf, double* hist, int* stat
     }
     {
       ProfScope ps(s, it == 0 ? 0 : 1, true);
-      HIPTRY(launch_flat_half<double>(s->st, op, w.next(), c + h, n, s->frhs, 0, false, nullptr,
+      HIPTRY(launch_flat_half<double>(s->st, op, w.next(), c + h, red, s->frhs, 0, false, nullptr,
                                       nullptr, it == 0 ? nullptr : c,
                                       it == 0 ? nullptr : norm_slot(s, slot)));
     }
@@ -3699,25 +3743,29 @@ int solve_flat(mg_solver* s, double tol, mg_info_t* inf, double* hist, int* stat
       if (d < 0) return fail(MG_ERR_HIP, "norm read-back failed");
       if (d) break;
     }
-    for (int k = 0; k < s->opts.nu1; ++k)
-      for (int col = k == 0 ? 1 : 0; col < 2; ++col) {
-        ProfScope ps(s, 0, true);
-        HIPTRY(launch_flat_half<double>(s->st, op, w.next(), n + (1 - col) * h, n + col * h,
-                                        s->frhs, col, false));
-      }
-    {
+    FlatLevel<double>& v1 = s->f64[1];
+    if (s->fmid) {
+      ProfScope ps(s, 0, true);
+      HIPTRY(launch_flat_block<double>(s->st, op, FlatBlockMode::pre_after_red, red, s->frhs,
+                                       s->fmid, v1.op.d, v1.f, nullptr));
+    } else {
+      for (int k = 0; k < s->opts.nu1; ++k)
+        for (int col = k == 0 ? 1 : 0; col < 2; ++col) {
+          ProfScope ps(s, 0, true);
+          HIPTRY(launch_flat_half<double>(s->st, op, w.next(), n + (1 - col) * h, n + col * h,
+                                          s->frhs, col, false));
+        }
       ProfScope ps(s, 1, true);
-      HIPTRY(launch_flat_restrict<double>(s->st, op, w.next(), n, s->frhs, s->f64[1].op.d,
-                                          s->f64[1].f));
+      HIPTRY(launch_flat_restrict<double>(s->st, op, w.next(), n, s->frhs, v1.op.d, v1.f));
     }
-    {
-      ProfScope ps(s, 5, true);
-      if (s->opts.use_graph)
-        HIPTRY(hipGraphLaunch(s->graph64, s->st));
-      else if ((rc = flat_cycle<double>(s, 1)))
-        return rc;
+    if ((rc = flat_below<double>(s, 0))) return rc;
+    if (s->fmid) {
+      ProfScope ps(s, 4, true);
+      HIPTRY(launch_flat_block<double>(s->st, op, flat_post_mode(s), s->fmid, s->frhs, n, v1.op.d,
+                                       nullptr, v1.out()));
+    } else if ((rc = flat_post<double>(s, 0, n, s->frhs, w))) {
+      return rc;
     }
-    if ((rc = flat_post<double>(s, 0, n, s->frhs, w))) return rc;
     if (!wait) {
       const int d = decide();
       if (d < 0) return fail(MG_ERR_HIP, "norm read-back failed");
@@ -3752,7 +3800,7 @@ int solve_flat_refine(mg_solver* s, double tol, mg_info_t* inf, double* hist, in
     if ((rc = flat_cycle<float>(s, 0))) return rc;
     {
       ProfScope ps(s, 6, true);
-      HIPTRY(launch_flat_update(s->st, 2ll * op.d.half, s->fphi[0], s->f32[0].e));
+      HIPTRY(launch_flat_update(s->st, 2ll * op.d.half, s->fphi[0], s->f32[0].out()));
     }
     ++it;
   }
@@ -3823,10 +3871,10 @@ int solve_flat_pcg(mg_solver* s, double tol, mg_info_t* inf, double* hist, int* 
     {
       ProfScope ps(s, 6, true);
       if (f32 && !s->singular) {
-        HIPTRY(launch_flat_dot<float>(s->st, n, r, s->f32[0].e, s->fpart, rho_new));
-        HIPTRY(launch_flat_cg_p<float>(s->st, n, p, s->f32[0].e, rho_new, rho_old, restart));
+        HIPTRY(launch_flat_dot<float>(s->st, n, r, s->f32[0].out(), s->fpart, rho_new));
+        HIPTRY(launch_flat_cg_p<float>(s->st, n, p, s->f32[0].out(), rho_new, rho_old, restart));
       } else {
-        if (f32) HIPTRY((launch_convert<float, double>(s->st, s->f32[0].e, s->fz, n)));
+        if (f32) HIPTRY((launch_convert<float, double>(s->st, s->f32[0].out(), s->fz, n)));
         if (s->singular)
           HIPTRY(launch_flat_remove_mean(s->st, op.d, s->fz, s->fpart, s->d_sum));
         HIPTRY(launch_flat_dot<double>(s->st, n, r, s->fz, s->fpart, rho_new));

@@ -1,6 +1,6 @@
 """GPU parity of the V-cycle on the split-colour layout where its kernels
 change form: rows whose pairs do not fill the last wide load, periodic rows that
-rule wide loads out, rows shorter than a cache line, domains with low corners
+rule wide loads out, rows shorter than a cache line, levels smoothed in blocks, domains with low corners
 away from zero, cell coefficients, the tail in LDS and in memory, and levels
 large enough for wide loads.  Two V-cycles against the oracle, cell by cell."""
 
@@ -19,6 +19,10 @@ CASES = [
     ((48, 24, 16), (-16, 32, 0), (False, True, False), 2, True, {}),
     ((64, 32, 32), (0, 0, 0), (True, True, True), 2, False, dict(coarse_tail=4096)),
     ((64, 32, 32), (0, 0, 0), (False, False, True), 2, True, dict(coarse_tail=8192)),
+    # two sweeps to a launch: FP64 blocks of 4 pairs with ragged ends above, FP32
+    # blocks of 8 pairs
+    ((56, 52, 60), (0, 0, 0), (False, False, True), 1, True, {}),
+    ((64, 64, 48), (0, 0, 0), (True, False, False), 2, False, dict(use_graph=0)),
     # two FP64 pairs per lane: rows that fill, leave a remainder, wrap
     ((132, 96, 96), (0, 0, 0), (False, False, False), 1, True, {}),
     ((136, 96, 88), (0, 0, 0), (True, False, True), 1, False, {}),
