@@ -44,7 +44,8 @@
  *   and the stop test are then always part of a smoothing pass and there are
  *   no ghost cells, so the options and tile shapes marked [boxes] change
  *   nothing; they apply to solvers that keep levels as boxes (a single level,
- *   nu1 or nu2 = 0, the composite solve) and tile shapes also to mg_apply and
+ *   nu1 or nu2 = 0) and to the composite solve outside its coarse V-cycle
+ *   (which is stored as above), tile shapes also to mg_apply and
  *   mg_time_smoother.  A face that two boxes share must hold the same
  *   coefficient in both (the one of the box above it is used).
  * - Streams: work is enqueued on the stream given (NULL = the default

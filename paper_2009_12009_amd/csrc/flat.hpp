@@ -101,14 +101,15 @@ hipError_t launch_flat_resid(hipStream_t st, const FlatOp<T>& op, FlatPass ps, c
                              const T* f, TO* out, unsigned long long* normbits, double* dots);
 int flat_resid_blocks(const FlatDims& d);
 
-// Box MultiFab (double, ng 0 or 1) <-> the split-colour array, valid cells.
+// Box arrays (ng 0 or 1) <-> the split-colour array, valid cells.
 // lo: low corner of the domain.  normbits (gather): max |value|.
+template <typename T>
 hipError_t launch_flat_gather(hipStream_t st, const BoxInfo* boxes, int nbox, int max_cells,
-                              const int lo[3], const FlatDims& d, const double* src, int ng,
-                              double* dst, unsigned long long* normbits);
+                              const int lo[3], const FlatDims& d, const T* src, int ng, T* dst,
+                              unsigned long long* normbits);
+template <typename T>
 hipError_t launch_flat_scatter(hipStream_t st, const BoxInfo* boxes, int nbox, int max_cells,
-                               const int lo[3], const FlatDims& d, const double* src, double* dst,
-                               int ng);
+                               const int lo[3], const FlatDims& d, const T* src, T* dst, int ng);
 // Coefficients from a level's box arrays: faces of direction dir scaled by
 // (beta b) ih (a face shared by two boxes is taken from the box above it),
 // cell coefficient as alpha * a.

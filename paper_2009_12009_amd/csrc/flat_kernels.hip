@@ -571,10 +571,10 @@ __device__ __forceinline__ int split_at(const FlatDims& d, int i, int j, int k) 
   return ((i + j + k) & 1) * d.half + (i >> 1) + d.sp * (j + d.ny * k);
 }
 
-template <bool GATHER>
+template <typename T, bool GATHER>
 __global__ void __launch_bounds__(256)
-    k_flat_boxes(const BoxInfo* __restrict__ boxes, int3 lo, FlatDims d, const double* src,
-                 double* dst, int ng, unsigned long long* normbits) {
+    k_flat_boxes(const BoxInfo* __restrict__ boxes, int3 lo, FlatDims d, const T* src, T* dst,
+                 int ng, unsigned long long* normbits) {
   const BoxInfo B = boxes[blockIdx.y];
   const int nx = B.hi[0] - B.lo[0] + 1, ny = B.hi[1] - B.lo[1] + 1, nz = B.hi[2] - B.lo[2] + 1;
   const long long off = ng ? B.off_g1 : B.off_g0;
@@ -587,7 +587,7 @@ __global__ void __launch_bounds__(256)
     const long long b = off + (il + ng) + (long long)sy * (jl + ng) + sz * (kl + ng);
     const int q = split_at(d, B.lo[0] - lo.x + il, B.lo[1] - lo.y + jl, B.lo[2] - lo.z + kl);
     if (GATHER) {
-      const double v = src[b];
+      const T v = src[b];
       dst[q] = v;
       const unsigned long long bits = absbits(v);
       mx = bits > mx ? bits : mx;
@@ -1147,18 +1147,19 @@ static dim3 box_grid(int nbox, int cells) {
   return dim3(std::min((cells + 1023) / 1024, 1024), nbox);
 }
 
+template <typename T>
 hipError_t launch_flat_gather(hipStream_t st, const BoxInfo* boxes, int nbox, int max_cells,
-                              const int lo[3], const FlatDims& d, const double* src, int ng,
-                              double* dst, unsigned long long* normbits) {
-  hipLaunchKernelGGL((k_flat_boxes<true>), box_grid(nbox, max_cells), dim3(256), 0, st, boxes,
+                              const int lo[3], const FlatDims& d, const T* src, int ng, T* dst,
+                              unsigned long long* normbits) {
+  hipLaunchKernelGGL((k_flat_boxes<T, true>), box_grid(nbox, max_cells), dim3(256), 0, st, boxes,
                      make_int3(lo[0], lo[1], lo[2]), d, src, dst, ng, normbits);
   return hipGetLastError();
 }
 
+template <typename T>
 hipError_t launch_flat_scatter(hipStream_t st, const BoxInfo* boxes, int nbox, int max_cells,
-                               const int lo[3], const FlatDims& d, const double* src, double* dst,
-                               int ng) {
-  hipLaunchKernelGGL((k_flat_boxes<false>), box_grid(nbox, max_cells), dim3(256), 0, st, boxes,
+                               const int lo[3], const FlatDims& d, const T* src, T* dst, int ng) {
+  hipLaunchKernelGGL((k_flat_boxes<T, false>), box_grid(nbox, max_cells), dim3(256), 0, st, boxes,
                      make_int3(lo[0], lo[1], lo[2]), d, src, dst, ng, nullptr);
   return hipGetLastError();
 }
@@ -1255,6 +1256,11 @@ hipError_t launch_flat_tail(hipStream_t st, const FlatTail<T>& t, const FlatTail
                                           const T*, unsigned long long*);                          \
   template hipError_t launch_flat_restrict<T>(hipStream_t, const FlatOp<T>&, FlatPass, const T*,   \
                                               const T*, const FlatDims&, T*);                      \
+  template hipError_t launch_flat_gather<T>(hipStream_t, const BoxInfo*, int, int, const int*,     \
+                                            const FlatDims&, const T*, int, T*,                    \
+                                            unsigned long long*);                                  \
+  template hipError_t launch_flat_scatter<T>(hipStream_t, const BoxInfo*, int, int, const int*,    \
+                                             const FlatDims&, const T*, T*, int);                  \
   template hipError_t launch_flat_faces<T>(hipStream_t, const BoxInfo*, int, int, const int*,      \
                                            const FlatDims&, int, const T*, T, T, T*);              \
   template hipError_t launch_flat_acoef<T>(hipStream_t, const BoxInfo*, int, int, const int*,      \

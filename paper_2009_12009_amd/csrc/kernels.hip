@@ -2014,11 +2014,11 @@ __global__ void __launch_bounds__(256)
                 const T* __restrict__ phic, const T* __restrict__ phif, const T* __restrict__ bc0,
                 const T* __restrict__ bc1, const T* __restrict__ bc2, const T* __restrict__ bf0,
                 const T* __restrict__ bf1, const T* __restrict__ bf2, T beta, T ihc0, T ihc1,
-                T ihc2, T ihf0, T ihf1, T ihf2, T* __restrict__ r) {
+                T ihc2, T ihf0, T ihf1, T ihf2, T* __restrict__ r, int coarse_term) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= ncell) return;
   const CfCell cc = cells[i];
-  const T pI = phic[cc.phi_idx];
+  const T pI = coarse_term ? phic[cc.phi_idx] : T(0);
   T acc = r[cc.r_idx];
   for (int k = 0; k < cc.count; ++k) {
     const CfFace f = faces[cc.first + k];
@@ -2027,7 +2027,7 @@ __global__ void __launch_bounds__(256)
     const T ic = f.d == 0 ? ihc0 : (f.d == 1 ? ihc1 : ihc2);
     const T ifn = f.d == 0 ? ihf0 : (f.d == 1 ? ihf1 : ihf2);
     const T c = (beta * bc[f.cb_idx]) * ic;
-    const T term_c = c * (pI - phic[f.j_idx]);
+    const T term_c = coarse_term ? c * (pI - phic[f.j_idx]) : T(0);
     T fl[4];
     for (int q = 0; q < 4; ++q) fl[q] = beta * bf[f.fb[q]] * (phif[f.fg[q]] - phif[f.fv[q]]);
     // mean fine flux / h_c, ifn = 1 / (h_f h_c)
@@ -3016,11 +3016,11 @@ template <typename T>
 hipError_t launch_cf_reflux(hipStream_t st, const CfCell* cells, int ncell, const CfFace* faces,
                             const T* phic, const T* phif, const T* bc0, const T* bc1,
                             const T* bc2, const T* bf0, const T* bf1, const T* bf2, double beta,
-                            const double ihc[3], const double ihf[3], T* r) {
+                            const double ihc[3], const double ihf[3], T* r, int coarse_term) {
   if (ncell <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_cf_reflux<T>, dim3((ncell + 255) / 256), dim3(256), 0, st, cells, ncell,
                      faces, phic, phif, bc0, bc1, bc2, bf0, bf1, bf2, (T)beta, (T)ihc[0],
-                     (T)ihc[1], (T)ihc[2], (T)ihf[0], (T)ihf[1], (T)ihf[2], r);
+                     (T)ihc[1], (T)ihc[2], (T)ihf[0], (T)ihf[1], (T)ihf[2], r, coarse_term);
   return hipGetLastError();
 }
 
@@ -3136,7 +3136,7 @@ hipError_t launch_bottom_bicgstab(hipStream_t st, const BottomTables& bt, const 
   template hipError_t launch_cf_reflux<T>(hipStream_t, const CfCell*, int, const CfFace*,        \
                                           const T*, const T*, const T*, const T*, const T*,      \
                                           const T*, const T*, const T*, double, const double*,   \
-                                          const double*, T*);                                    \
+                                          const double*, T*, int);                               \
   template hipError_t launch_maxabs<T>(hipStream_t, const Tile*, int, Shape, const BoxInfo*,     \
                                        const T*, int, unsigned long long*);                      \
   template hipError_t launch_restrict<T>(hipStream_t, const Tile*, int, Shape, const BoxInfo*,   \

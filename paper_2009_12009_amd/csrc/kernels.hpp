@@ -259,12 +259,13 @@ hipError_t launch_avgdown(hipStream_t st, const Tile* tiles, int ntiles, Shape s
 template <typename T>
 hipError_t launch_cf_ghost(hipStream_t st, const CfGhost* g, int n, const T* coarse, T* fine);
 // Coarse residual at coarse/fine faces: r += c (phi_I - phi_J) - mean fine flux / h_c,
-// ihc[d] = 1/h_c^2, ihf[d] = 1/(h_f h_c).
+// ihc[d] = 1/h_c^2, ihf[d] = 1/(h_f h_c).  coarse_term = 0: without the first
+// term, for an r that never held the coarse face's flux (phic is then not read).
 template <typename T>
 hipError_t launch_cf_reflux(hipStream_t st, const CfCell* cells, int ncell, const CfFace* faces,
                             const T* phic, const T* phif, const T* bc0, const T* bc1,
                             const T* bc2, const T* bf0, const T* bf1, const T* bf2, double beta,
-                            const double ihc[3], const double ihf[3], T* r);
+                            const double ihc[3], const double ihf[3], T* r, int coarse_term = 1);
 // v += w on valid cells (both ghost layer 1).
 hipError_t launch_axpy_valid(hipStream_t st, const Tile* tiles, int ntiles, Shape sh,
                              const BoxInfo* boxes, double* v, const double* w);

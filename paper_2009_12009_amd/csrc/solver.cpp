@@ -228,6 +228,7 @@ struct mg_solver {
   hipEvent_t ev_in = nullptr, ev_out = nullptr;
   hipEvent_t ev_norm[2] = {nullptr, nullptr};  // folded stop test: norm copies landed
   hipGraphExec_t graph64 = nullptr, graph32 = nullptr;
+  hipGraphExec_t fgraph = nullptr;  // split-colour levels from level 1 on
   // the level-0 residual pass writes its restriction into level 1's rhs
   bool rr_fold = false;
   // first level of the coarse tail (-1: none) and its device plan
@@ -589,10 +590,10 @@ bool stop_fold_on(const mg_solver* s) {
 // have even extents and even low corners (true of every level that has been
 // coarsened by 2; it makes the colours alternate across periodic wraps and a
 // pair's parent its own index) and fit 32-bit element offsets.  Otherwise - a
-// single level, nu1 or nu2 = 0, the composite solve - levels stay lists of
-// boxes.
+// single level, nu1 or nu2 = 0 - levels stay lists of boxes.  The composite
+// solve's coarse V-cycle takes the same layout, its other parts keep boxes.
 bool flat_on(const mg_solver* s) {
-  if (s->L.size() < 2 || s->composite || s->opts.nu1 < 1 || s->opts.nu2 < 1) return false;
+  if (s->L.size() < 2 || s->opts.nu1 < 1 || s->opts.nu2 < 1) return false;
   for (size_t l = 0; l + 1 < s->L.size(); ++l)
     for (int d = 0; d < 3; ++d)
       if (ext(s->L[l].domain, d) % 2 || s->L[l].domain.lo[d] % 2 ||
@@ -664,6 +665,13 @@ void layout_flat(mg_solver* s, size_t l, bool ef, Bump& bump) {
   v.op.a = v.a;
 }
 
+void finish_layout_flat(mg_solver* s, size_t from, Bump& bump) {
+  s->flat_bytes = bump.off - from;
+  s->d_fmap_rhs = bump.take<int>(s->nb);
+  s->d_fmap_out = s->d_fmap_rhs;  // same layout of both
+  s->d_ftail = s->flat_tail > 0 ? bump.take<char>(sizeof(FlatTail<double>)) : nullptr;
+}
+
 void layout_flat_all(mg_solver* s, Bump& bump) {
   const bool f32 = s->opts.precision == MG_PREC_F32_REFINE;
   s->f64.clear();
@@ -671,8 +679,13 @@ void layout_flat_all(mg_solver* s, Bump& bump) {
   s->flat_base = bump.take<char>(0);
   const size_t from = bump.off;
   for (size_t l = 0; l < s->L.size(); ++l) {
-    if (!f32 || l == 0) layout_flat<double>(s, l, !f32 && (l > 0 || s->opts.krylov), bump);
+    if (!f32 || (l == 0 && !s->composite))
+      layout_flat<double>(s, l, !f32 && (l > 0 || s->opts.krylov || s->composite), bump);
     if (f32) layout_flat<float>(s, l, true, bump);
+  }
+  if (s->composite) {
+    finish_layout_flat(s, from, bump);
+    return;
   }
   const size_t n = 2 * (size_t)s->f64[0].op.d.half;
   s->frhs = bump.take<double>(n);
@@ -698,10 +711,7 @@ void layout_flat_all(mg_solver* s, Bump& bump) {
     s->fq = bump.take<double>(n);
   }
   s->fpart = bump.take<double>(std::max(kFlatDotBlocks, flat_resid_blocks(s->f64[0].op.d)));
-  s->flat_bytes = bump.off - from;
-  s->d_fmap_rhs = bump.take<int>(s->nb);
-  s->d_fmap_out = s->d_fmap_rhs;  // same layout of both
-  s->d_ftail = s->flat_tail > 0 ? bump.take<char>(sizeof(FlatTail<double>)) : nullptr;
+  finish_layout_flat(s, from, bump);
 }
 
 // LDS bytes of the tail kernel starting at level t: the bottom CG's p (FP64
@@ -1604,7 +1614,7 @@ template <typename T>
 int flat_below(mg_solver* s, size_t l) {
   ProfScope ps(s, 5, l == 0);
   if (l > 0 || !s->opts.use_graph) return flat_cycle<T>(s, l + 1);
-  HIPTRY(hipGraphLaunch(sizeof(T) == 4 ? s->graph32 : s->graph64, s->st));
+  HIPTRY(hipGraphLaunch(s->fgraph, s->st));
   return MG_OK;
 }
 
@@ -1668,36 +1678,47 @@ int flat_cycle(mg_solver* s, size_t l) {
   return flat_post<T>(s, l, v.e, v.f, w);
 }
 
-int capture_graphs(mg_solver* s) {
-  if (!s->opts.use_graph || s->L.size() < 2) {
-    s->opts.use_graph = 0;
-    return MG_OK;
-  }
-  const bool f32 = s->opts.precision == MG_PREC_F32_REFINE;
+// The launches of `cycle` as an executable graph.
+template <typename F>
+int capture_graph(mg_solver* s, F&& cycle, hipGraphExec_t* ex) {
   hipGraph_t g;
   HIPTRY(hipStreamBeginCapture(s->st, hipStreamCaptureModeThreadLocal));
   const bool saved = s->profile;
   s->profile = false;
-  // the level-0 residual pass restricts into level 1 itself with rr_fold
-  int rc;
-  if (s->flat)
-    rc = f32 ? flat_cycle<float>(s, 1) : flat_cycle<double>(s, 1);
-  else
-    rc = f32 ? coarse_cycle<float>(s, 1, true, s->rr_fold ? nullptr : s->L[0].r32)
-             : coarse_cycle<double>(s, 1, false, s->rr_fold ? nullptr : s->L[0].r64);
+  const int rc = cycle();
   s->profile = saved;
   hipError_t e = hipStreamEndCapture(s->st, &g);
   if (rc) return rc;
   if (e != hipSuccess) return fail(MG_ERR_HIP, std::string("graph capture: ") + hipGetErrorString(e));
-  hipGraphExec_t ex;
-  e = hipGraphInstantiate(&ex, g, nullptr, nullptr, 0);
+  e = hipGraphInstantiate(ex, g, nullptr, nullptr, 0);
   hipGraphDestroy(g);
   if (e != hipSuccess) return fail(MG_ERR_HIP, std::string("graph instantiate: ") + hipGetErrorString(e));
-  if (f32)
-    s->graph32 = ex;
-  else
-    s->graph64 = ex;
   return MG_OK;
+}
+
+int capture_graphs(mg_solver* s) {
+  const bool f32 = s->opts.precision == MG_PREC_F32_REFINE;
+  int rc;
+  if (s->flat_tail > 0 && (rc = f32 ? upload_flat_tail<float>(s) : upload_flat_tail<double>(s)))
+    return rc;
+  if (!s->opts.use_graph || s->L.size() < 2) {
+    s->opts.use_graph = 0;
+    return MG_OK;
+  }
+  if (s->flat) {
+    rc = capture_graph(
+        s, [&]() { return f32 ? flat_cycle<float>(s, 1) : flat_cycle<double>(s, 1); }, &s->fgraph);
+    // a composite handle's own level 0 (mg_solve on it) cycles over boxes
+    if (rc || !s->composite) return rc;
+  }
+  // the level-0 residual pass restricts into level 1 itself with rr_fold
+  return capture_graph(
+      s,
+      [&]() {
+        return f32 ? coarse_cycle<float>(s, 1, true, s->rr_fold ? nullptr : s->L[0].r32)
+                   : coarse_cycle<double>(s, 1, false, s->rr_fold ? nullptr : s->L[0].r64);
+      },
+      f32 ? &s->graph32 : &s->graph64);
 }
 
 // Level-0 V-cycle on the caller's phi (direct form, FP64).  red_done: the
@@ -2951,14 +2972,24 @@ int composite_residual(mg_solver* s, T* phic, T* phif, const T* fc, int fc_ng, c
   const bool f32 = sizeof(T) == 4;
   int rc;
   if ((rc = avgdown<T>(s, phif, 1, phic, 1, 0))) return rc;
-  if ((rc = exchange<T>(s, L0, phic, false))) return rc;
+  // cover_from: the residual a fine correction leaves, phic being zero on the
+  // uncovered cells.  Their coarse residual is fc but for the faces they share
+  // with covered cells, whose coarse flux the refluxing would take off again
+  // (the covered cells' is overwritten): no pass over the coarse level.
+  const bool corr = cover_from != nullptr;
+  if (!corr && (rc = exchange<T>(s, L0, phic, false))) return rc;
   if ((rc = fine_ghosts<T>(s, phif, phic))) return rc;
   const StencilArgs<T> opf = stencil_of<T>(s, F, f32);
   const StencilArgs<T> opc = stencil_of<T>(s, L0, f32);
   HIPTRY((launch_residual<T, T>(s->st, F.d_cell, (int)F.t_cell.size(), F.s_cell, opf, phif, ff,
                                 ff_ng, Rf, normbits, 0)));
-  HIPTRY((launch_residual<T, T>(s->st, L0.d_cell, (int)L0.t_cell.size(), L0.s_cell, opc, phic, fc,
-                                fc_ng, Rc, nullptr, 0)));
+  if (corr) {
+    if (fc_ng != 0) return fail(MG_ERR_ARG, "composite correction: right-hand side with ghosts");
+    HIPTRY(hipMemcpyAsync(Rc, fc, sizeof(T) * L0.n_g0, hipMemcpyDeviceToDevice, s->st));
+  } else {
+    HIPTRY((launch_residual<T, T>(s->st, L0.d_cell, (int)L0.t_cell.size(), L0.s_cell, opc, phic,
+                                  fc, fc_ng, Rc, nullptr, 0)));
+  }
   double ihc[3], ihf[3];
   for (int d = 0; d < 3; ++d) {
     ihc[d] = 1.0 / (L0.h[d] * L0.h[d]);
@@ -2967,7 +2998,7 @@ int composite_residual(mg_solver* s, T* phic, T* phif, const T* fc, int fc_ng, c
   HIPTRY(launch_cf_reflux<T>(s->st, s->d_cfcell, (int)s->h_cfcell.size(), s->d_cfface, phic,
                              phif, bcoef<T>(L0, 0), bcoef<T>(L0, 1), bcoef<T>(L0, 2),
                              bcoef<T>(F, 0), bcoef<T>(F, 1), bcoef<T>(F, 2), s->beta, ihc, ihf,
-                             Rc));
+                             Rc, corr ? 0 : 1));
   if (cover_from) {
     if ((rc = avgdown<T>(s, cover_from, 0, Rc, 0, 0))) return rc;
   } else {
@@ -2994,6 +3025,23 @@ int fine_sweeps(mg_solver* s, T* ef, T* ec, const T* rhs, int sweeps) {
   return MG_OK;
 }
 
+// One V-cycle from zero on the whole coarse level: rhs -> e (valid cells).
+template <typename T>
+int coarse_correction(mg_solver* s) {
+  constexpr bool f32 = sizeof(T) == 4;
+  if (!s->flat) return coarse_cycle<T>(s, 0, f32);
+  Level& L0 = s->L[0];
+  const LevelData<T> D = ldata<T>(L0, f32);
+  FlatLevel<T>& v = flat_levels<T>(s)[0];
+  int rc;
+  HIPTRY(launch_flat_gather<T>(s->st, L0.d_info, L0.nbox, L0.max_faces, L0.domain.lo, v.op.d, D.rhs,
+                               0, v.f, nullptr));
+  if ((rc = flat_cycle<T>(s, 0))) return rc;
+  HIPTRY(launch_flat_scatter<T>(s->st, L0.d_info, L0.nbox, L0.max_faces, L0.domain.lo, v.op.d,
+                                v.out(), D.e, 1));
+  return MG_OK;
+}
+
 // The two-level correction of a composite residual (vc, vf) from zero, in
 // FP32 on (vc, vf) rounded once: result in ef32 (fine) and L0.e32 (coarse).
 int correction_core32(mg_solver* s, const double* vc, const double* vf) {
@@ -3010,7 +3058,7 @@ int correction_core32(mg_solver* s, const double* vc, const double* vf) {
   if ((rc = composite_residual<float>(s, L0.e32, s->ef32, s->Rc32, 0, s->Rf32, 0, L0.rhs32,
                                       s->rf2_32, nullptr, s->rf2_32)))
     return rc;
-  if ((rc = coarse_cycle<float>(s, 0, true))) return rc;
+  if ((rc = coarse_correction<float>(s))) return rc;
   HIPTRY(launch_prolong_add<float>(s->st, F.d_cell, (int)F.t_cell.size(), F.s_cell, F.d_info,
                                    L0.d_info, s->ef32, L0.e32));
   return fine_sweeps<float>(s, s->ef32, L0.e32, s->Rf32, 2 * s->opts.nu2);
@@ -3035,7 +3083,7 @@ int correction_core64(mg_solver* s, const double* vc, const double* vf, double* 
                                        s->rf2)))
     return rc;
   // one coarse V-cycle from zero on the whole coarse level
-  if ((rc = coarse_cycle<double>(s, 0, false))) return rc;
+  if ((rc = coarse_correction<double>(s))) return rc;
   HIPTRY(launch_prolong_add<double>(s->st, F.d_cell, (int)F.t_cell.size(), F.s_cell, F.d_info,
                                     L0.d_info, ef, L0.e64));
   return fine_sweeps<double>(s, ef, L0.e64, vf, 2 * s->opts.nu2);
@@ -3372,11 +3420,6 @@ int mg_create(const mg_box_t* boxes, int32_t nbox, const mg_geom_t* geom, const 
     if ((rc = upload_tables(s.get()))) return rc;
     if ((rc = setup_coefficients(s.get(), acoef, bcoef))) return rc;
     if ((rc = coarsen_all(s.get()))) return rc;
-    if (s->flat_tail > 0) {
-      rc = s->opts.precision == MG_PREC_F32_REFINE ? upload_flat_tail<float>(s.get())
-                                                   : upload_flat_tail<double>(s.get());
-      if (rc) return rc;
-    }
     if ((rc = autotune(s.get()))) return rc;
     if ((rc = capture_graphs(s.get()))) return rc;
     HIPTRY(hipStreamSynchronize(s->st));
@@ -3918,15 +3961,16 @@ int mg_solve(mg_solver_t* s, mg_multifab_t* phi, const mg_multifab_t* rhs, doubl
   const double* F = static_cast<const double*>(rhs->data);
   const int rng = rhs->ngrow;
   const bool f32 = s->opts.precision == MG_PREC_F32_REFINE;
+  const bool flat = s->flat && !s->composite;
   const StencilArgs<double> op = stencil_of<double>(s, l0, false);
   mg_info_t inf;
   std::memset(&inf, 0, sizeof(inf));
   inf.nlevels = (int)s->L.size();
-  inf.tail_level = std::max(s->flat ? s->flat_tail : s->tail_lev, 0);
+  inf.tail_level = std::max(flat ? s->flat_tail : s->tail_lev, 0);
   inf.setup_ms = s->setup_ms;
 
   HIPTRY(launch_fill_u64(s->st, s->d_norm, 4 * kNormSlot, 0ull));
-  if (s->flat)
+  if (flat)
     HIPTRY(launch_flat_gather(s->st, l0.d_info, l0.nbox, l0.max_faces, l0.domain.lo,
                               s->f64[0].op.d, F, rng, s->frhs, s->d_norm));
   else
@@ -3942,7 +3986,7 @@ int mg_solve(mg_solver_t* s, mg_multifab_t* phi, const mg_multifab_t* rhs, doubl
     HIPTRY(hipStreamSynchronize(s->st));
     inf.converged = 1;
     if (resid_history) resid_history[0] = 0.0;
-  } else if (s->flat) {
+  } else if (flat) {
     const double tol = std::max(rel_tol * normf, abs_tol);
     const FlatDims& d = s->f64[0].op.d;
     HIPTRY(launch_flat_gather(s->st, l0.d_info, l0.nbox, l0.max_faces, l0.domain.lo, d, P, 1,
@@ -4133,6 +4177,7 @@ void mg_destroy(mg_solver_t* s) {
   if (s->st) hipStreamSynchronize(s->st);
   if (s->graph64) hipGraphExecDestroy(s->graph64);
   if (s->graph32) hipGraphExecDestroy(s->graph32);
+  if (s->fgraph) hipGraphExecDestroy(s->fgraph);
   for (hipEvent_t e : s->ev_pool) hipEventDestroy(e);
   if (s->ev_in) hipEventDestroy(s->ev_in);
   if (s->ev_out) hipEventDestroy(s->ev_out);
@@ -4332,7 +4377,8 @@ int mg_solve_amr(mg_solver_t* s, mg_multifab_t* phi_c, mg_multifab_t* phi_f,
   mg_info_t inf;
   std::memset(&inf, 0, sizeof(inf));
   inf.nlevels = (int)s->L.size() + 1;
-  inf.tail_level = s->tail_lev > 0 ? s->tail_lev + 1 : 0;
+  const int tail = s->flat ? s->flat_tail : s->tail_lev;
+  inf.tail_level = tail > 0 ? tail + 1 : 0;
   inf.setup_ms = s->setup_ms;
   HIPTRY(launch_fill_u64(s->st, s->d_norm, 4 * kNormSlot, 0ull));
   HIPTRY(launch_copy_valid(s->st, L0.d_cell, (int)L0.t_cell.size(), L0.s_cell, L0.d_info, Fc,
