@@ -70,6 +70,15 @@ hipError_t launch_flat_half(hipStream_t st, const FlatOp<T>& op, FlatPass ps, co
                             const FlatDims* cd = nullptr, const T* ec = nullptr,
                             const T* old = nullptr, unsigned long long* normbits = nullptr);
 
+// One sweep, colour c0 then the other, from src into dst (both halves of two
+// arrays; of src only the colour that is not updated first is read).  The other
+// arguments and the result as for the two half-sweeps.
+template <typename T>
+hipError_t launch_flat_sweep(hipStream_t st, const FlatOp<T>& op, const T* src, T* dst, const T* f,
+                             int c0, bool zero_guess, const FlatDims* cd = nullptr,
+                             const T* ec = nullptr, const T* old = nullptr,
+                             unsigned long long* normbits = nullptr);
+
 // Coarse right-hand side of a level whose black cells were updated last: their
 // residual is zero, so cf = R r sums the red cells' residuals (four of the
 // eight children).  v, f: both halves of the fine level, cf both halves of

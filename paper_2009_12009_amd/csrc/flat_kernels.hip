@@ -384,6 +384,230 @@ __global__ void __launch_bounds__(256)
 }
 
 // ---------------------------------------------------------------------------
+// A whole sweep (both colours) in one pass over a level that streams from HBM:
+// everything is read once, 5.5 values per cell against 9 for two half-sweeps.
+// A work-group takes a column of the level, ox pairs by oy rows grown by a rim of
+// one pair and two rows, one lane per pair, and marches along z: in step k it
+// updates the first colour on plane k and the second on plane k - 1.  A lane's
+// neighbours along z are its own earlier and later values (registers), those in
+// the plane come through LDS (the first colour's input and its result, two
+// planes of each so that a step needs one barrier).  The rim's first-colour cells
+// are recomputed by every work-group that needs them; results go to another
+// array, because neighbours still read the input.  Coefficients of plane k + 1
+// are loaded while plane k is computed.
+// 256^3 FP64: 172 us against 2 x 113 for half-sweeps.  Bound by what the rims add:
+// 852 MB fetched where the input is 604 (neighbouring work-groups drift more
+// planes apart than an L2 holds); cached loads throughout, since the
+// non-temporal hint on the read-once arrays loses the rims as well (185-200 us).
+// FP32 93 us against 2 x 52.
+struct March {
+  int ox, oy;        // pairs and rows a work-group writes
+  int gx, gy;        // lanes: ox + 2, oy + 4
+  int nbx, nby, nb;  // work-groups along x, y, in all
+  int nz;            // planes a work-group writes
+};
+
+template <typename T, bool A>
+struct MarchIn {
+  T o, e0, e1, y[4], z[2], f[2], phi, par, old;
+  T a[A ? 2 : 1];
+};
+
+template <typename T>
+struct MarchCell {
+  T o, s, yl, yh, zl, zh, f, rd;
+};
+
+template <typename T, bool ZG, bool PE, bool ST, bool A>
+__global__ void __launch_bounds__(1024)
+    k_flat_march(FlatOp<T> op, March g, const T* __restrict__ src, T* __restrict__ dst,
+                 const T* __restrict__ f, int c0, FlatDims cd, const T* __restrict__ ec,
+                 const T* __restrict__ old, unsigned long long* normbits) {
+#pragma clang fp contract(off)
+  extern __shared__ __align__(16) unsigned char flat_lds[];
+  const FlatDims& d = op.d;
+  const int tid = threadIdx.x;
+  // two planes of the input and of the first colour, each with a row before
+  // and after
+  const int ps = g.gx * (g.gy + 2);
+  T* const lin = reinterpret_cast<T*>(flat_lds) + g.gx;
+  T* const lfirst = lin + 2 * ps;
+  const int t = xcd_tile(g.nb, 0);
+  const int bx = t % g.nbx, by = t / g.nbx % g.nby, bz = t / g.nbx / g.nby;
+  const int lx = tid % g.gx, ly = tid / g.gx;
+  const int z0 = bz * g.nz, z1 = min(z0 + g.nz, d.nz);
+  int p = bx * g.ox - 1 + lx, j = by * g.oy - 2 + ly;
+  const bool lane = ly < g.gy;
+  // the lane's pair belongs to the block (not its rim) and to the domain
+  const bool own = lane && lx >= 1 && lx <= g.ox && ly >= 2 && ly < 2 + g.oy && p < d.np && j < d.ny;
+  // the outermost rows only hold input
+  const bool upd = lane && ly >= 1 && ly < g.gy - 1;
+  // wrapped, or clamped: past a wall nothing that is read has a coefficient
+  p = (d.wall & 1) ? min(max(p, 0), d.np - 1) : (p % d.np + d.np) % d.np;
+  j = (d.wall & 4) ? min(max(j, 0), d.ny - 1) : (j % d.ny + d.ny) % d.ny;
+  const int plane = d.sp * d.ny, planey = d.sp * (d.ny + 1);
+  const int r0 = p + d.sp * j;
+  auto zi = [&](int k) { return (d.wall & 16) ? min(max(k, 0), d.nz - 1) : (k + d.nz) % d.nz; };
+  auto input = [&](int k) {
+    if (ZG || !lane) return T(0);
+    const T v = src[r0 + plane * zi(k)];
+    return v;
+  };
+  auto load = [&](MarchIn<T, A>& in, int k) {
+    if (!upd) return;
+    const int kz = zi(k), r = r0 + plane * kz, ry = r0 + planey * kz;
+    in.o = op.x[d.half + r];
+    in.e0 = op.x[r];
+    in.e1 = op.x[r + 1];
+    // low faces of the first and the second colour's cell, then the high ones
+    in.y[0] = op.y[c0 * d.yh + ry];
+    in.y[1] = op.y[(1 - c0) * d.yh + ry];
+    in.y[2] = op.y[(1 - c0) * d.yh + ry + d.sp];
+    in.y[3] = op.y[c0 * d.yh + ry + d.sp];
+    // the high z faces, which are plane k + 1's low ones (also for k = -1)
+    const int rz = r0 + plane * (k < 0 ? 0 : kz + 1);
+    in.z[0] = op.z[c0 * d.zh + rz];
+    in.z[1] = op.z[(1 - c0) * d.zh + rz];
+    in.f[0] = f[c0 * d.half + r];
+    in.f[1] = f[(1 - c0) * d.half + r];
+    if (A) {
+      in.a[0] = op.a[c0 * d.half + r];
+      in.a[A ? 1 : 0] = op.a[(1 - c0) * d.half + r];
+    }
+    if (ST) in.old = old[r];
+  };
+  auto parent = [&](int k) {
+    return PE && lane ? coarse_at(cd, ec, p, j >> 1, zi(k) >> 1) : T(0);
+  };
+  const int ka = z0 - 1, kb = z1;
+  MarchIn<T, A> pre, cur;
+  T ph[3], fi[3];  // input at planes k - 1, k, k + 1; first colour at k - 2, k - 1, k
+  T zc[2] = {T(0), T(0)};
+  ph[0] = input(ka - 1);
+  ph[1] = input(ka);
+  ph[2] = input(ka + 1);
+  if (PE) {
+    ph[0] = ph[0] + parent(ka - 1);
+    ph[1] = ph[1] + parent(ka);
+    ph[2] = ph[2] + parent(ka + 1);
+  }
+  T phn = T(0), parn = T(0);  // plane k + 2's, on their way
+  if (upd) {
+    const int r = r0 + plane * zi(ka);
+    zc[0] = op.z[c0 * d.zh + r];
+    zc[1] = op.z[(1 - c0) * d.zh + r];
+  }
+  load(pre, ka);
+  fi[0] = fi[1] = fi[2] = T(0);
+  MarchCell<T> sec{};  // the second colour's cell on plane k - 1
+  for (int q = tid; q < g.gx; q += 1024)
+    for (int m = 0; m < 2; ++m) {
+      lin[m * ps - g.gx + q] = T(0);
+      lin[m * ps + g.gx * g.gy + q] = T(0);
+      lfirst[m * ps - g.gx + q] = T(0);
+      lfirst[m * ps + g.gx * g.gy + q] = T(0);
+    }
+  if (lane) {
+    lin[tid] = ph[1];
+    lfirst[tid] = T(0);
+    lfirst[ps + tid] = T(0);
+  }
+  __syncthreads();
+  unsigned long long mx = 0;
+  int par = 0;
+  for (int k = ka; k <= kb; ++k) {
+    cur = pre;
+    if (k < kb) {
+      load(pre, k + 1);
+      phn = input(k + 2);
+      if (PE) parn = parent(k + 2);
+    }
+    const int sh = (j + k + c0) & 1;
+    const T* L = lin + par * ps + tid;
+    const T* M = lfirst + par * ps + tid;
+    MarchCell<T> nxt{};
+    if (upd) {
+      const bool wy0 = (d.wall & 4) && j == 0, wy1 = (d.wall & 8) && j == d.ny - 1;
+      const bool wz0 = (d.wall & 16) && k <= 0, wz1 = (d.wall & 32) && k >= d.nz - 1;
+      // both colours' cells of plane k: the first's pair beside lies before
+      // (sh = 0) or after, the second's on the other side
+      Coef<T, 1> c;
+      Walls w;
+      c.o[0] = cur.o;
+      c.s[0] = sh ? cur.e1 : cur.e0;
+      c.yl[0] = cur.y[0];
+      c.yh[0] = cur.y[2];
+      c.zl[0] = zc[0];
+      c.zh[0] = cur.z[1];
+      c.a[0] = cur.a[0];
+      w.s = sh ? (d.wall & 2) && p == d.np - 1 : (d.wall & 1) && p == 0;
+      w.yl = wy0;
+      w.yh = wy1;
+      w.zl = wz0;
+      w.zh = wz1;
+      const T diag = diag_of<T, 1>(op, c, 0, w);
+      drop_walls<T, 1>(c, 0, w);
+      T off = T(0);
+      if (!ZG) {
+        Nb<T, 1> n;
+        n.o[0] = ph[1];
+        n.s[0] = L[sh ? 1 : -1];
+        n.yl[0] = L[-g.gx];
+        n.yh[0] = L[g.gx];
+        n.zl[0] = ph[0];
+        n.zh[0] = ph[2];
+        off = off_of<T, 1>(c, n, 0);
+      }
+      fi[2] = (ZG ? cur.f[0] : cur.f[0] + off) * (T(1) / diag);
+      if (own && k >= z0 && k < z1) {
+        const int r = r0 + plane * k;
+        dst[c0 * d.half + r] = fi[2];
+        if (ST) {
+          const unsigned long long b = absbits(resid_of(cur.f[0], diag, cur.old, off));
+          mx = b > mx ? b : mx;
+        }
+      }
+      c.o[0] = cur.o;
+      c.s[0] = sh ? cur.e0 : cur.e1;
+      c.yl[0] = cur.y[1];
+      c.yh[0] = cur.y[3];
+      c.zl[0] = zc[1];
+      c.zh[0] = cur.z[0];
+      c.a[0] = cur.a[A ? 1 : 0];
+      w.s = sh ? (d.wall & 1) && p == 0 : (d.wall & 2) && p == d.np - 1;
+      const T diag2 = diag_of<T, 1>(op, c, 0, w);
+      drop_walls<T, 1>(c, 0, w);
+      nxt = {c.o[0], c.s[0], c.yl[0], c.yh[0], c.zl[0], c.zh[0], cur.f[1], T(1) / diag2};
+      zc[0] = cur.z[0];
+      zc[1] = cur.z[1];
+    }
+    if (own && k - 1 >= z0) {
+      // the second colour on plane k - 1 (same side as the first's on plane k)
+      T o = sec.o * fi[1];
+      o = fma_(sec.s, M[sh ? 1 : -1], o);
+      o = fma_(sec.yl, M[-g.gx], o);
+      o = fma_(sec.yh, M[g.gx], o);
+      o = fma_(sec.zl, fi[0], o);
+      o = fma_(sec.zh, fi[2], o);
+      dst[(1 - c0) * d.half + r0 + plane * (k - 1)] = (sec.f + o) * sec.rd;
+    }
+    if (lane) {
+      lin[(1 - par) * ps + tid] = ph[2];
+      lfirst[(1 - par) * ps + tid] = fi[2];
+    }
+    __syncthreads();
+    par ^= 1;
+    sec = nxt;
+    ph[0] = ph[1];
+    ph[1] = ph[2];
+    ph[2] = PE ? phn + parn : phn;
+    fi[0] = fi[1];
+    fi[1] = fi[2];
+  }
+  if (ST) block_max_u64(mx, normbits);
+}
+
+// ---------------------------------------------------------------------------
 // Two sweeps in one launch, for levels whose passes are launches rather than
 // memory traffic.  A work-group takes a block of OP pairs by OY by OZ rows,
 // grown by 4 cells on every side, and runs the half-sweeps on the grown block:
@@ -1087,6 +1311,66 @@ hipError_t launch_flat_restrict(hipStream_t st, const FlatOp<T>& op, FlatPass ps
   return hipGetLastError();
 }
 
+// Work-groups of a march: tiles at most 64 pairs wide (at 256^3 FP64 194 us with
+// 32 pairs, 172 with 64: a row's two rim pairs cost a cache line each where the
+// neighbour's copy has left the L2; 280 with rows off the lines at 43, 350 with
+// whole rows of 128, which leave 3 of 7 rows to write), as many rows as 1024 lanes
+// hold, and as many planes each as fill the chip evenly (`resident` work-groups
+// at a time).
+static March march_of(const FlatDims& d, int resident) {
+  March m{};
+  m.nbx = (d.np + 63) / 64;
+  m.ox = (d.np + m.nbx - 1) / m.nbx;
+  m.gx = m.ox + 2;
+  const int rows = std::min(1024 / m.gx - 4, d.ny);
+  m.nby = (d.ny + rows - 1) / rows;
+  m.oy = (d.ny + m.nby - 1) / m.nby;
+  m.gy = m.oy + 4;
+  double cost = 0;
+  for (int ns = 1; ns <= d.nz; ++ns) {
+    const int nz = (d.nz + ns - 1) / ns;
+    const int n = m.nbx * m.nby * ((d.nz + nz - 1) / nz);
+    // rounds, each as long as its planes and the two of the rim
+    const double c = double((n + resident - 1) / resident) * (nz + 4.0);
+    if (cost == 0 || c < cost) {
+      cost = c;
+      m.nz = nz;
+      m.nb = n;
+    }
+  }
+  return m;
+}
+
+template <typename T>
+hipError_t launch_flat_sweep(hipStream_t st, const FlatOp<T>& op, const T* src, T* dst, const T* f,
+                             int c0, bool zero_guess, const FlatDims* cd, const T* ec,
+                             const T* old, unsigned long long* normbits) {
+  const FlatDims& d = op.d;
+  const FlatDims c = cd ? *cd : FlatDims{};
+  // FP64 100-120 VGPRs: one work-group per CU; FP32 up to 66: two of most forms
+  const March m = march_of(d, sizeof(T) == 8 ? 256 : 512);
+  if (m.nb <= 0) return hipErrorInvalidValue;
+  const size_t lds = sizeof(T) * 4 * (size_t)m.gx * (m.gy + 2);
+  if (lds > 65536) return hipErrorInvalidValue;
+  const T* in = zero_guess ? nullptr : src + (1 - c0) * (size_t)d.half;
+#define FM2(Z, P, S, A)                                                                        \
+  hipLaunchKernelGGL((k_flat_march<T, Z, P, S, A>), dim3(m.nb), dim3(1024), lds, st, op, m, in, \
+                     dst, f, c0, c, ec, old, normbits)
+#define FM(A)                                  \
+  if (zero_guess) FM2(true, false, false, A);  \
+  else if (ec) FM2(false, true, false, A);     \
+  else if (old) FM2(false, false, true, A);    \
+  else FM2(false, false, false, A)
+  if (op.a) {
+    FM(true);
+  } else {
+    FM(false);
+  }
+#undef FM
+#undef FM2
+  return hipGetLastError();
+}
+
 // Blocks of OP pairs that cover a level.
 static long long blocks_of(const FlatDims& d, int op) {
   return (long long)((d.np + op - 1) / op) * ((d.ny + kBlkOY - 1) / kBlkOY) *
@@ -1269,6 +1553,9 @@ hipError_t launch_flat_tail(hipStream_t st, const FlatTail<T>& t, const FlatTail
                                          double*);                                                 \
   template hipError_t launch_flat_cg_p<T>(hipStream_t, long long, double*, const T*,               \
                                           const double*, const double*, int);                      \
+  template hipError_t launch_flat_sweep<T>(hipStream_t, const FlatOp<T>&, const T*, T*, const T*,  \
+                                           int, bool, const FlatDims*, const T*, const T*,         \
+                                           unsigned long long*);                                   \
   template hipError_t launch_flat_block<T>(hipStream_t, const FlatOp<T>&, FlatBlockMode, const T*, \
                                            const T*, T*, const FlatDims&, T*, const T*);           \
   template hipError_t launch_flat_tail<T>(hipStream_t, const FlatTail<T>&, const FlatTail<T>*);

@@ -2,7 +2,7 @@
 change form: rows whose pairs do not fill the last wide load, periodic rows that
 rule wide loads out, rows shorter than a cache line, levels smoothed in blocks, domains with low corners
 away from zero, cell coefficients, the tail in LDS and in memory, and levels
-large enough for wide loads.  Two V-cycles against the oracle, cell by cell."""
+large enough for wide loads and for whole sweeps per pass.  Two V-cycles against the oracle, cell by cell."""
 
 import numpy as np
 import pytest
@@ -30,6 +30,10 @@ CASES = [
     # four FP32 pairs per lane
     ((132, 128, 128), (0, 0, 0), (False, False, False), 1, False, {}),
     ((136, 128, 128), (0, 0, 0), (True, False, False), 1, True, {}),
+    # whole sweeps per pass (levels above 256 MiB): two tiles along x with a
+    # remainder, ragged rows and planes; FP64 alone at 7.5 M cells
+    ((260, 200, 148), (0, 0, 0), (False, True, False), 1, False, dict(only64=1)),
+    ((132, 244, 236), (0, 0, 0), (True, False, True), 1, True, dict(only64=1, nu1=1, nu2=1)),
 ]
 
 
@@ -37,6 +41,9 @@ CASES = [
 @pytest.mark.parametrize("krylov", [0, 1])
 @pytest.mark.parametrize("ext,lo,per,nx,with_a,opts", CASES)
 def test_two_cycles_vs_oracle(ext, lo, per, nx, with_a, opts, krylov):
+    opts = dict(opts)
+    only64 = opts.pop("only64", 0)
+    nu = dict(nu1=opts.get("nu1", 2), nu2=opts.get("nu2", 2))
     print(f"[flat] {ext} at {lo} periodic {per} krylov {krylov} {opts}", flush=True)
     P = lib()
     rng = np.random.default_rng(3)
@@ -62,14 +69,15 @@ def test_two_cycles_vs_oracle(ext, lo, per, nx, with_a, opts, krylov):
     bmf = [mf(b[d], ixtype=tuple(int(e == d) for e in range(3))) for d in range(3)]
     lev = O.make_level(boxes, dom, per, alpha, 1.0, ab, b, prob_len=plen)
     # few bottom iterations, the same on both sides: large bottoms stay cheap
-    oopts = O.Opts(max_iter=2, bottom_tol=0.0, bottom_max_iter=6, symmetric=bool(krylov))
+    oopts = O.Opts(max_iter=2, bottom_tol=0.0, bottom_max_iter=6, symmetric=bool(krylov),
+                   **nu)
     ophi = W.scatter_cells(guess, boxes, ng=1, dlo=lo)
     if krylov:
         oinfo = O.pcg_solve(lev, ophi, fb, 1e-30, opts=oopts)
     else:
         oinfo = O.solve(lev, ophi, fb, 1e-30, opts=oopts)
     ref = W.gather_cells(ophi, boxes, ext, ng=1, dlo=lo)
-    for precision in (0, 1):
+    for precision in (0,) if only64 else (0, 1):
         s = P.MLMG(boxes, dom, per, alpha, 1.0, a=mf(ab) if with_a else None, b=bmf,
                    opts=dict(tune=0, max_iter=2, bottom_rel_tol=0.0, bottom_max_iter=6,
                              precision=precision, krylov=krylov, **opts), prob_hi=plen)
