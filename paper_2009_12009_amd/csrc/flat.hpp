@@ -48,6 +48,7 @@ struct FlatOp {
   const T* z;
   const T* a;  // alpha * a, both halves, or null for a = 1
   T alpha;
+  const int* done = nullptr;  // if set and *done is not 0, a pass does nothing
 };
 
 // Launch order and cache hints of a pass: stream = the level's arrays exceed
@@ -177,5 +178,65 @@ struct FlatTail {
 // dt: a copy of t in device memory.
 template <typename T>
 hipError_t launch_flat_tail(hipStream_t st, const FlatTail<T>& t, const FlatTail<T>* dt);
+
+// ---------------------------------------------------------------------------
+// A large CG bottom (deep bottom): conjugate gradients on the bottom's
+// cells, preconditioned by one symmetric V-cycle on further coarsenings of it.
+// Odd extents of a level are made even by one more cell at the high end:
+//  - along a wall a cell without couplings (a = 1, right-hand side 0);
+//  - along a periodic direction a cell in the link from the last cell to the
+//    first, with no a and no right-hand side and both its links of twice the
+//    coefficient: a series of two such links conducts as the one did, so the
+//    padded system has the same solution on the level's cells.
+// Wall terms are part of a, faces on walls are 0.
+
+// Device state of the iteration, one per handle.  done: 0 going on, 1 converged,
+// 2 broken off (p q not positive).
+struct DeepState {
+  double rho, beta, b2;
+  int done, it;
+  unsigned count;
+};
+constexpr int kDeepBlocks = 256;  // partial sums per reduction at most
+
+// Faces and the two parts of a (mass: alpha a, wall: wall terms) of the padded
+// bottom, from its stencil; bt.map_out holds the cells' elements.  pad: cells
+// added along each direction.
+template <typename T>
+hipError_t launch_deep_fill(hipStream_t st, const BottomTables& bt, const StencilArgs<T>& op,
+                            const FlatDims& d, const int pad[3], T* x, T* y, T* z, T* mass,
+                            T* wall);
+// a = mass + wall, or 1 for a cell with neither a nor couplings.
+template <typename T>
+hipError_t launch_deep_diag(hipStream_t st, const FlatDims& d, const T* x, const T* y, const T* z,
+                            const T* mass, const T* wall, T* a);
+// Faces, mass and wall of the next coarser level: mean face over h_d^2 = a
+// sixteenth of the four faces' sum, mean mass, half the mean wall term.
+template <typename T>
+hipError_t launch_deep_coarsen(hipStream_t st, const FlatDims& d, const T* x, const T* y,
+                               const T* z, const T* mass, const T* wall, const FlatDims& cd,
+                               const int pad[3], T* cx, T* cy, T* cz, T* cmass, T* cwall);
+// diag and coef of launch_bottom_cg for the deepest level.
+template <typename T>
+hipError_t launch_deep_bottom(hipStream_t st, const BottomTables& bt, const FlatOp<T>& op, T* diag,
+                              T* coef);
+
+// The iteration's vector passes (n elements; partials: kDeepBlocks doubles).
+// r = f, x = 0, p = 0, |f|^2
+template <typename T>
+hipError_t launch_deep_init(hipStream_t st, long long n, const T* f, T* r, T* x, T* p,
+                            double* partials, DeepState* s);
+// rho = r.z and beta
+template <typename T>
+hipError_t launch_deep_rz(hipStream_t st, long long n, const T* r, const T* z, double* partials,
+                          DeepState* s);
+// p = z + beta p
+template <typename T>
+hipError_t launch_deep_p(hipStream_t st, long long n, const T* z, T* p, const DeepState* s);
+// x += al p, r -= al q, al = rho / sum of the npq partials of p.q;
+// done once |r|^2 <= tol2 |f|^2
+template <typename T>
+hipError_t launch_deep_xr(hipStream_t st, long long n, T* x, const T* p, T* r, const T* q,
+                          const double* pq, int npq, double tol2, double* partials, DeepState* s);
 
 }  // namespace amrmg

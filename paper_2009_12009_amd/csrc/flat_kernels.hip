@@ -137,16 +137,17 @@ template <typename T, int V>
 __device__ __forceinline__ void load_par(Par<T, V>& q, const FlatDims& d, const FlatDims& c,
                                          const T* e, int sh, int p0, int j, int k) {
   const int J = j >> 1, K = k >> 1;
-  // wrapped or clamped as the fine neighbours are (nx = 2 c.nx and so on)
-  const int Jn = (j & 1) ? (J < c.ny - 1 ? J + 1 : ((d.wall & 8) ? J : 0))
-                         : (J > 0 ? J - 1 : ((d.wall & 4) ? 0 : c.ny - 1));
-  const int Kn = (k & 1) ? (K < c.nz - 1 ? K + 1 : ((d.wall & 32) ? K : 0))
-                         : (K > 0 ? K - 1 : ((d.wall & 16) ? 0 : c.nz - 1));
+  const int cnx = d.nx / 2, cny = d.ny / 2, cnz = d.nz / 2;
+  // wrapped or clamped as the fine neighbours are (c may be padded)
+  const int Jn = (j & 1) ? (J < cny - 1 ? J + 1 : ((d.wall & 8) ? J : 0))
+                         : (J > 0 ? J - 1 : ((d.wall & 4) ? 0 : cny - 1));
+  const int Kn = (k & 1) ? (K < cnz - 1 ? K + 1 : ((d.wall & 32) ? K : 0))
+                         : (K > 0 ? K - 1 : ((d.wall & 16) ? 0 : cnz - 1));
 #pragma unroll
   for (int v = 0; v < V; ++v) {
-    const int I = p0 + v < c.nx ? p0 + v : c.nx - 1;
-    const int In = sh ? (I < c.nx - 1 ? I + 1 : ((d.wall & 2) ? I : 0))
-                      : (I > 0 ? I - 1 : ((d.wall & 1) ? 0 : c.nx - 1));
+    const int I = p0 + v < cnx ? p0 + v : cnx - 1;
+    const int In = sh ? (I < cnx - 1 ? I + 1 : ((d.wall & 2) ? I : 0))
+                      : (I > 0 ? I - 1 : ((d.wall & 1) ? 0 : cnx - 1));
     q.own[v] = coarse_at(c, e, I, J, K);
     q.x[v] = coarse_at(c, e, In, J, K);
     q.y[v] = coarse_at(c, e, I, Jn, K);
@@ -254,6 +255,7 @@ __global__ void __launch_bounds__(256)
                 const T* __restrict__ f, int colour, FlatDims cd, const T* __restrict__ ec,
                 const T* __restrict__ old, unsigned long long* normbits) {
 #pragma clang fp contract(off)
+  if (op.done && *op.done) return;
   const FlatDims& d = op.d;
   const int t = xcd_tile(g.nb, g.reverse);
   const int p0 = ((t % g.nbx << g.lxl) + (threadIdx.x & ((1 << g.lxl) - 1))) * V;
@@ -301,12 +303,14 @@ __global__ void __launch_bounds__(256)
     k_flat_restrict(FlatOp<T> op, Grid2 g, const T* __restrict__ v, const T* __restrict__ f,
                     FlatDims cd, T* __restrict__ cf) {
 #pragma clang fp contract(off)
+  if (op.done && *op.done) return;
   const FlatDims& d = op.d;
   const int t = xcd_tile(g.nb, g.reverse);
   const int I = (t % g.nbx << g.lxl) + (threadIdx.x & ((1 << g.lxl) - 1));
   const int row = (t / g.nbx) * (256 >> g.lxl) + (threadIdx.x >> g.lxl);
-  if (I >= d.np || row >= cd.ny * cd.nz) return;
-  const int K = row / cd.ny, J = row - K * cd.ny;
+  const int cny = d.ny / 2;  // cd may be padded
+  if (I >= d.np || row >= cny * (d.nz / 2)) return;
+  const int K = row / cny, J = row - K * cny;
   T zs[2];
 #pragma unroll
   for (int dk = 0; dk < 2; ++dk) {
@@ -328,7 +332,7 @@ __global__ void __launch_bounds__(256)
     }
     zs[dk] = r[0] + r[1];
   }
-  cf[((I + J + K) & 1) * cd.half + (I >> 1) + cd.sp * row] = (zs[0] + zs[1]) * T(0.125);
+  cf[((I + J + K) & 1) * cd.half + (I >> 1) + cd.sp * (J + cd.ny * K)] = (zs[0] + zs[1]) * T(0.125);
 }
 
 template <typename T, typename TO, int V, bool NT>
@@ -336,6 +340,7 @@ __global__ void __launch_bounds__(256)
     k_flat_resid(FlatOp<T> op, Grid2 g, const T* __restrict__ v, const T* __restrict__ f,
                  TO* __restrict__ out, unsigned long long* normbits, double* __restrict__ dots) {
 #pragma clang fp contract(off)
+  if (op.done && *op.done) return;
   const FlatDims& d = op.d;
   const int t = xcd_tile(g.nb, g.reverse);
   const int p0 = ((t % g.nbx << g.lxl) + (threadIdx.x & ((1 << g.lxl) - 1))) * V;
@@ -671,6 +676,7 @@ __global__ void __launch_bounds__(kBlkLanes)
                 kBlkOP = OP;
   __shared__ T lds[2][kBlkNP + 2 * kBlkPad];
   T* const e[2] = {lds[0] + kBlkPad, lds[1] + kBlkPad};
+  if (op.done && *op.done) return;
   const FlatDims& d = op.d;
   const int tid = threadIdx.x;
   const int bx = blockIdx.x % nbx, by = blockIdx.x / nbx % nby, bz = blockIdx.x / nbx / nby;
@@ -777,7 +783,7 @@ __global__ void __launch_bounds__(kBlkLanes)
     if (tid < kBlkOP * (kBlkOY / 2) * (kBlkOZ / 2)) {
       const int cx = tid % kBlkOP, cy = tid / kBlkOP % (kBlkOY / 2), cz = tid / (kBlkOP * (kBlkOY / 2));
       const int I = p0 + cx, J = y0 / 2 + cy, K = z0 / 2 + cz;
-      if (I < cd.nx && J < cd.ny && K < cd.nz) {
+      if (2 * I < d.nx && 2 * J < d.ny && 2 * K < d.nz) {
         const int q = kBlkH / 2 + cx + kBlkGX * (kBlkH + 2 * cy + kBlkGY * (kBlkH + 2 * cz));
         const T zl = e[0][q] + e[0][q + kBlkGX];
         const T zh = e[0][q + kBlkGX * kBlkGY] + e[0][q + kBlkGX * kBlkGY + kBlkGX];
@@ -1107,6 +1113,7 @@ __global__ void __launch_bounds__(NT) k_flat_tail(const FlatTail<T>* __restrict_
   T* const lds = reinterpret_cast<T*>(flat_lds);
   const int tid = threadIdx.x;
   const int nlev = tp->nlev;
+  if (tp->bt.done && *as_global(tp->bt.done)) return;
   if (LDS) {
     // the first level's right-hand side
     const int n = 2 * tp->lev[0].op.d.half;
@@ -1130,6 +1137,9 @@ __global__ void __launch_bounds__(NT) k_flat_tail(const FlatTail<T>* __restrict_
         tail_half<T, 0, false, false, NT>(op, A, own, npair, cd, nullptr);
       tail_half<T, 1, false, false, NT>(op, A, own, npair, cd, nullptr);
     }
+    // cells added to the coarser level have no right-hand side
+    if (LDS && (2 * cd.nx != d.nx || 2 * cd.ny != d.ny || 2 * cd.nz != d.nz))
+      for (int e = tid; e < 2 * cd.half; e += NT) C.f[e] = T(0);
     // residual of the red cells (the black ones' is zero)
     for (int q = tid; q < npair; q += NT) {
       if (npair > NT) own = tail_pair(op, q);
@@ -1139,9 +1149,9 @@ __global__ void __launch_bounds__(NT) k_flat_tail(const FlatTail<T>* __restrict_
       A.r[at] = resid_of(A.f[at], own.diag, A.e[at], off_of<T, 1>(own.c[0], n, 0));
     }
     __syncthreads();
-    const int ncell = cd.nx * cd.ny * cd.nz;
+    const int cny = d.ny / 2, ncell = d.np * cny * (d.nz / 2);  // cd may be padded
     for (int q = tid; q < ncell; q += NT) {
-      const int t = q / cd.nx, I = q - t * cd.nx, K = t / cd.ny, J = t - K * cd.ny;
+      const int t = q / d.np, I = q - t * d.np, K = t / cny, J = t - K * cny;
       const int b = I + d.sp * (2 * J + d.ny * 2 * K);
       const int bz = d.sp * d.ny;
       const T z0 = A.r[b] + A.r[b + d.sp];
@@ -1206,6 +1216,254 @@ __global__ void __launch_bounds__(NT) k_flat_tail(const FlatTail<T>* __restrict_
       to[at] = e[at];
       to[d.half + at] = e[d.half + at];
     }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Deep bottom: setup of the coarsenings and the vector passes of the iteration.
+// Latency bound: a bottom of 28^3 takes nine launches of 4 to 18 us an iteration
+// and 4 to 6 iterations (0.35 ms a cycle) where one work-group's CG from the L2
+// took 12 ms.  A reduction ends in the block that finishes last, so that a dot
+// product is one launch and its result decides on the device whether the rest
+// of the iteration does anything.
+
+__device__ __forceinline__ int xface_at(const FlatDims& d, int i, int j, int k) {
+  return (i & 1) * d.half + (i >> 1) + d.sp * (j + d.ny * k);
+}
+__device__ __forceinline__ int yface_at(const FlatDims& d, int i, int j, int k) {
+  return ((i + j + k) & 1) * d.yh + (i >> 1) + d.sp * (j + (d.ny + 1) * k);
+}
+__device__ __forceinline__ int zface_at(const FlatDims& d, int i, int j, int k) {
+  return ((i + j + k) & 1) * d.zh + (i >> 1) + d.sp * (j + d.ny * k);
+}
+__device__ __forceinline__ int face_at(const FlatDims& d, int dir, const int (&c)[3]) {
+  return dir == 0 ? xface_at(d, c[0], c[1], c[2])
+                  : dir == 1 ? yface_at(d, c[0], c[1], c[2]) : zface_at(d, c[0], c[1], c[2]);
+}
+__device__ __forceinline__ int3 cell_of(const FlatDims& d, int at) {
+  const int colour = at >= d.half, e = at - colour * d.half;
+  const int p = e % d.sp, row = e / d.sp, j = row % d.ny, k = row / d.ny;
+  return make_int3(2 * p + ((j + k + colour) & 1), j, k);
+}
+
+template <typename T>
+__global__ void __launch_bounds__(256)
+    k_deep_fill(BottomTables bt, StencilArgs<T> op, FlatDims d, int3 pad, T* __restrict__ x,
+                T* __restrict__ y, T* __restrict__ z, T* __restrict__ mass,
+                T* __restrict__ wall) {
+  const int c = blockIdx.x * 256 + threadIdx.x;
+  if (c >= bt.n) return;
+  const int at = bt.map_out[c];
+  const int3 q = cell_of(d, at);
+  const int ix[3] = {q.x, q.y, q.z}, N[3] = {d.nx, d.ny, d.nz}, m[3] = {pad.x, pad.y, pad.z};
+  const T* bs[3] = {op.b0, op.b1, op.b2};
+  const T ih[3] = {op.ih0, op.ih1, op.ih2};
+  T* dst[3] = {x, y, z};
+  T w = T(0);
+#pragma unroll
+  for (int dir = 0; dir < 3; ++dir) {
+    const int lo = 2 * dir * bt.n + c, hi = lo + bt.n;
+    const T cl = (op.beta * bs[dir][bt.fidx[lo]]) * ih[dir];
+    if (bt.nbr[hi] < 0) w = w + T(2) * ((op.beta * bs[dir][bt.fidx[hi]]) * ih[dir]);
+    if (bt.nbr[lo] < 0) {
+      w = w + T(2) * cl;
+    } else if (ix[dir] > 0) {
+      dst[dir][face_at(d, dir, ix)] = cl;
+    } else {
+      // the link from the last cell, in m + 1 pieces
+      int f[3] = {ix[0], ix[1], ix[2]};
+      const T v = T(m[dir] + 1) * cl;
+      dst[dir][face_at(d, dir, f)] = v;
+      for (f[dir] = N[dir] - m[dir]; f[dir] <= N[dir]; ++f[dir]) dst[dir][face_at(d, dir, f)] = v;
+    }
+  }
+  mass[at] = op.a ? op.alpha * op.a[bt.aidx[c]] : op.alpha;
+  wall[at] = w;
+}
+
+template <typename T>
+__global__ void __launch_bounds__(256)
+    k_deep_diag(FlatDims d, const T* __restrict__ x, const T* __restrict__ y,
+                const T* __restrict__ z, const T* __restrict__ mass, const T* __restrict__ wall,
+                T* __restrict__ a) {
+  const int c = blockIdx.x * 256 + threadIdx.x;
+  if (c >= d.nx * d.ny * d.nz) return;
+  const int i = c % d.nx, j = c / d.nx % d.ny, k = c / d.nx / d.ny;
+  const int at = split_at(d, i, j, k);
+  const T s = x[xface_at(d, i, j, k)] + x[xface_at(d, i + 1, j, k)] + y[yface_at(d, i, j, k)] +
+              y[yface_at(d, i, j + 1, k)] + z[zface_at(d, i, j, k)] + z[zface_at(d, i, j, k + 1)];
+  const T v = mass[at] + wall[at];
+  a[at] = v == T(0) && s == T(0) ? T(1) : v;
+}
+
+template <typename T>
+__global__ void __launch_bounds__(256)
+    k_deep_coarsen(FlatDims d, const T* __restrict__ x, const T* __restrict__ y,
+                   const T* __restrict__ z, const T* __restrict__ mass,
+                   const T* __restrict__ wall, FlatDims cd, int3 pad, T* __restrict__ cx,
+                   T* __restrict__ cy, T* __restrict__ cz, T* __restrict__ cmass,
+                   T* __restrict__ cwall) {
+  const int c = blockIdx.x * 256 + threadIdx.x;
+  const int n[3] = {d.nx / 2, d.ny / 2, d.nz / 2};  // without the cells added
+  const int per = ~d.wall, nx = n[0] + 1, ny = n[1] + 1;
+  if (c >= nx * ny * (n[2] + 1)) return;
+  const int I = c % nx, J = c / nx % ny, K = c / nx / ny;
+  const int i = 2 * I, j = 2 * J, k = 2 * K;
+  // ends of a periodic direction: the link in pad + 1 pieces
+  if (J < n[1] && K < n[2]) {
+    const bool link = (per & 1) && pad.x && (I == 0 || I == n[0]);
+    const T v = T(link ? 0.125 : 0.0625) *
+                ((x[xface_at(d, i, j, k)] + x[xface_at(d, i, j + 1, k)]) +
+                 (x[xface_at(d, i, j, k + 1)] + x[xface_at(d, i, j + 1, k + 1)]));
+    cx[xface_at(cd, I, J, K)] = v;
+    if (link && I) cx[xface_at(cd, I + 1, J, K)] = v;
+  }
+  if (I < n[0] && K < n[2]) {
+    const bool link = (per & 4) && pad.y && (J == 0 || J == n[1]);
+    const T v = T(link ? 0.125 : 0.0625) *
+                ((y[yface_at(d, i, j, k)] + y[yface_at(d, i + 1, j, k)]) +
+                 (y[yface_at(d, i, j, k + 1)] + y[yface_at(d, i + 1, j, k + 1)]));
+    cy[yface_at(cd, I, J, K)] = v;
+    if (link && J) cy[yface_at(cd, I, J + 1, K)] = v;
+  }
+  if (I < n[0] && J < n[1]) {
+    const bool link = (per & 16) && pad.z && (K == 0 || K == n[2]);
+    const T v = T(link ? 0.125 : 0.0625) *
+                ((z[zface_at(d, i, j, k)] + z[zface_at(d, i + 1, j, k)]) +
+                 (z[zface_at(d, i, j + 1, k)] + z[zface_at(d, i + 1, j + 1, k)]));
+    cz[zface_at(cd, I, J, K)] = v;
+    if (link && K) cz[zface_at(cd, I, J, K + 1)] = v;
+  }
+  if (I < n[0] && J < n[1] && K < n[2]) {
+    T m = T(0), w = T(0);
+    for (int u = 0; u < 8; ++u) {
+      const int at = split_at(d, i + (u & 1), j + (u >> 1 & 1), k + (u >> 2));
+      m = m + mass[at];
+      w = w + wall[at];
+    }
+    const int at = split_at(cd, I, J, K);
+    cmass[at] = T(0.125) * m;
+    cwall[at] = T(0.0625) * w;
+  }
+}
+
+template <typename T>
+__global__ void __launch_bounds__(256)
+    k_deep_bottom(BottomTables bt, FlatOp<T> op, T* __restrict__ diag, T* __restrict__ coef) {
+  const int c = blockIdx.x * 256 + threadIdx.x;
+  if (c >= bt.n) return;
+  const FlatDims& d = op.d;
+  const int at = bt.map_out[c];
+  const int3 q = cell_of(d, at);
+  const T f[6] = {op.x[xface_at(d, q.x, q.y, q.z)],     op.x[xface_at(d, q.x + 1, q.y, q.z)],
+                  op.y[yface_at(d, q.x, q.y, q.z)],     op.y[yface_at(d, q.x, q.y + 1, q.z)],
+                  op.z[zface_at(d, q.x, q.y, q.z)],     op.z[zface_at(d, q.x, q.y, q.z + 1)]};
+  T g = op.a[at];
+#pragma unroll
+  for (int u = 0; u < 6; ++u) {
+    g = g + f[u];
+    coef[u * bt.n + c] = bt.nbr[u * bt.n + c] < 0 ? T(0) : f[u];
+  }
+  diag[c] = g;
+}
+
+// The launch's partial sums s (one per block, all lanes hold it): true in the
+// block that finishes last, with their sum in *total, added in block order.
+__device__ __forceinline__ bool deep_total(double s, double* partials, unsigned* count,
+                                           double* red, int& phase, double* total) {
+  __shared__ bool last;
+  if (threadIdx.x == 0) {
+    partials[blockIdx.x] = s;
+    __threadfence();
+    last = atomicAdd(count, 1u) == gridDim.x - 1;
+  }
+  __syncthreads();
+  if (!last) return false;
+  __threadfence();
+  double t = 0.0;
+  for (int b = threadIdx.x; b < (int)gridDim.x; b += 256) t += partials[b];
+  *total = block_sum(t, red, phase);
+  if (threadIdx.x == 0) *count = 0;
+  return true;
+}
+
+template <typename T>
+__global__ void __launch_bounds__(256)
+    k_deep_init(long long n, const T* __restrict__ f, T* __restrict__ r, T* __restrict__ x,
+                T* __restrict__ p, double* __restrict__ partials, DeepState* st) {
+  __shared__ double red[32];
+  int phase = 0;
+  double s = 0.0;
+  for (long long e = blockIdx.x * 256ll + threadIdx.x; e < n; e += gridDim.x * 256ll) {
+    const T v = f[e];
+    r[e] = v;
+    x[e] = T(0);
+    p[e] = T(0);
+    s += (double)v * (double)v;
+  }
+  s = block_sum(s, red, phase);
+  double b2;
+  if (deep_total(s, partials, &st->count, red, phase, &b2) && threadIdx.x == 0) {
+    st->rho = 0.0;
+    st->b2 = b2;
+    st->it = 0;
+    st->done = b2 > 0.0 ? 0 : 1;
+  }
+}
+
+template <typename T>
+__global__ void __launch_bounds__(256)
+    k_deep_rz(long long n, const T* __restrict__ r, const T* __restrict__ z,
+              double* __restrict__ partials, DeepState* st) {
+  __shared__ double red[32];
+  if (st->done) return;
+  int phase = 0;
+  double s = 0.0;
+  for (long long e = blockIdx.x * 256ll + threadIdx.x; e < n; e += gridDim.x * 256ll)
+    s += (double)r[e] * (double)z[e];
+  s = block_sum(s, red, phase);
+  double rho;
+  if (deep_total(s, partials, &st->count, red, phase, &rho) && threadIdx.x == 0) {
+    st->beta = st->it > 0 ? rho / st->rho : 0.0;
+    st->rho = rho;
+  }
+}
+
+template <typename T>
+__global__ void __launch_bounds__(256)
+    k_deep_p(long long n, const T* __restrict__ z, T* __restrict__ p, const DeepState* st) {
+  if (st->done) return;
+  const T be = (T)st->beta;
+  for (long long e = blockIdx.x * 256ll + threadIdx.x; e < n; e += gridDim.x * 256ll)
+    p[e] = z[e] + be * p[e];
+}
+
+template <typename T>
+__global__ void __launch_bounds__(256)
+    k_deep_xr(long long n, T* __restrict__ x, const T* __restrict__ p, T* __restrict__ r,
+              const T* __restrict__ q, const double* __restrict__ pqs, int npq, double tol2,
+              double* __restrict__ partials, DeepState* st) {
+  __shared__ double red[32];
+  if (st->done) return;
+  int phase = 0;
+  double s = 0.0;
+  for (int b = threadIdx.x; b < npq; b += 256) s += pqs[b];
+  const double pq = block_sum(s, red, phase), al = st->rho / pq;
+  const bool ok = pq > 0.0 && fabs(al) < 1e300;
+  const T alT = ok ? (T)al : T(0);
+  s = 0.0;
+  if (ok)
+    for (long long e = blockIdx.x * 256ll + threadIdx.x; e < n; e += gridDim.x * 256ll) {
+      x[e] = x[e] + alT * p[e];
+      const T rv = r[e] - alT * q[e];
+      r[e] = rv;
+      s += (double)rv * (double)rv;
+    }
+  s = block_sum(s, red, phase);
+  double rr;
+  if (deep_total(s, partials, &st->count, red, phase, &rr) && threadIdx.x == 0) {
+    if (ok) ++st->it;
+    st->done = !ok ? 2 : !(rr > tol2 * st->b2) ? 1 : 0;
   }
 }
 
@@ -1296,12 +1554,17 @@ hipError_t launch_flat_half(hipStream_t st, const FlatOp<T>& op, FlatPass ps, co
   return hipGetLastError();
 }
 
+// Whether cd holds the coarsening of d, as it is or padded at its high ends.
+static bool coarse_fits(const FlatDims& d, const FlatDims& cd) {
+  return d.nx % 2 == 0 && d.ny % 2 == 0 && d.nz % 2 == 0 && 2 * cd.nx >= d.nx &&
+         2 * cd.ny >= d.ny && 2 * cd.nz >= d.nz;
+}
+
 template <typename T>
 hipError_t launch_flat_restrict(hipStream_t st, const FlatOp<T>& op, FlatPass ps, const T* v,
                                 const T* f, const FlatDims& cd, T* cf) {
-  if (cd.nx != op.d.np || 2 * cd.ny != op.d.ny || 2 * cd.nz != op.d.nz || 2 * cd.nx != op.d.nx)
-    return hipErrorInvalidValue;
-  const Grid2 g = grid_of(op.d.np, cd.ny * cd.nz, ps.reverse);
+  if (!coarse_fits(op.d, cd)) return hipErrorInvalidValue;
+  const Grid2 g = grid_of(op.d.np, op.d.ny / 2 * (op.d.nz / 2), ps.reverse);
   if (ps.stream)
     hipLaunchKernelGGL((k_flat_restrict<T, true>), dim3(g.nb), dim3(256), 0, st, op, g, v, f, cd,
                        cf);
@@ -1386,7 +1649,7 @@ template <typename T>
 hipError_t launch_flat_block(hipStream_t st, const FlatOp<T>& op, FlatBlockMode mode, const T* src,
                              const T* f, T* dst, const FlatDims& cd, T* cf, const T* ec) {
   const FlatDims& d = op.d;
-  if (2 * cd.nx != d.nx || 2 * cd.ny != d.ny || 2 * cd.nz != d.nz) return hipErrorInvalidValue;
+  if (!coarse_fits(d, cd)) return hipErrorInvalidValue;
   const int w = flat_block_pairs(d, sizeof(T));
   if (w == 0) return hipErrorInvalidValue;
   const int nbx = (d.np + w - 1) / w, nby = (d.ny + kBlkOY - 1) / kBlkOY;
@@ -1534,7 +1797,94 @@ hipError_t launch_flat_tail(hipStream_t st, const FlatTail<T>& t, const FlatTail
   return hipGetLastError();
 }
 
+template <typename T>
+hipError_t launch_deep_fill(hipStream_t st, const BottomTables& bt, const StencilArgs<T>& op,
+                            const FlatDims& d, const int pad[3], T* x, T* y, T* z, T* mass,
+                            T* wall) {
+  hipLaunchKernelGGL(k_deep_fill<T>, dim3((bt.n + 255) / 256), dim3(256), 0, st, bt, op, d,
+                     make_int3(pad[0], pad[1], pad[2]), x, y, z, mass, wall);
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_deep_diag(hipStream_t st, const FlatDims& d, const T* x, const T* y, const T* z,
+                            const T* mass, const T* wall, T* a) {
+  hipLaunchKernelGGL(k_deep_diag<T>, dim3((d.nx * d.ny * d.nz + 255) / 256), dim3(256), 0, st, d, x,
+                     y, z, mass, wall, a);
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_deep_coarsen(hipStream_t st, const FlatDims& d, const T* x, const T* y,
+                               const T* z, const T* mass, const T* wall, const FlatDims& cd,
+                               const int pad[3], T* cx, T* cy, T* cz, T* cmass, T* cwall) {
+  if (!coarse_fits(d, cd) || 2 * (cd.nx - pad[0]) != d.nx || 2 * (cd.ny - pad[1]) != d.ny ||
+      2 * (cd.nz - pad[2]) != d.nz || std::max({pad[0], pad[1], pad[2]}) > 1)
+    return hipErrorInvalidValue;
+  const int n = (d.nx / 2 + 1) * (d.ny / 2 + 1) * (d.nz / 2 + 1);
+  hipLaunchKernelGGL(k_deep_coarsen<T>, dim3((n + 255) / 256), dim3(256), 0, st, d, x, y, z, mass,
+                     wall, cd, make_int3(pad[0], pad[1], pad[2]), cx, cy, cz, cmass, cwall);
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_deep_bottom(hipStream_t st, const BottomTables& bt, const FlatOp<T>& op, T* diag,
+                              T* coef) {
+  hipLaunchKernelGGL(k_deep_bottom<T>, dim3((bt.n + 255) / 256), dim3(256), 0, st, bt, op, diag,
+                     coef);
+  return hipGetLastError();
+}
+
+static int deep_blocks(long long n) {
+  return (int)std::min<long long>((n + 1023) / 1024, kDeepBlocks);
+}
+
+template <typename T>
+hipError_t launch_deep_init(hipStream_t st, long long n, const T* f, T* r, T* x, T* p,
+                            double* partials, DeepState* s) {
+  hipLaunchKernelGGL(k_deep_init<T>, dim3(deep_blocks(n)), dim3(256), 0, st, n, f, r, x, p,
+                     partials, s);
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_deep_rz(hipStream_t st, long long n, const T* r, const T* z, double* partials,
+                          DeepState* s) {
+  hipLaunchKernelGGL(k_deep_rz<T>, dim3(deep_blocks(n)), dim3(256), 0, st, n, r, z, partials, s);
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_deep_p(hipStream_t st, long long n, const T* z, T* p, const DeepState* s) {
+  hipLaunchKernelGGL(k_deep_p<T>, dim3(deep_blocks(n)), dim3(256), 0, st, n, z, p, s);
+  return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_deep_xr(hipStream_t st, long long n, T* x, const T* p, T* r, const T* q,
+                          const double* pq, int npq, double tol2, double* partials, DeepState* s) {
+  hipLaunchKernelGGL(k_deep_xr<T>, dim3(deep_blocks(n)), dim3(256), 0, st, n, x, p, r, q, pq, npq,
+                     tol2, partials, s);
+  return hipGetLastError();
+}
+
 #define INST(T)                                                                                    \
+  template hipError_t launch_deep_fill<T>(hipStream_t, const BottomTables&, const StencilArgs<T>&, \
+                                          const FlatDims&, const int*, T*, T*, T*, T*, T*);        \
+  template hipError_t launch_deep_diag<T>(hipStream_t, const FlatDims&, const T*, const T*,        \
+                                          const T*, const T*, const T*, T*);                       \
+  template hipError_t launch_deep_coarsen<T>(hipStream_t, const FlatDims&, const T*, const T*,     \
+                                             const T*, const T*, const T*, const FlatDims&,        \
+                                             const int*, T*, T*, T*, T*, T*);                      \
+  template hipError_t launch_deep_bottom<T>(hipStream_t, const BottomTables&, const FlatOp<T>&,    \
+                                            T*, T*);                                               \
+  template hipError_t launch_deep_init<T>(hipStream_t, long long, const T*, T*, T*, T*, double*,   \
+                                          DeepState*);                                             \
+  template hipError_t launch_deep_rz<T>(hipStream_t, long long, const T*, const T*, double*,       \
+                                        DeepState*);                                               \
+  template hipError_t launch_deep_p<T>(hipStream_t, long long, const T*, T*, const DeepState*);    \
+  template hipError_t launch_deep_xr<T>(hipStream_t, long long, T*, const T*, T*, const T*,        \
+                                        const double*, int, double, double*, DeepState*);          \
   template hipError_t launch_flat_half<T>(hipStream_t, const FlatOp<T>&, FlatPass, const T*, T*,   \
                                           const T*, int, bool, const FlatDims*, const T*,          \
                                           const T*, unsigned long long*);                          \
@@ -1567,6 +1917,9 @@ INST(float)
 template hipError_t launch_flat_resid<double, double>(hipStream_t, const FlatOp<double>&, FlatPass,
                                                       const double*, const double*, double*,
                                                       unsigned long long*, double*);
+template hipError_t launch_flat_resid<float, float>(hipStream_t, const FlatOp<float>&, FlatPass,
+                                                    const float*, const float*, float*,
+                                                    unsigned long long*, double*);
 template hipError_t launch_flat_resid<double, float>(hipStream_t, const FlatOp<double>&, FlatPass,
                                                      const double*, const double*, float*,
                                                      unsigned long long*, double*);

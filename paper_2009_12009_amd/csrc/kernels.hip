@@ -1762,6 +1762,14 @@ __global__ void __launch_bounds__(1024)
   T* p = work + 2 * (long long)n;
   T* q = work + 3 * (long long)n;
   const int tid = threadIdx.x, nt = blockDim.x;
+  int it = 0;
+  if (bt.warm) {
+    it = bt.warm[1];
+    if (bt.warm[0] == 1) {
+      if (tid == 0) *iters_out = it;
+      return;
+    }
+  }
   double s = 0.0;
   for (int c = tid; c < n; c += nt) {
     const T v = rhs[bt.map_rhs[c]];
@@ -1778,8 +1786,23 @@ __global__ void __launch_bounds__(1024)
   for (int c = tid; c < n; c += nt) s += (double)r[c] * (double)r[c];
   double rho = block_sum(s, red, phase);
   const double bnorm = sqrt(rho);
-  int it = 0;
-  if (bnorm > 0.0) {
+  bool more = bnorm > 0.0;
+  if (bt.warm && more) {
+    s = 0.0;
+    for (int c = tid; c < n; c += nt) {
+      T off = T(0);
+      for (int f = 0; f < 6; ++f) {
+        const int nb = bt.nbr[f * n + c];
+        off = off + (nb < 0 ? T(0) : coef[f * n + c] * out[bt.map_out[nb]]);
+      }
+      x[c] = out[bt.map_out[c]];
+      r[c] = r[c] - (diag[c] * x[c] - off);
+      s += (double)r[c] * (double)r[c];
+    }
+    rho = block_sum(s, red, phase);
+    more = sqrt(rho) > tol * bnorm;
+  }
+  if (more) {
     for (int c = tid; c < n; c += nt) p[c] = r[c];
     while (it < maxiter) {
       __syncthreads();
@@ -2063,6 +2086,7 @@ __global__ void __launch_bounds__(1024)
     k_bottom_cg_lds(BottomTables bt, const T* __restrict__ diag, const T* __restrict__ coef,
                     const T* __restrict__ rhs, T* __restrict__ out, int accumulate, double tol,
                     int maxiter, int singular, int* iters_out) {
+  if (bt.done && *bt.done) return;
   extern __shared__ unsigned char lds_raw[];
   __shared__ double red[32];
   cg_lds_run<T, CPT>(bt, diag, coef, rhs, out, accumulate, tol, maxiter, singular, iters_out,
@@ -3063,7 +3087,7 @@ hipError_t launch_bottom_cg(hipStream_t st, const BottomTables& bt, const T* dia
                             int maxiter, int singular, int* iters_out) {
   if (bt.n <= 0) return hipSuccess;
   const size_t lds = sizeof(T) * (size_t)bt.n;
-  if (bt.cpt > 0) {
+  if (bt.cpt > 0 && !bt.warm) {
     const int lanes = bt.nb * bt.nc * ((bt.na + bt.cpt - 1) / bt.cpt);
     if (lanes > 1024 || bt.cpt < 2 || bt.cpt > kCgMaxRun || lds > 61440 ||
         bt.na * bt.nb * bt.nc != bt.n)
@@ -3085,7 +3109,7 @@ hipError_t launch_bottom_cg(hipStream_t st, const BottomTables& bt, const T* dia
 #undef CGC
     return hipGetLastError();
   }
-  if (lds <= 61440 && bt.n <= 8 * 1024) {  // stays under 64 KiB with the reduction scratch
+  if (lds <= 61440 && bt.n <= 8 * 1024 && !bt.warm) {  // stays under 64 KiB with the reduction scratch
     // up to 1024 cells one per lane in whole wavefronts, then 1024 lanes
     const int nt = bt.n <= 1024 ? (bt.n + 63) / 64 * 64 : 1024;
 #define CGL(C) \

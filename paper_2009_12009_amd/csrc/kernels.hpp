@@ -284,6 +284,11 @@ struct BottomTables {
   // cpt = 0: no such layout (see BottomColumns).
   const int* perm = nullptr;
   int cpt = 0, axa = 0, axb = 0, axc = 0, na = 0, nb = 0, nc = 0;
+  // if set and *done is not 0, CG kernels do nothing
+  const int* done = nullptr;
+  // k_bottom_cg goes on from out where done[0] != 1, counting from done[1]
+  // iterations; with done[0] = 1 it only reports them
+  const int* warm = nullptr;
 };
 
 // The column layout of a bottom level of extents ext[3], or cpt = 0 where the
