@@ -158,13 +158,16 @@ NdGeo geo_of(const int n[3], const int per[3]) {
 
 long long padded(const NdGeo& g) { return (long long)g.px * g.py * (g.mz + 2); }
 
-// Planes per work-group: as deep as 8 while the level still gets >= 2048
-// work-groups of 64 x 4 lanes (coarse levels: shallow, so that their
-// launches are not a few long serial marches).
-int default_tz(const NdGeo& g) {
+// Planes per work-group.  The finest level's kernels carry planes along z in
+// registers: up to 32 while that leaves 1024 work-groups of 64 x 4 lanes (a
+// Jacobi sweep at 256^3 158 us with 8 planes, 146 with 16, 139 with 32; at 128^3
+// 17.9 with 4, 16.7 with 8).  Coarse levels carry nothing: up to 4 while that
+// leaves 4096 (127^3 nodes 81 us with 4 planes, 85 with 8).
+int default_tz(const NdGeo& g, bool finest) {
   const long long cols = (long long)((g.mx + 63) / 64) * ((g.my + 3) / 4);
-  int tz = 8;
-  while (tz > 1 && cols * ((g.mz + tz - 1) / tz) < 2048) tz /= 2;
+  int tz = finest ? 32 : 4;
+  const int want = finest ? 1024 : 4096;
+  while (tz > 1 && cols * ((g.mz + tz - 1) / tz) < want) tz /= 2;
   return tz;
 }
 
@@ -199,7 +202,7 @@ int plan(mg_nodal* s, Bump& bump) {
     NdLevel lv;
     for (int d = 0; d < 3; ++d) lv.n[d] = n[d];
     lv.g = geo_of(n, s->periodic);
-    lv.g.tz = default_tz(lv.g);
+    lv.g.tz = default_tz(lv.g, s->L.empty());
     if (lv.g.mx < 1 || lv.g.my < 1 || lv.g.mz < 1)
       return fail(MG_ERR_INVALID_BOXARRAY, "a level has no unknown nodes");
     lv.size = padded(lv.g);
@@ -612,7 +615,7 @@ int mg_nodal_create(const mg_box_t* boxes, int32_t nbox, const mg_geom_t* geom,
       HIPTRY(hipEventCreate(&b));
       float best = 1e30f;
       int btz = l0.g.tz;
-      for (int tz : {2, 4, 8, 16}) {
+      for (int tz : {4, 8, 16, 32}) {
         l0.g.tz = tz;
         for (int k = 0; k < 8 && !rc; ++k) {
           if (k == 2 && hipEventRecord(a, s->st) != hipSuccess) rc = fail(MG_ERR_HIP, "event");
