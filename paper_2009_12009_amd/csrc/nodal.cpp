@@ -97,6 +97,8 @@ struct mg_nodal {
   double *kx = nullptr, *kr = nullptr, *kp = nullptr, *kq = nullptr;
   double* d_cg = nullptr;
   int* d_iters = nullptr;
+  int tail = -1;  // first level of the one-launch tail (-1: none)
+  NdTail* d_tail = nullptr;
   unsigned long long* d_norm = nullptr;  // 3 slots
   size_t ws_need = 0;
   hipStream_t user = nullptr, st = nullptr;
@@ -236,6 +238,7 @@ int plan(mg_nodal* s, Bump& bump) {
   }
   s->d_norm = bump.take<unsigned long long>(3 * (size_t)kNdNormSlot);
   s->d_iters = bump.take<int>(4);
+  s->d_tail = bump.take<NdTail>(1);
   if (s->opts.krylov) {
     s->kx = bump.take<double>(s->L[0].size);
     s->kr = bump.take<double>(s->L[0].size);
@@ -313,17 +316,73 @@ int sweep(mg_nodal* s, size_t l, const double* phi, const double* f, double* out
   return MG_OK;
 }
 
+// The tail from level l (l >= 1) to the bottom.
+NdTail tail_args(const mg_nodal* s, size_t l) {
+  NdTail t{};
+  const NdGeo& gb = s->L.back().g;
+  t.nlev = (int)(s->L.size() - 1 - l);
+  t.nu1 = s->opts.nu1;
+  t.nu2 = s->opts.nu2;
+  t.singular = s->singular ? 1 : 0;
+  t.maxit = s->opts.bottom_max_iter > 0 ? s->opts.bottom_max_iter : gb.mx * gb.my * gb.mz;
+  t.omega = s->omega;
+  t.tol = s->opts.bottom_rel_tol;
+  t.iters = s->d_iters;
+  for (int i = 0; i <= std::min(t.nlev, kNdTailLevels); ++i) {
+    const NdLevel& lv = s->L[l + i];
+    t.lev[i] = {lv.g, cst(lv.st), lv.f, lv.x[0]};
+  }
+  return t;
+}
+
+// First level of the tail (-1: none): all the levels that fit.  Levels of 7^3 and
+// 3^3 nodes: 15 us; with launches 7 + 6 for the one and 25 for the other's CG.
+int tail_level(const mg_nodal* s) {
+  int at = -1;
+  for (size_t l = s->L.size() - 1; l >= 1; --l) {
+    const NdTail t = tail_args(s, l);
+    if (t.nlev > kNdTailLevels || (t.nlev > 0 && (t.nu1 < 1 || t.nu2 < 0)) || nd_tail_lds(t) < 0)
+      break;
+    at = (int)l;
+  }
+  return at;
+}
+
+// Whether level l >= 1 runs each half of its cycle in one launch: two sweeps on
+// both sides, and few enough nodes that launches cost more than the rims (31^3
+// nodes: 10 + 8 us against 18 + 15 for the separate launches; 63^3 with tiles of
+// twice the edge 45 + 42 against 28 + 23).
+bool fused_level(const mg_nodal* s, size_t l) {
+  const NdGeo& g = s->L[l].g;
+  return s->opts.nu1 == 2 && s->opts.nu2 == 2 && (long long)g.mx * g.my * g.mz <= 65536;
+}
+
 // Levels l >= 1 from a zero guess on their f; returns in *res the index of
 // the level's iterate buffer that holds the correction.
 int coarse(mg_nodal* s, size_t l, int* res) {
   NdLevel& lv = s->L[l];
   int rc;
+  if ((int)l == s->tail) {
+    HIPTRY(nd_launch_tail(s->st, tail_args(s, l), s->d_tail));
+    *res = 0;
+    return MG_OK;
+  }
   if (l + 1 == s->L.size()) {
     const int maxit = s->opts.bottom_max_iter > 0 ? s->opts.bottom_max_iter
                                                   : lv.g.mx * lv.g.my * lv.g.mz;
     HIPTRY(nd_launch_bottom_cg(s->st, lv.g, cst(lv.st), lv.f, lv.x[0], s->bwork,
                                s->opts.bottom_rel_tol, maxit, s->singular ? 1 : 0, s->d_iters));
     *res = 0;
+    return MG_OK;
+  }
+  if (l > 0 && fused_level(s, l)) {
+    NdLevel& cl = s->L[l + 1];
+    HIPTRY(nd_launch_down(s->st, lv.g, cl.g, cst(lv.st), lv.f, lv.x[0], cl.f, s->omega));
+    int cres = 0;
+    if ((rc = coarse(s, l + 1, &cres))) return rc;
+    HIPTRY(nd_launch_up(s->st, lv.g, cl.g, cst(lv.st), lv.f, lv.x[0], cl.x[cres], lv.x[1],
+                        s->omega));
+    *res = 1;
     return MG_OK;
   }
   int cur = 0;
@@ -637,6 +696,17 @@ int mg_nodal_create(const mg_box_t* boxes, int32_t nbox, const mg_geom_t* geom,
       l0.g.tz = btz;
       if (s->opts.verbose)
         fprintf(stderr, "amrmg nodal tune: finest sweep %d planes, %.4f ms\n", btz, best / 6);
+    }
+    // the tail's device plan, through pinned staging
+    s->tail = tail_level(s.get());
+    if (s->tail > 0) {
+      NdTail* h = nullptr;
+      HIPTRY(hipHostMalloc((void**)&h, sizeof(NdTail), hipHostMallocDefault));
+      *h = tail_args(s.get(), s->tail);
+      hipError_t e = hipMemcpyAsync(s->d_tail, h, sizeof(NdTail), hipMemcpyHostToDevice, s->st);
+      if (e == hipSuccess) e = hipStreamSynchronize(s->st);
+      hipHostFree(h);
+      HIPTRY(e);
     }
     // the coarse part of the cycle as a graph, one per level-0 buffer it
     // interpolates into

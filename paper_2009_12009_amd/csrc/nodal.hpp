@@ -65,6 +65,14 @@ hipError_t nd_launch_restrict(hipStream_t st, const NdGeo& gf, const NdGeo& gc, 
 // phi_f += P e_c (trilinear; e_c ghosts not read).
 hipError_t nd_launch_interp_add(hipStream_t st, const NdGeo& gf, const NdGeo& gc,
                                 const double* ec, double* phif);
+// A coarse level's half of a cycle with two sweeps each: from zero, x = the
+// iterate and fc = the next coarser level's right-hand side; and out = two
+// sweeps of x + P ec (ghosts of x and ec not read, of x and out not written).
+hipError_t nd_launch_down(hipStream_t st, const NdGeo& g, const NdGeo& gc, const NdStencilC& s,
+                          const double* f, double* x, double* fc, double omega);
+hipError_t nd_launch_up(hipStream_t st, const NdGeo& g, const NdGeo& gc, const NdStencilC& s,
+                        const double* f, const double* x, const double* ec, double* out,
+                        double omega);
 // Wrapped copies into the ghosts of the periodic directions (walls untouched).
 hipError_t nd_launch_fill_ghosts(hipStream_t st, const NdGeo& g, double* a);
 // Galerkin coarse operator R A P of the finest level (from sigma) or of a
@@ -78,6 +86,26 @@ hipError_t nd_launch_rap(hipStream_t st, const NdGeo& gf, const NdGeo& gc, const
 hipError_t nd_launch_bottom_cg(hipStream_t st, const NdGeo& g, const NdStencilC& s,
                                const double* rhs, double* x, double* work, double tol, int maxit,
                                int singular, int* iters);
+// The coarsest levels of a cycle, down to the bottom's CG, in one launch of one
+// work-group: every level at most kNdTailNodes unknowns (one per lane), the
+// vectors in LDS.  lev[nlev] is the bottom; reads lev[0].f, writes lev[0].x.
+constexpr int kNdTailNodes = 1024, kNdTailLevels = 6;
+struct NdTailLevel {
+  NdGeo g;
+  NdStencilC w;
+  const double* f;
+  double* x;
+};
+struct NdTail {
+  int nlev, nu1, nu2, singular, maxit;
+  double omega, tol;
+  int* iters;
+  NdTailLevel lev[kNdTailLevels + 1];
+};
+// LDS bytes of the tail, -1 if it has none (too many nodes or bytes).
+int nd_tail_lds(const NdTail& t);
+// dt: a copy of t in device memory.
+hipError_t nd_launch_tail(hipStream_t st, const NdTail& t, const NdTail* dt);
 // max |v| over the valid nodes.
 hipError_t nd_launch_maxabs(hipStream_t st, const NdGeo& g, const double* v,
                             unsigned long long* norm);

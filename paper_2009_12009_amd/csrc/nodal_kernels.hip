@@ -14,6 +14,7 @@
 // plane, so a step loads one new plane of each.
 #include <hip/hip_runtime.h>
 
+#include "device.hpp"
 #include "nodal.hpp"
 
 namespace amrmg {
@@ -49,10 +50,6 @@ __device__ __forceinline__ int nd_ntx(const NdGeo& g) { return (g.mx + 63) / 64;
 __device__ __forceinline__ int nd_nty(const NdGeo& g) { return (g.my + 3) / 4; }
 __device__ __forceinline__ int nd_ntz(const NdGeo& g) { return (g.mz + g.tz - 1) / g.tz; }
 
-__device__ __forceinline__ unsigned long long absbits(double v) {
-  return (unsigned long long)__double_as_longlong(fabs(v));
-}
-
 // Unsigned max of a per-lane value over the work-group, folded into way
 // (blockIdx % kNdNormWays) of the slot at dst (skipped when the way already
 // holds at least that value).
@@ -76,7 +73,7 @@ __device__ void nd_block_max(unsigned long long v, unsigned long long* dst) {
 }
 
 // The 14 stored offsets, centre first, then (z, y, x) lexicographic.
-__constant__ int kUp[kNdStored][3] = {
+__device__ constexpr int kUp[kNdStored][3] = {
     {0, 0, 0},  {1, 0, 0},  {-1, 1, 0}, {0, 1, 0},  {1, 1, 0}, {-1, -1, 1}, {0, -1, 1},
     {1, -1, 1}, {-1, 0, 1}, {0, 0, 1},  {1, 0, 1},  {-1, 1, 1}, {0, 1, 1},  {1, 1, 1}};
 
@@ -678,6 +675,414 @@ __global__ void __launch_bounds__(1024)
   if (tid == 0) *iters = it;
 }
 
+// ---------------------------------------------------------------------------
+// A small level's half of a cycle in one launch, nu1 = nu2 = 2.  A work-group
+// takes a tile of the level and recomputes a rim of one node per remaining
+// pass, so that the passes need only LDS between them.  Bound by latency and by the
+// couplings, which come from the L2 once per pass and node; the tiles are
+// small (2^3 coarse nodes, 4^3 nodes), so that a level of 31^3 fills the chip:
+// 10 us down and 8 up there, 7 and 6 at 15^3, where the four and three launches
+// they replace took 14 to 18 and 12 to 15.
+
+// Regions may be longer than a small periodic level.
+__device__ __forceinline__ int wrapped(int x, int m) {
+  while (x < 0) x += m;
+  while (x >= m) x -= m;
+  return x;
+}
+
+// Node q of a region of NX x NY x NZ nodes that starts at (x0, y0, z0):
+// its padded element, wrapped along periodic directions, -1 past a wall.
+template <int NX, int NY>
+__device__ __forceinline__ int region_at(const NdGeo& g, int x0, int y0, int z0, int q) {
+  int x = x0 + q % NX, y = y0 + q / NX % NY, z = z0 + q / (NX * NY);
+  if (g.per & 1) x = wrapped(x, g.mx);
+  if (g.per & 2) y = wrapped(y, g.my);
+  if (g.per & 4) z = wrapped(z, g.mz);
+  const bool in = x >= 0 && x < g.mx && y >= 0 && y < g.my && z >= 0 && z < g.mz;
+  return in ? pidx(g, x, y, z) : -1;
+}
+
+// A v at padded element c; v: the node's place in an LDS region of row and
+// plane pitch NX, NX * NY that holds its neighbours.
+template <int NX, int NY>
+__device__ __forceinline__ double region_apply(const NdGeo& g, const NdStencilC& s, int c,
+                                               double diag, const double* v) {
+  double ap = diag * v[0];
+#pragma unroll
+  for (int q = 1; q < kNdStored; ++q) {
+    const int d = kUp[q][0] + g.px * (kUp[q][1] + g.py * kUp[q][2]);
+    const int l = kUp[q][0] + NX * (kUp[q][1] + NY * kUp[q][2]);
+    ap += s.w[q][c] * v[l];
+    ap += s.w[q][c - d] * v[-l];
+  }
+  return ap;
+}
+
+// Two sweeps from zero, residual, restriction: x = the level's iterate, fc =
+// the coarser level's right-hand side.  Tile: TX x TY x TZ coarse nodes.
+template <int TX, int TY, int TZ>
+__global__ void __launch_bounds__(256)
+    k_nd_down(NdGeo g, NdGeo gc, int ntx, int nty, NdStencilC s, const double* __restrict__ f,
+              double* __restrict__ x, double* __restrict__ fc, double omega) {
+  constexpr int RX = 2 * TX + 1, RY = 2 * TY + 1, RZ = 2 * TZ + 1;  // residual
+  constexpr int BX = RX + 2, BY = RY + 2, BZ = RZ + 2;              // second sweep
+  constexpr int AX = RX + 4, AY = RY + 4, AZ = RZ + 4;              // first sweep
+  __shared__ double A[AX * AY * AZ], B[BX * BY * BZ];
+  double* const R = A;
+  const int t = blockIdx.x;
+  const int I0 = t % ntx * TX, J0 = t / ntx % nty * TY, K0 = t / (ntx * nty) * TZ;
+  // first node of the residual's region: left of coarse node I0
+  const int x0 = 2 * I0 + (g.per & 1 ? 0 : 1) - 1, y0 = 2 * J0 + (g.per & 2 ? 0 : 1) - 1,
+            z0 = 2 * K0 + (g.per & 4 ? 0 : 1) - 1;
+  for (int q = threadIdx.x; q < AX * AY * AZ; q += 256) {
+    const int c = region_at<AX, AY>(g, x0 - 2, y0 - 2, z0 - 2, q);
+    A[q] = c >= 0 ? omega * f[c] / s.w[0][c] : 0.0;
+  }
+  __syncthreads();
+  for (int q = threadIdx.x; q < BX * BY * BZ; q += 256) {
+    const int c = region_at<BX, BY>(g, x0 - 1, y0 - 1, z0 - 1, q);
+    double v = 0.0;
+    if (c >= 0) {
+      const int bx = q % BX, by = q / BX % BY, bz = q / (BX * BY);
+      const double* a = A + (bx + 1) + AX * ((by + 1) + AY * (bz + 1));
+      const double diag = s.w[0][c];
+      const double r = f[c] - region_apply<AX, AY>(g, s, c, diag, a);
+      v = a[0] + omega * r / diag;
+    }
+    B[q] = v;
+  }
+  __syncthreads();
+  // the tile's own nodes: [x0 + 1, x0 + 2 TX] and so on, the first node of the
+  // level along a wall (x0 = 0) and the last ones with the end tiles
+  const bool ex = I0 + TX >= gc.mx, ey = J0 + TY >= gc.my, ez = K0 + TZ >= gc.mz;
+  for (int q = threadIdx.x; q < RX * RY * RZ; q += 256) {
+    const int rx = q % RX, ry = q / RX % RY, rz = q / (RX * RY);
+    const int c = region_at<RX, RY>(g, x0, y0, z0, q);
+    double r = 0.0;
+    if (c >= 0) {
+      const double* b = B + (rx + 1) + BX * ((ry + 1) + BY * (rz + 1));
+      r = f[c] - region_apply<BX, BY>(g, s, c, s.w[0][c], b);
+      // the tile's own nodes: from its first coarse node's left neighbour on
+      // along walls (the level's first node is one), from the coarse node on
+      // along periodic directions (never a wrapped one)
+      const int ux = x0 + rx, uy = y0 + ry, uz = z0 + rz;
+      const bool own = ((g.per & 1) ? rx > 0 && ux < g.mx : rx < 2 * TX || ex) &&
+                       ((g.per & 2) ? ry > 0 && uy < g.my : ry < 2 * TY || ey) &&
+                       ((g.per & 4) ? rz > 0 && uz < g.mz : rz < 2 * TZ || ez);
+      if (own) x[c] = b[0];
+    }
+    R[q] = r;
+  }
+  __syncthreads();
+  for (int q = threadIdx.x; q < TX * TY * TZ; q += 256) {
+    const int cx = q % TX, cy = q / TX % TY, cz = q / (TX * TY);
+    if (I0 + cx >= gc.mx || J0 + cy >= gc.my || K0 + cz >= gc.mz) continue;
+    const double* r = R + (2 * cx + 1) + RX * ((2 * cy + 1) + RY * (2 * cz + 1));
+    double acc = 0.0;
+#pragma unroll
+    for (int uz = -1; uz <= 1; ++uz)
+#pragma unroll
+      for (int uy = -1; uy <= 1; ++uy)
+#pragma unroll
+        for (int ux = -1; ux <= 1; ++ux)
+          acc += (pw1(ux) * pw1(uy) * pw1(uz)) * r[ux + RX * (uy + RY * uz)];
+    fc[pidx(gc, I0 + cx, J0 + cy, K0 + cz)] = acc * 0.125;
+  }
+}
+
+// Coarse correction added, then two sweeps: out = the level's iterate.  Tile:
+// TX x TY x TZ nodes.
+template <int TX, int TY, int TZ>
+__global__ void __launch_bounds__(256)
+    k_nd_up(NdGeo g, NdGeo gc, int ntx, int nty, NdStencilC s, const double* __restrict__ f,
+            const double* __restrict__ x, const double* __restrict__ ec,
+            double* __restrict__ out, double omega) {
+  constexpr int BX = TX + 2, BY = TY + 2, BZ = TZ + 2;
+  constexpr int AX = TX + 4, AY = TY + 4, AZ = TZ + 4;
+  __shared__ double A[AX * AY * AZ], B[BX * BY * BZ];
+  const int t = blockIdx.x;
+  const int x0 = t % ntx * TX, y0 = t / ntx % nty * TY, z0 = t / (ntx * nty) * TZ;
+  for (int q = threadIdx.x; q < AX * AY * AZ; q += 256) {
+    const int c = region_at<AX, AY>(g, x0 - 2, y0 - 2, z0 - 2, q);
+    double v = 0.0;
+    if (c >= 0) {
+      const int cx = c % g.px - 1, cy = c / g.px % g.py - 1, cz = c / (g.px * g.py) - 1;
+      int ix[2], iy[2], iz[2];
+      double wx[2], wy[2], wz[2];
+      interp1(cx, g.per & 1, gc.mx, ix[0], ix[1], wx[0], wx[1]);
+      interp1(cy, g.per & 2, gc.my, iy[0], iy[1], wy[0], wy[1]);
+      interp1(cz, g.per & 4, gc.mz, iz[0], iz[1], wz[0], wz[1]);
+      double p[2];
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        p[k] = 0.0;
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+          for (int a = 0; a < 2; ++a) p[k] += (wx[a] * wy[b]) * ec[pidx(gc, ix[a], iy[b], iz[k])];
+      }
+      v = x[c] + (wz[0] * p[0] + wz[1] * p[1]);
+    }
+    A[q] = v;
+  }
+  __syncthreads();
+  for (int q = threadIdx.x; q < BX * BY * BZ; q += 256) {
+    const int c = region_at<BX, BY>(g, x0 - 1, y0 - 1, z0 - 1, q);
+    double v = 0.0;
+    if (c >= 0) {
+      const int bx = q % BX, by = q / BX % BY, bz = q / (BX * BY);
+      const double* a = A + (bx + 1) + AX * ((by + 1) + AY * (bz + 1));
+      const double diag = s.w[0][c];
+      const double r = f[c] - region_apply<AX, AY>(g, s, c, diag, a);
+      v = a[0] + omega * r / diag;
+    }
+    B[q] = v;
+  }
+  __syncthreads();
+  for (int q = threadIdx.x; q < TX * TY * TZ; q += 256) {
+    const int ux = x0 + q % TX, uy = y0 + q / TX % TY, uz = z0 + q / (TX * TY);
+    if (ux >= g.mx || uy >= g.my || uz >= g.mz) continue;
+    const int c = pidx(g, ux, uy, uz);
+    const double* b = B + (q % TX + 1) + BX * ((q / TX % TY + 1) + BY * (q / (TX * TY) + 1));
+    const double diag = s.w[0][c];
+    const double r = f[c] - region_apply<BX, BY>(g, s, c, diag, b);
+    out[c] = b[0] + omega * r / diag;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// The tail (nd_launch_tail).  A lane owns one node of a level; its couplings are
+// loaded once for the way down and once for the way up, what it reads of its
+// neighbours is in LDS, so a pass is 27 LDS reads and a barrier.
+
+template <typename P>
+__device__ __forceinline__ P* nd_global(P* p) {
+  return (P*)(__attribute__((address_space(1))) P*)p;
+}
+
+// The level's LDS arrays: right-hand side and two iterates, padded by the wall
+// nodes (zeros).  Periodic neighbours are wrapped in the index, not copied.
+struct NdTailNode {
+  bool on;
+  int c;                       // element of an LDS array, and of the level's own arrays
+  int ox[3], oy[3], oz[3];     // element offsets to the neighbours -1, 0, 1
+  double w[27];                // couplings by (z + 1) 9 + (y + 1) 3 + (x + 1)
+};
+
+__device__ __forceinline__ void nd_tail_place(NdTailNode& n, const NdGeo& g, int i) {
+  n.on = i < g.mx * g.my * g.mz;
+  const int x = n.on ? i % g.mx : 0, y = n.on ? i / g.mx % g.my : 0,
+            z = n.on ? i / (g.mx * g.my) : 0;
+  n.c = pidx(g, x, y, z);
+  const int py = g.px, pz = g.px * g.py;
+  n.ox[0] = x == 0 && (g.per & 1) ? g.mx - 1 : -1;
+  n.ox[2] = x == g.mx - 1 && (g.per & 1) ? 1 - g.mx : 1;
+  n.oy[0] = y == 0 && (g.per & 2) ? (g.my - 1) * py : -py;
+  n.oy[2] = y == g.my - 1 && (g.per & 2) ? (1 - g.my) * py : py;
+  n.oz[0] = z == 0 && (g.per & 4) ? (g.mz - 1) * pz : -pz;
+  n.oz[2] = z == g.mz - 1 && (g.per & 4) ? (1 - g.mz) * pz : pz;
+  n.ox[1] = n.oy[1] = n.oz[1] = 0;
+}
+
+__device__ __forceinline__ void nd_tail_load(NdTailNode& n, const NdTail* tp, int l) {
+  const NdGeo g = tp->lev[l].g;
+#pragma unroll
+  for (int q = 0; q < kNdStored; ++q) {
+    const double* w = nd_global(tp->lev[l].w.w[q]);
+    const int d = kUp[q][0] + g.px * (kUp[q][1] + g.py * kUp[q][2]);
+    const int k = 13 + kUp[q][0] + 3 * kUp[q][1] + 9 * kUp[q][2];
+    n.w[k] = n.on ? w[n.c] : 0.0;
+    if (q > 0) n.w[26 - k] = n.on ? w[n.c - d] : 0.0;
+  }
+}
+
+__device__ __forceinline__ double nd_tail_apply(const NdTailNode& n, const double* v) {
+  double ap = n.w[13] * v[n.c];
+#pragma unroll
+  for (int q = 1; q < kNdStored; ++q) {
+    const int x = kUp[q][0], y = kUp[q][1], z = kUp[q][2], k = 13 + x + 3 * y + 9 * z;
+    ap += n.w[k] * v[n.c + n.ox[1 + x] + n.oy[1 + y] + n.oz[1 + z]];
+    ap += n.w[26 - k] * v[n.c + n.ox[1 - x] + n.oy[1 - y] + n.oz[1 - z]];
+  }
+  return ap;
+}
+
+__device__ __forceinline__ int nd_padded(const NdGeo& g) { return g.px * g.py * (g.mz + 2); }
+
+// Sum over the work-group; one wavefront needs no barrier.
+template <bool ONE>
+__device__ __forceinline__ double nd_tail_sum(double v, double* red, int& phase) {
+  return ONE ? wave_sum(v) : block_sum_w<true>(v, red, phase, (blockDim.x + 63) / 64);
+}
+
+// CG from zero on the bottom: p in LDS (padded), the rest in registers.  ONE: at
+// most 64 nodes, wavefront 0 alone.
+template <bool ONE>
+__device__ __forceinline__ void nd_tail_cg(const NdTail* tp, const double* f, double* x, double* p,
+                                           double* red) {
+  const NdGeo g = tp->lev[tp->nlev].g;
+  const int nn = g.mx * g.my * g.mz;
+  NdTailNode n;
+  nd_tail_place(n, g, threadIdx.x);
+  nd_tail_load(n, tp, tp->nlev);
+  int phase = 0;
+  auto sync = [&]() {
+    if (ONE) {
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    } else {
+      __syncthreads();
+    }
+  };
+  double b = n.on ? f[n.c] : 0.0, xv = 0.0;
+  if (tp->singular) {
+    const double m = nd_tail_sum<ONE>(b, red, phase) / nn;
+    b = n.on ? b - m : 0.0;
+  }
+  double r = b, pv = b;
+  double rr = nd_tail_sum<ONE>(r * r, red, phase);
+  const double nb = sqrt(rr), tol = tp->tol;
+  const int maxit = tp->maxit;
+  int it = 0;
+  while (nb > 0.0 && it < maxit && sqrt(rr) > tol * nb) {
+    if (n.on) p[n.c] = pv;
+    sync();
+    const double q = n.on ? nd_tail_apply(n, p) : 0.0;
+    // (the sum's barrier also keeps the next p from the lanes still reading)
+    const double alpha = rr / nd_tail_sum<ONE>(pv * q, red, phase);
+    xv += alpha * pv;
+    r -= alpha * q;
+    const double rn = nd_tail_sum<ONE>(r * r, red, phase);
+    const double beta = rn / rr;
+    rr = rn;
+    pv = r + beta * pv;
+    if (ONE) sync();
+    ++it;
+  }
+  if (tp->singular) xv -= nd_tail_sum<ONE>(xv, red, phase) / nn;
+  if (n.on) x[n.c] = xv;
+  if (threadIdx.x == 0) *nd_global(tp->iters) = it;
+}
+
+template <int NT>
+__global__ void __launch_bounds__(NT) k_nd_tail(const NdTail* __restrict__ tp) {
+  extern __shared__ __align__(16) double nd_lds[];
+  __shared__ double red[32];
+  const int tid = threadIdx.x, nlev = tp->nlev;
+  auto base = [&](int l) {
+    int o = 0;
+    for (int m = 0; m < l; ++m) o += 3 * nd_padded(tp->lev[m].g);
+    return nd_lds + o;
+  };
+  {
+    const int all = (int)(base(nlev + 1) - nd_lds);
+    for (int e = tid; e < all; e += NT) nd_lds[e] = 0.0;
+    __syncthreads();
+    NdTailNode n;
+    nd_tail_place(n, tp->lev[0].g, tid);
+    if (n.on) nd_lds[n.c] = nd_global(tp->lev[0].f)[n.c];
+    __syncthreads();
+  }
+  const double om = tp->omega;
+  for (int l = 0; l < nlev; ++l) {
+    const NdGeo g = tp->lev[l].g, gc = tp->lev[l + 1].g;
+    const int pad = nd_padded(g);
+    double* const f = base(l);
+    double* x = f + pad;
+    double* y = x + pad;
+    NdTailNode n;
+    nd_tail_place(n, g, tid);
+    nd_tail_load(n, tp, l);
+    const double fv = n.on ? f[n.c] : 0.0;
+    if (n.on) x[n.c] = om * fv / n.w[13];
+    __syncthreads();
+    for (int k = 1; k < tp->nu1; ++k) {
+      if (n.on) y[n.c] = x[n.c] + om * (fv - nd_tail_apply(n, x)) / n.w[13];
+      __syncthreads();
+      double* const t = x;
+      x = y;
+      y = t;
+    }
+    if (n.on) y[n.c] = fv - nd_tail_apply(n, x);
+    __syncthreads();
+    NdTailNode m;
+    nd_tail_place(m, gc, tid);
+    if (m.on) {
+      const int I = tid % gc.mx, J = tid / gc.mx % gc.my, K = tid / (gc.mx * gc.my);
+      double acc = 0.0;
+#pragma unroll
+      for (int uz = -1; uz <= 1; ++uz)
+#pragma unroll
+        for (int uy = -1; uy <= 1; ++uy)
+#pragma unroll
+          for (int ux = -1; ux <= 1; ++ux)
+            acc += (pw1(ux) * pw1(uy) * pw1(uz)) *
+                   y[pidx(g, fine_of(I, ux, g.per & 1, g.mx), fine_of(J, uy, g.per & 2, g.my),
+                          fine_of(K, uz, g.per & 4, g.mz))];
+      base(l + 1)[m.c] = acc * 0.125;
+    }
+    __syncthreads();
+  }
+  {
+    double* const f = base(nlev);
+    const int pad = nd_padded(tp->lev[nlev].g);
+    const NdGeo g = tp->lev[nlev].g;
+    if (g.mx * g.my * g.mz <= 64) {
+      if (tid < 64) nd_tail_cg<true>(tp, f, f + pad, f + 2 * pad, red);
+    } else {
+      nd_tail_cg<false>(tp, f, f + pad, f + 2 * pad, red);
+    }
+    __syncthreads();
+  }
+  // the iterate of a level is x after an odd number of sweeps down, else y
+  double* e = base(nlev) + nd_padded(tp->lev[nlev].g);
+  for (int l = nlev - 1; l >= 0; --l) {
+    const NdGeo g = tp->lev[l].g, gc = tp->lev[l + 1].g;
+    const int pad = nd_padded(g);
+    double* const f = base(l);
+    double* x = f + pad;
+    double* y = x + pad;
+    if (tp->nu1 % 2 == 0) {
+      double* const t = x;
+      x = y;
+      y = t;
+    }
+    NdTailNode n;
+    nd_tail_place(n, g, tid);
+    nd_tail_load(n, tp, l);
+    const double fv = n.on ? f[n.c] : 0.0;
+    double v = 0.0;
+    if (n.on) {
+      int ix[2], iy[2], iz[2];
+      double wx[2], wy[2], wz[2];
+      interp1(tid % g.mx, g.per & 1, gc.mx, ix[0], ix[1], wx[0], wx[1]);
+      interp1(tid / g.mx % g.my, g.per & 2, gc.my, iy[0], iy[1], wy[0], wy[1]);
+      interp1(tid / (g.mx * g.my), g.per & 4, gc.mz, iz[0], iz[1], wz[0], wz[1]);
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+          for (int a = 0; a < 2; ++a)
+            v += (wx[a] * wy[b] * wz[c]) * e[pidx(gc, ix[a], iy[b], iz[c])];
+      x[n.c] += v;
+    }
+    __syncthreads();
+    for (int k = 0; k < tp->nu2; ++k) {
+      if (n.on) y[n.c] = x[n.c] + om * (fv - nd_tail_apply(n, x)) / n.w[13];
+      __syncthreads();
+      double* const t = x;
+      x = y;
+      y = t;
+    }
+    e = x;
+  }
+  NdTailNode n;
+  nd_tail_place(n, tp->lev[0].g, tid);
+  if (n.on) nd_global(tp->lev[0].x)[n.c] = e[n.c];
+}
+
 __global__ void __launch_bounds__(256)
     k_nd_maxabs(NdGeo g, const double* __restrict__ v, unsigned long long* norm) {
   const int ux = blockIdx.x * 64 + threadIdx.x;
@@ -976,6 +1381,23 @@ hipError_t nd_launch_interp_add(hipStream_t st, const NdGeo& gf, const NdGeo& gc
   return hipGetLastError();
 }
 
+hipError_t nd_launch_down(hipStream_t st, const NdGeo& g, const NdGeo& gc, const NdStencilC& s,
+                          const double* f, double* x, double* fc, double omega) {
+  const int ntx = (gc.mx + 1) / 2, nty = (gc.my + 1) / 2, ntz = (gc.mz + 1) / 2;
+  hipLaunchKernelGGL((k_nd_down<2, 2, 2>), dim3(ntx * nty * ntz), dim3(256), 0, st, g, gc, ntx, nty,
+                     s, f, x, fc, omega);
+  return hipGetLastError();
+}
+
+hipError_t nd_launch_up(hipStream_t st, const NdGeo& g, const NdGeo& gc, const NdStencilC& s,
+                        const double* f, const double* x, const double* ec, double* out,
+                        double omega) {
+  const int ntx = (g.mx + 3) / 4, nty = (g.my + 3) / 4, ntz = (g.mz + 3) / 4;
+  hipLaunchKernelGGL((k_nd_up<4, 4, 4>), dim3(ntx * nty * ntz), dim3(256), 0, st, g, gc, ntx, nty, s,
+                     f, x, ec, out, omega);
+  return hipGetLastError();
+}
+
 hipError_t nd_launch_fill_ghosts(hipStream_t st, const NdGeo& g, double* a) {
   for (int d = 0; d < 3; ++d) {
     if (!(g.per & (1 << d))) continue;
@@ -1010,6 +1432,27 @@ hipError_t nd_launch_bottom_cg(hipStream_t st, const NdGeo& g, const NdStencilC&
   const long long sz = (long long)g.px * g.py * (g.mz + 2);
   hipLaunchKernelGGL(k_nd_bottom_cg, dim3(1), dim3(1024), 0, st, g, s, rhs, x, work,
                      work + sz, work + 2 * sz, tol, maxit, singular, iters);
+  return hipGetLastError();
+}
+
+int nd_tail_lds(const NdTail& t) {
+  long long el = 0;
+  for (int l = 0; l <= t.nlev; ++l) {
+    const NdGeo& g = t.lev[l].g;
+    if ((long long)g.mx * g.my * g.mz > kNdTailNodes) return -1;
+    el += 3ll * g.px * g.py * (g.mz + 2);
+  }
+  return el * 8 <= 60 * 1024 ? (int)(el * 8) : -1;
+}
+
+hipError_t nd_launch_tail(hipStream_t st, const NdTail& t, const NdTail* dt) {
+  const int lds = nd_tail_lds(t);
+  if (!dt || t.nlev < 0 || t.nlev > kNdTailLevels || lds < 0) return hipErrorInvalidValue;
+  const NdGeo& g = t.lev[0].g;
+  if (g.mx * g.my * g.mz <= 512)
+    hipLaunchKernelGGL(k_nd_tail<512>, dim3(1), dim3(512), lds, st, dt);
+  else
+    hipLaunchKernelGGL(k_nd_tail<1024>, dim3(1), dim3(1024), lds, st, dt);
   return hipGetLastError();
 }
 
