@@ -234,7 +234,7 @@ int plan(mg_nodal* s, Bump& bump) {
     // room for the partial sums of the shallowest launch depth
     NdGeo g1 = g0;
     g1.tz = 1;
-    s->partials = bump.take<double>((size_t)nd_sum_partials_count(g1));
+    s->partials = bump.take<double>((size_t)nd_sum_partials_count(g1) + 8);
   }
   s->d_norm = bump.take<unsigned long long>(3 * (size_t)kNdNormSlot);
   s->d_iters = bump.take<int>(4);
@@ -306,10 +306,11 @@ int fill_ghosts(mg_nodal* s, const NdLevel& lv, double* a) {
 
 // Sweep, residual or apply on level l.
 int sweep(mg_nodal* s, size_t l, const double* phi, const double* f, double* out, int mode,
-          unsigned long long* norm) {
+          unsigned long long* norm, double* dot = nullptr) {
   NdLevel& lv = s->L[l];
   if (l == 0)
-    HIPTRY(nd_launch_sweep0(s->st, lv.g, s->kap, s->sig, phi, f, out, s->omega, mode, norm));
+    HIPTRY(nd_launch_sweep0(s->st, lv.g, s->kap, s->sig, phi, f, out, s->omega, mode, norm,
+                            s->partials, dot));
   else
     HIPTRY(nd_launch_sweep_st(s->st, lv.g, cst(lv.st), phi, f, out, s->omega, mode, norm));
   if (mode != ND_RESID && mode != ND_APPLY) return fill_ghosts(s, lv, out);
@@ -432,8 +433,9 @@ int read_slot(mg_nodal* s, int slot, double* out) {
 }
 
 // z = M r: one finest-level V-cycle from zero on right-hand side r (the
-// Krylov preconditioner).  Returns the level-0 buffer holding z.
-int precond(mg_nodal* s, const double* r, int* zi) {
+// Krylov preconditioner).  Returns the level-0 buffer holding z.  The last sweep
+// leaves r . z in *rz where it can (*has_rz): not if z is changed afterwards.
+int precond(mg_nodal* s, const double* r, int* zi, double* rz, bool* has_rz) {
   NdLevel& l0 = s->L[0];
   int rc;
   int cur = 0;
@@ -448,8 +450,11 @@ int precond(mg_nodal* s, const double* r, int* zi) {
   } else if ((rc = coarse_part(s, l0.x[cur]))) {
     return rc;
   }
+  *has_rz = !s->singular && s->opts.nu2 > 0;
   for (int k = 0; k < s->opts.nu2; ++k) {
-    if ((rc = sweep(s, 0, l0.x[cur], r, l0.x[1 - cur], ND_JACOBI, nullptr))) return rc;
+    if ((rc = sweep(s, 0, l0.x[cur], r, l0.x[1 - cur], ND_JACOBI, nullptr,
+                    *has_rz && k + 1 == s->opts.nu2 ? rz : nullptr)))
+      return rc;
     cur = 1 - cur;
   }
   *zi = cur;
@@ -507,17 +512,17 @@ int solve_pcg(mg_nodal* s, double tol, mg_info_t* inf, double* hist, int* status
       break;
     }
     int zi = 0;
-    if ((rc = precond(s, r, &zi))) return rc;
-    double* z = l0.x[zi];
-    if (s->singular) HIPTRY(nd_launch_remove_mean(s->st, g, z, s->partials));
     double* rho_new = s->d_cg + (it & 1);
     double* rho_old = s->d_cg + ((it + 1) & 1);
-    HIPTRY(nd_launch_dot(s->st, g, r, z, s->partials, rho_new));
+    bool has_rz = false;
+    if ((rc = precond(s, r, &zi, rho_new, &has_rz))) return rc;
+    double* z = l0.x[zi];
+    if (s->singular) HIPTRY(nd_launch_remove_mean(s->st, g, z, s->partials));
+    if (!has_rz) HIPTRY(nd_launch_dot(s->st, g, r, z, s->partials, rho_new));
     HIPTRY(nd_launch_cg_p(s->st, g, p, z, rho_new, rho_old, restart ? 1 : 0));
     if ((rc = fill_ghosts(s, l0, p))) return rc;
     restart = false;
-    if ((rc = sweep(s, 0, p, l0.f, q, ND_APPLY, nullptr))) return rc;
-    HIPTRY(nd_launch_dot(s->st, g, p, q, s->partials, s->d_cg + 2));
+    if ((rc = sweep(s, 0, p, l0.f, q, ND_APPLY, nullptr, s->d_cg + 2))) return rc;
     HIPTRY(nd_launch_fill_u64(s->st, nslot(s, 2), kNdNormSlot, 0ull));
     HIPTRY(nd_launch_cg_xr(s->st, g, x, p, r, q, rho_new, s->d_cg + 2, nslot(s, 2)));
     ++it;

@@ -51,10 +51,12 @@ enum { ND_JACOBI = 0, ND_ZERO = 1, ND_RESID = 2, ND_APPLY = 3 };
 // phi + omega (f - A phi) / diag; ND_ZERO out = omega f / diag (phi not read);
 // ND_RESID out = f - A phi.  norm (nullable): max |f - A phi| folded in as
 // IEEE bits (NaN-propagating), one of kNdNormWays words per work-group;
-// ND_APPLY out = A phi.
+// ND_APPLY out = A phi.  dot (nullable; not with norm): phi . A phi of ND_APPLY,
+// f . out of ND_JACOBI (part: scratch of nd_sum_partials_count + 8 doubles).
 hipError_t nd_launch_sweep0(hipStream_t st, const NdGeo& g, const NdKappa& k, const double* sig,
                             const double* phi, const double* f, double* out, double omega,
-                            int mode, unsigned long long* norm);
+                            int mode, unsigned long long* norm, double* part = nullptr,
+                            double* dot = nullptr);
 // Coarse levels (stored couplings).
 hipError_t nd_launch_sweep_st(hipStream_t st, const NdGeo& g, const NdStencilC& s,
                               const double* phi, const double* f, double* out, double omega,

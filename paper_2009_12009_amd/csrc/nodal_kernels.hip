@@ -152,18 +152,24 @@ __device__ __forceinline__ double lane_of(double v, int lane) {
 // values took 207 accesses of the L1 per row and step, half the time of the
 // pass.  Now 134 MB an array four times in 134 to 139 us at 256^3 (Jacobi; 164
 // before, residual 162 -> 134, apply 141 -> 119), 4 TB/s.
-template <int MODE, bool NORM>
+// DOT: the block's part of phi . A phi (ND_APPLY) or f . out (ND_JACOBI).
+template <int MODE, bool NORM, bool DOT>
 __global__ void __launch_bounds__(256)
     k_nd_sweep0(NdGeo g, NdKappa kap, const double* __restrict__ sig,
                 const double* __restrict__ phi, const double* __restrict__ f,
-                double* __restrict__ out, double omega, unsigned long long* norm) {
+                double* __restrict__ out, double omega, unsigned long long* norm,
+                double* __restrict__ part) {
   int tx, ty, tz;
-  if (!nd_tile(nd_ntx(g), nd_nty(g), nd_ntz(g), tx, ty, tz)) return;  // whole block
+  if (!nd_tile(nd_ntx(g), nd_nty(g), nd_ntz(g), tx, ty, tz)) {  // whole block
+    if (DOT && threadIdx.x == 0 && threadIdx.y == 0) part[blockIdx.x] = 0.0;
+    return;
+  }
   const int lane = threadIdx.x;
   const int ux = tx * 64 + lane;
   const int uy = ty * 4 + threadIdx.y;
   const int z0 = tz * g.tz;
   unsigned long long mx = 0;
+  double dot = 0.0;
   if (uy < g.my && z0 < g.mz) {  // whole wavefronts
     const int z1 = min(z0 + g.tz, g.mz);
     const int sx = g.mx + 1, sy = g.my + 1;  // sigma pitches
@@ -263,10 +269,20 @@ __global__ void __launch_bounds__(256)
         }
         v = MODE == ND_RESID ? r : (MODE == ND_APPLY ? ap : P[1][1][1] + omega * r / diag);
       }
-      if (ux < g.mx) out[pidx(g, ux, uy, uz)] = v;
+      if (ux < g.mx) {
+        out[pidx(g, ux, uy, uz)] = v;
+        if (DOT) dot += MODE == ND_APPLY ? P[1][1][1] * v : fv * v;
+      }
     }
   }
   if (NORM) nd_block_max(mx, norm);
+  if (DOT) {
+    __shared__ double red[4];
+    dot = wave_sum(dot);
+    if (lane == 0) red[threadIdx.y] = dot;
+    __syncthreads();
+    if (lane == 0 && threadIdx.y == 0) part[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
+  }
 }
 
 // Coarse-level sweep (stored couplings), see nd_launch_sweep_st.
@@ -1343,14 +1359,20 @@ dim3 plane_grid_xcd(const NdGeo& g) {
 
 hipError_t nd_launch_sweep0(hipStream_t st, const NdGeo& g, const NdKappa& k, const double* sig,
                             const double* phi, const double* f, double* out, double omega,
-                            int mode, unsigned long long* norm) {
-  const dim3 b(64, 4);
-#define L0(M, N) \
-  hipLaunchKernelGGL((k_nd_sweep0<M, N>), sweep_grid_xcd(g), b, 0, st, g, k, sig, phi, f, out, omega, norm)
-  if (mode == ND_ZERO) L0(ND_ZERO, false);
-  else if (mode == ND_APPLY) L0(ND_APPLY, false);
-  else if (mode == ND_RESID) { if (norm) L0(ND_RESID, true); else L0(ND_RESID, false); }
-  else { if (norm) L0(ND_JACOBI, true); else L0(ND_JACOBI, false); }
+                            int mode, unsigned long long* norm, double* part, double* dot) {
+  const dim3 b(64, 4), gr = sweep_grid_xcd(g);
+#define L0(M, N, D)                                                                            \
+  hipLaunchKernelGGL((k_nd_sweep0<M, N, D>), gr, b, 0, st, g, k, sig, phi, f, out, omega, norm, \
+                     part)
+  if (dot) {
+    if (norm || (mode != ND_APPLY && mode != ND_JACOBI)) return hipErrorInvalidValue;
+    if (mode == ND_APPLY) L0(ND_APPLY, false, true);
+    else L0(ND_JACOBI, false, true);
+    hipLaunchKernelGGL(k_nd_sum_final, dim3(1), dim3(256), 0, st, part, (int)gr.x, dot);
+  } else if (mode == ND_ZERO) L0(ND_ZERO, false, false);
+  else if (mode == ND_APPLY) L0(ND_APPLY, false, false);
+  else if (mode == ND_RESID) { if (norm) L0(ND_RESID, true, false); else L0(ND_RESID, false, false); }
+  else { if (norm) L0(ND_JACOBI, true, false); else L0(ND_JACOBI, false, false); }
 #undef L0
   return hipGetLastError();
 }
