@@ -110,6 +110,10 @@ template <typename T, typename TO>
 hipError_t launch_flat_resid(hipStream_t st, const FlatOp<T>& op, FlatPass ps, const T* v,
                              const T* f, TO* out, unsigned long long* normbits, double* dots);
 int flat_resid_blocks(const FlatDims& d);
+// vn = v + e (vn != v) and out = f - A vn, max |out| as above.
+hipError_t launch_flat_update_resid(hipStream_t st, const FlatOp<double>& op, FlatPass ps,
+                                    const double* v, const float* e, double* vn, const double* f,
+                                    float* out, unsigned long long* normbits);
 
 // Box arrays (ng 0 or 1) <-> the split-colour array, valid cells.
 // lo: low corner of the domain.  normbits (gather): max |value|.
@@ -145,8 +149,6 @@ hipError_t launch_flat_cg_p(hipStream_t st, long long n, double* p, const TZ* z,
 hipError_t launch_flat_cg_xr(hipStream_t st, long long n, double* x, const double* p, double* r,
                              const double* q, const double* num, const double* den,
                              unsigned long long* normbits, float* r32);
-// v += e
-hipError_t launch_flat_update(hipStream_t st, long long n, double* v, const float* e);
 // v -= mean of v over the level's cells (padding untouched); partials and sum
 // as in launch_flat_dot
 hipError_t launch_flat_remove_mean(hipStream_t st, const FlatDims& d, double* v, double* partials,

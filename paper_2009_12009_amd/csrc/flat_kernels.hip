@@ -335,10 +335,16 @@ __global__ void __launch_bounds__(256)
   cf[((I + J + K) & 1) * cd.half + (I >> 1) + cd.sp * (J + cd.ny * K)] = (zs[0] + zs[1]) * T(0.125);
 }
 
-template <typename T, typename TO, int V, bool NT>
+// UPD (the pass of an FP32 correction): vn = v + e, and the residual of vn.  v and
+// e are read at the neighbours too, where the L2 has them, instead of vn
+// written by a pass before: 220 us at 256^3 against 65 + 210 for the two passes
+// (249 with the non-temporal hint: every face serves a cell of each colour, in
+// different rows; 228 with one pair per lane).
+template <typename T, typename TO, int V, bool UPD>
 __global__ void __launch_bounds__(256)
     k_flat_resid(FlatOp<T> op, Grid2 g, const T* __restrict__ v, const T* __restrict__ f,
-                 TO* __restrict__ out, unsigned long long* normbits, double* __restrict__ dots) {
+                 TO* __restrict__ out, unsigned long long* normbits, double* __restrict__ dots,
+                 const float* __restrict__ e, T* __restrict__ vn) {
 #pragma clang fp contract(off)
   if (op.done && *op.done) return;
   const FlatDims& d = op.d;
@@ -358,10 +364,27 @@ __global__ void __launch_bounds__(256)
       TO rv[V];
       Coef<T, V> c;
       Nb<T, V> n;
-      if (f) ldv<T, V, NT>(fv, f + colour * d.half + at);
+      if (f) ldv<T, V, false>(fv, f + colour * d.half + at);
       ldv<T, V, false>(cv, v + colour * d.half + at);
-      load_coef<T, V, NT>(c, op, colour, s, p0, j, k);
+      load_coef<T, V, false>(c, op, colour, s, p0, j, k);
       load_nb<T, V>(n, d, v + (1 - colour) * d.half, s, p0, j, k, rx);
+      if (UPD) {
+        Nb<float, V> ne;
+        float ce[V];
+        ldv<float, V, false>(ce, e + colour * d.half + at);
+        load_nb<float, V>(ne, d, e + (1 - colour) * d.half, s, p0, j, k, rx);
+#pragma unroll
+        for (int u = 0; u < V; ++u) {
+          cv[u] = cv[u] + (T)ce[u];
+          n.o[u] = n.o[u] + (T)ne.o[u];
+          n.s[u] = n.s[u] + (T)ne.s[u];
+          n.yl[u] = n.yl[u] + (T)ne.yl[u];
+          n.yh[u] = n.yh[u] + (T)ne.yh[u];
+          n.zl[u] = n.zl[u] + (T)ne.zl[u];
+          n.zh[u] = n.zh[u] + (T)ne.zh[u];
+        }
+        stv<T, V>(vn + colour * d.half + at, cv, d.np - p0);
+      }
 #pragma unroll
       for (int u = 0; u < V; ++u) {
         const Walls w = walls_of(d, s, p0 + u, j, k);
@@ -936,18 +959,6 @@ __global__ void __launch_bounds__(256)
     if (r32) stv<float, 2>(r32 + e, rs, 2);
   }
   block_max_u64(mx, normbits);
-}
-
-__global__ void __launch_bounds__(256)
-    k_flat_update(long long n, double* __restrict__ v, const float* __restrict__ e) {
-  for (long long i = (blockIdx.x * 256ll + threadIdx.x) * 2; i < n; i += gridDim.x * 512ll) {
-    double a[2];
-    float b[2];
-    ldv<double, 2, false>(a, v + i);
-    ldv<float, 2, false>(b, e + i);
-    for (int u = 0; u < 2; ++u) a[u] += (double)b[u];
-    stv<double, 2>(v + i, a, 2);
-  }
 }
 
 __global__ void __launch_bounds__(256)
@@ -1681,12 +1692,22 @@ template <typename T, typename TO>
 hipError_t launch_flat_resid(hipStream_t st, const FlatOp<T>& op, FlatPass ps, const T* v,
                              const T* f, TO* out, unsigned long long* normbits, double* dots) {
   const Grid2 g = grid_of(op.d.np, op.d.ny * op.d.nz, ps.reverse);
-  if (ps.stream)
-    hipLaunchKernelGGL((k_flat_resid<T, TO, 1, true>), dim3(g.nb), dim3(256), 0, st, op, g, v, f,
-                       out, normbits, dots);
-  else
-    hipLaunchKernelGGL((k_flat_resid<T, TO, 1, false>), dim3(g.nb), dim3(256), 0, st, op, g, v, f,
-                       out, normbits, dots);
+  hipLaunchKernelGGL((k_flat_resid<T, TO, 1, false>), dim3(g.nb), dim3(256), 0, st, op, g, v, f,
+                     out, normbits, dots, (const float*)nullptr, (T*)nullptr);
+  return hipGetLastError();
+}
+
+hipError_t launch_flat_update_resid(hipStream_t st, const FlatOp<double>& op, FlatPass ps,
+                                    const double* v, const float* e, double* vn, const double* f,
+                                    float* out, unsigned long long* normbits) {
+  const int V = flat_width<double>(op.d);
+  const Grid2 g = grid_of((op.d.np + V - 1) / V, op.d.ny * op.d.nz, ps.reverse);
+#define FU(V)                                                                                 \
+  hipLaunchKernelGGL((k_flat_resid<double, float, V, true>), dim3(g.nb), dim3(256), 0, st, op, \
+                     g, v, f, out, normbits, (double*)nullptr, e, vn)
+  if (V == 1) FU(1);
+  else FU(2);
+#undef FU
   return hipGetLastError();
 }
 
@@ -1750,11 +1771,6 @@ hipError_t launch_flat_cg_xr(hipStream_t st, long long n, double* x, const doubl
                              unsigned long long* normbits, float* r32) {
   hipLaunchKernelGGL(k_flat_cg_xr, dim3(vec_blocks(n)), dim3(256), 0, st, n, x, p, r, q, num, den,
                      normbits, r32);
-  return hipGetLastError();
-}
-
-hipError_t launch_flat_update(hipStream_t st, long long n, double* v, const float* e) {
-  hipLaunchKernelGGL(k_flat_update, dim3(vec_blocks(n)), dim3(256), 0, st, n, v, e);
   return hipGetLastError();
 }
 

@@ -214,7 +214,7 @@ struct mg_solver {
   std::vector<FlatLevel<double>> f64;  // FP32 refinement: level 0 only
   std::vector<FlatLevel<float>> f32;
   int flat_tail = -1;  // first level of the one-launch tail (-1: none)
-  double* fphi[2] = {nullptr, nullptr};  // iterates of the folded stop test; FP32: fphi[0]
+  double* fphi[2] = {nullptr, nullptr};  // iterates; preconditioned CG: fphi[0]
   double *fmid = nullptr, *fred = nullptr;  // finest level in blocks: between them, red half
   double* fthird = nullptr;                 // finest level in sweeps: the third array
   double* frhs = nullptr;
@@ -821,6 +821,7 @@ void layout_flat_all(mg_solver* s, Bump& bump) {
   s->frhs = bump.take<double>(n);
   s->fphi[0] = bump.take<double>(n);
   s->fmid = s->fred = s->fthird = nullptr;
+  if (f32 && !s->opts.krylov) s->fphi[1] = bump.take<double>(n);
   if (!f32 && !s->opts.krylov) {
     s->fphi[1] = bump.take<double>(n);
     s->f64[0].march = flat_in_sweeps(s, 0, s->f64[0].stream);
@@ -4096,28 +4097,33 @@ int solve_flat(mg_solver* s, double tol, mg_info_t* inf, double* hist, int* stat
 }
 
 // FP64 residual, one FP32 V-cycle from zero on it, FP64 update.
-int solve_flat_refine(mg_solver* s, double tol, mg_info_t* inf, double* hist, int* status) {
+int solve_flat_refine(mg_solver* s, double tol, mg_info_t* inf, double* hist, int* status,
+                      double** result) {
   const FlatOp<double>& op = s->f64[0].op;
   StopTest stop{s, tol, inf, hist};
   FlatWalk w(s->f64[0].stream);
+  double *x = s->fphi[0], *xn = s->fphi[1];
   int it = 0, rc;
   while (true) {
     HIPTRY(launch_fill_u64(s->st, norm_slot(s, 1), kNormSlot, 0ull));
     {
-      ProfScope ps(s, 1, true);
-      HIPTRY((launch_flat_resid<double, float>(s->st, op, w.next(), s->fphi[0], s->frhs,
-                                               s->f32[0].f, norm_slot(s, 1), nullptr)));
+      ProfScope ps(s, it ? 6 : 1, true);
+      if (it == 0) {
+        HIPTRY((launch_flat_resid<double, float>(s->st, op, w.next(), x, s->frhs, s->f32[0].f,
+                                                 norm_slot(s, 1), nullptr)));
+      } else {
+        HIPTRY(launch_flat_update_resid(s->st, op, w.next(), x, s->f32[0].out(), xn, s->frhs,
+                                        s->f32[0].f, norm_slot(s, 1)));
+        std::swap(x, xn);
+      }
     }
     double rn;
     if ((rc = read_norm(s, 1, &rn))) return rc;
     if (stop(it, rn)) break;
     if ((rc = flat_cycle<float>(s, 0))) return rc;
-    {
-      ProfScope ps(s, 6, true);
-      HIPTRY(launch_flat_update(s->st, 2ll * op.d.half, s->fphi[0], s->f32[0].out()));
-    }
     ++it;
   }
+  *result = x;
   *status = stop.status;
   inf->iters = it;
   inf->abs_resid = stop.rn;
@@ -4266,7 +4272,7 @@ int mg_solve(mg_solver_t* s, mg_multifab_t* phi, const mg_multifab_t* rhs, doubl
     if (s->opts.krylov)
       rc = solve_flat_pcg(s, tol, &inf, resid_history, &status);
     else if (f32)
-      rc = solve_flat_refine(s, tol, &inf, resid_history, &status);
+      rc = solve_flat_refine(s, tol, &inf, resid_history, &status, &x);
     else
       rc = solve_flat(s, tol, &inf, resid_history, &status, &x);
     if (rc) return rc;
