@@ -1542,9 +1542,18 @@ __global__ void __launch_bounds__(256)
   const long long fst[3] = {1, ffx, (long long)ffx * ffy};
   for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < total;
        e += (long long)gridDim.x * blockDim.x) {
-    const int a = e % nxc;
-    const int b = (e / nxc) % nyc;
-    const int c = e / ((long long)nxc * nyc);
+    // divisions in 64 bits would be most of the pass
+    int a, b, c;
+    if (total < (1ll << 31)) {
+      const int i = (int)e, row = i / nxc;
+      a = i - row * nxc;
+      c = row / nyc;
+      b = row - c * nyc;
+    } else {
+      a = e % nxc;
+      b = (e / nxc) % nyc;
+      c = e / ((long long)nxc * nyc);
+    }
     const int cl[3] = {a, b, c};  // relative to clo
     int fl[3];
     for (int q = 0; q < 3; ++q) fl[q] = 2 * (clo[q] + cl[q]) - F.lo[q];
@@ -2973,7 +2982,7 @@ hipError_t launch_coarsen_face(hipStream_t st, const BoxInfo* fine, int nbox_fin
                                const BoxInfo* coarse, int d, const double* bf, double* bc,
                                int max_faces_per_box) {
   if (nbox_fine <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_coarsen_face, dim3(grid_for(max_faces_per_box), nbox_fine), dim3(256), 0,
+  hipLaunchKernelGGL(k_coarsen_face, dim3(grid_for(max_faces_per_box / 4), nbox_fine), dim3(256), 0,
                      st, fine, coarse, d, bf, bc);
   return hipGetLastError();
 }
