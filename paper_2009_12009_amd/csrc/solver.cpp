@@ -273,6 +273,9 @@ struct mg_solver {
   CfFace* d_cfface = nullptr;
   double *Rc = nullptr, *ef = nullptr, *Rf = nullptr, *rf2 = nullptr;
   // FP32 correction of the composite solve (precision MG_PREC_F32_REFINE)
+  // (split-colour layout) coarse correction before the coarse V-cycle: the fine
+  // one's means on covered cells, 0 on the others for good
+  char* cezero = nullptr;
   float *Rc32 = nullptr, *ef32 = nullptr, *Rf32 = nullptr, *rf2_32 = nullptr;
   // flexible GMRES of the composite solve (krylov = 1): restart length,
   // basis (m+1 ghost-free pairs), preconditioned directions (m pairs, ng 1),
@@ -814,6 +817,7 @@ void layout_flat_all(mg_solver* s, Bump& bump) {
     if (f32) layout_flat<float>(s, l, true, bump);
   }
   if (s->composite) {
+    s->cezero = bump.take<char>((f32 ? 4 : 8) * s->L[0].n_g1);
     finish_layout_flat(s, from, bump);
     return;
   }
@@ -3237,7 +3241,8 @@ int composite_residual(mg_solver* s, T* phic, T* phif, const T* fc, int fc_ng, c
                                 ff_ng, Rf, normbits, 0)));
   if (corr) {
     if (fc_ng != 0) return fail(MG_ERR_ARG, "composite correction: right-hand side with ghosts");
-    HIPTRY(hipMemcpyAsync(Rc, fc, sizeof(T) * L0.n_g0, hipMemcpyDeviceToDevice, s->st));
+    if (Rc != fc)
+      HIPTRY(hipMemcpyAsync(Rc, fc, sizeof(T) * L0.n_g0, hipMemcpyDeviceToDevice, s->st));
   } else {
     HIPTRY((launch_residual<T, T>(s->st, L0.d_cell, (int)L0.t_cell.size(), L0.s_cell, opc, phic,
                                   fc, fc_ng, Rc, nullptr, 0)));
@@ -3277,16 +3282,17 @@ int fine_sweeps(mg_solver* s, T* ef, T* ec, const T* rhs, int sweeps) {
   return MG_OK;
 }
 
-// One V-cycle from zero on the whole coarse level: rhs -> e (valid cells).
+// One V-cycle from zero on the whole coarse level: rhs (the level's own unless
+// s->flat) -> e (valid cells).
 template <typename T>
-int coarse_correction(mg_solver* s) {
+int coarse_correction(mg_solver* s, const T* rhs) {
   constexpr bool f32 = sizeof(T) == 4;
   if (!s->flat) return coarse_cycle<T>(s, 0, f32);
   Level& L0 = s->L[0];
   const LevelData<T> D = ldata<T>(L0, f32);
   FlatLevel<T>& v = flat_levels<T>(s)[0];
   int rc;
-  HIPTRY(launch_flat_gather<T>(s->st, L0.d_info, L0.nbox, L0.max_faces, L0.domain.lo, v.op.d, D.rhs,
+  HIPTRY(launch_flat_gather<T>(s->st, L0.d_info, L0.nbox, L0.max_faces, L0.domain.lo, v.op.d, rhs,
                                0, v.f, nullptr));
   if ((rc = flat_cycle<T>(s, 0))) return rc;
   HIPTRY(launch_flat_scatter<T>(s->st, L0.d_info, L0.nbox, L0.max_faces, L0.domain.lo, v.op.d,
@@ -3304,38 +3310,45 @@ int correction_core32(mg_solver* s, const double* vc, const double* vf) {
   HIPTRY((launch_convert<double, float>(s->st, vf, s->Rf32, F.n_g0)));
   HIPTRY(launch_zero_valid<float>(s->st, F.d_cell, (int)F.t_cell.size(), F.s_cell, F.d_info,
                                   s->ef32, 1));
-  HIPTRY(launch_zero_valid<float>(s->st, L0.d_cell, (int)L0.t_cell.size(), L0.s_cell, L0.d_info,
-                                  L0.e32, 1));
-  if ((rc = fine_sweeps<float>(s, s->ef32, L0.e32, s->Rf32, 2 * s->opts.nu1))) return rc;
-  if ((rc = composite_residual<float>(s, L0.e32, s->ef32, s->Rc32, 0, s->Rf32, 0, L0.rhs32,
-                                      s->rf2_32, nullptr, s->rf2_32)))
+  float* const e0 = s->flat ? (float*)s->cezero : L0.e32;
+  float* const rhs = s->flat ? s->Rc32 : L0.rhs32;
+  if (!s->flat)
+    HIPTRY(launch_zero_valid<float>(s->st, L0.d_cell, (int)L0.t_cell.size(), L0.s_cell, L0.d_info,
+                                    L0.e32, 1));
+  if ((rc = fine_sweeps<float>(s, s->ef32, e0, s->Rf32, 2 * s->opts.nu1))) return rc;
+  if ((rc = composite_residual<float>(s, e0, s->ef32, s->Rc32, 0, s->Rf32, 0, rhs, s->rf2_32,
+                                      nullptr, s->rf2_32)))
     return rc;
-  if ((rc = coarse_correction<float>(s))) return rc;
+  if ((rc = coarse_correction<float>(s, rhs))) return rc;
   HIPTRY(launch_prolong_add<float>(s->st, F.d_cell, (int)F.t_cell.size(), F.s_cell, F.d_info,
                                    L0.d_info, s->ef32, L0.e32));
   return fine_sweeps<float>(s, s->ef32, L0.e32, s->Rf32, 2 * s->opts.nu2);
 }
 
-// The same in FP64: result in ef (fine, ng 1) and L0.e64 (coarse).
-int correction_core64(mg_solver* s, const double* vc, const double* vf, double* ef) {
+// The same in FP64: result in ef (fine, ng 1) and L0.e64 (coarse).  rhs: where
+// the coarse V-cycle's right-hand side goes, vc itself (s->flat only) or
+// L0.rhs64.
+int correction_core64(mg_solver* s, const double* vc, const double* vf, double* ef,
+                      double* rhs) {
   Level& L0 = s->L[0];
   Level& F = s->F;
   int rc;
   HIPTRY(launch_zero_valid<double>(s->st, F.d_cell, (int)F.t_cell.size(), F.s_cell, F.d_info, ef,
                                    1));
-  HIPTRY(launch_zero_valid<double>(s->st, L0.d_cell, (int)L0.t_cell.size(), L0.s_cell, L0.d_info,
-                                   L0.e64, 1));
+  double* const e0 = s->flat ? (double*)s->cezero : L0.e64;
+  if (!s->flat)
+    HIPTRY(launch_zero_valid<double>(s->st, L0.d_cell, (int)L0.t_cell.size(), L0.s_cell,
+                                     L0.d_info, L0.e64, 1));
   // the fine level gets twice the sweeps of the coarse V-cycle on each side: it
   // is a small share of the cells, and two sweeps leave its error decaying at
   // about 0.5 per correction against about 0.35 with four
-  if ((rc = fine_sweeps<double>(s, ef, L0.e64, vf, 2 * s->opts.nu1))) return rc;
+  if ((rc = fine_sweeps<double>(s, ef, e0, vf, 2 * s->opts.nu1))) return rc;
   // residual the fine correction leaves: fine part into rf2, coarse part into
-  // L0.rhs64 with covered cells = mean of rf2's children
-  if ((rc = composite_residual<double>(s, L0.e64, ef, vc, 0, vf, 0, L0.rhs64, s->rf2, nullptr,
-                                       s->rf2)))
+  // rhs with covered cells = mean of rf2's children
+  if ((rc = composite_residual<double>(s, e0, ef, vc, 0, vf, 0, rhs, s->rf2, nullptr, s->rf2)))
     return rc;
   // one coarse V-cycle from zero on the whole coarse level
-  if ((rc = coarse_correction<double>(s))) return rc;
+  if ((rc = coarse_correction<double>(s, rhs))) return rc;
   HIPTRY(launch_prolong_add<double>(s->st, F.d_cell, (int)F.t_cell.size(), F.s_cell, F.d_info,
                                     L0.d_info, ef, L0.e64));
   return fine_sweeps<double>(s, ef, L0.e64, vf, 2 * s->opts.nu2);
@@ -3354,7 +3367,7 @@ int composite_correction(mg_solver* s, double* phic, double* phif) {
     HIPTRY(launch_update(s->st, L0.d_cell, (int)L0.t_cell.size(), L0.s_cell, L0.d_info, phic,
                          L0.e32));
   } else {
-    if ((rc = correction_core64(s, s->Rc, s->Rf, s->ef))) return rc;
+    if ((rc = correction_core64(s, s->Rc, s->Rf, s->ef, s->flat ? s->Rc : L0.rhs64))) return rc;
     HIPTRY(launch_axpy_valid(s->st, F.d_cell, (int)F.t_cell.size(), F.s_cell, F.d_info, phif,
                              s->ef));
     HIPTRY(launch_axpy_valid(s->st, L0.d_cell, (int)L0.t_cell.size(), L0.s_cell, L0.d_info, phic,
@@ -3444,7 +3457,7 @@ int solve_amr_fgmres(mg_solver* s, double* Pc, double* Pf, const double* Fc, int
         HIPTRY((launch_convert<float, double>(s->st, s->ef32, Zfj, F.n_g1)));
         HIPTRY((launch_convert<float, double>(s->st, L0.e32, Zcj, L0.n_g1)));
       } else {
-        if ((rc = correction_core64(s, Vcj, Vfj, Zfj))) return rc;
+        if ((rc = correction_core64(s, Vcj, Vfj, Zfj, L0.rhs64))) return rc;
         HIPTRY(hipMemcpyAsync(Zcj, L0.e64, sizeof(double) * L0.n_g1, hipMemcpyDeviceToDevice,
                               s->st));
       }
