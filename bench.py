@@ -62,13 +62,13 @@ def parse():
 
 
 ROOT = os.path.dirname(os.path.abspath(__file__))
-TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "hbm_traffic_gsrb_abec256_lognormal_64boxes.md")
+TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "hbm_traffic_flat_sweep_abec256_lognormal_64boxes.md")
 
 
 def kernel_source_sha256():
     import hashlib
     h = hashlib.sha256()
-    for f in ("kernels.hip", "kernels.hpp", "tables.hpp"):
+    for f in ("flat_kernels.hip", "flat.hpp", "tables.hpp"):
         with open(os.path.join(ROOT, "paper_2009_12009_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()
@@ -81,7 +81,7 @@ def _classes_key(classes):
 
 
 def measured_traffic(kernel, shape, classes=None):
-    """HBM bytes per launch of the level-0 half-sweep from the committed counter
+    """HBM bytes per launch of the level-0 sweep from the committed counter
     summary (FETCH_SIZE and WRITE_SIZE scaled by a plain copy's readings), or
     None when the summary is missing, was taken on other kernel sources, or holds
     no block for this kernel, launch shape and per-class tile table (a block
@@ -231,7 +231,10 @@ def main():
         tot, cnt = s.kernel_stats(P._lib.FAM_SMOOTH)
         word = 4 if k.startswith("f32") else 8
         mean_ms = tot / max(cnt, 1)
-        alg_bytes = 6 * word * ncell  # phi in, phi out, f, b_x, b_y, b_z
+        # one whole sweep: phi of the other colour in, phi out, f, b_x, b_y, b_z; the
+        # FP64 V-cycle's launches of this family all read phi, of the other variants'
+        # three a cycle one starts from zero
+        alg_bytes = word * ncell * (5.5 if k == "f64" else 16.0 / 3.0)
         gs[k] = dict(mean_ms=mean_ms, launches=cnt, bytes=alg_bytes,
                      gbps=alg_bytes / (mean_ms * 1e-3) / 1e9 if cnt else None)
         fam = {}
@@ -254,7 +257,8 @@ def main():
     # the stand-alone smoother timing below sweeps the FP64 solver's phi in place)
     sols = {k: W.gather_cells(phis[k].valid_numpy(), boxes, n) for k in solvers}
 
-    # the level-0 FP64 half-sweep launched alone, without ghost write-through
+    # the box form's level-0 FP64 half-sweep launched alone, without ghost
+    # write-through (the fine level of composite solves, hierarchies of one level)
     ms_alone = solvers["f64"].time_smoother(phis["f64"], rhs, reps=20)
     smoother_alone = {"mean_ms": ms_alone, "gbps": 6 * 8 * ncell / (ms_alone * 1e-3) / 1e9}
 
@@ -314,12 +318,9 @@ def main():
         "smoother_alone_f64": smoother_alone,
     }
     g64 = gs["f64"]
-    kname = ("k_sweep<double> level 0, one fused red+black sweep (64 boxes of 64^3)"
-             if g64["fused"] else
-             "k_gsrb<double> level 0, one half-sweep with face-ghost write-through "
-             "(64 boxes of 64^3)")
-    traffic = None if g64["fused"] else measured_traffic(
-        "k_gsrb<double>", g64["tile_shapes"]["smoother"], g64["tile_shapes"]["smoother_classes"])
+    kname = ("k_flat_march<double> level 0, one red+black sweep of the split-colour layout "
+             "per launch (256^3 cells)")
+    traffic = measured_traffic("k_flat_march<double>", (0,))
     result["roofline"] = {
         "bound": "hbm",
         "achieved": g64["gbps"],

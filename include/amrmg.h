@@ -200,7 +200,8 @@ typedef struct {
 typedef struct {
   int32_t iters;               /* V-cycles done                                 */
   int32_t nlevels;             /* multigrid levels                              */
-  int32_t bottom_iters;        /* CG iterations of the last bottom solve        */
+  int32_t bottom_iters;        /* CG iterations of the last bottom solve (of the
+                                * preconditioned CG on large bottoms)           */
   int32_t converged;           /* 1 when the tolerance was met                  */
   double rel_resid;            /* max|f - A phi| / max|f| at return            */
   double abs_resid;            /* max|f - A phi| at return                      */

@@ -423,10 +423,12 @@ __global__ void __launch_bounds__(256)
 // are recomputed by every work-group that needs them; results go to another
 // array, because neighbours still read the input.  Coefficients of plane k + 1
 // are loaded while plane k is computed.
-// 256^3 FP64: 172 us against 2 x 113 for half-sweeps.  Bound by what the rims add:
-// 852 MB fetched where the input is 604 (neighbouring work-groups drift more
-// planes apart than an L2 holds); cached loads throughout, since the
-// non-temporal hint on the read-once arrays loses the rims as well (185-200 us).
+// 256^3 FP64: 172 us against 2 x 113 for half-sweeps, 650 MB fetched and 134
+// written (the arrays are 604 and 134): 4.6 TB/s where a copy reaches 6.2.  What
+// is left is the rims, 1.41 of a work-group's loads, and a barrier per plane;
+// smaller work-groups, two to a CU, have larger rims (512 lanes, 32 pairs: 198
+// us).  Cached loads throughout, since the non-temporal hint on the read-once
+// arrays loses the rims as well (185-200 us).
 // FP32 93 us against 2 x 52.
 struct March {
   int ox, oy;        // pairs and rows a work-group writes
