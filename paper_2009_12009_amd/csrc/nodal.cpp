@@ -99,6 +99,7 @@ struct mg_nodal {
   int* d_iters = nullptr;
   int tail = -1;  // first level of the one-launch tail (-1: none)
   NdTail* d_tail = nullptr;
+  NdTail h_tail{};
   unsigned long long* d_norm = nullptr;  // 3 slots
   size_t ws_need = 0;
   hipStream_t user = nullptr, st = nullptr;
@@ -702,16 +703,11 @@ int mg_nodal_create(const mg_box_t* boxes, int32_t nbox, const mg_geom_t* geom,
       if (s->opts.verbose)
         fprintf(stderr, "amrmg nodal tune: finest sweep %d planes, %.4f ms\n", btz, best / 6);
     }
-    // the tail's device plan, through pinned staging
+    // the tail's device plan
     s->tail = tail_level(s.get());
     if (s->tail > 0) {
-      NdTail* h = nullptr;
-      HIPTRY(hipHostMalloc((void**)&h, sizeof(NdTail), hipHostMallocDefault));
-      *h = tail_args(s.get(), s->tail);
-      hipError_t e = hipMemcpyAsync(s->d_tail, h, sizeof(NdTail), hipMemcpyHostToDevice, s->st);
-      if (e == hipSuccess) e = hipStreamSynchronize(s->st);
-      hipHostFree(h);
-      HIPTRY(e);
+      s->h_tail = tail_args(s.get(), s->tail);
+      HIPTRY(hipMemcpyAsync(s->d_tail, &s->h_tail, sizeof(NdTail), hipMemcpyHostToDevice, s->st));
     }
     // the coarse part of the cycle as a graph, one per level-0 buffer it
     // interpolates into

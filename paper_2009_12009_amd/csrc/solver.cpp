@@ -223,6 +223,7 @@ struct mg_solver {
   std::vector<int> h_fmap_rhs, h_fmap_out;
   int *d_fmap_rhs = nullptr, *d_fmap_out = nullptr;
   char* d_ftail = nullptr;  // FlatTail of the solver's precision
+  std::vector<char> h_ftail;
   // Deep bottom (deep_plan): coarsenings of the bottom level (0: CG on the bottom
   // alone), every level's extents and the cells added to them.  The level vectors go on past
   // the bottom: [L.size()] its operator, the cycle's right-hand side (the
@@ -1735,17 +1736,13 @@ FlatTail<T> flat_tail_args(mg_solver* s) {
   return t;
 }
 
-// The tail's device plan, through pinned staging (the operators' alpha is set
-// with the first coefficients and never changes).
+// The tail's device plan (the operators' alpha is set with the first coefficients
+// and never changes).
 template <typename T>
 int upload_flat_tail(mg_solver* s) {
-  FlatTail<T>* h = nullptr;
-  HIPTRY(hipHostMalloc((void**)&h, sizeof(FlatTail<T>), hipHostMallocDefault));
-  *h = flat_tail_args<T>(s);
-  hipError_t e = hipMemcpyAsync(s->d_ftail, h, sizeof(FlatTail<T>), hipMemcpyHostToDevice, s->st);
-  if (e == hipSuccess) e = hipStreamSynchronize(s->st);
-  hipHostFree(h);
-  HIPTRY(e);
+  const FlatTail<T> t = flat_tail_args<T>(s);
+  s->h_ftail.assign((const char*)&t, (const char*)&t + sizeof(t));
+  HIPTRY(hipMemcpyAsync(s->d_ftail, s->h_ftail.data(), sizeof(t), hipMemcpyHostToDevice, s->st));
   return MG_OK;
 }
 
