@@ -220,8 +220,8 @@ struct mg_solver {
   double* frhs = nullptr;
   double *fr = nullptr, *fp = nullptr, *fq = nullptr, *fz = nullptr;  // preconditioned CG
   double* fpart = nullptr;
-  std::vector<int> h_fmap_rhs, h_fmap_out;
-  int *d_fmap_rhs = nullptr, *d_fmap_out = nullptr;
+  std::vector<int> h_fmap;  // the bottom's cells: elements of its f and e
+  int* d_fmap = nullptr;
   char* d_ftail = nullptr;  // FlatTail of the solver's precision
   std::vector<char> h_ftail;
   // Deep bottom (deep_plan): coarsenings of the bottom level (0: CG on the bottom
@@ -790,8 +790,7 @@ void finish_layout_flat(mg_solver* s, size_t from, Bump& bump) {
     s->d_dnbr = bump.take<int>(s->h_dnbr.size());
     s->d_dmap = bump.take<int>(s->h_dmap.size());
   }
-  s->d_fmap_rhs = bump.take<int>(s->nb);
-  s->d_fmap_out = s->d_fmap_rhs;  // same layout of both
+  s->d_fmap = bump.take<int>(s->nb);
   s->d_ftail = s->flat_tail > 0 ? bump.take<char>(sizeof(FlatTail<double>)) : nullptr;
 }
 
@@ -1099,7 +1098,7 @@ int build_plan(mg_solver* s, const std::vector<IBox>& boxes, Bump& bump) {
   s->h_aidx.assign(nb, 0);
   s->h_map_rhs.assign(nb, 0);
   s->h_map_out.assign(nb, 0);
-  s->h_fmap_rhs.assign(s->flat ? nb : 0, 0);
+  s->h_fmap.assign(s->flat ? nb : 0, 0);
   FlatDims fb{};
   {
     const IBox& D = bl.domain;
@@ -1143,7 +1142,7 @@ int build_plan(mg_solver* s, const std::vector<IBox>& boxes, Bump& bump) {
                 (int)(I.off_g1 + (il + 1) + (int64_t)(nx + 2) * ((jl + 1) + (int64_t)(ny + 2) * (kl + 1)));
             if (s->flat) {
               const int I = i - D.lo[0], J = j - D.lo[1], K = k - D.lo[2];
-              s->h_fmap_rhs[c] = ((I + J + K) & 1) * fb.half + (I >> 1) + fb.sp * (J + fb.ny * K);
+              s->h_fmap[c] = ((I + J + K) & 1) * fb.half + (I >> 1) + fb.sp * (J + fb.ny * K);
             }
             const int p[3] = {i, j, k};
             const int loc[3] = {il, jl, kl};
@@ -1398,8 +1397,8 @@ int setup_coefficients(mg_solver* s, const mg_multifab_t* acoef, const mg_multif
 // The bottom's tables with the split-colour layout's element maps.
 BottomTables flat_bottom_tables(const mg_solver* s) {
   BottomTables bt = bottom_tables(s);
-  bt.map_rhs = s->d_fmap_rhs;
-  bt.map_out = s->d_fmap_out;
+  bt.map_rhs = s->d_fmap;
+  bt.map_out = s->d_fmap;
   return bt;
 }
 
@@ -2906,7 +2905,7 @@ int upload_tables(mg_solver* s) {
       HIPTRY(hipMemcpyAsync(s->d_dmap, s->h_dmap.data(), sizeof(int) * s->h_dmap.size(),
                             hipMemcpyHostToDevice, s->st));
     }
-    HIPTRY(hipMemcpyAsync(s->d_fmap_rhs, s->h_fmap_rhs.data(), sizeof(int) * nb,
+    HIPTRY(hipMemcpyAsync(s->d_fmap, s->h_fmap.data(), sizeof(int) * nb,
                           hipMemcpyHostToDevice, s->st));
   }
   if (s->d_perm)
