@@ -141,13 +141,14 @@ constexpr int kFlatDotBlocks = 1024;
 template <typename TZ>
 hipError_t launch_flat_dot(hipStream_t st, long long n, const double* a, const TZ* z,
                            double* partials, double* out);
-// p = z (first) or z + (*num / *den) p
+// p = z (first) or z + (*num / *den) p; padding stays 0
 template <typename TZ>
-hipError_t launch_flat_cg_p(hipStream_t st, long long n, double* p, const TZ* z,
+hipError_t launch_flat_cg_p(hipStream_t st, const FlatDims& d, double* p, const TZ* z,
                             const double* num, const double* den, int first);
-// x += al p, r -= al q, al = *num / *den; max |r|; r32 (nullable) = r rounded
-hipError_t launch_flat_cg_xr(hipStream_t st, long long n, double* x, const double* p, double* r,
-                             const double* q, const double* num, const double* den,
+// x += al p, r -= al q, al = *num / *den; max |r|; r32 (nullable) = r rounded;
+// padding stays 0
+hipError_t launch_flat_cg_xr(hipStream_t st, const FlatDims& d, double* x, const double* p,
+                             double* r, const double* q, const double* num, const double* den,
                              unsigned long long* normbits, float* r32);
 // v -= mean of v over the level's cells (padding untouched); partials and sum
 // as in launch_flat_dot

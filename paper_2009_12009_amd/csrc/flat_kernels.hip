@@ -899,7 +899,14 @@ __global__ void __launch_bounds__(256)
 
 // ---------------------------------------------------------------------------
 // Vectors: both halves of an array as one run of n elements (a multiple of 4),
-// padding included.
+// padding included.  The padding is 0 for good: no gather, sweep or residual
+// writes it and the sums below read it, so what a solve that fails leaves there
+// would fail every later one.  A finite factor times 0 keeps it; where the
+// factor is not finite (a uniform branch) the update skips it.
+__device__ __forceinline__ bool is_cell(const FlatDims& d, long long e) {
+  if (e >= d.half) e -= d.half;
+  return e < (long long)d.sp * d.ny * d.nz && (int)e % d.sp < d.np;
+}
 
 template <typename TZ>
 __global__ void __launch_bounds__(256)
@@ -923,24 +930,30 @@ __global__ void __launch_bounds__(256)
 
 template <typename TZ>
 __global__ void __launch_bounds__(256)
-    k_flat_cg_p(long long n, double* __restrict__ p, const TZ* __restrict__ z, const double* num,
+    k_flat_cg_p(FlatDims d, double* __restrict__ p, const TZ* __restrict__ z, const double* num,
                 const double* den, int first) {
+  const long long n = 2ll * d.half;
   const double be = first ? 0.0 : *num / *den;
+  const bool all = isfinite(be);
   for (long long e = (blockIdx.x * 256ll + threadIdx.x) * 2; e < n; e += gridDim.x * 512ll) {
     TZ zv[2];
     double pv[2] = {0.0, 0.0};
     ldv<TZ, 2, false>(zv, z + e);
     if (!first) ldv<double, 2, false>(pv, p + e);
-    for (int v = 0; v < 2; ++v) pv[v] = first ? (double)zv[v] : (double)zv[v] + be * pv[v];
+    for (int v = 0; v < 2; ++v)
+      if (all || is_cell(d, e + v))
+        pv[v] = first ? (double)zv[v] : (double)zv[v] + be * pv[v];
     stv<double, 2>(p + e, pv, 2);
   }
 }
 
 __global__ void __launch_bounds__(256)
-    k_flat_cg_xr(long long n, double* __restrict__ x, const double* __restrict__ p,
+    k_flat_cg_xr(FlatDims d, double* __restrict__ x, const double* __restrict__ p,
                  double* __restrict__ r, const double* __restrict__ q, const double* num,
                  const double* den, unsigned long long* normbits, float* __restrict__ r32) {
+  const long long n = 2ll * d.half;
   const double al = *num / *den;
+  const bool all = isfinite(al);
   unsigned long long mx = 0;
   for (long long e = (blockIdx.x * 256ll + threadIdx.x) * 2; e < n; e += gridDim.x * 512ll) {
     double xv[2], pv[2], rv[2], qv[2];
@@ -950,8 +963,10 @@ __global__ void __launch_bounds__(256)
     ldv<double, 2, false>(qv, q + e);
     float rs[2];
     for (int v = 0; v < 2; ++v) {
-      xv[v] += al * pv[v];
-      rv[v] -= al * qv[v];
+      if (all || is_cell(d, e + v)) {
+        xv[v] += al * pv[v];
+        rv[v] -= al * qv[v];
+      }
       rs[v] = (float)rv[v];
       const unsigned long long bits = absbits(rv[v]);
       mx = bits > mx ? bits : mx;
@@ -1761,18 +1776,18 @@ hipError_t launch_flat_dot(hipStream_t st, long long n, const double* a, const T
 }
 
 template <typename TZ>
-hipError_t launch_flat_cg_p(hipStream_t st, long long n, double* p, const TZ* z,
+hipError_t launch_flat_cg_p(hipStream_t st, const FlatDims& d, double* p, const TZ* z,
                             const double* num, const double* den, int first) {
-  hipLaunchKernelGGL((k_flat_cg_p<TZ>), dim3(vec_blocks(n)), dim3(256), 0, st, n, p, z, num, den,
-                     first);
+  hipLaunchKernelGGL((k_flat_cg_p<TZ>), dim3(vec_blocks(2ll * d.half)), dim3(256), 0, st, d, p, z,
+                     num, den, first);
   return hipGetLastError();
 }
 
-hipError_t launch_flat_cg_xr(hipStream_t st, long long n, double* x, const double* p, double* r,
-                             const double* q, const double* num, const double* den,
+hipError_t launch_flat_cg_xr(hipStream_t st, const FlatDims& d, double* x, const double* p,
+                             double* r, const double* q, const double* num, const double* den,
                              unsigned long long* normbits, float* r32) {
-  hipLaunchKernelGGL(k_flat_cg_xr, dim3(vec_blocks(n)), dim3(256), 0, st, n, x, p, r, q, num, den,
-                     normbits, r32);
+  hipLaunchKernelGGL(k_flat_cg_xr, dim3(vec_blocks(2ll * d.half)), dim3(256), 0, st, d, x, p, r, q,
+                     num, den, normbits, r32);
   return hipGetLastError();
 }
 
@@ -1919,7 +1934,7 @@ hipError_t launch_deep_xr(hipStream_t st, long long n, T* x, const T* p, T* r, c
                                            const FlatDims&, const T*, T, T*);                      \
   template hipError_t launch_flat_dot<T>(hipStream_t, long long, const double*, const T*, double*, \
                                          double*);                                                 \
-  template hipError_t launch_flat_cg_p<T>(hipStream_t, long long, double*, const T*,               \
+  template hipError_t launch_flat_cg_p<T>(hipStream_t, const FlatDims&, double*, const T*,         \
                                           const double*, const double*, int);                      \
   template hipError_t launch_flat_sweep<T>(hipStream_t, const FlatOp<T>&, const T*, T*, const T*,  \
                                            int, bool, const FlatDims*, const T*, const T*,         \

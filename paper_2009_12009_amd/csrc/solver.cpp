@@ -4201,13 +4201,13 @@ int solve_flat_pcg(mg_solver* s, double tol, mg_info_t* inf, double* hist, int* 
       ProfScope ps(s, 6, true);
       if (f32 && !s->singular) {
         HIPTRY(launch_flat_dot<float>(s->st, n, r, s->f32[0].out(), s->fpart, rho_new));
-        HIPTRY(launch_flat_cg_p<float>(s->st, n, p, s->f32[0].out(), rho_new, rho_old, restart));
+        HIPTRY(launch_flat_cg_p<float>(s->st, op.d, p, s->f32[0].out(), rho_new, rho_old, restart));
       } else {
         if (f32) HIPTRY((launch_convert<float, double>(s->st, s->f32[0].out(), s->fz, n)));
         if (s->singular)
           HIPTRY(launch_flat_remove_mean(s->st, op.d, s->fz, s->fpart, s->d_sum));
         HIPTRY(launch_flat_dot<double>(s->st, n, r, s->fz, s->fpart, rho_new));
-        HIPTRY(launch_flat_cg_p<double>(s->st, n, p, s->fz, rho_new, rho_old, restart));
+        HIPTRY(launch_flat_cg_p<double>(s->st, op.d, p, s->fz, rho_new, rho_old, restart));
       }
     }
     restart = false;
@@ -4220,7 +4220,7 @@ int solve_flat_pcg(mg_solver* s, double tol, mg_info_t* inf, double* hist, int* 
       ProfScope ps(s, 6, true);
       HIPTRY(launch_sum_final(s->st, s->fpart, flat_resid_blocks(op.d), s->d_cg + 2));
       HIPTRY(launch_fill_u64(s->st, norm_slot(s, 2), kNormSlot, 0ull));
-      HIPTRY(launch_flat_cg_xr(s->st, n, x, p, r, q, rho_new, s->d_cg + 2, norm_slot(s, 2),
+      HIPTRY(launch_flat_cg_xr(s->st, op.d, x, p, r, q, rho_new, s->d_cg + 2, norm_slot(s, 2),
                                f32 ? s->f32[0].f : nullptr));
       r32_current = f32;
     }
