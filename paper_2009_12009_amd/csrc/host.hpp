@@ -88,6 +88,18 @@ struct LevelBoxes {
 std::vector<LevelBoxes> hierarchy(const std::vector<IBox>& boxes, const IBox& domain,
                                   int min_bottom_edge, bool aggregate);
 
+// The first level of a tail: of the levels from `lo` on (cells: cell counts of all
+// levels, the last the tail's bottom), as many above the bottom as hold at most
+// `limit` cells each, at most max_levels (the tail's tables have no more); -1 if
+// there is none.
+inline int first_tail_level(const std::vector<long long>& cells, int lo, long long limit,
+                            int max_levels) {
+  const int bottom = (int)cells.size() - 1;
+  int start = bottom;
+  while (start > lo && bottom - start < max_levels && cells[start - 1] <= limit) --start;
+  return start < bottom ? start : -1;
+}
+
 // Thread-local error message used by mg_last_error.
 void set_error(const std::string& msg);
 const char* last_error();

@@ -704,20 +704,13 @@ bool flat_smoothed(const mg_solver* s, size_t l) {
 // kTailMaxBottom cells hold at most opts.coarse_tail cells each.
 int flat_tail_level(const mg_solver* s) {
   const int nl = (int)s->L.size();
-  if (s->deep) {
-    // the same rule on the bottom's coarsenings
-    int start = nl + s->deep;
-    while (start > nl + 1 && flat_cells(s, start - 1) <= s->opts.coarse_tail) --start;
-    return start < nl + s->deep ? start : -1;
-  }
-  if (s->opts.coarse_tail <= 0 || nl < 3 || s->opts.bottom_solver != 0 ||
-      s->L.back().ncell > kTailMaxBottom)
+  if (!s->deep && (s->opts.coarse_tail <= 0 || nl < 3 || s->opts.bottom_solver != 0 ||
+                   s->L.back().ncell > kTailMaxBottom))
     return -1;
-  int start = nl - 1;
-  while (start > 1 && nl - start < kTailMaxLevels + 1 &&
-         s->L[start - 1].ncell <= s->opts.coarse_tail)
-    --start;
-  return start < nl - 1 ? start : -1;
+  std::vector<long long> cells(flat_count(s));
+  for (size_t l = 0; l < cells.size(); ++l) cells[l] = flat_cells(s, l);
+  // with a deep bottom the same rule on the bottom's coarsenings
+  return first_tail_level(cells, s->deep ? nl + 1 : 1, s->opts.coarse_tail, kTailMaxLevels);
 }
 
 // Whether level l (extents d, elements of elem bytes) is smoothed two sweeps to
