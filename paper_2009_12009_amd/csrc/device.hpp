@@ -118,6 +118,22 @@ __device__ __forceinline__ void cg_sync() {
   }
 }
 
+// The stop test ||r|| > tol ||rhs|| of the bottom CGs.  Compared as squares, one
+// square root less on the chain of dependent steps, but where tol^2 ||rhs||^2
+// comes near the smallest numbers (right-hand sides below some 1e-140) and would
+// underflow to a test that never ends.
+struct CgStop {
+  double tol, bnorm, sq;
+  bool squares;
+  __device__ __forceinline__ CgStop(double t, double rho) : tol(t), bnorm(0.0), sq(t * t * rho) {
+    squares = sq >= 0x1p-960;
+    if (!squares) bnorm = sqrt(rho);
+  }
+  __device__ __forceinline__ bool more(double rr) const {
+    return squares ? rr > sq : sqrt(rr) > tol * bnorm;
+  }
+};
+
 template <typename T, int CPT, bool ONE_WAVE = false>
 __device__ __forceinline__ void cg_lds_run(const BottomTables& bt, const T* __restrict__ diag,
                                            const T* __restrict__ coef, const T* __restrict__ rhs,
@@ -166,8 +182,7 @@ __device__ __forceinline__ void cg_lds_run(const BottomTables& bt, const T* __re
 #pragma unroll
   for (int m = 0; m < CPT; ++m) s += (double)r[m] * (double)r[m];
   double rho = cg_sum<ONE_WAVE>(s, red, phase, nw);
-  // stop at ||r|| <= tol ||rhs||, compared as squares
-  const double stop = tol * tol * rho;
+  const CgStop stop(tol, rho);
   int it = 0;
   if (rho > 0.0) {
 #pragma unroll
@@ -213,8 +228,9 @@ __device__ __forceinline__ void cg_lds_run(const BottomTables& bt, const T* __re
       }
       ++it;
       const double rho_new = cg_sum<ONE_WAVE>(s, red, phase, nw);
-      if (!(rho_new > stop)) break;
-      const T btT = (T)(rho_new * inv);
+      if (!stop.more(rho_new)) break;
+      // (the reciprocal of a subnormal rho may overflow)
+      const T btT = (T)(inv <= 0x1.fffffffffffffp1023 ? rho_new * inv : rho_new / rho);
 #pragma unroll
       for (int m = 0; m < CPT; ++m) {
         const int c = tid + m * nt;

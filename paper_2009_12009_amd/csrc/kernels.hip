@@ -2184,7 +2184,7 @@ __global__ void __launch_bounds__(1024)
 #pragma unroll
   for (int m = 0; m < CPT; ++m) s += (double)r[m] * (double)r[m];
   double rho = block_sum_w<true>(s, red, phase, nw);
-  const double stop = tol * tol * rho;
+  const CgStop stop(tol, rho);
   int it = 0;
   if (rho > 0.0) {
 #pragma unroll
@@ -2231,7 +2231,7 @@ __global__ void __launch_bounds__(1024)
       }
       ++it;
       const double rho_new = block_sum_w<true>(s, red, phase, nw);
-      if (!(rho_new > stop)) break;
+      if (!stop.more(rho_new)) break;
       const T btT = (T)(rho_new / rho);
       // every lane has read its neighbours' p: the reductions' barriers
 #pragma unroll
