@@ -303,7 +303,9 @@ int mg_set_coefficients_global(mg_solver_t* s, const void* acoef_global,
  * MG_F64 cell MultiFab, ngrow 0 or 1.  Both over the solver's boxes.  For an
  * all-periodic singular problem the returned phi has zero mean.
  * resid_history: host array of max_iter + 1 doubles or NULL; entry k is the
- * max-norm residual after k cycles.  Returns MG_ERR_NOT_CONVERGED (phi and
+ * max-norm residual after k cycles (FP64 V-cycles: the entries before the last
+ * may leave out cells whose residual is rounding, the ones updated last; the
+ * stop decision and info leave out none).  Returns MG_ERR_NOT_CONVERGED (phi and
  * info written) when max_iter is reached, MG_ERR_NAN on a non-finite norm. */
 int mg_solve(mg_solver_t* s, mg_multifab_t* phi, const mg_multifab_t* rhs, double rel_tol,
              double abs_tol, mg_info_t* info, double* resid_history);

@@ -3959,6 +3959,10 @@ struct StopTest {
   double* hist;
   int status = MG_OK, rising = 0;
   double rn = 0, first = 0, prev = 0, prev2 = 0;
+  // whether a norm of at least this may end the solve
+  bool may_stop(int it, double norm) const {
+    return norm <= tol || it == s->opts.max_iter || rising >= 2;
+  }
   int operator()(int it, double norm) {
     rn = norm;
     if (hist) hist[it] = rn;
@@ -3990,13 +3994,14 @@ struct StopTest {
 // FP64 V-cycles on the split-colour layout.  The stop test shares a pass with
 // the next cycle's first half-sweep: the red update of a cell computes
 // everything its residual needs, and after a black half-sweep the black cells'
-// residual is zero (to rounding), so the norm over the red cells is the norm.
-// (The first test, of the caller's guess, takes both colours in a pass of its
-// own.)  That half-sweep and the black one after it write the other iterate
-// array - neither reads the colour it writes - so the iterate a norm was taken
-// of survives its cycle: the norm travels to the host while the cycle runs and
-// is read before the next test, except where the norms' geometric trend puts it
-// near the tolerance (a converged solve would run one cycle for nothing).
+// residual is zero to rounding, so the norm over the red cells says whether to
+// go on.  Rounding counts where the norm may end the solve: there, and for the
+// caller's guess, it is taken of both colours in a pass of its own.  That
+// half-sweep and the black one after it write the other iterate array - neither
+// reads the colour it writes - so the iterate a norm was taken of survives its
+// cycle: the norm travels to the host while the cycle runs and is read before
+// the next test, except where the norms' geometric trend puts it near the
+// tolerance (a converged solve would run one cycle for nothing).
 int solve_flat(mg_solver* s, double tol, mg_info_t* inf, double* hist, int* status,
                double** result) {
   FlatLevel<double>& v = s->f64[0];
@@ -4008,6 +4013,7 @@ int solve_flat(mg_solver* s, double tol, mg_info_t* inf, double* hist, int* stat
   // of them)
   double* arr[3] = {s->fphi[0], s->fphi[1], s->fthird};
   int it = 0, rc;
+  bool both = true;  // whether the norm on its way is of both colours
   auto decide = [&]() -> int {
     if (hipEventSynchronize(s->ev_norm[it & 1]) != hipSuccess) return -1;
     const unsigned long long* hn = s->h_norm + (size_t)(1 + (it & 1)) * kNormSlot;
@@ -4015,6 +4021,14 @@ int solve_flat(mg_solver* s, double tol, mg_info_t* inf, double* hist, int* stat
     for (int k = 0; k < kNormWays; ++k) m = std::max(m, hn[k * kNormStride]);
     double rn;
     std::memcpy(&rn, &m, sizeof(double));
+    if (!both && std::isfinite(rn) && stop.may_stop(it, rn)) {
+      // a cycle that runs meanwhile leaves the iterate arr[0] as it is
+      if (launch_fill_u64(s->st, norm_slot(s, 3), kNormSlot, 0ull) != hipSuccess ||
+          launch_flat_resid<double, double>(s->st, op, w.next(), arr[0], s->frhs, nullptr,
+                                            norm_slot(s, 3), nullptr) != hipSuccess ||
+          read_norm(s, 3, &rn) != MG_OK)
+        return -1;
+    }
     return stop(it, rn);
   };
   while (true) {
@@ -4023,7 +4037,12 @@ int solve_flat(mg_solver* s, double tol, mg_info_t* inf, double* hist, int* stat
     double* red = s->fmid ? s->fred : n;  // the red half after the first half-sweep
     const int slot = 1 + (it & 1);
     HIPTRY(launch_fill_u64(s->st, norm_slot(s, slot), kNormSlot, 0ull));
-    if (it == 0) {
+    // what the norms' geometric trend makes of this one
+    const double pred = it < 2 ? 0 : stop.prev * (stop.prev / stop.prev2);
+    // (a norm close above the tolerance is worth the pass too; where it turns out
+    // below it without, the pass comes after, with a wait of its own)
+    both = it == 0 || it >= s->opts.max_iter || (it >= 2 && !(pred > 1.5 * tol));
+    if (both) {
       ProfScope ps(s, 1, true);
       HIPTRY((launch_flat_resid<double, double>(s->st, op, w.next(), c, s->frhs, nullptr,
                                                 norm_slot(s, slot), nullptr)));
@@ -4042,8 +4061,7 @@ int solve_flat(mg_solver* s, double tol, mg_info_t* inf, double* hist, int* stat
     HIPTRY(hipMemcpyAsync(s->h_norm + (size_t)slot * kNormSlot, norm_slot(s, slot),
                           sizeof(unsigned long long) * kNormSlot, hipMemcpyDeviceToHost, s->st));
     HIPTRY(hipEventRecord(s->ev_norm[it & 1], s->st));
-    bool wait = it < 2 || it >= s->opts.max_iter;
-    if (!wait) wait = !(stop.prev * (stop.prev / stop.prev2) > 8.0 * tol);
+    const bool wait = it < 2 || it >= s->opts.max_iter || !(pred > 8.0 * tol);
     if (wait) {
       const int d = decide();
       if (d < 0) return fail(MG_ERR_HIP, "norm read-back failed");
