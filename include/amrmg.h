@@ -299,7 +299,9 @@ int mg_set_coefficients_global(mg_solver_t* s, const void* acoef_global,
 /* Solve A phi = rhs by V-cycles until max|rhs - A phi| <= max(rel_tol *
  * max|rhs|, abs_tol) ("Linear Solvers"; the stop norm is the max norm of
  * "Parallel Reductions").  phi: MG_F64 cell MultiFab with ngrow 1, in:
- * initial guess, out: solution (its ghost cells may be overwritten).  rhs:
+ * initial guess, out: solution (its ghost cells are overwritten: with rhs
+ * nonzero, those across the faces between boxes and across periodic faces hold
+ * the solution there).  rhs:
  * MG_F64 cell MultiFab, ngrow 0 or 1.  Both over the solver's boxes.  For an
  * all-periodic singular problem the returned phi has zero mean.
  * resid_history: host array of max_iter + 1 doubles or NULL; entry k is the

@@ -4371,6 +4371,9 @@ int mg_solve(mg_solver_t* s, mg_multifab_t* phi, const mg_multifab_t* rhs, doubl
     HIPTRY(launch_shift_valid(s->st, l0.d_cell, (int)l0.t_cell.size(), l0.s_cell, l0.d_info, P, 1,
                               s->d_sum, l0.ncell));
   }
+  // solves over boxes leave the ghosts current, but for the mean; the scatter
+  // writes valid cells
+  if ((flat || s->singular) && normf != 0.0 && (rc = exchange<double>(s, l0, P, false))) return rc;
   HIPTRY(hipMemcpyAsync(s->h_iters, s->d_iters, sizeof(int), hipMemcpyDeviceToHost, s->st));
   HIPTRY(hipStreamSynchronize(s->st));
   inf.bottom_iters = *s->h_iters;
