@@ -46,8 +46,9 @@
  *   nothing; they apply to solvers that keep levels as boxes (a single level,
  *   nu1 or nu2 = 0) and to the composite solve outside its coarse V-cycle
  *   (which is stored as above), tile shapes also to mg_apply and
- *   mg_time_smoother.  A face that two boxes share must hold the same
- *   coefficient in both (the one of the box above it is used).
+ *   mg_time_smoother.  Each box's coefficients are its own: where two boxes
+ *   hold different ones for a face they share (or the two ends of a periodic
+ *   direction do), a solve keeps its levels as boxes.
  * - Streams: work is enqueued on the stream given (NULL = the default
  *   stream).  mg_solve returns after its result is complete; fill_boundary,
  *   mg_apply and mg_face_grad_logb are asynchronous with respect to the host.

@@ -125,12 +125,20 @@ template <typename T>
 hipError_t launch_flat_scatter(hipStream_t st, const BoxInfo* boxes, int nbox, int max_cells,
                                const int lo[3], const FlatDims& d, const T* src, T* dst, int ng);
 // Coefficients from a level's box arrays: faces of direction dir scaled by
-// (beta b) ih (a face shared by two boxes is taken from the box above it),
-// cell coefficient as alpha * a.
+// (beta b) ih (a face shared by two boxes is taken from the box above it, see
+// launch_flat_shared), cell coefficient as alpha * a.
 template <typename T>
 hipError_t launch_flat_faces(hipStream_t st, const BoxInfo* boxes, int nbox, int max_faces,
                              const int lo[3], const FlatDims& d, int dir, const T* b, T beta, T ih,
                              T* dst);
+// *differ = 1 if a box holds another value (scaled as above) for a face than the box
+// above it, or than the other end of a periodic direction; b: the level's face
+// arrays, op: its faces as launch_flat_faces left them.  max_plane: the most faces
+// of a box in one plane.
+template <typename T>
+hipError_t launch_flat_shared(hipStream_t st, const BoxInfo* boxes, int nbox, int max_plane,
+                              const int lo[3], const FlatOp<T>& op, const T* const b[3], T beta,
+                              const T ih[3], unsigned long long* differ);
 template <typename T>
 hipError_t launch_flat_acoef(hipStream_t st, const BoxInfo* boxes, int nbox, int max_cells,
                              const int lo[3], const FlatDims& d, const T* a, T alpha, T* dst);

@@ -825,6 +825,19 @@ __global__ void __launch_bounds__(kBlkLanes)
 __device__ __forceinline__ int split_at(const FlatDims& d, int i, int j, int k) {
   return ((i + j + k) & 1) * d.half + (i >> 1) + d.sp * (j + d.ny * k);
 }
+__device__ __forceinline__ int xface_at(const FlatDims& d, int i, int j, int k) {
+  return (i & 1) * d.half + (i >> 1) + d.sp * (j + d.ny * k);
+}
+__device__ __forceinline__ int yface_at(const FlatDims& d, int i, int j, int k) {
+  return ((i + j + k) & 1) * d.yh + (i >> 1) + d.sp * (j + (d.ny + 1) * k);
+}
+__device__ __forceinline__ int zface_at(const FlatDims& d, int i, int j, int k) {
+  return ((i + j + k) & 1) * d.zh + (i >> 1) + d.sp * (j + d.ny * k);
+}
+__device__ __forceinline__ int face_at(const FlatDims& d, int dir, const int (&c)[3]) {
+  return dir == 0 ? xface_at(d, c[0], c[1], c[2])
+                  : dir == 1 ? yface_at(d, c[0], c[1], c[2]) : zface_at(d, c[0], c[1], c[2]);
+}
 
 template <typename T, bool GATHER>
 __global__ void __launch_bounds__(256)
@@ -873,14 +886,46 @@ __global__ void __launch_bounds__(256)
     // a box's last face is the next box's first, unless the domain ends there
     if (q[dir] == n[dir] - 1 && B.hi[dir] - l[dir] + 1 != dn[dir]) continue;
     for (int a = 0; a < 3; ++a) q[a] += B.lo[a] - l[a];
-    const T c = (beta * b[B.off_f[dir] + e]) * ih;
-    if (dir == 0)
-      dst[(q[0] & 1) * d.half + (q[0] >> 1) + d.sp * (q[1] + d.ny * q[2])] = c;
-    else if (dir == 1)
-      dst[((q[0] + q[1] + q[2]) & 1) * d.yh + (q[0] >> 1) + d.sp * (q[1] + (d.ny + 1) * q[2])] = c;
-    else
-      dst[((q[0] + q[1] + q[2]) & 1) * d.zh + (q[0] >> 1) + d.sp * (q[1] + d.ny * q[2])] = c;
+    dst[face_at(d, dir, q)] = (beta * b[B.off_f[dir] + e]) * ih;
   }
+}
+
+// grid.z = direction, grid.y = box; lanes stride the box's last plane of faces.
+// They are a 65th of the faces of 64^3 boxes, so what this costs is a launch.
+template <typename T>
+struct BoxFaces {
+  const T* b[3];
+  T ih[3];
+};
+template <typename T>
+__global__ void __launch_bounds__(256)
+    k_flat_shared(const BoxInfo* __restrict__ boxes, int3 lo, FlatOp<T> op, BoxFaces<T> faces,
+                  T beta, unsigned long long* differ) {
+#pragma clang fp contract(off)
+  const FlatDims& d = op.d;
+  const int dir = blockIdx.z, u = dir == 0 ? 1 : 0, v = dir == 2 ? 1 : 2;
+  const BoxInfo B = boxes[blockIdx.y];
+  int n[3];
+  for (int a = 0; a < 3; ++a) n[a] = B.hi[a] - B.lo[a] + 1 + (a == dir ? 1 : 0);
+  const int dn[3] = {d.nx, d.ny, d.nz};
+  const int l[3] = {lo.x, lo.y, lo.z};
+  const bool end = B.hi[dir] - l[dir] + 1 == dn[dir];
+  if (end && (d.wall >> (2 * dir) & 1)) return;
+  const T* b = (dir == 0 ? faces.b[0] : dir == 1 ? faces.b[1] : faces.b[2]) + B.off_f[dir];
+  const T* c = dir == 0 ? op.x : dir == 1 ? op.y : op.z;
+  const T ih = dir == 0 ? faces.ih[0] : dir == 1 ? faces.ih[1] : faces.ih[2];
+  bool bad = false;
+  for (int e = blockIdx.x * 256 + threadIdx.x; e < n[u] * n[v]; e += gridDim.x * 256) {
+    int q[3];
+    q[dir] = n[dir] - 1;
+    q[v] = e / n[u];
+    q[u] = e - q[v] * n[u];
+    const T own = (beta * b[q[0] + n[0] * ((long long)q[1] + n[1] * (long long)q[2])]) * ih;
+    for (int a = 0; a < 3; ++a) q[a] += B.lo[a] - l[a];
+    if (end) q[dir] = 0;
+    bad = bad || !(own == c[face_at(d, dir, q)]);
+  }
+  if (bad) atomicOr(differ, 1ull);
 }
 
 template <typename T>
@@ -1255,19 +1300,6 @@ __global__ void __launch_bounds__(NT) k_flat_tail(const FlatTail<T>* __restrict_
 // product is one launch and its result decides on the device whether the rest
 // of the iteration does anything.
 
-__device__ __forceinline__ int xface_at(const FlatDims& d, int i, int j, int k) {
-  return (i & 1) * d.half + (i >> 1) + d.sp * (j + d.ny * k);
-}
-__device__ __forceinline__ int yface_at(const FlatDims& d, int i, int j, int k) {
-  return ((i + j + k) & 1) * d.yh + (i >> 1) + d.sp * (j + (d.ny + 1) * k);
-}
-__device__ __forceinline__ int zface_at(const FlatDims& d, int i, int j, int k) {
-  return ((i + j + k) & 1) * d.zh + (i >> 1) + d.sp * (j + d.ny * k);
-}
-__device__ __forceinline__ int face_at(const FlatDims& d, int dir, const int (&c)[3]) {
-  return dir == 0 ? xface_at(d, c[0], c[1], c[2])
-                  : dir == 1 ? yface_at(d, c[0], c[1], c[2]) : zface_at(d, c[0], c[1], c[2]);
-}
 __device__ __forceinline__ int3 cell_of(const FlatDims& d, int at) {
   const int colour = at >= d.half, e = at - colour * d.half;
   const int p = e % d.sp, row = e / d.sp, j = row % d.ny, k = row / d.ny;
@@ -1759,6 +1791,22 @@ hipError_t launch_flat_faces(hipStream_t st, const BoxInfo* boxes, int nbox, int
 }
 
 template <typename T>
+hipError_t launch_flat_shared(hipStream_t st, const BoxInfo* boxes, int nbox, int max_plane,
+                              const int lo[3], const FlatOp<T>& op, const T* const b[3], T beta,
+                              const T ih[3], unsigned long long* differ) {
+  dim3 g = box_grid(nbox, max_plane);
+  g.z = 3;
+  BoxFaces<T> f;
+  for (int a = 0; a < 3; ++a) {
+    f.b[a] = b[a];
+    f.ih[a] = ih[a];
+  }
+  hipLaunchKernelGGL((k_flat_shared<T>), g, dim3(256), 0, st, boxes,
+                     make_int3(lo[0], lo[1], lo[2]), op, f, beta, differ);
+  return hipGetLastError();
+}
+
+template <typename T>
 hipError_t launch_flat_acoef(hipStream_t st, const BoxInfo* boxes, int nbox, int max_cells,
                              const int lo[3], const FlatDims& d, const T* a, T alpha, T* dst) {
   hipLaunchKernelGGL((k_flat_acoef<T>), box_grid(nbox, max_cells), dim3(256), 0, st, boxes,
@@ -1930,6 +1978,9 @@ hipError_t launch_deep_xr(hipStream_t st, long long n, T* x, const T* p, T* r, c
                                              const FlatDims&, const T*, T*, int);                  \
   template hipError_t launch_flat_faces<T>(hipStream_t, const BoxInfo*, int, int, const int*,      \
                                            const FlatDims&, int, const T*, T, T, T*);              \
+  template hipError_t launch_flat_shared<T>(hipStream_t, const BoxInfo*, int, int, const int*,     \
+                                            const FlatOp<T>&, const T* const*, T, const T*,        \
+                                            unsigned long long*);                                  \
   template hipError_t launch_flat_acoef<T>(hipStream_t, const BoxInfo*, int, int, const int*,      \
                                            const FlatDims&, const T*, T, T*);                      \
   template hipError_t launch_flat_dot<T>(hipStream_t, long long, const double*, const T*, double*, \

@@ -1473,6 +1473,12 @@ __global__ void k_fill_u64(unsigned long long* p, int n, unsigned long long v) {
   if (i < n) p[i] = v;
 }
 
+__global__ void __launch_bounds__(64)
+    k_start_norms(unsigned long long* p, int n, const unsigned long long* spare) {
+  const int i = blockIdx.x * 64 + threadIdx.x;
+  if (i < n) p[i] = i == kNormSpare ? *spare : 0ull;
+}
+
 // Plain device copy, one 16-byte element per lane (the achievable streaming
 // rate and the reference for the HBM traffic counters).
 __global__ void __launch_bounds__(256)
@@ -2936,6 +2942,13 @@ hipError_t fb_scratch_address(void** ptr) {
 hipError_t launch_fill_u64(hipStream_t st, unsigned long long* p, int n, unsigned long long v) {
   if (n <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_fill_u64, dim3((n + 63) / 64), dim3(64), 0, st, p, n, v);
+  return hipGetLastError();
+}
+
+hipError_t launch_start_norms(hipStream_t st, unsigned long long* p, int n,
+                              const unsigned long long* spare) {
+  if (n <= kNormSpare || !spare) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_start_norms, dim3((n + 63) / 64), dim3(64), 0, st, p, n, spare);
   return hipGetLastError();
 }
 

@@ -31,6 +31,8 @@ struct StencilArgs {
 constexpr int kNormWays = 64;
 constexpr int kNormStride = 16;
 constexpr int kNormSlot = kNormWays * kNormStride;
+// Word of a slot that belongs to no way.
+constexpr int kNormSpare = 1;
 
 // Launch shape of a tiled kernel: block (lx, ly), each block marching tz
 // planes, u planes gathered per step (smoother and residual only).
@@ -213,6 +215,10 @@ hipError_t launch_fill_boundary(hipStream_t st, const FbTag* tags, const FbChunk
 
 // Plain element-wise helpers over n elements.
 hipError_t launch_fill_u64(hipStream_t st, unsigned long long* p, int n, unsigned long long v);
+// p[0 .. n) = 0, with *spare in word kNormSpare: what a norm's way to the host
+// can take along.
+hipError_t launch_start_norms(hipStream_t st, unsigned long long* p, int n,
+                              const unsigned long long* spare);
 
 // Size of the static device scratch of the allocation-free ghost exchange,
 // and its address on the current device (looked up once per device).

@@ -209,8 +209,12 @@ struct mg_solver {
   double* d_sum = nullptr;
   double* d_partials = nullptr;
   double* tune_scratch = nullptr;
-  // the solve's own storage: every level in the split-colour layout (flat_on)
-  bool flat = false;
+  // the solve's own storage: every level in the split-colour layout (flat_on:
+  // flat_plan), unless two boxes hold different coefficients for a face
+  // (*d_differ not 0, set with the coefficients): then each box's own count, and
+  // solves work on the boxes.  flat: what the running solve does.
+  bool flat = false, flat_plan = false;
+  unsigned long long* d_differ = nullptr;
   std::vector<FlatLevel<double>> f64;  // FP32 refinement: level 0 only
   std::vector<FlatLevel<float>> f32;
   int flat_tail = -1;  // first level of the one-launch tail (-1: none)
@@ -602,7 +606,7 @@ bool make_wt_tables(Level& lv, const int periodic[3]) {
 // cycle's first half-sweep (needs the level hierarchy: call after it is set).
 bool stop_fold_on(const mg_solver* s) {
   return s->opts.stop_fold && s->opts.precision == MG_PREC_F64 && !s->opts.krylov &&
-         !s->composite && s->opts.nu1 >= 1 && s->L.size() > 1 && !s->L[0].fused && !s->flat;
+         !s->composite && s->opts.nu1 >= 1 && s->L.size() > 1 && !s->L[0].fused && !s->flat_plan;
 }
 
 // Whether mg_solve keeps its levels in the split-colour layout: a hierarchy
@@ -637,7 +641,7 @@ constexpr int kDeepMin = 5120, kDeepMax = 8;
 void deep_plan(mg_solver* s) {
   s->deep = 0;
   const Level& bl = s->L.back();
-  if (!s->flat || s->opts.bottom_solver != 0 || s->opts.bottom_max_iter != 0 ||
+  if (!s->flat_plan || s->opts.bottom_solver != 0 || s->opts.bottom_max_iter != 0 ||
       !(s->opts.bottom_rel_tol > 0) || s->opts.nu1 != s->opts.nu2 || bl.ncell <= kDeepMin)
     return;
   std::array<int, 3> n{}, pad{};
@@ -1069,9 +1073,9 @@ int build_plan(mg_solver* s, const std::vector<IBox>& boxes, Bump& bump) {
     c.fold_rs = l >= 2;
   }
 
-  s->flat = flat_on(s);
+  s->flat_plan = flat_on(s);
   deep_plan(s);
-  s->flat_tail = s->flat ? flat_tail_level(s) : -1;
+  s->flat_tail = s->flat_plan ? flat_tail_level(s) : -1;
 
   // the level-0 residual restricts as it goes: every level-0 box splits
   // into whole 2x2x2 blocks (true whenever there is a level 1)
@@ -1091,7 +1095,7 @@ int build_plan(mg_solver* s, const std::vector<IBox>& boxes, Bump& bump) {
   s->h_aidx.assign(nb, 0);
   s->h_map_rhs.assign(nb, 0);
   s->h_map_out.assign(nb, 0);
-  s->h_fmap.assign(s->flat ? nb : 0, 0);
+  s->h_fmap.assign(s->flat_plan ? nb : 0, 0);
   FlatDims fb{};
   {
     const IBox& D = bl.domain;
@@ -1133,7 +1137,7 @@ int build_plan(mg_solver* s, const std::vector<IBox>& boxes, Bump& bump) {
             s->h_map_rhs[c] = (int)(I.off_g0 + g0);
             s->h_map_out[c] =
                 (int)(I.off_g1 + (il + 1) + (int64_t)(nx + 2) * ((jl + 1) + (int64_t)(ny + 2) * (kl + 1)));
-            if (s->flat) {
+            if (s->flat_plan) {
               const int I = i - D.lo[0], J = j - D.lo[1], K = k - D.lo[2];
               s->h_fmap[c] = ((I + J + K) & 1) * fb.half + (I >> 1) + fb.sp * (J + fb.ny * K);
             }
@@ -1230,11 +1234,12 @@ int build_plan(mg_solver* s, const std::vector<IBox>& boxes, Bump& bump) {
   s->d_norm = bump.take<unsigned long long>(4 * kNormSlot);
   s->d_cg = bump.take<double>(4);
   s->d_iters = bump.take<int>(4);
+  s->d_differ = reinterpret_cast<unsigned long long*>(s->d_iters + 2);
   s->d_sum = bump.take<double>(2);
   s->d_partials =
       bump.take<double>(std::max<size_t>({1, s->L[0].cap_cell, s->L[0].t_vec.size()}));
   if (s->opts.tune == 2) s->tune_scratch = bump.take<double>(s->L[0].n_g1);
-  if (s->flat) layout_flat_all(s, bump);
+  if (s->flat_plan) layout_flat_all(s, bump);
   s->d_tail = s->tail_lev > 0 ? bump.take<char>(sizeof(TailPlan<double>)) : nullptr;
   s->ws_need = bump.off + 256;
   return MG_OK;
@@ -1445,6 +1450,26 @@ int flat_coefficients(mg_solver* s) {
   return MG_OK;
 }
 
+// Whether the boxes of level 0 agree on the faces they share, into *d_differ (the
+// coarser levels' faces are means of level 0's in a fixed order, so they then
+// agree too).
+template <typename T>
+int check_shared_faces(mg_solver* s) {
+  const Level& l0 = s->L[0];
+  if (l0.nbox == 1 && !s->periodic[0] && !s->periodic[1] && !s->periodic[2]) return MG_OK;
+  const StencilArgs<T> op = stencil_of<T>(s, l0, sizeof(T) == 4);
+  const T* b[3] = {op.b0, op.b1, op.b2};
+  const T ih[3] = {op.ih0, op.ih1, op.ih2};
+  int plane = 1;
+  for (const IBox& B : l0.boxes) {
+    const int n[3] = {ext(B, 0), ext(B, 1), ext(B, 2)};
+    plane = std::max({plane, n[0] * n[1], n[0] * n[2], n[1] * n[2]});
+  }
+  HIPTRY(launch_flat_shared<T>(s->st, l0.d_info, l0.nbox, plane, l0.domain.lo,
+                               flat_levels<T>(s)[0].op, b, op.beta, ih, s->d_differ));
+  return MG_OK;
+}
+
 int coarsen_all(mg_solver* s) {
   const bool f32 = s->opts.precision == MG_PREC_F32_REFINE;
   for (size_t l = 0; l + 1 < s->L.size(); ++l) {
@@ -1464,10 +1489,16 @@ int coarsen_all(mg_solver* s) {
       if (s->has_a) HIPTRY((launch_convert<double, float>(s->st, lv.a64, lv.a32, lv.n_g0)));
     }
   }
-  if (s->flat) {
+  HIPTRY(launch_fill_u64(s->st, s->d_differ, 1, 0ull));
+  if (s->flat_plan) {
     int rc;
     if ((rc = flat_coefficients<double>(s))) return rc;
     if (f32 && (rc = flat_coefficients<float>(s))) return rc;
+    if (s->composite && f32)
+      rc = check_shared_faces<float>(s);
+    else
+      rc = check_shared_faces<double>(s);
+    if (rc) return rc;
   }
   const Level& bl = s->L.back();
   BottomTables bt = bottom_tables(s);
@@ -1935,6 +1966,22 @@ int capture_graph(mg_solver* s, F&& cycle, hipGraphExec_t* ex) {
   return MG_OK;
 }
 
+// The coarse levels over boxes; a handle whose solves work in the split-colour
+// layout captures them with the first solve that does not.
+int capture_box_graph(mg_solver* s) {
+  const bool f32 = s->opts.precision == MG_PREC_F32_REFINE;
+  hipGraphExec_t* ex = f32 ? &s->graph32 : &s->graph64;
+  if (!s->opts.use_graph || *ex) return MG_OK;
+  // the level-0 residual pass restricts into level 1 itself with rr_fold
+  return capture_graph(
+      s,
+      [&]() {
+        return f32 ? coarse_cycle<float>(s, 1, true, s->rr_fold ? nullptr : s->L[0].r32)
+                   : coarse_cycle<double>(s, 1, false, s->rr_fold ? nullptr : s->L[0].r64);
+      },
+      ex);
+}
+
 int capture_graphs(mg_solver* s) {
   const bool f32 = s->opts.precision == MG_PREC_F32_REFINE;
   int rc;
@@ -1944,20 +1991,10 @@ int capture_graphs(mg_solver* s) {
     s->opts.use_graph = 0;
     return MG_OK;
   }
-  if (s->flat) {
-    rc = capture_graph(
+  if (s->flat_plan)
+    return capture_graph(
         s, [&]() { return f32 ? flat_cycle<float>(s, 1) : flat_cycle<double>(s, 1); }, &s->fgraph);
-    // a composite handle's own level 0 (mg_solve on it) cycles over boxes
-    if (rc || !s->composite) return rc;
-  }
-  // the level-0 residual pass restricts into level 1 itself with rr_fold
-  return capture_graph(
-      s,
-      [&]() {
-        return f32 ? coarse_cycle<float>(s, 1, true, s->rr_fold ? nullptr : s->L[0].r32)
-                   : coarse_cycle<double>(s, 1, false, s->rr_fold ? nullptr : s->L[0].r64);
-      },
-      f32 ? &s->graph32 : &s->graph64);
+  return capture_box_graph(s);
 }
 
 // Level-0 V-cycle on the caller's phi (direct form, FP64).  red_done: the
@@ -2889,7 +2926,7 @@ int upload_tables(mg_solver* s) {
   HIPTRY(hipMemcpyAsync(s->d_aidx, s->h_aidx.data(), sizeof(int) * nb, hipMemcpyHostToDevice, s->st));
   HIPTRY(hipMemcpyAsync(s->d_map_rhs, s->h_map_rhs.data(), sizeof(int) * nb, hipMemcpyHostToDevice, s->st));
   HIPTRY(hipMemcpyAsync(s->d_map_out, s->h_map_out.data(), sizeof(int) * nb, hipMemcpyHostToDevice, s->st));
-  if (s->flat) {
+  if (s->flat_plan) {
     // padding and guard elements are zero for good
     HIPTRY(hipMemsetAsync(s->flat_base, 0, s->flat_bytes, s->st));
     if (s->deep) {
@@ -4258,15 +4295,14 @@ int mg_solve(mg_solver_t* s, mg_multifab_t* phi, const mg_multifab_t* rhs, doubl
   const double* F = static_cast<const double*>(rhs->data);
   const int rng = rhs->ngrow;
   const bool f32 = s->opts.precision == MG_PREC_F32_REFINE;
-  const bool flat = s->flat && !s->composite;
+  bool flat = s->flat_plan && !s->composite;
   const StencilArgs<double> op = stencil_of<double>(s, l0, false);
   mg_info_t inf;
   std::memset(&inf, 0, sizeof(inf));
   inf.nlevels = (int)s->L.size();
-  inf.tail_level = std::max(flat ? (s->deep ? -1 : s->flat_tail) : s->tail_lev, 0);
   inf.setup_ms = s->setup_ms;
 
-  HIPTRY(launch_fill_u64(s->st, s->d_norm, 4 * kNormSlot, 0ull));
+  HIPTRY(launch_start_norms(s->st, s->d_norm, 4 * kNormSlot, s->d_differ));
   if (flat)
     HIPTRY(launch_flat_gather(s->st, l0.d_info, l0.nbox, l0.max_faces, l0.domain.lo,
                               s->f64[0].op.d, F, rng, s->frhs, s->d_norm));
@@ -4275,6 +4311,9 @@ int mg_solve(mg_solver_t* s, mg_multifab_t* phi, const mg_multifab_t* rhs, doubl
                                  rng, s->d_norm));
   double normf;
   if ((rc = read_norm(s, 0, &normf))) return rc;
+  flat = flat && !s->h_norm[kNormSpare];
+  if (!flat && (rc = capture_box_graph(s))) return rc;
+  inf.tail_level = std::max(flat ? (s->deep ? -1 : s->flat_tail) : s->tail_lev, 0);
   int status = MG_OK;
   if (!std::isfinite(normf)) return fail(MG_ERR_NAN, "rhs holds a non-finite value");
   if (normf == 0.0) {
@@ -4677,10 +4716,8 @@ int mg_solve_amr(mg_solver_t* s, mg_multifab_t* phi_c, mg_multifab_t* phi_f,
   mg_info_t inf;
   std::memset(&inf, 0, sizeof(inf));
   inf.nlevels = (int)s->L.size() + 1;
-  const int tail = s->flat ? (s->deep ? -1 : s->flat_tail) : s->tail_lev;
-  inf.tail_level = tail > 0 ? tail + 1 : 0;
   inf.setup_ms = s->setup_ms;
-  HIPTRY(launch_fill_u64(s->st, s->d_norm, 4 * kNormSlot, 0ull));
+  HIPTRY(launch_start_norms(s->st, s->d_norm, 4 * kNormSlot, s->d_differ));
   HIPTRY(launch_copy_valid(s->st, L0.d_cell, (int)L0.t_cell.size(), L0.s_cell, L0.d_info, Fc,
                            rhs_c->ngrow, s->Rc, 0));
   if ((rc = avgdown<double>(s, nullptr, 0, s->Rc, 0, 1))) return rc;
@@ -4690,6 +4727,10 @@ int mg_solve_amr(mg_solver_t* s, mg_multifab_t* phi_c, mg_multifab_t* phi_f,
                                rhs_f->ngrow, s->d_norm));
   double normf;
   if ((rc = read_norm(s, 0, &normf))) return rc;
+  s->flat = s->flat_plan && !s->h_norm[kNormSpare];
+  if (!s->flat && (rc = capture_box_graph(s))) return rc;
+  const int tail = s->flat ? (s->deep ? -1 : s->flat_tail) : s->tail_lev;
+  inf.tail_level = tail > 0 ? tail + 1 : 0;
   int status = MG_OK;
   if (!std::isfinite(normf)) return fail(MG_ERR_NAN, "rhs holds a non-finite value");
   if (normf == 0.0) {
