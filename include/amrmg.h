@@ -45,7 +45,8 @@
  *   no ghost cells, so the options and tile shapes marked [boxes] change
  *   nothing; they apply to solvers that keep levels as boxes (a single level,
  *   nu1 or nu2 = 0) and to the composite solve outside its coarse V-cycle
- *   (which is stored as above), tile shapes also to mg_apply and
+ *   (which is stored as above), to handles with a smaller workspace than
+ *   mg_query_workspace asks for, tile shapes also to mg_apply and
  *   mg_time_smoother.  Each box's coefficients are its own: where two boxes
  *   hold different ones for a face they share (or the two ends of a periodic
  *   direction do), a solve keeps its levels as boxes.
@@ -251,6 +252,9 @@ void mg_default_opts(mg_opts_t* opts);
 int mg_query_workspace_amr(const mg_box_t* cboxes, int32_t ncb, const mg_box_t* fboxes,
                            int32_t nfb, const mg_geom_t* geom, const mg_opts_t* opts,
                            size_t* bytes);
+int mg_query_workspace_amr_least(const mg_box_t* cboxes, int32_t ncb, const mg_box_t* fboxes,
+                                 int32_t nfb, const mg_geom_t* geom, const mg_opts_t* opts,
+                                 size_t* bytes);
 int mg_create_amr(const mg_box_t* cboxes, int32_t ncb, const mg_box_t* fboxes, int32_t nfb,
                   const mg_geom_t* geom, double alpha, double beta,
                   const mg_multifab_t* const* bcoef_c, const mg_multifab_t* const* bcoef_f,
@@ -267,6 +271,12 @@ int mg_solve_amr(mg_solver_t* s, mg_multifab_t* phi_c, mg_multifab_t* phi_f,
 int mg_query_workspace(const mg_box_t* boxes, int32_t nbox, const mg_geom_t* geom,
                        const mg_opts_t* opts, int32_t has_acoef, size_t* bytes);
 
+/* ... with which mg_create still makes a solver: one that keeps its levels as
+ * boxes (same results to rounding, slower).  A workspace between the two sizes
+ * is used as far as it goes. */
+int mg_query_workspace_least(const mg_box_t* boxes, int32_t nbox, const mg_geom_t* geom,
+                             const mg_opts_t* opts, int32_t has_acoef, size_t* bytes);
+
 /* Build a solver for one level ("Linear Solvers"; box array and geometry of
  * "Basic data structures").  Validates the boxes (disjoint, inside, covering
  * the domain), builds the multigrid hierarchy, the ghost-exchange plans (hash
@@ -276,8 +286,8 @@ int mg_query_workspace(const mg_box_t* boxes, int32_t nbox, const mg_geom_t* geo
  * bcoef: three face MultiFabs (ixtype e_d, ngrow 0) or NULL (b = 1); both
  * MG_F64 over the same boxes.  bc_lo/bc_hi: MG_BC_PERIODIC exactly in the
  * periodic directions of geom, MG_BC_DIRICHLET0 elsewhere.  opts NULL =
- * defaults.  workspace: device memory of at least mg_query_workspace bytes,
- * 256-byte aligned.  hip_stream: hipStream_t or NULL. */
+ * defaults.  workspace: device memory of mg_query_workspace bytes (at least
+ * mg_query_workspace_least), 256-byte aligned.  hip_stream: hipStream_t or NULL. */
 int mg_create(const mg_box_t* boxes, int32_t nbox, const mg_geom_t* geom,
               const int32_t bc_lo[3], const int32_t bc_hi[3], double alpha, double beta,
               const mg_multifab_t* acoef, const mg_multifab_t* const* bcoef,

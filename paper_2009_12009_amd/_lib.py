@@ -78,6 +78,8 @@ SIGNATURES = {
     "mg_default_opts": (None, [P(MgOpts)]),
     "mg_query_workspace": (C.c_int, [P(MgBox), C.c_int32, P(MgGeom), P(MgOpts), C.c_int32,
                                      P(C.c_size_t)]),
+    "mg_query_workspace_least": (C.c_int, [P(MgBox), C.c_int32, P(MgGeom), P(MgOpts), C.c_int32,
+                                           P(C.c_size_t)]),
     "mg_create": (C.c_int, [P(MgBox), C.c_int32, P(MgGeom), P(C.c_int32), P(C.c_int32),
                             C.c_double, C.c_double, P(MgMultiFab), P(P(MgMultiFab)), P(MgOpts),
                             C.c_void_p, C.c_size_t, C.c_void_p, P(C.c_void_p)]),
@@ -110,6 +112,8 @@ SIGNATURES = {
                                     C.c_int32]),
     "mg_query_workspace_amr": (C.c_int, [P(MgBox), C.c_int32, P(MgBox), C.c_int32, P(MgGeom),
                                          P(MgOpts), P(C.c_size_t)]),
+    "mg_query_workspace_amr_least": (C.c_int, [P(MgBox), C.c_int32, P(MgBox), C.c_int32,
+                                               P(MgGeom), P(MgOpts), P(C.c_size_t)]),
     "mg_create_amr": (C.c_int, [P(MgBox), C.c_int32, P(MgBox), C.c_int32, P(MgGeom), C.c_double,
                                 C.c_double, P(P(MgMultiFab)), P(P(MgMultiFab)), P(MgOpts),
                                 C.c_void_p, C.c_size_t, C.c_void_p, P(C.c_void_p)]),

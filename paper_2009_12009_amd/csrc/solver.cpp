@@ -215,6 +215,13 @@ struct mg_solver {
   // solves work on the boxes.  flat: what the running solve does.
   bool flat = false, flat_plan = false;
   unsigned long long* d_differ = nullptr;
+  // What the workspace holds: 0 everything; 1 no split-colour levels; 2 nor the
+  // bottom CG's column layout.
+  int lean = 0;
+  // The split-colour arrays lie over those that only solves over boxes use; such
+  // a solve clears them when it is done (their padding is zero), and their
+  // coefficients come back with the next ones set.
+  bool overlay = false;
   std::vector<FlatLevel<double>> f64;  // FP32 refinement: level 0 only
   std::vector<FlatLevel<float>> f32;
   int flat_tail = -1;  // first level of the one-launch tail (-1: none)
@@ -606,7 +613,7 @@ bool make_wt_tables(Level& lv, const int periodic[3]) {
 // cycle's first half-sweep (needs the level hierarchy: call after it is set).
 bool stop_fold_on(const mg_solver* s) {
   return s->opts.stop_fold && s->opts.precision == MG_PREC_F64 && !s->opts.krylov &&
-         !s->composite && s->opts.nu1 >= 1 && s->L.size() > 1 && !s->L[0].fused && !s->flat_plan;
+         !s->composite && s->opts.nu1 >= 1 && s->L.size() > 1 && !s->L[0].fused;
 }
 
 // Whether mg_solve keeps its levels in the split-colour layout: a hierarchy
@@ -781,16 +788,6 @@ void layout_flat(mg_solver* s, size_t l, bool ef, Bump& bump) {
   if (deep) v.op.done = &s->dstate->done;
 }
 
-void finish_layout_flat(mg_solver* s, size_t from, Bump& bump) {
-  s->flat_bytes = bump.off - from;
-  if (s->deep) {
-    s->d_dnbr = bump.take<int>(s->h_dnbr.size());
-    s->d_dmap = bump.take<int>(s->h_dmap.size());
-  }
-  s->d_fmap = bump.take<int>(s->nb);
-  s->d_ftail = s->flat_tail > 0 ? bump.take<char>(sizeof(FlatTail<double>)) : nullptr;
-}
-
 void layout_flat_all(mg_solver* s, Bump& bump) {
   const bool f32 = s->opts.precision == MG_PREC_F32_REFINE;
   s->f64.clear();
@@ -815,7 +812,7 @@ void layout_flat_all(mg_solver* s, Bump& bump) {
   }
   if (s->composite) {
     s->cezero = bump.take<char>((f32 ? 4 : 8) * s->L[0].n_g1);
-    finish_layout_flat(s, from, bump);
+    s->flat_bytes = bump.off - from;
     return;
   }
   const size_t n = 2 * (size_t)s->f64[0].op.d.half;
@@ -845,7 +842,7 @@ void layout_flat_all(mg_solver* s, Bump& bump) {
     s->fq = bump.take<double>(n);
   }
   s->fpart = bump.take<double>(std::max(kFlatDotBlocks, flat_resid_blocks(s->f64[0].op.d)));
-  finish_layout_flat(s, from, bump);
+  s->flat_bytes = bump.off - from;
 }
 
 // LDS bytes of the tail kernel starting at level t: the bottom CG's p (FP64
@@ -948,6 +945,39 @@ void build_tail_tables(mg_solver* s) {
             lv.h_trc.push_back(tail_pack(b, i - clo[0], j - clo[1], k - clo[2]));
     }
   }
+}
+
+// The levels' vectors as boxes.
+void layout_boxes(mg_solver* s, Bump& bump) {
+  const bool f32 = s->opts.precision == MG_PREC_F32_REFINE;
+  for (size_t l = 0; l < s->L.size(); ++l) {
+    Level& lv = s->L[l];
+    const bool bottom = l + 1 == s->L.size();
+    if (l == 0) {
+      lv.r64 = bump.take<double>(lv.n_g0);
+      if (s->composite || s->opts.krylov) {
+        lv.e64 = bump.take<double>(lv.n_g1);
+        lv.rhs64 = bump.take<double>(lv.n_g0);
+      }
+      if (s->opts.krylov) lv.p64 = bump.take<double>(lv.n_g1);
+      if (stop_fold_on(s)) lv.next64 = bump.take<double>(lv.n_g1);
+    } else if (!f32) {
+      lv.e64 = bump.take<double>(lv.n_g1);
+      lv.rhs64 = bump.take<double>(lv.n_g0);
+      if (!bottom) lv.r64 = bump.take<double>(lv.n_g0);
+    }
+    if (lv.fused) {
+      // the array each precision smooths on this level gets a twin
+      if (!f32 || (l == 0 && s->composite)) lv.alt64 = bump.take<double>(lv.n_g1);
+      if (f32) lv.alt32 = bump.take<float>(lv.n_g1);
+    }
+    if (f32) {
+      lv.e32 = bump.take<float>(lv.n_g1);
+      lv.rhs32 = bump.take<float>(lv.n_g0);
+      if (!bottom) lv.r32 = bump.take<float>(lv.n_g0);
+    }
+  }
+  if (s->opts.tune == 2) s->tune_scratch = bump.take<double>(s->L[0].n_g1);
 }
 
 int build_plan(mg_solver* s, const std::vector<IBox>& boxes, Bump& bump) {
@@ -1073,7 +1103,8 @@ int build_plan(mg_solver* s, const std::vector<IBox>& boxes, Bump& bump) {
     c.fold_rs = l >= 2;
   }
 
-  s->flat_plan = flat_on(s);
+  s->flat_plan = s->lean == 0 && flat_on(s);
+  s->overlay = s->flat_plan && !s->composite;
   deep_plan(s);
   s->flat_tail = s->flat_plan ? flat_tail_level(s) : -1;
 
@@ -1113,7 +1144,7 @@ int build_plan(mg_solver* s, const std::vector<IBox>& boxes, Bump& bump) {
             gmap[(i - D.lo[0]) + (size_t)gn[0] * ((j - D.lo[1]) + (size_t)gn[1] * (k - D.lo[2]))] =
                 c++;
     }
-    s->bcols = bottom_columns(gn);
+    s->bcols = s->lean < 2 ? bottom_columns(gn) : BottomColumns{};
     s->h_perm.clear();
     if (s->bcols.cpt > 0) {
       const BottomColumns& bc = s->bcols;
@@ -1177,20 +1208,6 @@ int build_plan(mg_solver* s, const std::vector<IBox>& boxes, Bump& bump) {
     lv.d_chunks = bump.take<FbChunk>(lv.chunks.size());
     for (int d = 0; d < 3; ++d) lv.b64[d] = bump.take<double>(lv.n_f[d]);
     if (s->has_a) lv.a64 = bump.take<double>(lv.n_g0);
-    const bool bottom = l + 1 == nlev;
-    if (l == 0) {
-      lv.r64 = bump.take<double>(lv.n_g0);
-      if (s->composite || s->opts.krylov) {
-        lv.e64 = bump.take<double>(lv.n_g1);
-        lv.rhs64 = bump.take<double>(lv.n_g0);
-      }
-      if (s->opts.krylov) lv.p64 = bump.take<double>(lv.n_g1);
-      if (stop_fold_on(s)) lv.next64 = bump.take<double>(lv.n_g1);
-    } else if (!f32) {
-      lv.e64 = bump.take<double>(lv.n_g1);
-      lv.rhs64 = bump.take<double>(lv.n_g0);
-      if (!bottom) lv.r64 = bump.take<double>(lv.n_g0);
-    }
     if (l == 0) {
       lv.d_vec = bump.take<Tile>(lv.t_vec.size());
       lv.d_rr = lv.t_rr.empty() ? nullptr : bump.take<Tile>(lv.cap_rr);
@@ -1204,16 +1221,10 @@ int build_plan(mg_solver* s, const std::vector<IBox>& boxes, Bump& bump) {
     if (lv.fused) {
       lv.d_sweep = bump.take<Tile>(lv.cap_sweep);
       lv.d_rim = bump.take<RimTile>(lv.t_rim.size());
-      // the array each precision smooths on this level gets a twin
-      if (!f32 || (l == 0 && s->composite)) lv.alt64 = bump.take<double>(lv.n_g1);
-      if (f32) lv.alt32 = bump.take<float>(lv.n_g1);
     }
     if (f32) {
       for (int d = 0; d < 3; ++d) lv.b32[d] = bump.take<float>(lv.n_f[d]);
       if (s->has_a) lv.a32 = bump.take<float>(lv.n_g0);
-      lv.e32 = bump.take<float>(lv.n_g1);
-      lv.rhs32 = bump.take<float>(lv.n_g0);
-      if (!bottom) lv.r32 = bump.take<float>(lv.n_g0);
     }
   }
   s->d_nbr = bump.take<int>(6 * (size_t)nb);
@@ -1238,11 +1249,40 @@ int build_plan(mg_solver* s, const std::vector<IBox>& boxes, Bump& bump) {
   s->d_sum = bump.take<double>(2);
   s->d_partials =
       bump.take<double>(std::max<size_t>({1, s->L[0].cap_cell, s->L[0].t_vec.size()}));
-  if (s->opts.tune == 2) s->tune_scratch = bump.take<double>(s->L[0].n_g1);
-  if (s->flat_plan) layout_flat_all(s, bump);
+  if (s->flat_plan) {
+    s->d_fmap = bump.take<int>(s->nb);
+    s->d_ftail = s->flat_tail > 0 ? bump.take<char>(sizeof(FlatTail<double>)) : nullptr;
+    if (s->deep) {
+      s->d_dnbr = bump.take<int>(s->h_dnbr.size());
+      s->d_dmap = bump.take<int>(s->h_dmap.size());
+    }
+  }
+  const size_t from = bump.off;
+  layout_boxes(s, bump);
+  if (s->flat_plan) {
+    const size_t boxes_end = bump.off;
+    if (s->overlay) bump.off = from;
+    layout_flat_all(s, bump);
+    bump.off = std::max(bump.off, boxes_end);
+  }
   s->d_tail = s->tail_lev > 0 ? bump.take<char>(sizeof(TailPlan<double>)) : nullptr;
-  s->ws_need = bump.off + 256;
+  s->ws_need = bump.off + (s->lean ? 0 : 256);
   return MG_OK;
+}
+
+// The fullest plan that ws_bytes hold, as mg_solver::lean; measure(lean, &bytes)
+// plans without a workspace.
+template <typename F>
+int plan_within(size_t ws_bytes, int* lean, F&& measure) {
+  size_t need[3];
+  for (*lean = 0; *lean <= 2; ++*lean) {
+    const int rc = measure(*lean, &need[*lean]);
+    if (rc) return rc;
+    if (need[*lean] <= ws_bytes) return MG_OK;
+  }
+  return fail(MG_ERR_WORKSPACE, "workspace too small: need " + std::to_string(need[0]) +
+                                    " bytes (at least " + std::to_string(need[2]) + "), got " +
+                                    std::to_string(ws_bytes));
 }
 
 int check_geom(const mg_geom_t* geom, const int32_t* bc_lo, const int32_t* bc_hi, mg_solver* s) {
@@ -1470,6 +1510,24 @@ int check_shared_faces(mg_solver* s) {
   return MG_OK;
 }
 
+// The split-colour levels: padding and guard elements are zero for good.
+int clear_flat(mg_solver* s) {
+  HIPTRY(hipMemsetAsync(s->flat_base, 0, s->flat_bytes, s->st));
+  return MG_OK;
+}
+
+// The split-colour levels' coefficients.
+int setup_flat(mg_solver* s) {
+  const bool f32 = s->opts.precision == MG_PREC_F32_REFINE;
+  HIPTRY(launch_fill_u64(s->st, s->d_differ, 1, 0ull));
+  if (!s->flat_plan) return MG_OK;
+  int rc;
+  if ((rc = flat_coefficients<double>(s))) return rc;
+  if (f32 && (rc = flat_coefficients<float>(s))) return rc;
+  return s->composite && f32 ? check_shared_faces<float>(s) : check_shared_faces<double>(s);
+}
+
+// The levels' coefficients as boxes, and the bottom's.
 int coarsen_all(mg_solver* s) {
   const bool f32 = s->opts.precision == MG_PREC_F32_REFINE;
   for (size_t l = 0; l + 1 < s->L.size(); ++l) {
@@ -1488,17 +1546,6 @@ int coarsen_all(mg_solver* s) {
         HIPTRY((launch_convert<double, float>(s->st, lv.b64[d], lv.b32[d], lv.n_f[d])));
       if (s->has_a) HIPTRY((launch_convert<double, float>(s->st, lv.a64, lv.a32, lv.n_g0)));
     }
-  }
-  HIPTRY(launch_fill_u64(s->st, s->d_differ, 1, 0ull));
-  if (s->flat_plan) {
-    int rc;
-    if ((rc = flat_coefficients<double>(s))) return rc;
-    if (f32 && (rc = flat_coefficients<float>(s))) return rc;
-    if (s->composite && f32)
-      rc = check_shared_faces<float>(s);
-    else
-      rc = check_shared_faces<double>(s);
-    if (rc) return rc;
   }
   const Level& bl = s->L.back();
   BottomTables bt = bottom_tables(s);
@@ -2927,8 +2974,6 @@ int upload_tables(mg_solver* s) {
   HIPTRY(hipMemcpyAsync(s->d_map_rhs, s->h_map_rhs.data(), sizeof(int) * nb, hipMemcpyHostToDevice, s->st));
   HIPTRY(hipMemcpyAsync(s->d_map_out, s->h_map_out.data(), sizeof(int) * nb, hipMemcpyHostToDevice, s->st));
   if (s->flat_plan) {
-    // padding and guard elements are zero for good
-    HIPTRY(hipMemsetAsync(s->flat_base, 0, s->flat_bytes, s->st));
     if (s->deep) {
       HIPTRY(hipMemcpyAsync(s->d_dnbr, s->h_dnbr.data(), sizeof(int) * s->h_dnbr.size(),
                             hipMemcpyHostToDevice, s->st));
@@ -3198,7 +3243,7 @@ int build_composite(mg_solver* s, const std::vector<IBox>& fboxes, Bump& bump) {
     s->Rf32 = bump.take<float>(F.n_g0);
     s->rf2_32 = bump.take<float>(F.n_g0);
   }
-  s->ws_need = bump.off + 256;
+  s->ws_need = bump.off + (s->lean ? 0 : 256);
   return MG_OK;
 }
 
@@ -3615,8 +3660,8 @@ static int check_opts(const mg_opts_t* o) {
   return MG_OK;
 }
 
-int mg_query_workspace(const mg_box_t* boxes, int32_t nbox, const mg_geom_t* geom,
-                       const mg_opts_t* opts, int32_t has_acoef, size_t* bytes) {
+static int query_workspace(const mg_box_t* boxes, int32_t nbox, const mg_geom_t* geom,
+                           const mg_opts_t* opts, int32_t has_acoef, int lean, size_t* bytes) {
   if (!boxes || nbox <= 0 || !bytes) return fail(MG_ERR_ARG, "null boxes or size pointer");
   std::unique_ptr<mg_solver> s(new mg_solver());
   if (opts)
@@ -3627,12 +3672,23 @@ int mg_query_workspace(const mg_box_t* boxes, int32_t nbox, const mg_geom_t* geo
   if ((rc = check_opts(&s->opts))) return rc;
   if ((rc = check_geom(geom, nullptr, nullptr, s.get()))) return rc;
   s->has_a = has_acoef != 0;
+  s->lean = lean;
   std::vector<IBox> bx(nbox);
   for (int i = 0; i < nbox; ++i) bx[i] = to_ibox(boxes[i]);
   Bump bump{nullptr};
   if ((rc = build_plan(s.get(), bx, bump))) return rc;
   *bytes = s->ws_need;
   return MG_OK;
+}
+
+int mg_query_workspace(const mg_box_t* boxes, int32_t nbox, const mg_geom_t* geom,
+                       const mg_opts_t* opts, int32_t has_acoef, size_t* bytes) {
+  return query_workspace(boxes, nbox, geom, opts, has_acoef, 0, bytes);
+}
+
+int mg_query_workspace_least(const mg_box_t* boxes, int32_t nbox, const mg_geom_t* geom,
+                             const mg_opts_t* opts, int32_t has_acoef, size_t* bytes) {
+  return query_workspace(boxes, nbox, geom, opts, has_acoef, 2, bytes);
 }
 
 int mg_num_levels(const mg_box_t* boxes, int32_t nbox, const mg_geom_t* geom,
@@ -3674,16 +3730,19 @@ int mg_create(const mg_box_t* boxes, int32_t nbox, const mg_geom_t* geom, const 
   s->has_a = acoef != nullptr;
   std::vector<IBox> bx(nbox);
   for (int i = 0; i < nbox; ++i) bx[i] = to_ibox(boxes[i]);
-  {
-    Bump measure{nullptr};
-    if ((rc = build_plan(s.get(), bx, measure))) return rc;
-  }
+  int lean;
+  rc = plan_within(workspace ? ws_bytes : SIZE_MAX, &lean, [&](int l, size_t* need) {
+    Bump bump{nullptr};
+    s->lean = l;
+    const int e = build_plan(s.get(), bx, bump);
+    *need = s->ws_need;
+    return e;
+  });
+  if (rc && rc != MG_ERR_WORKSPACE) return rc;
   if (!workspace) return fail(MG_ERR_WORKSPACE, "workspace is null");
   if ((reinterpret_cast<uintptr_t>(workspace) & 255) != 0)
     return fail(MG_ERR_WORKSPACE, "workspace must be 256-byte aligned");
-  if (ws_bytes < s->ws_need)
-    return fail(MG_ERR_WORKSPACE, "workspace too small: need " + std::to_string(s->ws_need) +
-                                      " bytes, got " + std::to_string(ws_bytes));
+  if (rc) return rc;
   {
     Bump real{static_cast<char*>(workspace)};
     if ((rc = build_plan(s.get(), bx, real))) return rc;
@@ -3711,7 +3770,9 @@ int mg_create(const mg_box_t* boxes, int32_t nbox, const mg_geom_t* geom, const 
     if ((rc = upload_tables(s.get()))) return rc;
     if ((rc = setup_coefficients(s.get(), acoef, bcoef))) return rc;
     if ((rc = coarsen_all(s.get()))) return rc;
-    if ((rc = autotune(s.get()))) return rc;
+    if ((rc = autotune(s.get()))) return rc;  // works in the box arrays
+    if (s->flat_plan && (rc = clear_flat(s.get()))) return rc;
+    if ((rc = setup_flat(s.get()))) return rc;
     if ((rc = capture_graphs(s.get()))) return rc;
     HIPTRY(hipStreamSynchronize(s->st));
     if ((rc = call.finish())) return rc;
@@ -3736,6 +3797,7 @@ int mg_set_coefficients(mg_solver_t* s, const mg_multifab_t* acoef,
   if ((rc = call.rc())) return rc;
   if ((rc = setup_coefficients(s, acoef, bcoef))) return rc;
   if ((rc = coarsen_all(s))) return rc;
+  if ((rc = setup_flat(s))) return rc;
   return call.finish();
 }
 
@@ -3762,6 +3824,7 @@ int mg_set_coefficients_global(mg_solver_t* s, const void* acoef_global,
     HIPTRY(launch_scatter_cells(s->st, l0.d_cell, (int)l0.t_cell.size(), l0.s_cell, l0.d_info, dlo,
                                 dn, (const double*)acoef_global, l0.a64));
   if ((rc = coarsen_all(s))) return rc;
+  if ((rc = setup_flat(s))) return rc;
   return call.finish();
 }
 
@@ -4280,6 +4343,16 @@ int solve_flat_pcg(mg_solver* s, double tol, mg_info_t* inf, double* hist, int* 
   return MG_OK;
 }
 
+// Clears the split-colour arrays when a solve over boxes that worked in their
+// place ends, however it ends.
+struct ClearFlat {
+  mg_solver* s;
+  explicit ClearFlat(mg_solver* s_) : s(s_) {}
+  ~ClearFlat() {
+    if (s) (void)clear_flat(s);
+  }
+};
+
 int mg_solve(mg_solver_t* s, mg_multifab_t* phi, const mg_multifab_t* rhs, double rel_tol,
              double abs_tol, mg_info_t* info, double* resid_history) {
   const auto t0 = std::chrono::steady_clock::now();
@@ -4313,6 +4386,7 @@ int mg_solve(mg_solver_t* s, mg_multifab_t* phi, const mg_multifab_t* rhs, doubl
   if ((rc = read_norm(s, 0, &normf))) return rc;
   flat = flat && !s->h_norm[kNormSpare];
   if (!flat && (rc = capture_box_graph(s))) return rc;
+  ClearFlat clear(!flat && s->overlay && normf != 0.0 ? s : nullptr);
   inf.tail_level = std::max(flat ? (s->deep ? -1 : s->flat_tail) : s->tail_lev, 0);
   int status = MG_OK;
   if (!std::isfinite(normf)) return fail(MG_ERR_NAN, "rhs holds a non-finite value");
@@ -4613,15 +4687,28 @@ static int amr_plan(mg_solver* s, const mg_box_t* cboxes, int32_t ncb, const mg_
   return MG_OK;
 }
 
-int mg_query_workspace_amr(const mg_box_t* cboxes, int32_t ncb, const mg_box_t* fboxes,
-                           int32_t nfb, const mg_geom_t* geom, const mg_opts_t* opts,
-                           size_t* bytes) {
+static int query_workspace_amr(const mg_box_t* cboxes, int32_t ncb, const mg_box_t* fboxes,
+                               int32_t nfb, const mg_geom_t* geom, const mg_opts_t* opts, int lean,
+                               size_t* bytes) {
   if (!bytes) return fail(MG_ERR_ARG, "bytes is null");
   std::unique_ptr<mg_solver> s(new mg_solver());
+  s->lean = lean;
   int rc;
   if ((rc = amr_plan(s.get(), cboxes, ncb, fboxes, nfb, geom, opts, nullptr))) return rc;
   *bytes = s->ws_need;
   return MG_OK;
+}
+
+int mg_query_workspace_amr(const mg_box_t* cboxes, int32_t ncb, const mg_box_t* fboxes,
+                           int32_t nfb, const mg_geom_t* geom, const mg_opts_t* opts,
+                           size_t* bytes) {
+  return query_workspace_amr(cboxes, ncb, fboxes, nfb, geom, opts, 0, bytes);
+}
+
+int mg_query_workspace_amr_least(const mg_box_t* cboxes, int32_t ncb, const mg_box_t* fboxes,
+                                 int32_t nfb, const mg_geom_t* geom, const mg_opts_t* opts,
+                                 size_t* bytes) {
+  return query_workspace_amr(cboxes, ncb, fboxes, nfb, geom, opts, 2, bytes);
 }
 
 int mg_create_amr(const mg_box_t* cboxes, int32_t ncb, const mg_box_t* fboxes, int32_t nfb,
@@ -4633,18 +4720,23 @@ int mg_create_amr(const mg_box_t* cboxes, int32_t ncb, const mg_box_t* fboxes, i
   if (!out) return fail(MG_ERR_ARG, "out is null");
   *out = nullptr;
   if (!std::isfinite(alpha) || !std::isfinite(beta)) return fail(MG_ERR_ARG, "alpha/beta not finite");
-  std::unique_ptr<mg_solver> s(new mg_solver());
   int rc;
-  if ((rc = amr_plan(s.get(), cboxes, ncb, fboxes, nfb, geom, opts, nullptr))) return rc;
+  int lean;
+  rc = plan_within(workspace ? ws_bytes : SIZE_MAX, &lean, [&](int l, size_t* need) {
+    mg_solver m;
+    m.lean = l;
+    const int e = amr_plan(&m, cboxes, ncb, fboxes, nfb, geom, opts, nullptr);
+    *need = m.ws_need;
+    return e;
+  });
+  if (rc && rc != MG_ERR_WORKSPACE) return rc;
   if (!workspace) return fail(MG_ERR_WORKSPACE, "workspace is null");
   if ((reinterpret_cast<uintptr_t>(workspace) & 255) != 0)
     return fail(MG_ERR_WORKSPACE, "workspace must be 256-byte aligned");
-  if (ws_bytes < s->ws_need)
-    return fail(MG_ERR_WORKSPACE, "workspace too small: need " + std::to_string(s->ws_need) +
-                                      " bytes, got " + std::to_string(ws_bytes));
-  std::unique_ptr<mg_solver> r(new mg_solver());
-  if ((rc = amr_plan(r.get(), cboxes, ncb, fboxes, nfb, geom, opts, (char*)workspace))) return rc;
-  s.swap(r);
+  if (rc) return rc;
+  std::unique_ptr<mg_solver> s(new mg_solver());
+  s->lean = lean;
+  if ((rc = amr_plan(s.get(), cboxes, ncb, fboxes, nfb, geom, opts, (char*)workspace))) return rc;
   set_h(s.get(), geom);
   for (int d = 0; d < 3; ++d) s->F.h[d] = 0.5 * s->L[0].h[d];
   s->alpha = alpha;
@@ -4684,6 +4776,8 @@ int mg_create_amr(const mg_box_t* cboxes, int32_t ncb, const mg_box_t* fboxes, i
     }
     if ((rc = coarsen_all(s.get()))) return rc;
     if ((rc = autotune(s.get()))) return rc;
+    if (s->flat_plan && (rc = clear_flat(s.get()))) return rc;
+    if ((rc = setup_flat(s.get()))) return rc;
     if ((rc = capture_graphs(s.get()))) return rc;
     HIPTRY(hipStreamSynchronize(s->st));
     if ((rc = call.finish())) return rc;

@@ -36,14 +36,29 @@ def copy_tags(boxes, domain, periodic, ngrow):
     return out
 
 
-def workspace_bytes(boxes, domain, periodic, opts=None, has_acoef=False):
+def workspace_bytes(boxes, domain, periodic, opts=None, has_acoef=False, least=False):
+    """Device bytes MLMG asks for; least: with which it still works."""
     bx = L.boxes_array(boxes)
     g = L.geom_struct(domain, periodic)
     o = opts if opts is not None else L.default_opts()
     n = C.c_size_t(0)
-    L.check(L.lib.mg_query_workspace(bx, len(boxes), C.byref(g), C.byref(o), int(has_acoef),
-                                     C.byref(n)), "mg_query_workspace")
+    name = "mg_query_workspace_least" if least else "mg_query_workspace"
+    L.check(getattr(L.lib, name)(bx, len(boxes), C.byref(g), C.byref(o), int(has_acoef),
+                                 C.byref(n)), name)
     return n.value
+
+
+def _allocate(size_of, least):
+    """A workspace of size_of(False) bytes, or where the device has not that much
+    (or least is set) of size_of(True), the least that works."""
+    try:
+        n = size_of(least)
+        return n, torch.empty(n + 256, dtype=torch.uint8, device="cuda")
+    except torch.cuda.OutOfMemoryError:
+        if least:
+            raise
+    n = size_of(True)
+    return n, torch.empty(n + 256, dtype=torch.uint8, device="cuda")
 
 
 def num_levels(boxes, domain, periodic, opts=None):
@@ -87,10 +102,12 @@ class MLMG:
     boxes: list of (lo, hi) cell boxes covering ``domain``; periodic: 3 bools
     (other directions are homogeneous Dirichlet walls); a: cell MultiFab or
     None (a = 1); b: three face MultiFabs or None (b = 1); opts: keyword
-    overrides of mg_opts_t (see include/amrmg.h)."""
+    overrides of mg_opts_t (see include/amrmg.h); least_workspace: take as little
+    device memory as the solver works with (also done where there is no more)."""
 
     def __init__(self, boxes, domain, periodic, alpha, beta, a=None, b=None, opts=None,
-                 prob_lo=(0.0, 0.0, 0.0), prob_hi=(1.0, 1.0, 1.0), stream=None):
+                 prob_lo=(0.0, 0.0, 0.0), prob_hi=(1.0, 1.0, 1.0), stream=None,
+                 least_workspace=False):
         self.boxes = [(tuple(lo), tuple(hi)) for lo, hi in boxes]
         self.domain = domain
         self.periodic = tuple(bool(p) for p in periodic)
@@ -99,8 +116,9 @@ class MLMG:
         self._bx = L.boxes_array(self.boxes)
         self._geom = L.geom_struct(domain, periodic, prob_lo, prob_hi)
         bc = (C.c_int32 * 3)(*[L.MG_BC_PERIODIC if p else L.MG_BC_DIRICHLET0 for p in periodic])
-        nbytes = workspace_bytes(self.boxes, domain, periodic, self.opts, a is not None)
-        self.workspace = torch.empty(nbytes + 256, dtype=torch.uint8, device="cuda")
+        nbytes, self.workspace = _allocate(
+            lambda least: workspace_bytes(self.boxes, domain, periodic, self.opts, a is not None,
+                                          least), least_workspace)
         ptr = self.workspace.data_ptr()
         self._ws_ptr = (ptr + 255) // 256 * 256
         self._stream = stream
@@ -264,10 +282,12 @@ class CompositeMLMG:
     """Two-level composite solve: coarse boxes covering a Dirichlet-walled domain
     and fine boxes (coarse index space refined by 2) over part of it.
 
-    b_c / b_f: three face MultiFabs on the coarse / fine boxes, or None for b = 1."""
+    b_c / b_f: three face MultiFabs on the coarse / fine boxes, or None for b = 1;
+    least_workspace: as for MLMG."""
 
     def __init__(self, coarse_boxes, fine_boxes, domain, alpha, beta, b_c=None, b_f=None,
-                 opts=None, prob_lo=(0.0, 0.0, 0.0), prob_hi=(1.0, 1.0, 1.0), stream=None):
+                 opts=None, prob_lo=(0.0, 0.0, 0.0), prob_hi=(1.0, 1.0, 1.0), stream=None,
+                 least_workspace=False):
         self.boxes = [(tuple(lo), tuple(hi)) for lo, hi in coarse_boxes]
         self.fine_boxes = [(tuple(lo), tuple(hi)) for lo, hi in fine_boxes]
         self.domain = domain
@@ -275,13 +295,15 @@ class CompositeMLMG:
         self._cb = L.boxes_array(self.boxes)
         self._fb = L.boxes_array(self.fine_boxes)
         self._geom = L.geom_struct(domain, (False, False, False), prob_lo, prob_hi)
-        n = C.c_size_t(0)
-        L.check(L.lib.mg_query_workspace_amr(self._cb, len(self.boxes), self._fb,
-                                             len(self.fine_boxes), C.byref(self._geom),
-                                             C.byref(self.opts), C.byref(n)),
-                "mg_query_workspace_amr")
-        nbytes = n.value
-        self.workspace = torch.empty(nbytes + 256, dtype=torch.uint8, device="cuda")
+        def size_of(least):
+            n = C.c_size_t(0)
+            name = "mg_query_workspace_amr_least" if least else "mg_query_workspace_amr"
+            L.check(getattr(L.lib, name)(self._cb, len(self.boxes), self._fb,
+                                         len(self.fine_boxes), C.byref(self._geom),
+                                         C.byref(self.opts), C.byref(n)), name)
+            return n.value
+
+        nbytes, self.workspace = _allocate(size_of, least_workspace)
         ws = (self.workspace.data_ptr() + 255) // 256 * 256
 
         def faces(mfs):
