@@ -100,6 +100,9 @@ struct mg_nodal {
   int tail = -1;  // first level of the one-launch tail (-1: none)
   NdTail* d_tail = nullptr;
   NdTail h_tail{};
+  // a workspace without room for the tail's plan and the sweeps' dot products:
+  // launches and passes of their own
+  bool lean = false;
   unsigned long long* d_norm = nullptr;  // 3 slots
   size_t ws_need = 0;
   hipStream_t user = nullptr, st = nullptr;
@@ -235,11 +238,11 @@ int plan(mg_nodal* s, Bump& bump) {
     // room for the partial sums of the shallowest launch depth
     NdGeo g1 = g0;
     g1.tz = 1;
-    s->partials = bump.take<double>((size_t)nd_sum_partials_count(g1) + 8);
+    s->partials = bump.take<double>((size_t)nd_sum_partials_count(g1) + (s->lean ? 0 : 8));
   }
   s->d_norm = bump.take<unsigned long long>(3 * (size_t)kNdNormSlot);
   s->d_iters = bump.take<int>(4);
-  s->d_tail = bump.take<NdTail>(1);
+  if (!s->lean) s->d_tail = bump.take<NdTail>(1);
   if (s->opts.krylov) {
     s->kx = bump.take<double>(s->L[0].size);
     s->kr = bump.take<double>(s->L[0].size);
@@ -269,7 +272,7 @@ int plan(mg_nodal* s, Bump& bump) {
     s->max_elems[t] = mx;
     s->d_box[t] = bump.take<NdBox>(s->boxes.size());
   }
-  s->ws_need = bump.off + 256;
+  s->ws_need = bump.off + (s->lean ? 0 : 256);
   return MG_OK;
 }
 
@@ -341,7 +344,7 @@ NdTail tail_args(const mg_nodal* s, size_t l) {
 // 3^3 nodes: 15 us; with launches 7 + 6 for the one and 25 for the other's CG.
 int tail_level(const mg_nodal* s) {
   int at = -1;
-  for (size_t l = s->L.size() - 1; l >= 1; --l) {
+  for (size_t l = s->L.size() - 1; l >= 1 && !s->lean; --l) {
     const NdTail t = tail_args(s, l);
     if (t.nlev > kNdTailLevels || (t.nlev > 0 && (t.nu1 < 1 || t.nu2 < 0)) || nd_tail_lds(t) < 0)
       break;
@@ -451,7 +454,7 @@ int precond(mg_nodal* s, const double* r, int* zi, double* rz, bool* has_rz) {
   } else if ((rc = coarse_part(s, l0.x[cur]))) {
     return rc;
   }
-  *has_rz = !s->singular && s->opts.nu2 > 0;
+  *has_rz = !s->singular && s->opts.nu2 > 0 && !s->lean;
   for (int k = 0; k < s->opts.nu2; ++k) {
     if ((rc = sweep(s, 0, l0.x[cur], r, l0.x[1 - cur], ND_JACOBI, nullptr,
                     *has_rz && k + 1 == s->opts.nu2 ? rz : nullptr)))
@@ -523,7 +526,9 @@ int solve_pcg(mg_nodal* s, double tol, mg_info_t* inf, double* hist, int* status
     HIPTRY(nd_launch_cg_p(s->st, g, p, z, rho_new, rho_old, restart ? 1 : 0));
     if ((rc = fill_ghosts(s, l0, p))) return rc;
     restart = false;
-    if ((rc = sweep(s, 0, p, l0.f, q, ND_APPLY, nullptr, s->d_cg + 2))) return rc;
+    if ((rc = sweep(s, 0, p, l0.f, q, ND_APPLY, nullptr, s->lean ? nullptr : s->d_cg + 2)))
+      return rc;
+    if (s->lean) HIPTRY(nd_launch_dot(s->st, g, p, q, s->partials, s->d_cg + 2));
     HIPTRY(nd_launch_fill_u64(s->st, nslot(s, 2), kNdNormSlot, 0ull));
     HIPTRY(nd_launch_cg_xr(s->st, g, x, p, r, q, rho_new, s->d_cg + 2, nslot(s, 2)));
     ++it;
@@ -625,6 +630,13 @@ int mg_nodal_create(const mg_box_t* boxes, int32_t nbox, const mg_geom_t* geom,
   {
     Bump dry{nullptr};
     if ((rc = plan(s.get(), dry))) return rc;
+  }
+  const size_t full = s->ws_need;
+  if (workspace && ws_bytes < full) {
+    s->lean = true;
+    Bump dry{nullptr};
+    if ((rc = plan(s.get(), dry))) return rc;
+    if (ws_bytes < s->ws_need) s->ws_need = full;
   }
   if (!workspace || ws_bytes < s->ws_need)
     return fail(MG_ERR_WORKSPACE, "workspace needs " + std::to_string(s->ws_need) + " bytes");

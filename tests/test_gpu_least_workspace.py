@@ -8,6 +8,7 @@ import torch
 
 import workloads as W
 from gpu_util import lib, rel_l2, to_global
+from test_gpu_nodal import _nodal_mf
 
 CASES = [
     # cfg maker, opts
@@ -99,3 +100,41 @@ def test_between_the_sizes_and_composite(monkeypatch):
         sol.append(np.concatenate([pc.valid_numpy()[0].ravel(), pf.valid_numpy()[0].ravel()]))
         s.close()
     assert rel_l2(sol[1], sol[0]) <= 1e-8
+
+
+# bytes mg_nodal_create took before the tail's plan and the sweeps' dot products
+# had a place in the workspace
+NODAL = [
+    (64, 32, (True, False, True), {}, 19984128),
+    (24, 12, (True, True, True), dict(krylov=1), 1902080),
+    (40, 40, (False, False, False), {}, 4865568),
+    (128, 64, (False, False, False), {}, 148303872),
+]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,edge,per,opts,size", NODAL)
+def test_nodal_in_its_former_workspace(n, edge, per, opts, size, monkeypatch):
+    print(f"[least workspace] nodal {n} {per} {opts}", flush=True)
+    P = lib()
+    import paper_2009_12009_amd.nodal as N
+    boxes = W.uniform_boxes(n, edge)
+    rng = np.random.default_rng(6)
+    f = rng.standard_normal(W.nodal_unknown_shape(n, per))
+    f -= f.mean()
+    sol = []
+    for former in (False, True):
+        if former:
+            monkeypatch.setattr(N, "nodal_workspace_bytes", lambda *a: size)
+        s = P.NodalMLMG(boxes, W.domain_box(n), per, opts=dict(tune=0, **opts))
+        phi = s.node_mf(0, fill=0.0)
+        info = s.solve(phi, _nodal_mf(P, boxes, f, n, per, 0), 1e-10)
+        torch.cuda.synchronize()
+        assert info["converged"]
+        sol.append(np.concatenate([x.ravel() for x in phi.to_numpy()]))
+        s.close()
+    assert rel_l2(sol[1], sol[0]) <= 1e-8
+    monkeypatch.setattr(N, "nodal_workspace_bytes", lambda *a: size - 4096)
+    with pytest.raises(P.MGError) as e:
+        P.NodalMLMG(boxes, W.domain_box(n), per, opts=dict(tune=0, **opts))
+    assert e.value.code == P._lib.MG_ERR_WORKSPACE
