@@ -118,21 +118,12 @@ __device__ __forceinline__ void cg_sync() {
   }
 }
 
-// The stop test ||r|| > tol ||rhs|| of the bottom CGs.  Compared as squares, one
-// square root less on the chain of dependent steps, but where tol^2 ||rhs||^2
-// comes near the smallest numbers (right-hand sides below some 1e-140) and would
-// underflow to a test that never ends.
-struct CgStop {
-  double tol, bnorm, sq;
-  bool squares;
-  __device__ __forceinline__ CgStop(double t, double rho) : tol(t), bnorm(0.0), sq(t * t * rho) {
-    squares = sq >= 0x1p-960;
-    if (!squares) bnorm = sqrt(rho);
-  }
-  __device__ __forceinline__ bool more(double rr) const {
-    return squares ? rr > sq : sqrt(rr) > tol * bnorm;
-  }
-};
+// Scale of the bottom CGs' scalars r.r, a power of two: right-hand sides below
+// some 1e-140 bring tol^2 r.r and 1 / r.r to the ends of the range, where the one
+// underflows and the other overflows.  A factor costs a multiplication; a branch
+// with the square root and the quotient of the plain forms in the loop cost the
+// kernels that use all their registers 8 % of their time.
+__device__ __forceinline__ double cg_scale(double rho) { return rho < 0x1p-700 ? 0x1p600 : 1.0; }
 
 template <typename T, int CPT, bool ONE_WAVE = false>
 __device__ __forceinline__ void cg_lds_run(const BottomTables& bt, const T* __restrict__ diag,
@@ -182,7 +173,8 @@ __device__ __forceinline__ void cg_lds_run(const BottomTables& bt, const T* __re
 #pragma unroll
   for (int m = 0; m < CPT; ++m) s += (double)r[m] * (double)r[m];
   double rho = cg_sum<ONE_WAVE>(s, red, phase, nw);
-  const CgStop stop(tol, rho);
+  // stop at ||r|| <= tol ||rhs||, compared as squares
+  const double sc = cg_scale(rho), stop = tol * tol * (sc * rho);
   int it = 0;
   if (rho > 0.0) {
 #pragma unroll
@@ -191,7 +183,7 @@ __device__ __forceinline__ void cg_lds_run(const BottomTables& bt, const T* __re
     while (it < maxiter) {
       cg_sync<ONE_WAVE>();
       // off the chain of dependent steps, unlike a quotient by rho below
-      const double inv = 1.0 / rho;
+      const double inv = 1.0 / (sc * rho);
       s = 0.0;
 #pragma unroll
       for (int m = 0; m < CPT; ++m) {
@@ -228,9 +220,8 @@ __device__ __forceinline__ void cg_lds_run(const BottomTables& bt, const T* __re
       }
       ++it;
       const double rho_new = cg_sum<ONE_WAVE>(s, red, phase, nw);
-      if (!stop.more(rho_new)) break;
-      // (the reciprocal of a subnormal rho may overflow)
-      const T btT = (T)(inv <= 0x1.fffffffffffffp1023 ? rho_new * inv : rho_new / rho);
+      if (!(sc * rho_new > stop)) break;
+      const T btT = (T)(sc * rho_new * inv);
 #pragma unroll
       for (int m = 0; m < CPT; ++m) {
         const int c = tid + m * nt;

@@ -2190,7 +2190,7 @@ __global__ void __launch_bounds__(1024)
 #pragma unroll
   for (int m = 0; m < CPT; ++m) s += (double)r[m] * (double)r[m];
   double rho = block_sum_w<true>(s, red, phase, nw);
-  const CgStop stop(tol, rho);
+  const double sc = cg_scale(rho), stop = tol * tol * (sc * rho);
   int it = 0;
   if (rho > 0.0) {
 #pragma unroll
@@ -2237,7 +2237,7 @@ __global__ void __launch_bounds__(1024)
       }
       ++it;
       const double rho_new = block_sum_w<true>(s, red, phase, nw);
-      if (!stop.more(rho_new)) break;
+      if (!(sc * rho_new > stop)) break;
       const T btT = (T)(rho_new / rho);
       // every lane has read its neighbours' p: the reductions' barriers
 #pragma unroll
