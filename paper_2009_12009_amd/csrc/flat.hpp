@@ -115,7 +115,8 @@ hipError_t launch_flat_update_resid(hipStream_t st, const FlatOp<double>& op, Fl
                                     const double* v, const float* e, double* vn, const double* f,
                                     float* out, unsigned long long* normbits);
 
-// Box arrays (ng 0 or 1) <-> the split-colour array, valid cells.
+// Box arrays (ng 0 or 1) <-> the split-colour array, valid cells (scatter with
+// ghosts, ng 1: and the ghost cells inside the domain or across periodic faces).
 // lo: low corner of the domain.  normbits (gather): max |value|.
 template <typename T>
 hipError_t launch_flat_gather(hipStream_t st, const BoxInfo* boxes, int nbox, int max_cells,
@@ -123,7 +124,8 @@ hipError_t launch_flat_gather(hipStream_t st, const BoxInfo* boxes, int nbox, in
                               unsigned long long* normbits);
 template <typename T>
 hipError_t launch_flat_scatter(hipStream_t st, const BoxInfo* boxes, int nbox, int max_cells,
-                               const int lo[3], const FlatDims& d, const T* src, T* dst, int ng);
+                               const int lo[3], const FlatDims& d, const T* src, T* dst, int ng,
+                               bool ghosts);
 // Coefficients from a level's box arrays: faces of direction dir scaled by
 // (beta b) ih (a face shared by two boxes is taken from the box above it, see
 // launch_flat_shared), cell coefficient as alpha * a.

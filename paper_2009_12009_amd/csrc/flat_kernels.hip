@@ -839,7 +839,9 @@ __device__ __forceinline__ int face_at(const FlatDims& d, int dir, const int (&c
                   : dir == 1 ? yface_at(d, c[0], c[1], c[2]) : zface_at(d, c[0], c[1], c[2]);
 }
 
-template <typename T, bool GATHER>
+// GHOSTS (scatter): the ghost layer too, wrapped along periodic directions; what
+// lies past a wall is left as it is.
+template <typename T, bool GATHER, bool GHOSTS>
 __global__ void __launch_bounds__(256)
     k_flat_boxes(const BoxInfo* __restrict__ boxes, int3 lo, FlatDims d, const T* src, T* dst,
                  int ng, unsigned long long* normbits) {
@@ -848,6 +850,23 @@ __global__ void __launch_bounds__(256)
   const long long off = ng ? B.off_g1 : B.off_g0;
   const int sy = nx + 2 * ng;
   const long long sz = (long long)sy * (ny + 2 * ng);
+  if (GHOSTS) {
+    const int n0 = nx + 2, n1 = ny + 2;
+    const unsigned all = (unsigned)n0 * n1 * (nz + 2);
+    for (unsigned e = blockIdx.x * 256 + threadIdx.x; e < all; e += gridDim.x * 256) {
+      const unsigned t = e / n0, gk = t / n1;
+      int i = (int)(e - t * n0) - 1 + B.lo[0] - lo.x, j = (int)(t - gk * n1) - 1 + B.lo[1] - lo.y,
+          k = (int)gk - 1 + B.lo[2] - lo.z;
+      const bool in = ((d.wall & 1) == 0 || (i >= 0 && i < d.nx)) &&
+                      ((d.wall & 4) == 0 || (j >= 0 && j < d.ny)) &&
+                      ((d.wall & 16) == 0 || (k >= 0 && k < d.nz));
+      i = i < 0 ? i + d.nx : i >= d.nx ? i - d.nx : i;
+      j = j < 0 ? j + d.ny : j >= d.ny ? j - d.ny : j;
+      k = k < 0 ? k + d.nz : k >= d.nz ? k - d.nz : k;
+      if (in) dst[off + e] = src[split_at(d, i, j, k)];
+    }
+    return;
+  }
   const unsigned total = nx * ny * nz;
   unsigned long long mx = 0;
   for (unsigned e = blockIdx.x * 256 + threadIdx.x; e < total; e += gridDim.x * 256) {
@@ -1768,16 +1787,23 @@ template <typename T>
 hipError_t launch_flat_gather(hipStream_t st, const BoxInfo* boxes, int nbox, int max_cells,
                               const int lo[3], const FlatDims& d, const T* src, int ng, T* dst,
                               unsigned long long* normbits) {
-  hipLaunchKernelGGL((k_flat_boxes<T, true>), box_grid(nbox, max_cells), dim3(256), 0, st, boxes,
+  hipLaunchKernelGGL((k_flat_boxes<T, true, false>), box_grid(nbox, max_cells), dim3(256), 0, st, boxes,
                      make_int3(lo[0], lo[1], lo[2]), d, src, dst, ng, normbits);
   return hipGetLastError();
 }
 
 template <typename T>
 hipError_t launch_flat_scatter(hipStream_t st, const BoxInfo* boxes, int nbox, int max_cells,
-                               const int lo[3], const FlatDims& d, const T* src, T* dst, int ng) {
-  hipLaunchKernelGGL((k_flat_boxes<T, false>), box_grid(nbox, max_cells), dim3(256), 0, st, boxes,
-                     make_int3(lo[0], lo[1], lo[2]), d, src, dst, ng, nullptr);
+                               const int lo[3], const FlatDims& d, const T* src, T* dst, int ng,
+                               bool ghosts) {
+  if (ghosts && ng != 1) return hipErrorInvalidValue;
+  const int3 l = make_int3(lo[0], lo[1], lo[2]);
+  if (ghosts)
+    hipLaunchKernelGGL((k_flat_boxes<T, false, true>), box_grid(nbox, max_cells), dim3(256), 0, st,
+                       boxes, l, d, src, dst, ng, nullptr);
+  else
+    hipLaunchKernelGGL((k_flat_boxes<T, false, false>), box_grid(nbox, max_cells), dim3(256), 0,
+                       st, boxes, l, d, src, dst, ng, nullptr);
   return hipGetLastError();
 }
 
@@ -1975,7 +2001,7 @@ hipError_t launch_deep_xr(hipStream_t st, long long n, T* x, const T* p, T* r, c
                                             const FlatDims&, const T*, int, T*,                    \
                                             unsigned long long*);                                  \
   template hipError_t launch_flat_scatter<T>(hipStream_t, const BoxInfo*, int, int, const int*,    \
-                                             const FlatDims&, const T*, T*, int);                  \
+                                             const FlatDims&, const T*, T*, int, bool);            \
   template hipError_t launch_flat_faces<T>(hipStream_t, const BoxInfo*, int, int, const int*,      \
                                            const FlatDims&, int, const T*, T, T, T*);              \
   template hipError_t launch_flat_shared<T>(hipStream_t, const BoxInfo*, int, int, const int*,     \

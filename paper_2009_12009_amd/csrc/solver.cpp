@@ -3367,7 +3367,7 @@ int coarse_correction(mg_solver* s, const T* rhs) {
                                0, v.f, nullptr));
   if ((rc = flat_cycle<T>(s, 0))) return rc;
   HIPTRY(launch_flat_scatter<T>(s->st, L0.d_info, L0.nbox, L0.max_faces, L0.domain.lo, v.op.d,
-                                v.out(), D.e, 1));
+                                v.out(), D.e, 1, false));
   return MG_OK;
 }
 
@@ -4139,9 +4139,11 @@ int solve_flat(mg_solver* s, double tol, mg_info_t* inf, double* hist, int* stat
     HIPTRY(launch_fill_u64(s->st, norm_slot(s, slot), kNormSlot, 0ull));
     // what the norms' geometric trend makes of this one
     const double pred = it < 2 ? 0 : stop.prev * (stop.prev / stop.prev2);
-    // (a norm close above the tolerance is worth the pass too; where it turns out
-    // below it without, the pass comes after, with a wait of its own)
-    both = it == 0 || it >= s->opts.max_iter || (it >= 2 && !(pred > 1.5 * tol));
+    // Black cells too where the trend puts the norm below the tolerance.  Where
+    // it comes out there against the trend their pass follows, with a wait of its
+    // own (some 20 us), and so it always does on levels that stream, whose pass
+    // costs more than that (0.15 ms at 256^3) and may be one too early.
+    both = it == 0 || it >= s->opts.max_iter || (it >= 2 && !v.stream && !(pred > tol));
     if (both) {
       ProfScope ps(s, 1, true);
       HIPTRY((launch_flat_resid<double, double>(s->st, op, w.next(), c, s->frhs, nullptr,
@@ -4410,7 +4412,7 @@ int mg_solve(mg_solver_t* s, mg_multifab_t* phi, const mg_multifab_t* rhs, doubl
       rc = solve_flat(s, tol, &inf, resid_history, &status, &x);
     if (rc) return rc;
     HIPTRY(launch_flat_scatter(s->st, l0.d_info, l0.nbox, l0.max_faces, l0.domain.lo, d,
-                               x, P, 1));
+                               x, P, 1, true));
     inf.rel_resid = inf.abs_resid / normf;
   } else if (s->opts.krylov) {
     status = solve_pcg(s, P, F, rng, std::max(rel_tol * normf, abs_tol), &inf, resid_history);
@@ -4483,10 +4485,9 @@ int mg_solve(mg_solver_t* s, mg_multifab_t* phi, const mg_multifab_t* rhs, doubl
                             s->d_partials, s->d_sum));
     HIPTRY(launch_shift_valid(s->st, l0.d_cell, (int)l0.t_cell.size(), l0.s_cell, l0.d_info, P, 1,
                               s->d_sum, l0.ncell));
+    // the ghosts hold the solution before that
+    if (normf != 0.0 && (rc = exchange<double>(s, l0, P, false))) return rc;
   }
-  // solves over boxes leave the ghosts current, but for the mean; the scatter
-  // writes valid cells
-  if ((flat || s->singular) && normf != 0.0 && (rc = exchange<double>(s, l0, P, false))) return rc;
   HIPTRY(hipMemcpyAsync(s->h_iters, s->d_iters, sizeof(int), hipMemcpyDeviceToHost, s->st));
   HIPTRY(hipStreamSynchronize(s->st));
   inf.bottom_iters = *s->h_iters;
