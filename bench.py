@@ -65,10 +65,14 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "hbm_traffic_flat_sweep_abec256_lognormal_64boxes.md")
 
 
+# what the counted kernel is compiled from
+KERNEL_SOURCES = ("flat_kernels.hip", "device.hpp", "flat.hpp", "kernels.hpp", "tables.hpp")
+
+
 def kernel_source_sha256():
     import hashlib
     h = hashlib.sha256()
-    for f in ("flat_kernels.hip", "flat.hpp", "tables.hpp"):
+    for f in KERNEL_SOURCES:
         with open(os.path.join(ROOT, "paper_2009_12009_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()
