@@ -84,3 +84,35 @@ def test_which_storage_a_handle_solves_on(least_workspace, monkeypatch):
         seen.append(s.kernel_stats(P._lib.FAM_EXCHANGE)[1])
         s.close()
     assert seen[0] > 0 and seen[1] == 0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("precision", [0, 1])
+def test_mg_solve_on_a_composite_handle(precision):
+    """mg_solve on a composite handle solves its coarse level alone, over boxes:
+    the bits of a handle without the fine level, before and after a composite
+    solve."""
+    import ctypes as C
+    print(f"[boxes] mg_solve on a composite handle precision {precision}", flush=True)
+    P = lib()
+    cfg = W.config_lognormal(32, 16)
+    boxes, opts = cfg["boxes"], dict(tune=0, precision=precision, stop_fold=0)
+    rhs = P.MultiFab.from_numpy(boxes, W.scatter_cells(cfg["rhs"], boxes), 0)
+    one = P.MLMG(boxes, W.domain_box(32), (False,) * 3, cfg["alpha"], cfg["beta"], opts=opts)
+    ref = one.cell_mf(1, fill=0.0)
+    one.solve(ref, rhs, 1e-10)
+    fine = [((8, 8, 8), (23, 23, 23))]
+    s = P.CompositeMLMG(boxes, fine, W.domain_box(32), cfg["alpha"], cfg["beta"], opts=opts)
+    for _ in range(2):
+        phi = P.MultiFab(boxes, 1, fill=0.0)
+        pm, rm, info = phi.c_struct(), rhs.c_struct(), P._lib.MgInfo()
+        P._lib.check(P._lib.lib.mg_solve(s.handle, C.byref(pm), C.byref(rm), 1e-10, 0.0,
+                                         C.byref(info), None), "mg_solve")
+        torch.cuda.synchronize()
+        assert info.converged
+        for x, y in zip(phi.valid_numpy(), ref.valid_numpy()):
+            assert (x == y).all()
+        pc, pf = P.MultiFab(boxes, 1, fill=0.0), P.MultiFab(fine, 1, fill=0.0)
+        assert s.solve(pc, pf, rhs, P.MultiFab(fine, 0, fill=1.0), 1e-8)["converged"]
+    one.close()
+    s.close()
