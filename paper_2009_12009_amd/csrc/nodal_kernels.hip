@@ -150,8 +150,8 @@ __device__ __forceinline__ double lane_of(double v, int lane) {
 // lanes brings what lies past the row's ends (lanes 2 r + 0 / 1: left and right
 // of phi row r; lanes 6 + r: right of sigma row r).  Own loads of all thirteen
 // values took 207 accesses of the L1 per row and step, half the time of the
-// pass.  Now 134 MB an array four times in 134 to 139 us at 256^3 (Jacobi; 164
-// before, residual 162 -> 134, apply 141 -> 119), 4 TB/s.
+// pass.  Now 134 MB an array four times in 140 us at 256^3 (Jacobi; 164 before,
+// residual 162 -> 134 to 137, apply 141 -> 121), 3.8 TB/s.
 // DOT: the block's part of phi . A phi (ND_APPLY) or f . out (ND_JACOBI).
 template <int MODE, bool NORM, bool DOT>
 __global__ void __launch_bounds__(256)
