@@ -48,8 +48,9 @@
  *   (which is stored as above), to handles with a smaller workspace than
  *   mg_query_workspace asks for, tile shapes also to mg_apply and
  *   mg_time_smoother.  Each box's coefficients are its own: where two boxes
- *   hold different ones for a face they share (or the two ends of a periodic
- *   direction do), a solve keeps its levels as boxes.
+ *   hold different ones (beyond four units in the last place) for a face they
+ *   share, or the two ends of a periodic direction do, a solve keeps its levels
+ *   as boxes.
  * - Streams: work is enqueued on the stream given (NULL = the default
  *   stream).  mg_solve returns after its result is complete; fill_boundary,
  *   mg_apply and mg_face_grad_logb are asynchronous with respect to the host.

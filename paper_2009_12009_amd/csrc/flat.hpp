@@ -133,8 +133,9 @@ template <typename T>
 hipError_t launch_flat_faces(hipStream_t st, const BoxInfo* boxes, int nbox, int max_faces,
                              const int lo[3], const FlatDims& d, int dir, const T* b, T beta, T ih,
                              T* dst);
-// *differ = 1 if a box holds another value (scaled as above) for a face than the box
-// above it, or than the other end of a periodic direction; b: the level's face
+// *differ = 1 if a box holds another value (scaled as above, beyond four units in
+// the last place) for a face than the box above it, or than the other end of a
+// periodic direction; b: the level's face
 // arrays, op: its faces as launch_flat_faces left them.  max_plane: the most faces
 // of a box in one plane.
 template <typename T>

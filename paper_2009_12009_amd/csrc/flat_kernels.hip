@@ -911,7 +911,9 @@ __global__ void __launch_bounds__(256)
 
 // grid.z = direction, grid.y = box; lanes stride the box's last plane of faces.
 // They are a 65th of the faces of 64^3 boxes, along x one cache line each: 23 us at
-// 256^3, 11.5 at 128^3.
+// 256^3, 11.5 at 128^3.  Up to four units in the last place count as the same:
+// less than what the operator's own products round, and what two boxes' owners
+// may differ by that computed the face each in its own way.
 template <typename T>
 struct BoxFaces {
   const T* b[3];
@@ -934,6 +936,7 @@ __global__ void __launch_bounds__(256)
   const T* b = (dir == 0 ? faces.b[0] : dir == 1 ? faces.b[1] : faces.b[2]) + B.off_f[dir];
   const T* c = dir == 0 ? op.x : dir == 1 ? op.y : op.z;
   const T ih = dir == 0 ? faces.ih[0] : dir == 1 ? faces.ih[1] : faces.ih[2];
+  const T ulps = sizeof(T) == 8 ? T(0x1p-50) : T(0x1p-21);
   bool bad = false;
   for (int e = blockIdx.x * 256 + threadIdx.x; e < n[u] * n[v]; e += gridDim.x * 256) {
     int q[3];
@@ -943,7 +946,8 @@ __global__ void __launch_bounds__(256)
     const T own = (beta * b[q[0] + n[0] * ((long long)q[1] + n[1] * (long long)q[2])]) * ih;
     for (int a = 0; a < 3; ++a) q[a] += B.lo[a] - l[a];
     if (end) q[dir] = 0;
-    bad = bad || !(own == c[face_at(d, dir, q)]);
+    const T other = c[face_at(d, dir, q)];
+    bad = bad || !(own == other || fabs(own - other) <= ulps * fabs(other));
   }
   if (bad) atomicOr(differ, 1ull);
 }

@@ -92,3 +92,35 @@ def test_each_boxes_own_faces(ext, nb, per, d, with_a, opts):
             assert xinfo["history"] == ginfo["history"]
         s.set_coefficients(a=amf, b=faces(own))
     s.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("ulps,boxes_used", [(1, False), (8, True)])
+def test_rounding_is_no_difference(ulps, boxes_used):
+    """Boxes whose shared faces differ by rounding keep the fast storage, where
+    nothing is exchanged; the solution is the oracle's either way."""
+    print(f"[shared faces] {ulps} units in the last place", flush=True)
+    P = lib()
+    ext, per, d = (32, 16, 32), (False, False, True), 0
+    dom = ((0, 0, 0), tuple(n - 1 for n in ext))
+    boxes, good, _, f, _ = problem(ext, (2, 2), per, d, False)
+    own = [[x.copy() for x in g] for g in good]
+    for x in own[d]:
+        x[-1] *= 1.0 + ulps * 2.0 ** -52
+    lev = O.make_level(boxes, dom, per, 0.8, 1.0, None, own)
+    ophi = O.new_cell_data(lev)
+    O.solve(lev, ophi, f, 1e-10, opts=O.Opts(bottom_tol=1e-12))
+    s = P.MLMG(boxes, dom, per, 0.8, 1.0,
+               b=[P.MultiFab.from_numpy(boxes, own[e], 0,
+                                        ixtype=tuple(int(e == q) for q in range(3)))
+                  for e in range(3)],
+               opts=dict(tune=0, bottom_rel_tol=1e-12, ghost_write=0))
+    phi = s.cell_mf(1, fill=0.0)
+    s.profile(True)
+    s.solve(phi, P.MultiFab.from_numpy(boxes, f, 0), 1e-10)
+    torch.cuda.synchronize()
+    assert (s.kernel_stats(P._lib.FAM_EXCHANGE)[1] > 0) == boxes_used
+    got = W.gather_cells(phi.valid_numpy(), boxes, ext, ng=0)
+    ref = W.gather_cells(ophi, boxes, ext, ng=1)
+    assert np.max(np.abs(got - ref)) <= 2e-10 * max(np.max(np.abs(x)) for x in f) / 0.8
+    s.close()
